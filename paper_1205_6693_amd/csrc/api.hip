@@ -182,7 +182,8 @@ void take_bound(const truss_graph* g, Arena& a, Plan& p) {
 void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   p.d_err = a.take<int>(64);
   p.d_total = a.take<unsigned long long>(8);
-  build_workspace(g, a, true);
+  size_t tmp_bytes = 0;
+  build_workspace(g, a, true, &tmp_bytes);
   p.sr = a.take<int2>((size_t)g->m + 1);
   p.truss_canon = a.take<int32_t>((size_t)g->m + 1);
   take_bound(g, a, p);
@@ -190,6 +191,7 @@ void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   dg.n = g->n;
   dg.m = g->m;
   if (dg_for_sizes) dg = *dg_for_sizes;
+  dg.tmp_bytes = tmp_bytes;
   support_workspace(dg, a);
   peel_workspace(dg, a);
 }

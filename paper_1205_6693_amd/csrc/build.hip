@@ -370,6 +370,7 @@ struct Layout {
   int2* rtab;
   int64_t* rtoff;
   int32_t* tsz;
+  size_t tmp_at, tmp_bytes;  // the temporaries' place in the arena
   // relabelling: vertex sort keys and values (ping-pong), their radix scratch, ranks, degrees
   uint64_t *vkey, *vkey_alt;
   int32_t *vval, *vval_alt, *vtmp, *rank, *vdeg;
@@ -392,7 +393,8 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
   L.rtoff = a.take<int64_t>(n + 1);
   L.tsz = a.take<int32_t>(n + 1);
   L.row_ptr = edges ? a.take<int64_t>(n + 1) : nullptr;
-  // temporaries (could alias peeling state; kept separate for clarity)
+  // temporaries: free once the build has returned (DevGraph::tmp)
+  L.tmp_at = a.used;
   L.kf = a.take<int32_t>(m2 + 1);
   L.opos = a.take<int64_t>(m2 + 1);
   L.stmp = a.take<int64_t>(scan_tmp_elems(m2 + 1) + scan_tmp_elems(n + 1));
@@ -424,6 +426,7 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
     L.vkey = L.vkey_alt = nullptr;
     L.vval = L.vval_alt = L.vtmp = L.rank = L.vdeg = nullptr;
   }
+  L.tmp_bytes = a.used - L.tmp_at;
 }
 
 // ranks of the vertices in (degree, id) order; degrees from row_ptr, else from deg
@@ -474,9 +477,10 @@ int rows_from_keys(int32_t n, int64_t m, int vb, Layout& L, int* d_err, hipStrea
 
 }  // namespace
 
-size_t build_workspace(const truss_graph* g, Arena& a, bool relabel) {
+size_t build_workspace(const truss_graph* g, Arena& a, bool relabel, size_t* tmp_bytes) {
   Layout L;
   carve(g, relabel, a, L);
+  if (tmp_bytes) *tmp_bytes = L.tmp_bytes;
   return a.used;
 }
 
@@ -489,6 +493,8 @@ int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStr
   const int vb = bits_for(n) > 0 ? bits_for(n) : 1;
   dg.n = n;
   dg.m = m;
+  dg.tmp = a.base + L.tmp_at;
+  dg.tmp_bytes = L.tmp_bytes;
   hipLaunchKernelGGL(k_init_err, dim3(1), dim3(1), 0, s, d_err);
 
   if (g->fmt == TRUSS_FMT_EDGES) {

@@ -58,7 +58,6 @@ struct DevGraph {
   const int64_t* row_ptr = nullptr;  // n+1, symmetric CSR offsets
   int32_t* col = nullptr;            // 2m neighbours (rows ascending; compacted in place)
   int32_t* seid = nullptr;           // 2m edge id of each CSR entry
-  int32_t* rlen = nullptr;           // n live row lengths (peeling)
   int32_t* eu = nullptr;             // m smaller-id endpoint
   int32_t* ev = nullptr;             // m larger-id endpoint
   int64_t* orow = nullptr;           // n+1 oriented CSR offsets
@@ -67,6 +66,8 @@ struct DevGraph {
   int32_t* perm = nullptr;           // m canonical edge -> input index (EDGES only)
   int2* rtab = nullptr;               // row hash tables (neighbour, edge id), back to back
   const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two)
+  void* tmp = nullptr;               // the build's temporaries, free for later phases once it has returned
+  size_t tmp_bytes = 0;
 };
 
 // Build: validation + canonical edge ids + symmetric and oriented CSR.
@@ -75,7 +76,8 @@ struct BuildBufs;
 // relabel: vertices renumbered by (degree, id) inside the build (dg.perm then
 // always maps the build's edges to the caller's); off where the caller reads
 // vertex ids back out of dg
-size_t build_workspace(const truss_graph* g, Arena& a, bool relabel = false);
+// tmp_bytes (nullable): bytes of the temporaries that later phases may use (DevGraph::tmp)
+size_t build_workspace(const truss_graph* g, Arena& a, bool relabel = false, size_t* tmp_bytes = nullptr);
 int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel = false);
 
 // Scheduling of the exact methods (the scheduler never changes results).

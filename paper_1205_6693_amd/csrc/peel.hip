@@ -14,9 +14,20 @@
 //
 // Triangles through a frontier edge e = (u, v) are found as in Algorithm 2,
 // by its triangle walk: walk the adjacency row of the endpoint with the shorter live row,
-// and look each neighbour w up in the other endpoint's sorted row by binary
-// search.  Deleted edges are only marked (Section 3.1); the rows are compacted
-// in place whenever the live edge count has halved.
+// and look each neighbour w up in the other endpoint's row (hash table or
+// binary search).  Deleted edges are only marked (Section 3.1); the rows are compacted
+// in place whenever the live edge count has fallen below 80 % of their entries.
+//
+// What bounds a round is a chain of dependent memory accesses (about 0.7 us
+// each at the coherent level) up to some 10^6 walk entries, and memory
+// throughput above.  So a frontier is kept as finished walk records, appended
+// when an edge joins it (its endpoints are at hand then) together with the
+// start of its walk among all walks of the round laid end to end: the next
+// round cuts that length into equal parts and every workgroup finds the
+// records of its part by itself, with no work handed from one workgroup to another.
+// Drawing chunks of the frontier and announcing pieces of their walks to idle
+// workgroups took 47 us for a round of 580 K entries and 105 us for one of 2 M, this
+// 36 and 73 us (R-MAT of 15.7 M edges: rounds 110.8 -> 86.4 ms of a call).
 //
 // The level loop runs in a persistent kernel, one 1024-thread workgroup per
 // compute unit.  The grid is never larger than the number of workgroups the
@@ -47,6 +58,8 @@
 // hash table, or a binary search of the other endpoint's sorted row).  The scheduler
 // (plain, a fixed heuristic, or the learned network evaluated by the control
 // wavefront) only picks among these exact methods.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "mlp.hpp"
@@ -57,26 +70,23 @@ namespace {
 
 constexpr int kT = 1024;
 constexpr int kWaves = kT / kWave;
-// adjacency entries per segment of a chunk's walks: smaller segments spread
-// mid-size rounds over more workgroups, larger ones cut the announcement
-// traffic of rounds with big frontiers
-constexpr int kSegSmall = 1 * 1024, kSegLarge = 8 * 1024;
-constexpr int kSegLargeFrontier = 8192;  // frontiers of at least this many edges use kSegLarge
 constexpr int kIntMax = 0x7fffffff;
 constexpr int kHistBins = 6;
 constexpr long long kCompactNum = 8, kCompactDen = 10;  // row compaction threshold
 constexpr int kStageA = 8192;  // LDS staging of live-list appends (entries)
 constexpr int kStageQ = 2048;  // LDS staging of frontier-queue appends
 static_assert(4 * kT <= kStageA && 2 * kT <= kStageQ, "sweep staging capacity");
-constexpr int kMinChunk = 64;  // smallest frontier chunk
 
-// Frontier edges per chunk in a round with qn frontier edges: the frontier is
-// spread over all workgroups, with between kMinChunk and kT edges a chunk.
-__device__ __forceinline__ int chunk_size(int qn, int groups) {
-  int cs = (qn + groups - 1) / groups;
-  cs = (cs + kMinChunk - 1) / kMinChunk * kMinChunk;
-  return cs < kMinChunk ? kMinChunk : cs > kT ? kT : cs;
-}
+// A round's walks, laid end to end in queue order, are cut into parts of equal
+// length: one a workgroup while that length lies between kMinChunk and kPartMax
+// entries; shorter rounds use fewer workgroups, and longer ones cut parts of
+// kPartMax entries which the workgroups draw one after another, so that no
+// workgroup waits long for the last one.  Measured (whole calls, R-MAT of 1.2 M
+// and 15.7 M edges, Chung-Lu of 15.5 M): kMinChunk 64 / 256 / 1024: 22.1 / 22.6 /
+// 23.7, 114.0 / 115.1 / 117.2 and 117.4 / 117.9 / 123.2 ms; kPartMax 8192 / 16384 /
+// 32768: 117.9 / 116.0 / 116.3 ms on the second.
+constexpr int kMinChunk = 64;  // entries of the smallest part: one a lane of one wavefront
+constexpr long long kPartMax = 16384;
 
 enum Phase : int {
   PH_SWEEP = 0,    // compact the live-edge list, minimum live support
@@ -98,13 +108,10 @@ struct alignas(256) PeelCtl {
   unsigned grp_count[kGroups][32];  // workgroups arrived, per group (one 128-byte line each)
   // working counters, reset by the control step; each on its own 128-byte
   // line so that polling one does not slow the atomics on another
-  alignas(128) int w_fetch;               // frontier chunk fetch
-  alignas(128) int w_qlen;                // next-frontier queue length
+  alignas(128) int w_fetch;               // parts of the round drawn
+  alignas(128) unsigned long long w_q;    // next frontier: (walk units << qbits) | edges
   alignas(128) int w_alive;               // live-list length
   alignas(128) int w_minsup;              // minimum live support
-  alignas(128) unsigned long long w_pfetch;  // segment indices drawn
-  alignas(128) int w_chunks;              // frontier chunks finished
-  alignas(128) unsigned long long w_pieces;  // segments announced (may exceed the slot capacity)
   alignas(128) unsigned long long w_work;
   alignas(128) unsigned long long w_fwork;  // level start: sum over F_0 of the shorter live row
   alignas(128) int pad3;
@@ -113,11 +120,11 @@ struct alignas(256) PeelCtl {
   int k;
   int r;
   int qlen;
+  unsigned long long qunits;  // walk units of the round
   int acnt;
   int acur;
   int first;
   int mode;
-  int pcap;
   int kmax;
   int levels;
   long long removed_level;
@@ -136,33 +143,47 @@ struct alignas(256) PeelCtl {
   int sched;               // TRUSS_SCHED_* in effect
   int fix_bits, fix_vals;  // action bits fixed by the options
   int m_edges;
+  int qbits;               // bits of the edge count in w_q
+  unsigned long long wbound;  // bound on the entries of one round's walks
   int stop_level;          // > 0: no level above it is started
   long long lvl_sub0;      // sub-rounds before the current level
   long long prev_sub;      // sub-rounds of the previous level
   unsigned long long t_dec;  // wall clock at the current level's decision
 };
 
+// What a walk needs of a vertex, in one 16-byte load: its row (a symmetric CSR
+// of m < 2^31 edges has fewer than 2^32 entries), the live row length and its
+// hash table (offset of up to 2^34 slots, log2 of the slots).
+struct alignas(16) VInfo {
+  uint32_t base;
+  int32_t len;
+  unsigned long long tab;  // (offset << 6) | lg
+};
+
+// A frontier, as its walks: record x is edge e = (a, b) with a the endpoint of
+// the shorter live row, which is walked and whose neighbours are looked up
+// in b's table.  pre is the start of the walk among the frontier's walks laid
+// end to end, in units of 2^shift entries.
+struct FrontierQueue {
+  unsigned long long* pre;
+  unsigned long long* eb;   // (row start of a << 32) | e
+  unsigned long long* ab;   // (b << 32) | a
+  unsigned long long* tab;  // b's table
+};
+
 struct PeelArgs {
   int32_t n;
   int64_t m;
-  const int64_t* row_ptr;
   const int32_t* col;
   const int32_t* seid;
-  const int32_t* rlen;
+  const VInfo* vinfo;
   const int32_t* eu;
   const int32_t* ev;
   int2* sr;
   int32_t* truss;
   int32_t* alist[2];
-  int32_t* fq[2];
-  unsigned long long* pslot;  // segment slots: 0 = free, ((chunk start + 1) << 32) | segment = announced
-  int32_t* rec_e;             // per frontier position: edge, search endpoint, row start, prefix
-  int32_t* rec_b;
-  int64_t* rec_base;
-  int32_t* rec_pre;
-  int32_t* rec_tot;           // per chunk of 64 positions: total walk length
+  FrontierQueue fq[2];
   const int2* rtab;           // row hash tables
-  const int64_t* rtoff;
   PeelCtl* ctl;
   const float* model;         // peeling model part (learned scheduler), or null
   float* tr_feat;             // per-level trace (tr_cap rows), or null
@@ -195,6 +216,16 @@ __device__ __forceinline__ int hist_bin(long long q) {
   return q <= 1 ? 0 : q <= 16 ? 1 : q <= 256 ? 2 : q <= 4096 ? 3 : q <= 65536 ? 4 : 5;
 }
 
+// Entries per walk unit (log2): 0 wherever the longest round the graph allows
+// (wbound entries: the sum of the shorter row over all edges) fits in the
+// counter's 64 - qbits bits, as on every graph of up to some 100 M edges;
+// otherwise the smallest power of two for which the units fit.
+__device__ __forceinline__ int walk_shift(unsigned long long wbound, int64_t m, int qbits) {
+  int s = 0;
+  while ((wbound >> s) + (unsigned long long)m >= (1ULL << (63 - qbits))) ++s;
+  return s;
+}
+
 // The heuristic's action for a level (bit 0 probe, bit 1 mode).
 __device__ __forceinline__ int heuristic_action(const float* x) {
   (void)x;
@@ -206,7 +237,7 @@ __device__ __forceinline__ int heuristic_action(const float* x) {
 // decision is made in registers, and lane 0 stores the outputs at the end.
 // Every value is the same in all lanes; the lanes evaluate the scheduler's
 // network together (one hidden unit each).
-__device__ void control_step(PeelCtl* c, const PeelArgs& P) {
+__device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
   const bool lead = lane_id() == 0;
   int phase = ldc(&c->phase);
   int k = ldc(&c->k);
@@ -221,10 +252,13 @@ __device__ void control_step(PeelCtl* c, const PeelArgs& P) {
   long long heavy_rounds = ldc(&c->heavy_rounds);
   const long long maxsr = ldc(&c->max_subrounds);
   const unsigned long long t_last = ldc(&c->t_last);
-  const int w_qlen = ldc(&c->w_qlen);
+  const int qbits = ldc(&c->qbits);
+  const int shift = walk_shift(ldc(&c->wbound), P.m, qbits);
+  const unsigned long long w_q = ldc(&c->w_q);
+  const int w_qlen = (int)(w_q & ((1ULL << qbits) - 1ULL));
+  const unsigned long long qunits_in = ldc(&c->qunits);
   const int w_alive = ldc(&c->w_alive);
   const int w_minsup = ldc(&c->w_minsup);
-  const unsigned long long w_pieces = ldc(&c->w_pieces);
   const unsigned long long w_fwork = ldc(&c->w_fwork);
   const int sched = ldc(&c->sched);
   const int fix_bits = ldc(&c->fix_bits);
@@ -236,7 +270,7 @@ __device__ void control_step(PeelCtl* c, const PeelArgs& P) {
   const int phase_in = phase;
   const unsigned long long now = wall_clock64();
   int qlen_out = -1, mode_out = -1, probe_out = -1, first_out = -1, hist_bin_out = -1;
-  bool reset_sweep = false, reset_queue = false, reset_proc = false;
+  bool reset_sweep = false, reset_queue = false;
 
   auto begin_round = [&](int q) {
     qlen_out = q;
@@ -336,8 +370,7 @@ __device__ void control_step(PeelCtl* c, const PeelArgs& P) {
       else phase = PH_SWEEP;
       break;
     case PH_PROC:
-      reset_proc = true;
-      if (w_pieces != 0ULL) heavy_rounds += 1;
+      if ((qunits_in << shift) > (unsigned long long)kT) heavy_rounds += 1;
       if (mode_in == TRUSS_PEEL_DENSE) {
         reset_queue = true;
         phase = PH_DENSE;
@@ -367,15 +400,13 @@ __device__ void control_step(PeelCtl* c, const PeelArgs& P) {
     stc(&c->w_fwork, 0ULL);
   }
   if (reset_queue) {
-    stc(&c->w_qlen, 0);
+    stc(&c->w_q, 0ULL);
     stc(&c->w_fetch, 0);
   }
-  if (reset_proc) {
-    stc(&c->w_pieces, 0ULL);
-    stc(&c->w_pfetch, 0ULL);
-    stc(&c->w_chunks, 0);
+  if (qlen_out >= 0) {
+    stc(&c->qlen, qlen_out);
+    stc(&c->qunits, w_q >> qbits);
   }
-  if (qlen_out >= 0) stc(&c->qlen, qlen_out);
   if (mode_out >= 0) stc(&c->mode, mode_out);
   if (probe_out >= 0) stc(&c->probe, probe_out);
   if (first_out >= 0) stc(&c->first, first_out);
@@ -398,7 +429,7 @@ __device__ void control_step(PeelCtl* c, const PeelArgs& P) {
 // Grid barrier without cache maintenance (see the coherence note above); the
 // first wavefront of the last workgroup to arrive runs control_step before
 // release.  Returns false if the wait timed out, and the kernel then winds down.
-__device__ bool phase_barrier(PeelCtl* c, const PeelArgs& P) {
+__device__ __forceinline__ bool phase_barrier(PeelCtl* c, const PeelArgs& P) {
   __shared__ int s_ok, s_last;
   mem_wait();
   __syncthreads();
@@ -449,16 +480,26 @@ __device__ bool phase_barrier(PeelCtl* c, const PeelArgs& P) {
 
 __device__ __forceinline__ bool removed_at(int rnd, int r) { return rnd != 0 && rnd < r; }
 
+// The frontier records of one part being walked (LDS).
+struct WalkTabs {
+  int pre[kT + 1];          // start of the walk, in units, relative to the part
+  int e[kT], a[kT], b[kT];
+  uint32_t base[kT];
+  unsigned long long tab[kT];
+  int len[kT];              // only with more than one entry a unit
+};
+
 // NI adjacency entries of walks, one step at a time for all of them so that
 // their memory accesses are in flight together.  Entry q is position j[q] of
-// the row walked for frontier edge e[q] = (a, b[q]), valid if ok[q].  Outputs
-// the (up to two) edges per entry whose support crossed k-1 -> k-2 and must be
-// enqueued.
+// the row walked for the frontier record x[q] of W (edge e = (a, b)), valid if
+// ok[q].  Outputs the (up to two) edges per entry whose support crossed
+// k-1 -> k-2 and must be enqueued: f1 = (a, w) and f2 = (b, w).
 template <int NI>
-__device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t (&e)[NI], const int32_t (&b)[NI],
-                                                const int64_t (&j)[NI], bool (&ok)[NI], int r, int l, int k,
-                                                bool sparse, int probe, int32_t (&f1)[NI], int32_t (&f2)[NI]) {
-  int32_t w[NI], e1[NI], e2[NI], s1[NI], s2[NI];
+__device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTabs& W, const int (&x)[NI],
+                                                const uint32_t (&j)[NI], bool (&ok)[NI], int r, int l, int k,
+                                                bool sparse, int probe, int32_t (&w)[NI], int32_t (&f1)[NI],
+                                                int32_t (&f2)[NI]) {
+  int32_t e1[NI], e2[NI], s1[NI], s2[NI];
 #pragma unroll
   for (int q = 0; q < NI; ++q) {
     f1[q] = -1;
@@ -476,7 +517,7 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t
   // the first other edge (a, w) must not be removed
 #pragma unroll
   for (int q = 0; q < NI; ++q) {
-    ok[q] = ok[q] && w[q] != b[q];
+    ok[q] = ok[q] && w[q] != W.b[x[q]];
     if (ok[q]) s1[q] = ldc_stamp(&P.sr[e1[q]]);
   }
 #pragma unroll
@@ -495,9 +536,9 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t
       mask[q] = 0;
       sl[q] = make_int2(-1, 0);
       if (ok[q]) {
-        const int64_t off = P.rtoff[b[q]];
-        const int lg = row_table_lg(P.rtoff[b[q] + 1] - off);
-        tb[q] = P.rtab + off;
+        const unsigned long long tab = W.tab[x[q]];
+        const int lg = (int)(tab & 63);
+        tb[q] = P.rtab + (tab >> 6);
         mask[q] = (1u << lg) - 1u;
         h[q] = row_slot(w[q], lg);
         sl[q] = tb[q][h[q]];
@@ -517,8 +558,9 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
       if (!ok[q]) continue;
-      const int64_t rb = P.row_ptr[b[q]];
-      const int64_t re = rb + P.rlen[b[q]];
+      const VInfo vb = P.vinfo[W.b[x[q]]];
+      const int64_t rb = vb.base;
+      const int64_t re = rb + vb.len;
       const int64_t p = lower_bound_i32<int64_t>(P.col, rb, re, w[q]);
       if (p < re && P.col[p] == w[q]) e2[q] = P.seid[p];
       else ok[q] = false;
@@ -533,8 +575,8 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t
   int old1[NI], old2[NI];
 #pragma unroll
   for (int q = 0; q < NI; ++q) {
-    const bool live = ok[q] && !removed_at(s2[q], r) && !(s1[q] == r && e1[q] < e[q]) &&
-                      !(s2[q] == r && e2[q] < e[q]);
+    const int e = W.e[x[q]];
+    const bool live = ok[q] && !removed_at(s2[q], r) && !(s1[q] == r && e1[q] < e) && !(s2[q] == r && e2[q] < e);
     d1[q] = live && s1[q] != r;
     d2[q] = live && s2[q] != r;
     old1[q] = 0;
@@ -558,36 +600,146 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const int32_t
   }
 }
 
-// Next-frontier edges are gathered per wavefront in LDS and appended to the
-// global queue 64 or more at a time, so the queue counter sees one atomic per
-// flush instead of one per wavefront iteration.
-constexpr int kWq = 192;  // capacity: a flush happens before 64 + 2 * 64 entries are exceeded
-struct WaveQueue {
-  int* buf;     // LDS, kWq entries, private to the wavefront
-  int cnt;      // wave-uniform fill level
-  int32_t* q;   // global next-frontier queue
-  int* count;   // its length
+// One edge of a new frontier with endpoints u, v: which row is walked (the
+// shorter live one, ties by id), where it starts and its length.
+struct Walk {
+  int32_t a, b;
+  uint32_t base;
+  int len;
+  unsigned long long tab;
+};
+__device__ __forceinline__ Walk walk_of(const PeelArgs& P, int32_t u, int32_t v) {
+  const VInfo x = P.vinfo[u], y = P.vinfo[v];
+  const bool ua = x.len < y.len || (x.len == y.len && u < v);
+  Walk r;
+  r.a = ua ? u : v;
+  r.b = ua ? v : u;
+  r.base = ua ? x.base : y.base;
+  r.len = ua ? x.len : y.len;
+  r.tab = ua ? y.tab : x.tab;
+  return r;
+}
+
+__device__ __forceinline__ void put_record(const FrontierQueue& Q, int64_t at, unsigned long long pre, int32_t e,
+                                           const Walk& w) {
+  stc(&Q.pre[at], pre);
+  stc(&Q.eb[at], ((unsigned long long)w.base << 32) | (uint32_t)e);
+  stc(&Q.ab[at], ((unsigned long long)(uint32_t)w.b << 32) | (uint32_t)w.a);
+  stc(&Q.tab[at], w.tab);
+}
+
+// A frontier queue being appended to.  Its counter holds the walk units and
+// the edges appended so far in one word, so that one atomic gives a group of
+// edges both its places in the queue and its stretch of the walks, in the same
+// order.
+struct QueueOut {
+  FrontierQueue q;
+  unsigned long long* count;  // (units << qbits) | edges
+  int qbits, shift;
 };
 
-__device__ __forceinline__ void wq_flush(WaveQueue& wq) {
+__device__ __forceinline__ unsigned long long walk_units(int len, int shift) {
+  return ((unsigned long long)len + (1ULL << shift) - 1ULL) >> shift;
+}
+
+// Next-frontier edges are gathered per wavefront in LDS and appended to the
+// global queue 64 or more at a time, so the queue counter sees one atomic per
+// flush instead of one per wavefront iteration.  A flush looks up both
+// endpoints' rows and appends the finished walk record, so that the next
+// round starts from the records alone.
+constexpr int kWq = 192;  // capacity: a flush happens before 64 + 2 * 64 entries are exceeded
+struct WaveQueue {
+  int* e;       // LDS, kWq entries each, private to the wavefront: edge and endpoints
+  int* u;
+  int* v;
+  int cnt;      // wave-uniform fill level
+};
+
+__device__ __forceinline__ void wq_flush(const PeelArgs& P, WaveQueue& wq, const QueueOut& out) {
   if (wq.cnt == 0) return;
   wave_sync();
-  int base = 0;
-  if (lane_id() == 0) base = atomicAdd(wq.count, wq.cnt);
-  base = __shfl(base, 0, kWave);
-  for (int i = lane_id(); i < wq.cnt; i += kWave) stc(&wq.q[base + i], wq.buf[i]);
+  const int lane = lane_id();
+  for (int i0 = 0; i0 < wq.cnt; i0 += kWave) {
+    const int i = i0 + lane;
+    const bool in = i < wq.cnt;
+    int32_t e = 0;
+    Walk w = {0, 0, 0u, 0, 0ULL};
+    if (in) {
+      e = wq.e[i];
+      w = walk_of(P, wq.u[i], wq.v[i]);
+    }
+    const unsigned long long units = in ? walk_units(w.len, out.shift) : 0ULL;
+    const unsigned long long inc = wave_inclusive_sum(units);
+    const int n = wq.cnt - i0 < kWave ? wq.cnt - i0 : kWave;
+    unsigned long long at = 0;
+    if (lane == kWave - 1) at = atomicAdd(out.count, (inc << out.qbits) | (unsigned)n);
+    at = __shfl(at, kWave - 1, kWave);
+    if (in)
+      put_record(out.q, (int64_t)(at & ((1ULL << out.qbits) - 1ULL)) + lane,
+                 (at >> out.qbits) + inc - units, e, w);
+  }
   wq.cnt = 0;
   wave_sync();
 }
 
-__device__ __forceinline__ void wq_push(WaveQueue& wq, int32_t f1, int32_t f2) {
-  const uint64_t m1 = ballot(f1 >= 0);
-  if (f1 >= 0) wq.buf[wq.cnt + rank_below(m1)] = f1;
-  wq.cnt += __popcll(m1);
-  const uint64_t m2 = ballot(f2 >= 0);
-  if (f2 >= 0) wq.buf[wq.cnt + rank_below(m2)] = f2;
-  wq.cnt += __popcll(m2);
-  if (wq.cnt >= kWave) wq_flush(wq);
+// What the wavefronts of a workgroup still hold at the end of a round (fewer
+// than kWave edges each), appended together with one atomic.  Same-address
+// atomics are served one after another (about 17 ns each): with one per
+// wavefront instead, the 4096 of a full grid held up a round of some 500 K
+// entries by 30 us.  qe, qu, qv: all wavefronts' buffers; tmp: kWaves ints, tmp64:
+// kWaves entries of LDS.
+__device__ __forceinline__ void block_flush(const PeelArgs& P, const WaveQueue& wq, const int (*qe)[kWq],
+                                            const int (*qu)[kWq], const int (*qv)[kWq], const QueueOut& out, int* tmp,
+                                            unsigned long long* tmp64) {
+  __shared__ unsigned long long s_at;
+  const int tid = threadIdx.x, wv = tid / kWave;
+  if (lane_id() == 0) tmp[wv] = wq.cnt;
+  __syncthreads();
+  int n = 0, src = 0, first = 0;
+#pragma unroll 4
+  for (int q = 0; q < kWaves; ++q) {
+    const int c = tmp[q];
+    if (tid >= n && tid < n + c) {
+      src = q;
+      first = n;
+    }
+    n += c;
+  }
+  if (n == 0) return;
+  const bool in = tid < n;
+  int32_t e = 0;
+  Walk w = {0, 0, 0u, 0, 0ULL};
+  if (in) {
+    e = qe[src][tid - first];
+    w = walk_of(P, qu[src][tid - first], qv[src][tid - first]);
+  }
+  const unsigned long long units = in ? walk_units(w.len, out.shift) : 0ULL;
+  const unsigned long long inc = wave_inclusive_sum(units);
+  if (lane_id() == kWave - 1) tmp64[wv] = inc;
+  __syncthreads();
+  unsigned long long base = 0, all = 0;
+#pragma unroll 4
+  for (int q = 0; q < kWaves; ++q) {
+    const unsigned long long v = tmp64[q];
+    if (q < wv) base += v;
+    all += v;
+  }
+  if (tid == 0) s_at = atomicAdd(out.count, (all << out.qbits) | (unsigned)n);
+  __syncthreads();
+  const unsigned long long at = s_at;
+  if (in)
+    put_record(out.q, (int64_t)(at & ((1ULL << out.qbits) - 1ULL)) + tid, (at >> out.qbits) + base + inc - units, e, w);
+}
+
+__device__ __forceinline__ void wq_push(WaveQueue& wq, int32_t f, int32_t u, int32_t v) {
+  const uint64_t m = ballot(f >= 0);
+  if (f >= 0) {
+    const int at = wq.cnt + rank_below(m);
+    wq.e[at] = f;
+    wq.u[at] = u;
+    wq.v[at] = v;
+  }
+  wq.cnt += __popcll(m);
 }
 
 // Appends of a whole workgroup gathered in LDS and written to a global list in
@@ -615,32 +767,63 @@ __device__ __forceinline__ void staged_flush(StagedList& L) {
   __syncthreads();
 }
 
-// tmp: kWaves ints of LDS
-__device__ __forceinline__ void staged_append(StagedList& L, bool want, int32_t val, int* tmp) {
-  const int lane = lane_id(), w = threadIdx.x / kWave;
-  const uint64_t m = ballot(want);
-  if (lane == 0) tmp[w] = __popcll(m);
+// The same for a frontier queue: a flush appends the walk records of the
+// staged edges, one atomic per kT of them.  tmp: kWaves entries of LDS.
+struct StagedQueue {
+  int* buf;
+  int cap;
+  int* fill;
+  unsigned long long* tmp;
+  QueueOut out;
+};
+
+__device__ __forceinline__ void staged_flush(const PeelArgs& P, StagedQueue& L) {
+  __shared__ unsigned long long s_at;
   __syncthreads();
-  int wbase = 0, tot = 0;
-  for (int q = 0; q < kWaves; ++q) {
-    const int x = tmp[q];
-    if (q < w) wbase += x;
-    tot += x;
+  const int n = *L.fill;
+  if (n == 0) return;
+  const int wv = threadIdx.x / kWave;
+  for (int i0 = 0; i0 < n; i0 += kT) {
+    const int i = i0 + (int)threadIdx.x;
+    const bool in = i < n;
+    int32_t e = 0;
+    Walk w = {0, 0, 0u, 0, 0ULL};
+    if (in) {
+      e = L.buf[i];
+      w = walk_of(P, P.eu[e], P.ev[e]);
+    }
+    const unsigned long long units = in ? walk_units(w.len, L.out.shift) : 0ULL;
+    const unsigned long long inc = wave_inclusive_sum(units);
+    if (lane_id() == kWave - 1) L.tmp[wv] = inc;
+    __syncthreads();
+    unsigned long long base = 0, all = 0;
+#pragma unroll 4
+    for (int q = 0; q < kWaves; ++q) {
+      const unsigned long long v = L.tmp[q];
+      if (q < wv) base += v;
+      all += v;
+    }
+    if (threadIdx.x == 0) s_at = atomicAdd(L.out.count, (all << L.out.qbits) | (unsigned)(n - i0 < kT ? n - i0 : kT));
+    __syncthreads();
+    const unsigned long long at = s_at;
+    if (in)
+      put_record(L.out.q, (int64_t)(at & ((1ULL << L.out.qbits) - 1ULL)) + (int)threadIdx.x,
+                 (at >> L.out.qbits) + base + inc - units, e, w);
+    __syncthreads();
   }
-  if (*L.fill + tot > L.cap) staged_flush(L);
-  const int f = *L.fill;
-  if (want) L.buf[f + wbase + rank_below(m)] = val;
-  __syncthreads();
-  if (threadIdx.x == 0) *L.fill = f + tot;
+  if (threadIdx.x == 0) *L.fill = 0;
   __syncthreads();
 }
 
-// The same for U candidate entries per thread (vals[u] kept where want[u]);
-// a thread's kept entries stay in order and follow the previous thread's.
-// U * kT must not exceed the list's LDS capacity.
-template <int U>
-__device__ __forceinline__ void staged_append_n(StagedList& L, const bool (&want)[U], const int32_t (&vals)[U],
-                                                int* tmp) {
+__device__ __forceinline__ void staged_flush(const PeelArgs&, StagedList& L) { staged_flush(L); }
+
+// U candidate entries per thread (vals[u] kept where want[u]) into a staged
+// list or queue; a thread's kept entries stay in order and follow the
+// previous thread's.  U * kT must not exceed the LDS capacity.  tmp: kWaves
+// ints of LDS.
+template <int U, typename Staged>
+__device__ __forceinline__ void staged_append_n(const PeelArgs& P, Staged& L, const bool (&want)[U],
+                                                const int32_t (&vals)[U], int* tmp) {
   const int lane = lane_id(), w = threadIdx.x / kWave;
   int cnt = 0;
 #pragma unroll
@@ -649,12 +832,13 @@ __device__ __forceinline__ void staged_append_n(StagedList& L, const bool (&want
   if (lane == kWave - 1) tmp[w] = incl;
   __syncthreads();
   int wbase = 0, tot = 0;
+#pragma unroll 4
   for (int q = 0; q < kWaves; ++q) {
     const int x = tmp[q];
     if (q < w) wbase += x;
     tot += x;
   }
-  if (*L.fill + tot > L.cap) staged_flush(L);
+  if (*L.fill + tot > L.cap) staged_flush(P, L);
   int pos = *L.fill + wbase + incl - cnt;
 #pragma unroll
   for (int u = 0; u < U; ++u)
@@ -691,52 +875,59 @@ __device__ __forceinline__ void block_sum_to(unsigned long long x, unsigned long
   __syncthreads();
 }
 
-// Block-wide inclusive prefix sum of one int per thread; total in *total.
-__device__ __forceinline__ int block_inclusive_sum(int x, int* tmp, int* total) {
-  const int lane = lane_id(), w = threadIdx.x / kWave;
-  const int inc = wave_inclusive_sum(x);
-  if (lane == kWave - 1) tmp[w] = inc;
+// Number of threads of the workgroup with `p` set; tmp: kWaves ints of LDS.
+__device__ __forceinline__ int block_count(bool p, int* tmp) {
+  const uint64_t m = ballot(p);
+  if (lane_id() == 0) tmp[threadIdx.x / kWave] = __popcll(m);
   __syncthreads();
-  int base = 0, all = 0;
-  for (int q = 0; q < kWaves; ++q) {
-    const int v = tmp[q];
-    if (q < w) base += v;
-    all += v;
-  }
-  *total = all;
+  int n = 0;
+  for (int q = 0; q < kWaves; ++q) n += tmp[q];
   __syncthreads();
-  return base + inc;
+  return n;
 }
+
+using KernArgs = const __attribute__((address_space(4))) PeelArgs*;
 
 // NI: walk entries in flight per thread; SU (2 or 4): live-list entries per
 // thread and step of the level sweep
 template <int NI, int SU>
-__device__ __forceinline__ void peel_body(const PeelArgs& P) {
+__device__ __forceinline__ void peel_body() {
   static_assert(SU == 2 || SU == 4, "sweep step");
-  __shared__ int s_pre[kT + 1];
-  __shared__ int s_e[kT];
-  __shared__ int s_b[kT];
-  __shared__ int64_t s_base[kT];
-  __shared__ int s_wq[kWaves][kWq];
+  // the walking phase and the list phases use the same LDS
+  struct RoundLds {
+    WalkTabs W;
+    int qe[kWaves][kWq], qu[kWaves][kWq], qv[kWaves][kWq];
+  };
+  struct ListLds {
+    int a[kStageA];
+    int q[kStageQ];
+  };
+  __shared__ union {
+    RoundLds r;
+    ListLds l;
+  } S;
   __shared__ int s_tmp[kWaves + 2];
-  __shared__ int s_c0;
-  __shared__ unsigned long long s_pv;
+  __shared__ int s_part;
   __shared__ unsigned long long s_w64[kWaves];
-  __shared__ int s_stage_a[kStageA];
-  __shared__ int s_stage_q[kStageQ];
   __shared__ int s_fill[4];
-  PeelCtl* c = P.ctl;
+  KernArgs ka = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  PeelCtl* const c = ((const PeelArgs*)ka)->ctl;
   if (threadIdx.x == 0) {
     s_fill[0] = 0;
     s_fill[2] = 0;
   }
   __syncthreads();
   const int tid = threadIdx.x;
-  const int lane = lane_id();
   const int wv = tid / kWave;
-  unsigned long long my_work = 0;
+  const int qbits = ldc(&c->qbits);
+  const int shift = walk_shift(ldc(&c->wbound), ((const PeelArgs*)ka)->m, qbits);
+  unsigned long long my_work = 0;  // entries walked by this wavefront
 
   for (;;) {
+    // the arguments are read anew in each phase: kept in scalar registers over
+    // all phases they would spill, and take vector registers with them
+    asm volatile("" : "+s"(ka));
+    const PeelArgs& P = *(const PeelArgs*)ka;
     const int phase = ldc(&c->phase);
     if (phase == PH_DONE || phase == PH_COMPACT) break;
     const int k = ldc(&c->k);
@@ -751,8 +942,8 @@ __device__ __forceinline__ void peel_body(const PeelArgs& P) {
       const int first = ldc(&c->first);
       const int64_t cnt = first ? P.m : (int64_t)ldc(&c->acnt);
       const int32_t* A = P.alist[acur];
-      StagedList LA{s_stage_a, kStageA, &s_fill[0], &s_fill[1], &c->w_alive, P.alist[acur ^ 1]};
-      StagedList LQ{s_stage_q, kStageQ, &s_fill[2], &s_fill[3], &c->w_qlen, P.fq[(r + 1) & 1]};
+      StagedList LA{S.l.a, kStageA, &s_fill[0], &s_fill[1], &c->w_alive, P.alist[acur ^ 1]};
+      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[(r + 1) & 1], &c->w_q, qbits, shift}};
       const int kt = k + 1, stamp = r + 1;
       int mins = kIntMax;
       unsigned long long wsum = 0;
@@ -782,22 +973,22 @@ __device__ __forceinline__ void peel_body(const PeelArgs& P) {
             if (take[u]) {
               stc_stamp(&P.sr[e[u]], stamp);
               P.truss[e[u]] = kt;
-              const int du = P.rlen[P.eu[e[u]]], dv = P.rlen[P.ev[e[u]]];
+              const int du = P.vinfo[P.eu[e[u]]].len, dv = P.vinfo[P.ev[e[u]]].len;
               wsum += (unsigned long long)(du < dv ? du : dv);
             }
           }
         }
-        staged_append_n<SU>(LA, live, e, s_tmp);
+        staged_append_n<SU>(P, LA, live, e, s_tmp);
         // the frontier stage holds two entries a thread per append
 #pragma unroll
         for (int h = 0; h < SU; h += 2) {
           const bool th[2] = {take[h], take[h + 1]};
           const int32_t eh[2] = {e[h], e[h + 1]};
-          staged_append_n<2>(LQ, th, eh, s_tmp);
+          staged_append_n<2>(P, LQ, th, eh, s_tmp);
         }
       }
       staged_flush(LA);
-      staged_flush(LQ);
+      staged_flush(P, LQ);
       block_min_to(mins, s_tmp, &c->w_minsup);
       block_sum_to(wsum, s_w64, &c->w_fwork);
     } else if (phase == PH_START || phase == PH_DENSE) {
@@ -805,215 +996,140 @@ __device__ __forceinline__ void peel_body(const PeelArgs& P) {
       const int64_t cnt = ldc(&c->acnt);
       const int32_t* A = P.alist[acur];
       const int stamp = phase == PH_START ? r : r + 1;
-      StagedList LQ{s_stage_q, kStageQ, &s_fill[2], &s_fill[3], &c->w_qlen, P.fq[stamp & 1]};
+      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[stamp & 1], &c->w_q, qbits, shift}};
       unsigned long long wsum = 0;  // level start: shorter live row over the frontier
       for (int64_t base = (int64_t)blockIdx.x * kT; base < cnt; base += (int64_t)gridDim.x * kT) {
         const int64_t i = base + tid;
-        bool take = false;
-        int32_t e = 0;
+        bool take[1] = {false};
+        int32_t e[1] = {0};
         if (i < cnt) {
-          e = ldc(&A[i]);
-          const int2 sv = ldc2(&P.sr[e]);
-          take = sv.y == 0 && sv.x <= l;
-          if (take) {
-            stc_stamp(&P.sr[e], stamp);
-            P.truss[e] = k;
+          e[0] = ldc(&A[i]);
+          const int2 sv = ldc2(&P.sr[e[0]]);
+          take[0] = sv.y == 0 && sv.x <= l;
+          if (take[0]) {
+            stc_stamp(&P.sr[e[0]], stamp);
+            P.truss[e[0]] = k;
             if (phase == PH_START) {
-              const int du = P.rlen[P.eu[e]], dv = P.rlen[P.ev[e]];
+              const int du = P.vinfo[P.eu[e[0]]].len, dv = P.vinfo[P.ev[e[0]]].len;
               wsum += (unsigned long long)(du < dv ? du : dv);
             }
           }
         }
-        staged_append(LQ, take, e, s_tmp);
+        staged_append_n<1>(P, LQ, take, e, s_tmp);
       }
-      staged_flush(LQ);
+      staged_flush(P, LQ);
       if (phase == PH_START) block_sum_to(wsum, s_w64, &c->w_fwork);
     } else if (phase == PH_PROC) {
+      // The round's walks, laid end to end, in parts of equal length (see
+      // kMinChunk): every workgroup finds the record its part starts in by a
+      // search of the records' starts, kT probes at a time, stages the part's
+      // records in LDS and walks its entries, a thread taking NI of them at
+      // once.  Nothing is handed from one workgroup to another.
       const int qn = ldc(&c->qlen);
+      const unsigned long long units = ldc(&c->qunits);
       const bool sparse = ldc(&c->mode) == TRUSS_PEEL_SPARSE;
       const int probe = ldc(&c->probe);
-      const int32_t* Q = P.fq[r & 1];
-      WaveQueue wq{s_wq[wv], 0, P.fq[(r + 1) & 1], &c->w_qlen};
-      const unsigned long long cap = (unsigned long long)ldc(&c->pcap);
-      unsigned long long* slots = P.pslot;
-      // walk items [lo, hi) of the chunk held in the workgroup's LDS tables
-      auto walk = [&](int lo, int hi) {
-        for (int t0 = lo; t0 < hi; t0 += NI * kT) {
-          int32_t e[NI], b[NI], f1[NI], f2[NI];
-          int64_t j[NI];
-          bool ok[NI];
+      const FrontierQueue Q = P.fq[r & 1];
+      const QueueOut out{P.fq[(r + 1) & 1], &c->w_q, qbits, shift};
+      WaveQueue wq{S.r.qe[wv], S.r.qu[wv], S.r.qv[wv], 0};
+      WalkTabs& W = S.r.W;
+      const int umask = (1 << shift) - 1;
+      unsigned long long pu = (units + gridDim.x - 1) / gridDim.x;  // units a part
+      if (pu < (unsigned long long)(kMinChunk >> shift)) pu = (unsigned long long)(kMinChunk >> shift);
+      if (pu > (unsigned long long)(kPartMax >> shift)) pu = (unsigned long long)(kPartMax >> shift);
+      if (pu < (units >> 30)) pu = units >> 30;  // the draw counter is an int
+      if (pu < 1) pu = 1;
+      const unsigned long long parts = (units + pu - 1) / pu;
+      const bool drawn = parts > gridDim.x;  // more parts than workgroups: the later ones are drawn
+      for (unsigned long long part = blockIdx.x; part < parts;) {
+        // the next part is drawn early: its number is needed after this one's walk
+        if (drawn && tid == 0) s_part = atomicAdd(&c->w_fetch, 1);
+        const unsigned long long lo = part * pu;
+        const unsigned long long hi = lo + pu < units ? lo + pu : units;
+        // x0: the last record that starts at or before unit lo
+        int64_t x0 = 0;
+        for (int64_t span = lo > 0 ? qn : 1; span > 1;) {
+          const int64_t st = (span + kT - 1) / kT;
+          const int64_t d = tid * st;
+          const int n = block_count(d < span && ldc(&Q.pre[x0 + d]) <= lo, s_tmp);
+          x0 += (int64_t)(n - 1) * st;
+          span = span - (int64_t)(n - 1) * st < st ? span - (int64_t)(n - 1) * st : st;
+        }
+        for (;;) {
+          // up to kT records from x0 on
+          const int64_t x = x0 + tid;
+          unsigned long long pre = ~0ULL, eb = 0, ab = 0, tab = 0, next = hi;
+          if (x < qn) {
+            pre = ldc(&Q.pre[x]);
+            eb = ldc(&Q.eb[x]);
+            ab = ldc(&Q.ab[x]);
+            tab = ldc(&Q.tab[x]);
+          }
+          if (x0 + kT < qn) {
+            next = ldc(&Q.pre[x0 + kT]);
+            next = next < hi ? next : hi;
+          }
+          const bool in = pre < hi;
+          if (in) {
+            W.pre[tid] = (int)((long long)pre - (long long)lo);
+            W.e[tid] = (int32_t)(uint32_t)eb;
+            W.base[tid] = (uint32_t)(eb >> 32);
+            W.a[tid] = (int32_t)(uint32_t)ab;
+            W.b[tid] = (int32_t)(ab >> 32);
+            W.tab[tid] = tab;
+            if (shift > 0) W.len[tid] = P.vinfo[(uint32_t)ab].len;
+          }
+          const int nrec = block_count(in, s_tmp);
+          const int ub = W.pre[0] > 0 ? W.pre[0] : 0, ue = (int)(next - lo);
+          int top = 1;
+          while (2 * top < nrec) top <<= 1;
+          const int hi_t = ue << shift;
+          for (int t0 = ub << shift; t0 < hi_t; t0 += NI * kT) {
+            int x_[NI];
+            int32_t w[NI], f1[NI], f2[NI];
+            uint32_t j[NI];
+            bool ok[NI];
 #pragma unroll
-          for (int q = 0; q < NI; ++q) {
-            const int t = t0 + q * kT + tid;
-            ok[q] = t < hi;
-            e[q] = 0;
-            b[q] = 0;
-            j[q] = 0;
-            if (ok[q]) {
-              int x = 0, y = kT - 1;  // last edge whose range starts at or before t
-              while (x < y) {
-                const int mid = (x + y + 1) >> 1;
-                if (s_pre[mid] <= t) x = mid; else y = mid - 1;
+            for (int q = 0; q < NI; ++q) x_[q] = 0;
+            // the record of each entry: the last whose walk starts at or before it
+            for (int st = top; st > 0; st >>= 1) {
+#pragma unroll
+              for (int q = 0; q < NI; ++q) {
+                const int y = x_[q] + st;
+                if (y < nrec && W.pre[y] <= ((t0 + q * kT + tid) >> shift)) x_[q] = y;
               }
-              e[q] = s_e[x];
-              b[q] = s_b[x];
-              j[q] = s_base[x] + (t - s_pre[x]);
+            }
+#pragma unroll
+            for (int q = 0; q < NI; ++q) {
+              const int t = t0 + q * kT + tid;
+              const int off = (((t >> shift) - W.pre[x_[q]]) << shift) + (t & umask);
+              ok[q] = t < hi_t && (shift == 0 || off < W.len[x_[q]]);
+              j[q] = W.base[x_[q]] + (uint32_t)off;
+              my_work += __popcll(ballot(ok[q]));
+            }
+            process_entries<NI>(P, W, x_, j, ok, r, l, k, sparse, probe, w, f1, f2);
+            if (sparse) {
+#pragma unroll
+              for (int q = 0; q < NI; ++q) {
+                wq_push(wq, f1[q], W.a[x_[q]], w[q]);
+                wq_push(wq, f2[q], W.b[x_[q]], w[q]);
+                if (wq.cnt >= kWave) wq_flush(P, wq, out);
+              }
             }
           }
-          process_entries<NI>(P, e, b, j, ok, r, l, k, sparse, probe, f1, f2);
-#pragma unroll
-          for (int q = 0; q < NI; ++q) wq_push(wq, f1[q], f2[q]);
-        }
-        if (tid == 0) my_work += (unsigned long long)(hi - lo);
-      };
-      // (1) frontier edges in chunks of cs <= kT, one edge a thread (the first
-      // chunk of every workgroup is static, the rest are fetched).  Small
-      // frontiers are spread over all workgroups (cs ~ |F| / workgroups, at
-      // least 64).  The walks of a chunk are laid end to end and cut into
-      // segments of seg entries; the workgroup walks segment 0 and announces
-      // the others for any workgroup to take.  A segment is announced by one
-      // 64-bit store into a slot.
-      const int cs = chunk_size(qn, (int)gridDim.x);
-      const int seg = qn >= kSegLargeFrontier ? kSegLarge : kSegSmall;
-      bool first_chunk = true;
-      for (;;) {
-        if (tid == 0) s_c0 = first_chunk ? (int)blockIdx.x * cs : (int)gridDim.x * cs + atomicAdd(&c->w_fetch, cs);
-        first_chunk = false;
-        __syncthreads();
-        const int c0 = s_c0;
-        if (c0 >= qn) break;
-        const int i = c0 + tid;
-        int32_t e = 0, a = 0, b = 0;
-        int work = 0;
-        if (tid < cs && i < qn) {
-          e = ldc(&Q[i]);
-          const int32_t u = P.eu[e], v = P.ev[e];
-          const int du = P.rlen[u], dv = P.rlen[v];
-          const bool ua = du < dv || (du == dv && u < v);
-          a = ua ? u : v;
-          b = ua ? v : u;
-          work = ua ? du : dv;
-        }
-        const int64_t ra = P.row_ptr[a];
-        int W = 0;
-        const int inc = block_inclusive_sum(work, s_tmp, &W);
-        s_pre[tid + 1] = inc;
-        if (tid == 0) s_pre[0] = 0;
-        s_e[tid] = e;
-        s_b[tid] = b;
-        s_base[tid] = ra;
-        const int nseg = (W + seg - 1) / seg;
-        int npub = 0;  // segments 1..npub are announced
-        if (nseg > 1) {
-          // chunk tables for other workgroups, then the segment announcements
-          if (tid < cs) {
-            stc(&P.rec_e[i], e);
-            stc(&P.rec_b[i], b);
-            stc(&P.rec_base[i], ra);
-            stc(&P.rec_pre[i], inc - work);
-          }
-          if (tid == 0) stc(&P.rec_tot[c0 / cs], W);
-          mem_wait();
           __syncthreads();
-          if (tid == 0) s_pv = atomicAdd(&c->w_pieces, (unsigned long long)(nseg - 1));
-          __syncthreads();
-          const unsigned long long pbase = s_pv;
-          const unsigned long long room = pbase < cap ? cap - pbase : 0ULL;
-          npub = room < (unsigned long long)(nseg - 1) ? (int)room : nseg - 1;
-          const unsigned long long code0 = (unsigned long long)(c0 + 1) << 32;
-          for (int sg = 1 + tid; sg <= npub; sg += kT)
-            stc(&slots[pbase + (unsigned long long)(sg - 1)], code0 | (unsigned)sg);
+          x0 += kT;
+          if (x0 >= qn || next >= hi) break;
         }
-        __syncthreads();
-        walk(0, W < seg ? W : seg);
-        // segments that found no slot
-        for (int sg = npub + 1; sg < nseg; ++sg) walk(sg * seg, (sg + 1) * seg < W ? (sg + 1) * seg : W);
-        if (tid == 0) atomicAdd(&c->w_chunks, 1);
+        if (!drawn) break;
+        part = (unsigned long long)gridDim.x + (unsigned)s_part;
         __syncthreads();
       }
-      // (2) take announced segments.  A workgroup draws one index of the
-      // announcement order at a time and keeps it until that slot is
-      // announced (then takes and clears it) or until every chunk is finished
-      // with fewer announcements than the index (then stops).  Indices are
-      // drawn in order and never dropped, so each announced slot is taken
-      // exactly once.
-      const int nchunks = (qn + cs - 1) / cs;
-      for (;;) {
-        if (tid == 0) {
-          unsigned long long pv = ~0ULL;
-          // nothing announced and nothing left to announce: skip the draw
-          bool draw = true;
-          const uint64_t t0 = wall_clock64();
-          for (;;) {
-            if (ldc(&c->w_chunks) >= nchunks && ldc(&c->w_pieces) == 0ULL) {
-              draw = false;
-              break;
-            }
-            if (ldc(&c->w_pieces) != 0ULL) break;
-            __builtin_amdgcn_s_sleep(2);
-            if (wall_clock64() - t0 > 3000000000ULL) {  // 30 s: give up, wind down
-              stc(&c->abort, 1);
-              draw = false;
-              break;
-            }
-          }
-          if (draw) {
-            const unsigned long long q = atomicAdd(&c->w_pfetch, 1ULL);
-            for (;;) {
-              const unsigned long long cl = ldc(&c->w_pieces);
-              const unsigned long long limit = cl < cap ? cl : cap;
-              if (q < limit) {
-                // the owner announces right after claiming the slot range
-                unsigned long long v;
-                while ((v = ldc(&slots[q])) == 0ULL) {
-                  __builtin_amdgcn_s_sleep(1);
-                  if (wall_clock64() - t0 > 3000000000ULL) break;
-                }
-                if (v == 0ULL) {
-                  stc(&c->abort, 1);
-                  break;
-                }
-                stc(&slots[q], 0ULL);
-                pv = v;
-                break;
-              }
-              if (ldc(&c->w_chunks) >= nchunks) {
-                const unsigned long long cl2 = ldc(&c->w_pieces);
-                if (q >= (cl2 < cap ? cl2 : cap)) break;  // final count reached: stop
-                continue;
-              }
-              __builtin_amdgcn_s_sleep(2);
-              if (wall_clock64() - t0 > 3000000000ULL) {  // 30 s: give up, wind down
-                stc(&c->abort, 1);
-                break;
-              }
-            }
-          }
-          s_pv = pv;
-        }
-        __syncthreads();
-        const unsigned long long pv = s_pv;
-        __syncthreads();
-        if (pv == ~0ULL) break;
-        const int c0 = (int)(pv >> 32) - 1;
-        const int sg = (int)(pv & 0xffffffffu);
-        const int i = c0 + tid;
-        const bool ok = tid < cs && i < qn;
-        s_pre[tid] = ok ? ldc(&P.rec_pre[i]) : kIntMax;
-        s_e[tid] = ok ? ldc(&P.rec_e[i]) : 0;
-        s_b[tid] = ok ? ldc(&P.rec_b[i]) : 0;
-        s_base[tid] = ok ? ldc(&P.rec_base[i]) : 0;
-        const int W = ldc(&P.rec_tot[c0 / cs]);
-        if (tid == 0) s_pre[kT] = W;
-        __syncthreads();
-        walk(sg * seg, (sg + 1) * seg < W ? (sg + 1) * seg : W);
-        __syncthreads();
-      }
-      wq_flush(wq);
+      if (sparse) block_flush(P, wq, S.r.qe, S.r.qu, S.r.qv, out, s_tmp, s_w64);
     }
     if (!phase_barrier(c, P)) break;
   }
-  if (tid == 0 && my_work) atomicAdd(&c->w_work, my_work);
+  if (lane_id() == 0 && my_work) atomicAdd(&c->w_work, my_work);
 }
 
 // The persistent peeling kernel in two shapes over the same state machine:
@@ -1021,9 +1137,9 @@ __device__ __forceinline__ void peel_body(const PeelArgs& P) {
 // per thread, or two workgroups per compute unit (registers capped for eight
 // wavefronts per SIMD) with two entries per thread, which hides more latency
 // when walks are long.  All state lives in global memory between launches.
-__global__ void __launch_bounds__(kT) k_peel(PeelArgs P) { peel_body<4, 4>(P); }
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) k_peel_wide(PeelArgs P) {
-  peel_body<2, 2>(P);
+__global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<4, 4>(); }
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) k_peel_wide(PeelArgs) {
+  peel_body<2, 2>();
 }
 
 // One bit per edge, set when the edge is removed: the liveness test of the
@@ -1043,8 +1159,8 @@ __global__ void __launch_bounds__(256) k_dead_bits(const int2* __restrict__ sr, 
 
 // Stable in-place compaction of every row to its live entries (a wavefront a row).
 constexpr int kCompactUnroll = 4;
-__global__ void __launch_bounds__(256) k_compact(const int64_t* __restrict__ row_ptr, int32_t* __restrict__ col,
-                                                 int32_t* __restrict__ seid, int32_t* __restrict__ rlen, int32_t n,
+__global__ void __launch_bounds__(256) k_compact(int32_t* __restrict__ col,
+                                                 int32_t* __restrict__ seid, VInfo* __restrict__ vinfo, int32_t n,
                                                  const unsigned long long* __restrict__ dead, PeelCtl* c) {
   const int lane = lane_id();
   const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
@@ -1054,8 +1170,9 @@ __global__ void __launch_bounds__(256) k_compact(const int64_t* __restrict__ row
     c->t_last = 0;
   }
   for (int64_t v = gw; v < n; v += nw) {
-    const int64_t rb = row_ptr[v];
-    const int len = rlen[v];
+    const VInfo vi = vinfo[v];
+    const int64_t rb = vi.base;
+    const int len = vi.len;
     int wpos = 0;
     // kCompactUnroll chunks of kWave entries are read before any is written
     // back, so their loads overlap; entries only move to lower positions, so
@@ -1089,38 +1206,58 @@ __global__ void __launch_bounds__(256) k_compact(const int64_t* __restrict__ row
         wpos += __popcll(km);
       }
     }
-    if (lane == 0) rlen[v] = wpos;
+    if (lane == 0) vinfo[v].len = wpos;
   }
 }
 
-__global__ void k_peel_init(PeelCtl* c, const int64_t* __restrict__ row_ptr, int32_t* __restrict__ rlen, int32_t n,
-                            int64_t m, long long max_subrounds, int sched, int fix_bits, int fix_vals, int pcap,
-                            unsigned long long* __restrict__ pslot, int first_level, int stop_level) {
+// The vertices' walk records and the control block; wbound (zeroed before)
+// receives the sum of the shorter row over all edges: with the ids ranked by
+// degree an edge's shorter row is that of its first endpoint in the
+// orientation, so the sum is that of out-degree times degree.
+__global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __restrict__ row_ptr,
+                                                   const int64_t* __restrict__ orow, const int64_t* __restrict__ rtoff,
+                                                   VInfo* __restrict__ vinfo, int32_t n, int64_t m,
+                                                   long long max_subrounds, int sched, int fix_bits, int fix_vals,
+                                                   int qbits, int first_level, int stop_level) {
+  __shared__ unsigned long long s_w[4];
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) rlen[i] = (int32_t)(row_ptr[i + 1] - row_ptr[i]);
-  if (i < pcap) pslot[i] = 0ULL;
+  unsigned long long wsum = 0;
+  if (i < n) {
+    const int64_t rb = row_ptr[i], d = row_ptr[i + 1] - rb;
+    const int64_t to = rtoff[i], slots = rtoff[i + 1] - to;
+    VInfo v;
+    v.base = (uint32_t)rb;
+    v.len = (int32_t)d;
+    v.tab = ((unsigned long long)to << 6) | (unsigned)(slots > 0 ? row_table_lg(slots) : 0);
+    vinfo[i] = v;
+    wsum = (unsigned long long)(orow[i + 1] - orow[i]) * (unsigned long long)d;
+  }
+  wsum = wave_sum(wsum);
+  if (lane_id() == 0) s_w[threadIdx.x / kWave] = wsum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long w = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+    if (w) atomicAdd(&c->wbound, w);
+  }
   if (i == 0) {
     c->bar_count = 0;
     c->bar_gen = 0;
     for (int g = 0; g < kGroups; ++g) c->grp_count[g][0] = 0;
     c->w_fetch = 0;
-    c->w_qlen = 0;
+    c->w_q = 0ULL;
     c->w_alive = 0;
     c->w_minsup = kIntMax;
-    c->w_pfetch = 0ULL;
-    c->w_chunks = 0;
-    c->w_pieces = 0ULL;
     c->w_work = 0ULL;
     c->w_fwork = 0ULL;
     c->phase = PH_SWEEP;
     c->k = first_level - 1;  // the first sweep takes the frontier of level first_level
     c->r = 0;
     c->qlen = 0;
+    c->qunits = 0ULL;
     c->acnt = (int)m;
     c->acur = 0;
     c->first = 1;
     c->mode = TRUSS_PEEL_SPARSE;
-    c->pcap = pcap;
     c->kmax = 0;
     c->levels = 0;
     c->removed_level = 0;
@@ -1140,38 +1277,46 @@ __global__ void k_peel_init(PeelCtl* c, const int64_t* __restrict__ row_ptr, int
     c->fix_vals = fix_vals;
     c->stop_level = stop_level;
     c->m_edges = (int)m;
+    c->qbits = qbits;
     c->lvl_sub0 = 0;
     c->prev_sub = 0;
     c->t_dec = 0;
   }
 }
 
+__global__ void k_zero_bound(PeelCtl* c) { c->wbound = 0ULL; }
+
 struct PeelLayout {
   PeelCtl* ctl;
-  int32_t* rlen;
+  VInfo* vinfo;
   int32_t* alist[2];
-  int32_t* fq[2];
-  unsigned long long* pslot;
-  int32_t *rec_e, *rec_b, *rec_pre, *rec_tot;
-  int64_t* rec_base;
+  FrontierQueue fq[2];
   unsigned long long* dead;  // removed-edge bitmap for the row compaction
-  int pcap;
 };
 
+// The records of the frontier queues and the vertices lie in what the build
+// leaves unused (dg.tmp) as far as that reaches, the rest in the arena.
 void carve(const DevGraph& dg, Arena& a, PeelLayout& L) {
   const int64_t m = dg.m;
+  Arena t;
+  t.base = static_cast<char*>(dg.tmp);
+  t.cap = dg.tmp_bytes;
+  t.counting = a.counting;
+  auto place = [&](auto* type, size_t count) {
+    using T = std::remove_pointer_t<decltype(type)>;
+    const size_t bytes = (count * sizeof(T) + 255) & ~size_t(255);
+    return t.used + bytes <= t.cap ? t.take<T>(count) : a.take<T>(count);
+  };
   L.ctl = a.take<PeelCtl>(1);
-  L.rlen = a.take<int32_t>(dg.n + 1);
   for (int i = 0; i < 2; ++i) L.alist[i] = a.take<int32_t>(m + 1);
-  for (int i = 0; i < 2; ++i) L.fq[i] = a.take<int32_t>(m + 1);
-  L.pcap = (int)(m < (1 << 22) ? m : (1 << 22));
-  L.pslot = a.take<unsigned long long>(L.pcap + 1);
-  L.rec_e = a.take<int32_t>(m + kT);
-  L.rec_b = a.take<int32_t>(m + kT);
-  L.rec_pre = a.take<int32_t>(m + kT);
-  L.rec_base = a.take<int64_t>(m + kT);
-  L.rec_tot = a.take<int32_t>(m / kMinChunk + 2);
-  L.dead = a.take<unsigned long long>(m / kWave + 2);
+  L.vinfo = place((VInfo*)nullptr, (size_t)dg.n + 1);
+  for (int i = 0; i < 2; ++i) {
+    L.fq[i].pre = place((unsigned long long*)nullptr, (size_t)m + 1);
+    L.fq[i].eb = place((unsigned long long*)nullptr, (size_t)m + 1);
+    L.fq[i].ab = place((unsigned long long*)nullptr, (size_t)m + 1);
+    L.fq[i].tab = place((unsigned long long*)nullptr, (size_t)m + 1);
+  }
+  L.dead = place((unsigned long long*)nullptr, (size_t)(m / kWave + 2));
 }
 
 int g_peel_blocks = 0;       // grid of k_peel: one workgroup per compute unit
@@ -1199,11 +1344,12 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
   *res = PeelResult();
   if (dg.m == 0) return TRUSS_OK;
   const long long maxsr = plan.max_subrounds;
-  int64_t initn = dg.n > L.pcap ? dg.n : L.pcap;
-  if (initn < 1) initn = 1;
-  hipLaunchKernelGGL(k_peel_init, dim3((unsigned)((initn + 255) / 256)), dim3(256), 0, s, L.ctl, dg.row_ptr, L.rlen,
-                     dg.n, dg.m, maxsr, plan.sched, plan.fix_bits, plan.fix_vals, L.pcap, L.pslot,
-                     plan.first_level < 2 ? 2 : plan.first_level, plan.stop_level);
+  int qbits = 1;
+  while ((dg.m >> qbits) != 0) ++qbits;  // a frontier holds up to m edges
+  hipLaunchKernelGGL(k_zero_bound, dim3(1), dim3(1), 0, s, L.ctl);
+  hipLaunchKernelGGL(k_peel_init, dim3((unsigned)(((int64_t)(dg.n > 0 ? dg.n : 1) + 255) / 256)), dim3(256), 0, s,
+                     L.ctl, dg.row_ptr, dg.orow, dg.rtoff, L.vinfo, dg.n, dg.m, maxsr, plan.sched, plan.fix_bits,
+                     plan.fix_vals, qbits, plan.first_level < 2 ? 2 : plan.first_level, plan.stop_level);
   if (g_peel_blocks == 0) {
     int dev = 0, cus = 0, occ = 0;
     TRUSS_HIP(hipGetDevice(&dev));
@@ -1226,10 +1372,9 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
   PeelArgs P;
   P.n = dg.n;
   P.m = dg.m;
-  P.row_ptr = dg.row_ptr;
   P.col = dg.col;
   P.seid = dg.seid;
-  P.rlen = L.rlen;
+  P.vinfo = L.vinfo;
   P.eu = dg.eu;
   P.ev = dg.ev;
   P.sr = sr;
@@ -1238,14 +1383,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
     P.alist[i] = L.alist[i];
     P.fq[i] = L.fq[i];
   }
-  P.pslot = L.pslot;
-  P.rec_e = L.rec_e;
-  P.rec_b = L.rec_b;
-  P.rec_pre = L.rec_pre;
-  P.rec_base = L.rec_base;
-  P.rec_tot = L.rec_tot;
   P.rtab = dg.rtab;
-  P.rtoff = dg.rtoff;
   P.ctl = L.ctl;
   P.model = plan.sched == TRUSS_SCHED_LEARNED ? plan.model : nullptr;
   P.tr_cap = trace && trace->level_feat && trace->level_ms && trace->level_action ? trace->level_cap : 0;
@@ -1274,8 +1412,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
     }
     if (h.abort || h.err || h.phase != PH_COMPACT) break;
     hipLaunchKernelGGL(k_dead_bits, dim3(4096), dim3(256), 0, s, sr, dg.m, L.dead);
-    hipLaunchKernelGGL(k_compact, dim3(2048), dim3(256), 0, s, dg.row_ptr, dg.col, dg.seid, L.rlen, dg.n, L.dead,
-                       L.ctl);
+    hipLaunchKernelGGL(k_compact, dim3(2048), dim3(256), 0, s, dg.col, dg.seid, L.vinfo, dg.n, L.dead, L.ctl);
   }
   if (ev0) (void)hipEventDestroy(ev0);
   if (ev1) (void)hipEventDestroy(ev1);
