@@ -100,21 +100,34 @@ enum Phase : int {
 
 constexpr int kGroups = 8;  // barrier arrival groups (workgroup id mod 8: one per XCD under round-robin dispatch)
 
+// Working counters of one phase, each on its own 128-byte line.  Two sets
+// alternate from phase to phase: the control step that reads one resets it
+// for the phase after the next, so the release of the next phase need not
+// wait for the reset.
+struct alignas(128) PhaseCounts {
+  alignas(128) int fetch;                  // parts of the round drawn
+  alignas(128) unsigned long long q;       // next frontier: (walk units << qbits) | edges
+  alignas(128) int alive;                  // live-list length
+  alignas(128) int minsup;                 // minimum live support
+  alignas(128) unsigned long long fwork;   // level start: sum over F_0 of the shorter live row
+};
+
+// What the workgroups need of the control state in a phase, released by the
+// control step as kPub words of which each carries the low 16 bits of the
+// barrier's generation above its value: a workgroup polls the words themselves,
+// so the release takes one store and one load instead of state, flag and
+// state again.
+enum Pub : int { PUB_FLAGS = 0, PUB_K = 1, PUB_R = 2, PUB_UNITS = 3, PUB_ACNT = 4, kPub = 5 };
+constexpr int kPubBits = 48;
+
 struct alignas(256) PeelCtl {
-  unsigned bar_count;          // groups arrived
+  unsigned bar_count;          // groups arrived at all barriers so far
   unsigned pad0[63];
-  unsigned bar_gen;
-  unsigned pad1[63];
-  unsigned grp_count[kGroups][32];  // workgroups arrived, per group (one 128-byte line each)
-  // working counters, reset by the control step; each on its own 128-byte
-  // line so that polling one does not slow the atomics on another
-  alignas(128) int w_fetch;               // parts of the round drawn
-  alignas(128) unsigned long long w_q;    // next frontier: (walk units << qbits) | edges
-  alignas(128) int w_alive;               // live-list length
-  alignas(128) int w_minsup;              // minimum live support
+  unsigned long long pub[kPub];
+  alignas(256) unsigned grp_count[kGroups][32];  // workgroups arrived at all barriers so far, per group (a 128-byte line each)
+  PhaseCounts w[2];
   alignas(128) unsigned long long w_work;
-  alignas(128) unsigned long long w_fwork;  // level start: sum over F_0 of the shorter live row
-  alignas(128) int pad3;
+  alignas(128) unsigned bar_gen;  // barriers passed before this launch
   // published control state, written only by the control step
   int phase;
   int k;
@@ -226,6 +239,44 @@ __device__ __forceinline__ int walk_shift(unsigned long long wbound, int64_t m, 
   return s;
 }
 
+// The published state of a phase.
+struct PhaseState {
+  int phase, acur, mode, probe, first, qlen, k, r, acnt;
+  unsigned long long units;
+};
+__device__ __forceinline__ unsigned long long pub_word(const PhaseState& s, int i) {
+  switch (i) {
+    case PUB_FLAGS:
+      return (unsigned long long)(unsigned)(s.phase | (s.acur << 3) | (s.mode << 4) | (s.probe << 6) | (s.first << 7)) |
+             ((unsigned long long)(unsigned)s.qlen << 8);
+    case PUB_K: return (unsigned)s.k;
+    case PUB_R: return (unsigned)s.r;
+    case PUB_UNITS: return s.units;
+    default: return (unsigned)s.acnt;
+  }
+}
+__device__ __forceinline__ unsigned long long scalar64(unsigned long long x) {
+  return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+         (unsigned)__builtin_amdgcn_readfirstlane((int)x);
+}
+// from the words (tags cleared) in LDS; the same in all lanes
+__device__ __forceinline__ PhaseState phase_state(const unsigned long long* pub) {
+  PhaseState s;
+  const unsigned long long f = scalar64(pub[PUB_FLAGS]);
+  s.phase = (int)(f & 7);
+  s.acur = (int)(f >> 3) & 1;
+  s.mode = (int)(f >> 4) & 3;
+  s.probe = (int)(f >> 6) & 1;
+  s.first = (int)(f >> 7) & 1;
+  s.qlen = (int)(f >> 8);
+  s.k = (int)scalar64(pub[PUB_K]);
+  s.r = (int)scalar64(pub[PUB_R]);
+  s.acnt = (int)scalar64(pub[PUB_ACNT]);
+  s.units = scalar64(pub[PUB_UNITS]);
+  return s;
+}
+static_assert(TRUSS_PEEL_SPARSE < 4 && TRUSS_PEEL_DENSE < 4 && PH_DONE < 8, "fields of PUB_FLAGS");
+
 // The heuristic's action for a level (bit 0 probe, bit 1 mode).
 __device__ __forceinline__ int heuristic_action(const float* x) {
   (void)x;
@@ -233,18 +284,23 @@ __device__ __forceinline__ int heuristic_action(const float* x) {
 }
 
 // ---- control step: the first wavefront of the last workgroup to reach a barrier ---------------
-// All inputs are loaded first (independent loads in flight together), the
-// decision is made in registers, and lane 0 stores the outputs at the end.
-// Every value is the same in all lanes; the lanes evaluate the scheduler's
-// network together (one hidden unit each).
-__device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
+// All inputs are loaded first (independent loads in flight together; the
+// published state is at hand), the decision is made in registers and released,
+// and lane 0 stores the rest of the state afterwards: the next control step
+// reads it after this workgroup's next arrival.  Every value is the same in all
+// lanes; the lanes evaluate the scheduler's network together (one hidden unit
+// each).  st: the state of the phase that has ended, on return that of the
+// next one; gen: barriers passed including this one.
+__device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, PhaseState& st, unsigned gen, int shift) {
   const bool lead = lane_id() == 0;
-  int phase = ldc(&c->phase);
-  int k = ldc(&c->k);
-  int r = ldc(&c->r);
-  int acnt = ldc(&c->acnt);
-  int acur = ldc(&c->acur);
-  const int mode_in = ldc(&c->mode);
+  PhaseCounts* const w = &c->w[(gen - 1) & 1];
+  int phase = st.phase;
+  int k = st.k;
+  int r = st.r;
+  int acnt = st.acnt;
+  int acur = st.acur;
+  const int mode_in = st.mode;
+  const unsigned long long qunits_in = st.units;
   int levels = ldc(&c->levels);
   long long removed_level = ldc(&c->removed_level);
   long long csr_live = ldc(&c->csr_live);
@@ -253,13 +309,11 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
   const long long maxsr = ldc(&c->max_subrounds);
   const unsigned long long t_last = ldc(&c->t_last);
   const int qbits = ldc(&c->qbits);
-  const int shift = walk_shift(ldc(&c->wbound), P.m, qbits);
-  const unsigned long long w_q = ldc(&c->w_q);
+  const unsigned long long w_q = ldc(&w->q);
   const int w_qlen = (int)(w_q & ((1ULL << qbits) - 1ULL));
-  const unsigned long long qunits_in = ldc(&c->qunits);
-  const int w_alive = ldc(&c->w_alive);
-  const int w_minsup = ldc(&c->w_minsup);
-  const unsigned long long w_fwork = ldc(&c->w_fwork);
+  const int w_alive = ldc(&w->alive);
+  const int w_minsup = ldc(&w->minsup);
+  const unsigned long long w_fwork = ldc(&w->fwork);
   const int sched = ldc(&c->sched);
   const int fix_bits = ldc(&c->fix_bits);
   const int fix_vals = ldc(&c->fix_vals);
@@ -268,18 +322,19 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
   long long prev_sub = ldc(&c->prev_sub);
   unsigned long long t_dec = ldc(&c->t_dec);
   const int phase_in = phase;
+  const unsigned long long t_ph = ldc(&c->t_phase[phase_in]);
   const unsigned long long now = wall_clock64();
-  int qlen_out = -1, mode_out = -1, probe_out = -1, first_out = -1, hist_bin_out = -1;
-  bool reset_sweep = false, reset_queue = false;
+  int hist_bin_out = -1;
+  bool failed = false;
 
   auto begin_round = [&](int q) {
-    qlen_out = q;
+    st.qlen = q;
+    st.units = w_q >> qbits;
     subrounds += 1;
     hist_bin_out = hist_bin(q);
     phase = PH_PROC;
   };
   auto next_round = [&]() {
-    reset_queue = true;
     if (w_qlen > 0) {
       r += 1;
       removed_level += w_qlen;
@@ -325,8 +380,8 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
           const int pref = sched == TRUSS_SCHED_PLAIN ? 3 : heuristic_action(x);
           act = (pref & ~fix_bits) | fix_vals;
         }
-        mode_out = (act & 2) ? (int)TRUSS_PEEL_DENSE : (int)TRUSS_PEEL_SPARSE;
-        probe_out = act & 1;
+        st.mode = (act & 2) ? (int)TRUSS_PEEL_DENSE : (int)TRUSS_PEEL_SPARSE;
+        st.probe = act & 1;
         const int li = levels - 1;  // trace row of the level
         if (lead && li < P.tr_cap && P.tr_feat) {
           for (int i = 0; i < kPeelF; ++i) P.tr_feat[(int64_t)li * kPeelF + i] = x[i];
@@ -342,11 +397,9 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
       // of level k+1 (stamped r+1); it is the level's F_0 unless empty, which
       // happens exactly when the minimum live support is at least k, so that
       // the next level is min + 2 and needs its own start phase
-      reset_sweep = true;
-      reset_queue = true;
       acnt = w_alive;
       acur ^= 1;
-      first_out = 0;
+      st.first = 0;
       if (w_alive == 0 || (stop_level > 0 && (w_qlen > 0 ? k + 1 : w_minsup + 2) > stop_level)) {
         phase = PH_DONE;
         break;
@@ -364,7 +417,6 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
       }
       break;
     case PH_START:
-      reset_queue = true;
       removed_level = w_qlen;
       if (w_qlen > 0) start_level();
       else phase = PH_SWEEP;
@@ -372,7 +424,6 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
     case PH_PROC:
       if ((qunits_in << shift) > (unsigned long long)kT) heavy_rounds += 1;
       if (mode_in == TRUSS_PEEL_DENSE) {
-        reset_queue = true;
         phase = PH_DENSE;
         break;
       }
@@ -385,36 +436,37 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
       phase = PH_DONE;
   }
   if (maxsr > 0 && subrounds > maxsr && phase != PH_DONE) {
-    if (lead) stc(&c->err, (int)TRUSS_E_INTERNAL);
+    failed = true;
     phase = PH_DONE;
   }
+  st.phase = phase;
+  st.k = k;
+  st.r = r;
+  st.acnt = acnt;
+  st.acur = acur;
+  const unsigned long long tag = (unsigned long long)(gen & 0xffffu) << kPubBits;
+  if (lane_id() < kPub) stc(&c->pub[lane_id()], tag | pub_word(st, lane_id()));
   if (!lead) return;
-  // outputs
-  if (t_last != 0 && phase_in >= 0 && phase_in < 8)
-    stc(&c->t_phase[phase_in], ldc(&c->t_phase[phase_in]) + (now - t_last));
+  if (failed) stc(&c->err, (int)TRUSS_E_INTERNAL);
+  if (t_last != 0) stc(&c->t_phase[phase_in], t_ph + (now - t_last));
   stc(&c->t_last, now);
   if (hist_bin_out >= 0) stc(&c->hist[hist_bin_out], ldc(&c->hist[hist_bin_out]) + 1);
-  if (reset_sweep) {
-    stc(&c->w_alive, 0);
-    stc(&c->w_minsup, kIntMax);
-    stc(&c->w_fwork, 0ULL);
-  }
-  if (reset_queue) {
-    stc(&c->w_q, 0ULL);
-    stc(&c->w_fetch, 0);
-  }
-  if (qlen_out >= 0) {
-    stc(&c->qlen, qlen_out);
-    stc(&c->qunits, w_q >> qbits);
-  }
-  if (mode_out >= 0) stc(&c->mode, mode_out);
-  if (probe_out >= 0) stc(&c->probe, probe_out);
-  if (first_out >= 0) stc(&c->first, first_out);
+  stc(&w->fetch, 0);
+  stc(&w->q, 0ULL);
+  stc(&w->alive, 0);
+  stc(&w->minsup, kIntMax);
+  stc(&w->fwork, 0ULL);
+  stc(&c->bar_gen, gen);
   stc(&c->k, k);
   stc(&c->kmax, k);
   stc(&c->r, r);
   stc(&c->acnt, acnt);
   stc(&c->acur, acur);
+  stc(&c->first, st.first);
+  stc(&c->mode, st.mode);
+  stc(&c->probe, st.probe);
+  stc(&c->qlen, st.qlen);
+  stc(&c->qunits, st.units);
   stc(&c->levels, levels);
   stc(&c->removed_level, removed_level);
   stc(&c->csr_live, csr_live);
@@ -427,54 +479,59 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P) {
 }
 
 // Grid barrier without cache maintenance (see the coherence note above); the
-// first wavefront of the last workgroup to arrive runs control_step before
-// release.  Returns false if the wait timed out, and the kernel then winds down.
-__device__ __forceinline__ bool phase_barrier(PeelCtl* c, const PeelArgs& P) {
-  __shared__ int s_ok, s_last;
+// first wavefront of the last workgroup to arrive runs control_step, whose
+// release ends the wait of the others.  The arrival counters only grow, so
+// none has to be reset before the next barrier.  st (published state, the
+// same in all threads) and pub (kPub words of LDS): on return those of the next
+// phase.  gen: barriers passed, including this one.  Returns false if the
+// wait timed out, and the kernel then winds down.
+__device__ __forceinline__ bool phase_barrier(PeelCtl* c, const PeelArgs& P, PhaseState& st, unsigned gen, int shift,
+                                              unsigned long long* pub) {
+  __shared__ int s_ok;
   mem_wait();
   __syncthreads();
-  unsigned gen = 0;
-  if (threadIdx.x == 0) {
-    gen = ldc(&c->bar_gen);
+  if (threadIdx.x < kWave) {
+    const int lane = lane_id();
     // two-level arrival: the last workgroup of a group arrives for the group
-    const unsigned g = blockIdx.x % kGroups;
-    const unsigned gsize = (gridDim.x - g + kGroups - 1) / kGroups;
-    const unsigned ngroups = gridDim.x < (unsigned)kGroups ? gridDim.x : (unsigned)kGroups;
-    bool last = false;
-    const unsigned pg = __hip_atomic_fetch_add(&c->grp_count[g][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (pg == gsize - 1) {
-      stc(&c->grp_count[g][0], 0u);
-      mem_wait();
-      const unsigned prev = __hip_atomic_fetch_add(&c->bar_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = prev == ngroups - 1;
-    }
-    s_last = last ? 1 : 0;
-  }
-  __syncthreads();
-  if (s_last) {
-    if (threadIdx.x < kWave) control_step(c, P);
-    if (threadIdx.x == 0) {
-      stc(&c->bar_count, 0u);
-      mem_wait();
-      __hip_atomic_fetch_add(&c->bar_gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_ok = 1;
-    }
-  } else if (threadIdx.x == 0) {
-    int ok = 1;
-    const uint64_t t0 = wall_clock64();
-    while (ldc(&c->bar_gen) == gen) {
-      __builtin_amdgcn_s_sleep(1);
-      if (ldc(&c->abort)) { ok = 0; break; }
-      // 100 MHz constant clock: give up after 30 s
-      if (wall_clock64() - t0 > 3000000000ULL) {
-        stc(&c->abort, 1);
-        ok = 0;
-        break;
+    int last = 0;
+    if (lane == 0) {
+      const unsigned g = blockIdx.x % kGroups;
+      const unsigned gsize = (gridDim.x - g + kGroups - 1) / kGroups;
+      const unsigned ngroups = gridDim.x < (unsigned)kGroups ? gridDim.x : (unsigned)kGroups;
+      const unsigned pg = __hip_atomic_fetch_add(&c->grp_count[g][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (pg + 1 == gen * gsize) {
+        const unsigned prev = __hip_atomic_fetch_add(&c->bar_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = prev + 1 == gen * ngroups ? 1 : 0;
       }
     }
-    s_ok = ok;
+    last = __builtin_amdgcn_readfirstlane(last);
+    int ok = 1;
+    if (last) {
+      control_step(c, P, st, gen, shift);
+      if (lane < kPub) pub[lane] = pub_word(st, lane);
+    } else {
+      const unsigned long long want = (unsigned long long)(gen & 0xffffu);
+      const uint64_t t0 = wall_clock64();
+      unsigned long long x = 0;
+      for (int spin = 1;; ++spin) {
+        x = ldc(&c->pub[lane < kPub ? lane : 0]);
+        if (ballot((x >> kPubBits) != want) == 0) break;
+        __builtin_amdgcn_s_sleep(1);
+        if ((spin & 63) != 0) continue;
+        // 100 MHz constant clock: give up after 30 s
+        const bool late = wall_clock64() - t0 > 3000000000ULL;
+        if (late && lane == 0) stc(&c->abort, 1);
+        if (__builtin_amdgcn_readfirstlane(late || ldc(&c->abort) != 0 ? 1 : 0)) {
+          ok = 0;
+          break;
+        }
+      }
+      if (lane < kPub) pub[lane] = x & ((1ULL << kPubBits) - 1ULL);
+    }
+    if (lane == 0) s_ok = ok;
   }
   __syncthreads();
+  st = phase_state(pub);
   return s_ok != 0;
 }
 
@@ -888,6 +945,18 @@ __device__ __forceinline__ int block_count(bool p, int* tmp) {
 
 using KernArgs = const __attribute__((address_space(4))) PeelArgs*;
 
+// The same for two conditions: (threads with q << 16) | threads with p (kT < 2^16).
+__device__ __forceinline__ int block_count2(bool p, bool q, int* tmp) {
+  const uint64_t mp = ballot(p), mq = ballot(q);
+  if (lane_id() == 0) tmp[threadIdx.x / kWave] = (__popcll(mq) << 16) | __popcll(mp);
+  __syncthreads();
+  int n = 0;
+#pragma unroll 4
+  for (int i = 0; i < kWaves; ++i) n += tmp[i];
+  __syncthreads();
+  return n;
+}
+
 // NI: walk entries in flight per thread; SU (2 or 4): live-list entries per
 // thread and step of the level sweep
 template <int NI, int SU>
@@ -923,27 +992,43 @@ __device__ __forceinline__ void peel_body() {
   const int shift = walk_shift(ldc(&c->wbound), ((const PeelArgs*)ka)->m, qbits);
   unsigned long long my_work = 0;  // entries walked by this wavefront
 
+  __shared__ unsigned long long s_pub[kPub];
+  // the state left by the previous launch (or k_peel_init)
+  unsigned gen = ldc(&c->bar_gen);
+  PhaseState st;
+  st.phase = ldc(&c->phase);
+  st.acur = ldc(&c->acur);
+  st.mode = ldc(&c->mode);
+  st.probe = ldc(&c->probe);
+  st.first = ldc(&c->first);
+  st.qlen = 0;
+  st.k = ldc(&c->k);
+  st.r = ldc(&c->r);
+  st.acnt = ldc(&c->acnt);
+  st.units = 0;
+
   for (;;) {
     // the arguments are read anew in each phase: kept in scalar registers over
     // all phases they would spill, and take vector registers with them
     asm volatile("" : "+s"(ka));
     const PeelArgs& P = *(const PeelArgs*)ka;
-    const int phase = ldc(&c->phase);
+    const int phase = st.phase;
     if (phase == PH_DONE || phase == PH_COMPACT) break;
-    const int k = ldc(&c->k);
+    const int k = st.k;
     const int l = k - 2;
-    const int r = ldc(&c->r);
-    const int acur = ldc(&c->acur);
+    const int r = st.r;
+    const int acur = st.acur;
+    PhaseCounts* const cw = &c->w[gen & 1];
     if (phase == PH_SWEEP) {
       // live-edge list of the new level and its minimum support; the live
       // edges with sup <= k-1 are taken at once as the frontier of level k+1
       // (the control step keeps them only if that level is not skipped, in
       // which case none is taken)
-      const int first = ldc(&c->first);
-      const int64_t cnt = first ? P.m : (int64_t)ldc(&c->acnt);
+      const int first = st.first;
+      const int64_t cnt = first ? P.m : (int64_t)st.acnt;
       const int32_t* A = P.alist[acur];
-      StagedList LA{S.l.a, kStageA, &s_fill[0], &s_fill[1], &c->w_alive, P.alist[acur ^ 1]};
-      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[(r + 1) & 1], &c->w_q, qbits, shift}};
+      StagedList LA{S.l.a, kStageA, &s_fill[0], &s_fill[1], &cw->alive, P.alist[acur ^ 1]};
+      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[(r + 1) & 1], &cw->q, qbits, shift}};
       const int kt = k + 1, stamp = r + 1;
       int mins = kIntMax;
       unsigned long long wsum = 0;
@@ -989,14 +1074,14 @@ __device__ __forceinline__ void peel_body() {
       }
       staged_flush(LA);
       staged_flush(P, LQ);
-      block_min_to(mins, s_tmp, &c->w_minsup);
-      block_sum_to(wsum, s_w64, &c->w_fwork);
+      block_min_to(mins, s_tmp, &cw->minsup);
+      block_sum_to(wsum, s_w64, &cw->fwork);
     } else if (phase == PH_START || phase == PH_DENSE) {
       // collect live edges with sup <= k-2 (level start after a skip, or dense re-scan)
-      const int64_t cnt = ldc(&c->acnt);
+      const int64_t cnt = st.acnt;
       const int32_t* A = P.alist[acur];
       const int stamp = phase == PH_START ? r : r + 1;
-      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[stamp & 1], &c->w_q, qbits, shift}};
+      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[stamp & 1], &cw->q, qbits, shift}};
       unsigned long long wsum = 0;  // level start: shorter live row over the frontier
       for (int64_t base = (int64_t)blockIdx.x * kT; base < cnt; base += (int64_t)gridDim.x * kT) {
         const int64_t i = base + tid;
@@ -1018,19 +1103,19 @@ __device__ __forceinline__ void peel_body() {
         staged_append_n<1>(P, LQ, take, e, s_tmp);
       }
       staged_flush(P, LQ);
-      if (phase == PH_START) block_sum_to(wsum, s_w64, &c->w_fwork);
+      if (phase == PH_START) block_sum_to(wsum, s_w64, &cw->fwork);
     } else if (phase == PH_PROC) {
       // The round's walks, laid end to end, in parts of equal length (see
       // kMinChunk): every workgroup finds the record its part starts in by a
       // search of the records' starts, kT probes at a time, stages the part's
       // records in LDS and walks its entries, a thread taking NI of them at
       // once.  Nothing is handed from one workgroup to another.
-      const int qn = ldc(&c->qlen);
-      const unsigned long long units = ldc(&c->qunits);
-      const bool sparse = ldc(&c->mode) == TRUSS_PEEL_SPARSE;
-      const int probe = ldc(&c->probe);
+      const int qn = st.qlen;
+      const unsigned long long units = st.units;
+      const bool sparse = st.mode == TRUSS_PEEL_SPARSE;
+      const int probe = st.probe;
       const FrontierQueue Q = P.fq[r & 1];
-      const QueueOut out{P.fq[(r + 1) & 1], &c->w_q, qbits, shift};
+      const QueueOut out{P.fq[(r + 1) & 1], &cw->q, qbits, shift};
       WaveQueue wq{S.r.qe[wv], S.r.qu[wv], S.r.qv[wv], 0};
       WalkTabs& W = S.r.W;
       const int umask = (1 << shift) - 1;
@@ -1043,17 +1128,19 @@ __device__ __forceinline__ void peel_body() {
       const bool drawn = parts > gridDim.x;  // more parts than workgroups: the later ones are drawn
       for (unsigned long long part = blockIdx.x; part < parts;) {
         // the next part is drawn early: its number is needed after this one's walk
-        if (drawn && tid == 0) s_part = atomicAdd(&c->w_fetch, 1);
+        if (drawn && tid == 0) s_part = atomicAdd(&cw->fetch, 1);
         const unsigned long long lo = part * pu;
         const unsigned long long hi = lo + pu < units ? lo + pu : units;
-        // x0: the last record that starts at or before unit lo
+        // x0: the last record that starts at or before unit lo.  A frontier of
+        // up to kT records is read whole, and x0 found among the records read.
         int64_t x0 = 0;
-        for (int64_t span = lo > 0 ? qn : 1; span > 1;) {
-          const int64_t st = (span + kT - 1) / kT;
-          const int64_t d = tid * st;
+        const bool whole = qn <= kT;
+        for (int64_t span = lo > 0 && !whole ? qn : 1; span > 1;) {
+          const int64_t sp = (span + kT - 1) / kT;
+          const int64_t d = tid * sp;
           const int n = block_count(d < span && ldc(&Q.pre[x0 + d]) <= lo, s_tmp);
-          x0 += (int64_t)(n - 1) * st;
-          span = span - (int64_t)(n - 1) * st < st ? span - (int64_t)(n - 1) * st : st;
+          x0 += (int64_t)(n - 1) * sp;
+          span = span - (int64_t)(n - 1) * sp < sp ? span - (int64_t)(n - 1) * sp : sp;
         }
         for (;;) {
           // up to kT records from x0 on
@@ -1069,17 +1156,21 @@ __device__ __forceinline__ void peel_body() {
             next = ldc(&Q.pre[x0 + kT]);
             next = next < hi ? next : hi;
           }
-          const bool in = pre < hi;
-          if (in) {
-            W.pre[tid] = (int)((long long)pre - (long long)lo);
-            W.e[tid] = (int32_t)(uint32_t)eb;
-            W.base[tid] = (uint32_t)(eb >> 32);
-            W.a[tid] = (int32_t)(uint32_t)ab;
-            W.b[tid] = (int32_t)(ab >> 32);
-            W.tab[tid] = tab;
-            if (shift > 0) W.len[tid] = P.vinfo[(uint32_t)ab].len;
+          // records before x0 (whole only) and records in the part
+          const int cnt2 = block_count2(whole && pre <= lo, pre < hi, s_tmp);
+          const int skip = whole ? (cnt2 & 0xffff) - 1 : 0;
+          const int nrec = (cnt2 >> 16) - skip;
+          const int y0 = tid - skip;
+          if (y0 >= 0 && pre < hi) {
+            W.pre[y0] = (int)((long long)pre - (long long)lo);
+            W.e[y0] = (int32_t)(uint32_t)eb;
+            W.base[y0] = (uint32_t)(eb >> 32);
+            W.a[y0] = (int32_t)(uint32_t)ab;
+            W.b[y0] = (int32_t)(ab >> 32);
+            W.tab[y0] = tab;
+            if (shift > 0) W.len[y0] = P.vinfo[(uint32_t)ab].len;
           }
-          const int nrec = block_count(in, s_tmp);
+          __syncthreads();
           const int ub = W.pre[0] > 0 ? W.pre[0] : 0, ue = (int)(next - lo);
           int top = 1;
           while (2 * top < nrec) top <<= 1;
@@ -1127,7 +1218,8 @@ __device__ __forceinline__ void peel_body() {
       }
       if (sparse) block_flush(P, wq, S.r.qe, S.r.qu, S.r.qv, out, s_tmp, s_w64);
     }
-    if (!phase_barrier(c, P)) break;
+    ++gen;
+    if (!phase_barrier(c, P, st, gen, shift, s_pub)) break;
   }
   if (lane_id() == 0 && my_work) atomicAdd(&c->w_work, my_work);
 }
@@ -1243,12 +1335,15 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     c->bar_count = 0;
     c->bar_gen = 0;
     for (int g = 0; g < kGroups; ++g) c->grp_count[g][0] = 0;
-    c->w_fetch = 0;
-    c->w_q = 0ULL;
-    c->w_alive = 0;
-    c->w_minsup = kIntMax;
+    for (int i = 0; i < kPub; ++i) c->pub[i] = 0ULL;  // tag 0: the first barrier waits for 1
+    for (int i = 0; i < 2; ++i) {
+      c->w[i].fetch = 0;
+      c->w[i].q = 0ULL;
+      c->w[i].alive = 0;
+      c->w[i].minsup = kIntMax;
+      c->w[i].fwork = 0ULL;
+    }
     c->w_work = 0ULL;
-    c->w_fwork = 0ULL;
     c->phase = PH_SWEEP;
     c->k = first_level - 1;  // the first sweep takes the frontier of level first_level
     c->r = 0;
