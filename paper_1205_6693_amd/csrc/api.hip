@@ -23,12 +23,12 @@ __global__ void k_scatter_out(const int32_t* __restrict__ val, const int32_t* __
   if (e < m) out[perm ? perm[e] : e] = val[e];
 }
 
-__global__ void k_scatter_sup(const int2* __restrict__ sr, const int32_t* __restrict__ perm, int64_t m,
+__global__ void k_scatter_sup(const int32_t* __restrict__ sup, const int32_t* __restrict__ perm, int64_t m,
                               int32_t* __restrict__ out, unsigned long long* total) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   unsigned long long x = 0;
   if (e < m) {
-    const int s = sr[e].x;
+    const int s = sup[e];
     out[perm ? perm[e] : e] = s;
     x = (unsigned long long)s;
   }
@@ -40,10 +40,10 @@ __global__ void k_zero_u64(unsigned long long* p) { *p = 0; }
 
 // supports out of reach of every level for edges that must not be peeled
 constexpr int kFrozenSup = 1 << 29;
-__global__ void k_freeze(int2* __restrict__ sr, const int32_t* __restrict__ perm, const uint8_t* __restrict__ frozen,
+__global__ void k_freeze(int32_t* __restrict__ sup, const int32_t* __restrict__ perm, const uint8_t* __restrict__ frozen,
                          int64_t m) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e < m && frozen[perm ? perm[e] : e]) sr[e].x = kFrozenSup;
+  if (e < m && frozen[perm ? perm[e] : e]) sup[e] = kFrozenSup;
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ x, int64_t m, int32_t v) {
@@ -51,10 +51,10 @@ __global__ void k_fill_i32(int32_t* __restrict__ x, int64_t m, int32_t v) {
   if (i < m) x[i] = v;
 }
 
-__global__ void k_sum_sup(const int2* __restrict__ sr, int64_t m, unsigned long long* total) {
+__global__ void k_sum_sup(const int32_t* __restrict__ sup, int64_t m, unsigned long long* total) {
   unsigned long long x = 0;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
-    x += (unsigned long long)sr[e].x;
+    x += (unsigned long long)sup[e];
   x = wave_sum(x);
   if (lane_id() == 0 && x) atomicAdd(total, x);
 }
@@ -164,7 +164,7 @@ void resolve(const truss_options* in, SupPlan* sp, PeelPlan* pp, int* fallback, 
 struct Plan {
   int* d_err = nullptr;
   unsigned long long* d_total = nullptr;
-  int2* sr = nullptr;
+  int32_t *sup = nullptr, *stamp = nullptr;
   int32_t* truss_canon = nullptr;
   int32_t *h = nullptr, *ch = nullptr, *psi = nullptr;  // upper bound (Procedure 6)
 };
@@ -184,7 +184,8 @@ void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   p.d_total = a.take<unsigned long long>(8);
   size_t tmp_bytes = 0;
   build_workspace(g, a, true, &tmp_bytes);
-  p.sr = a.take<int2>((size_t)g->m + 1);
+  p.sup = a.take<int32_t>((size_t)g->m + 1);
+  p.stamp = a.take<int32_t>((size_t)g->m + 1);
   p.truss_canon = a.take<int32_t>((size_t)g->m + 1);
   take_bound(g, a, p);
   DevGraph dg;
@@ -265,10 +266,11 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
   rc = build_graph(g, a, dg, p.d_err, s, true);
   if (rc) return rc;
   tm.mark(1);
-  p.sr = a.take<int2>((size_t)g->m + 1);
+  p.sup = a.take<int32_t>((size_t)g->m + 1);
+  p.stamp = a.take<int32_t>((size_t)g->m + 1);
   p.truss_canon = a.take<int32_t>((size_t)g->m + 1);
   take_bound(g, a, p);
-  rc = compute_support(dg, sp, p.sr, a, s, trace);
+  rc = compute_support(dg, sp, p.sup, p.stamp, a, s, trace);
   if (rc) return rc;
   tm.mark(2);
   PeelResult pr;
@@ -278,7 +280,7 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
     // the counters of long rows live in the (unused) peeling region
     int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
     if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
-    compute_upper_bound(dg, p.sr, p.h, p.ch, p.psi, hs, s);
+    compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
     if (g->m > 0)
       hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, p.psi, dg.perm, g->m, out);
     TRUSS_HIP(hipGetLastError());
@@ -286,25 +288,25 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
     tm.mark(3);
   } else if (mode == kModeSupport) {
     if (g->m > 0)
-      hipLaunchKernelGGL(k_scatter_sup, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sr, dg.perm, g->m, out, p.d_total);
+      hipLaunchKernelGGL(k_scatter_sup, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sup, dg.perm, g->m, out, p.d_total);
     TRUSS_HIP(hipMemcpyAsync(&tot, p.d_total, sizeof(tot), hipMemcpyDeviceToHost, s));
     TRUSS_HIP(hipStreamSynchronize(s));
     if (triangles) *triangles = (int64_t)(tot / 3);
     tm.mark(3);
   } else {
-    if (stats && g->m > 0) hipLaunchKernelGGL(k_sum_sup, dim3(1024), dim3(kT), 0, s, p.sr, g->m, p.d_total);
+    if (stats && g->m > 0) hipLaunchKernelGGL(k_sum_sup, dim3(1024), dim3(kT), 0, s, p.sup, g->m, p.d_total);
     int32_t* tc = dg.perm ? p.truss_canon : out;
     if (sub && g->m > 0) {
       if (sub->sup_out)
-        hipLaunchKernelGGL(k_scatter_sup, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sr, dg.perm, g->m, sub->sup_out,
+        hipLaunchKernelGGL(k_scatter_sup, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sup, dg.perm, g->m, sub->sup_out,
                            p.d_total);
       if (sub->frozen)
-        hipLaunchKernelGGL(k_freeze, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sr, dg.perm, sub->frozen, g->m);
+        hipLaunchKernelGGL(k_freeze, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sup, dg.perm, sub->frozen, g->m);
       if (sub->stop_level > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, g->m, 0);
       pp.first_level = sub->first_level;
       pp.stop_level = sub->stop_level;
     }
-    rc = peel(dg, pp, p.sr, tc, a, &pr, s, trace);
+    rc = peel(dg, pp, p.sup, p.stamp, tc, a, &pr, s, trace);
     if (rc) return rc;
     if (dg.perm && g->m > 0)
       hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, dg.perm, g->m, out);
@@ -463,15 +465,16 @@ int run_topdown(const truss_graph* g, int32_t t, int32_t* out, int32_t* kmin_out
   DevGraph dg;
   rc = build_graph(g, a, dg, p.d_err, s);
   if (rc) return rc;
-  p.sr = a.take<int2>((size_t)g->m + 1);
+  p.sup = a.take<int32_t>((size_t)g->m + 1);
+  p.stamp = a.take<int32_t>((size_t)g->m + 1);
   p.truss_canon = g->fmt == TRUSS_FMT_EDGES ? a.take<int32_t>((size_t)g->m + 1) : nullptr;
   take_bound(g, a, p);
-  rc = compute_support(dg, sp, p.sr, a, s, nullptr);
+  rc = compute_support(dg, sp, p.sup, nullptr, a, s, nullptr);
   if (rc) return rc;
   {
     int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
     if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
-    compute_upper_bound(dg, p.sr, p.h, p.ch, p.psi, hs, s);
+    compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
   }
   // the top-down region follows the whole single-graph layout
   Arena full;

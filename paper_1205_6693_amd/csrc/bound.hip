@@ -29,7 +29,7 @@ __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)
 // vertex's slice of hs (deg+1 counters starting at row_ptr[v] + v), then a
 // scan from the top finds the largest y with at least y supports >= y.
 __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ seid,
-                                               const int2* __restrict__ sr, int32_t n, int32_t* __restrict__ h,
+                                               const int32_t* __restrict__ sup, int32_t n, int32_t* __restrict__ h,
                                                int32_t* __restrict__ ch, int32_t* __restrict__ hs) {
   const int lane = lane_id();
   const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_p
     const int64_t d = row_ptr[v + 1] - rb;
     int64_t hv = 0, cv = 0;
     if (d <= kWave) {
-      const int s = lane < d ? sr[seid[rb + lane]].x : -1;
+      const int s = lane < d ? sup[seid[rb + lane]] : -1;
       int64_t lo = 0, hi = d;
       while (lo < hi) {
         const int64_t x = (lo + hi + 1) >> 1;
@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_p
       wait_memory();
       wave_sync();
       for (int64_t j = lane; j < d; j += kWave) {
-        const int64_t sv = sr[seid[rb + j]].x;
+        const int64_t sv = sup[seid[rb + j]];
         atomicAdd(&cnt[sv < d ? sv : d], 1);
       }
       wait_memory();
@@ -83,11 +83,11 @@ __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_p
 }
 
 __global__ void __launch_bounds__(kT) k_psi(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
-                                            const int2* __restrict__ sr, const int32_t* __restrict__ h,
+                                            const int32_t* __restrict__ sup, const int32_t* __restrict__ h,
                                             const int32_t* __restrict__ ch, int64_t m, int32_t* __restrict__ psi) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
-  const int s = sr[e].x;
+  const int s = sup[e];
   const int u = eu[e], v = ev[e];
   const int hu = h[u], hv = h[v];
   const int xu = (s >= hu && ch[u] == hu) ? hu - 1 : hu;
@@ -99,13 +99,13 @@ __global__ void __launch_bounds__(kT) k_psi(const int32_t* __restrict__ eu, cons
 
 }  // namespace
 
-void compute_upper_bound(const DevGraph& dg, const int2* sr, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
+void compute_upper_bound(const DevGraph& dg, const int32_t* sup, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
                          hipStream_t s) {
   if (dg.m == 0) return;
   const unsigned gw = 256 * 8;
-  hipLaunchKernelGGL(k_hindex, dim3(gw), dim3(kT), 0, s, dg.row_ptr, dg.seid, sr, dg.n, h, ch, hs);
+  hipLaunchKernelGGL(k_hindex, dim3(gw), dim3(kT), 0, s, dg.row_ptr, dg.seid, sup, dg.n, h, ch, hs);
   const int64_t b = (dg.m + kT - 1) / kT;
-  hipLaunchKernelGGL(k_psi, dim3((unsigned)b), dim3(kT), 0, s, dg.eu, dg.ev, sr, h, ch, dg.m, psi);
+  hipLaunchKernelGGL(k_psi, dim3((unsigned)b), dim3(kT), 0, s, dg.eu, dg.ev, sup, h, ch, dg.m, psi);
 }
 
 }  // namespace truss

@@ -99,13 +99,13 @@ struct PeelPlan {
   bool timed = true;    // time the kernel's launches with HIP events
 };
 
-// Support: sr[e].x = sup(e) for every canonical edge (sr must be zeroed inside).
+// Support: sup[e] for every canonical edge; stamp[e] = 0 (round stamps of the peeling, nullable).
 // trace (nullable): receives each bin's method, features and time.
 size_t support_workspace(const DevGraph& dg, Arena& a);
-int compute_support(const DevGraph& dg, const SupPlan& plan, int2* sr, Arena& a, hipStream_t s,
+int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32_t* stamp, Arena& a, hipStream_t s,
                     truss_trace* trace);
 
-// Peeling: truss[e] for every canonical edge; sr holds sup on entry.
+// Peeling: truss[e] for every canonical edge; sup holds the supports and stamp zeros on entry.
 struct PeelResult {
   int32_t kmax = 0, levels = 0;
   int64_t subrounds = 0, work = 0;
@@ -116,12 +116,12 @@ struct PeelResult {
   double kernel_ms = 0;  // time inside the persistent peeling kernel (all launches)
 };
 size_t peel_workspace(const DevGraph& dg, Arena& a);
-int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_canon, Arena& a,
+int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp, int32_t* truss_canon, Arena& a,
          PeelResult* res, hipStream_t s, truss_trace* trace);
 
-// Upper bound psi(e) (Procedure 6) for every canonical edge; sr holds sup.
+// Upper bound psi(e) (Procedure 6) for every canonical edge from the supports.
 // h, ch: n entries of scratch each; psi: m entries; hs: 2m + n + 1 entries.
-void compute_upper_bound(const DevGraph& dg, const int2* sr, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
+void compute_upper_bound(const DevGraph& dg, const int32_t* sup, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
                          hipStream_t s);
 
 // Core numbers of every vertex (k-cores); syncs the stream once per peeling

@@ -192,7 +192,12 @@ struct PeelArgs {
   const VInfo* vinfo;
   const int32_t* eu;
   const int32_t* ev;
-  int2* sr;
+  // support and round stamp, in arrays of their own: a walk's first edges have
+  // consecutive ids, and both its stamp reads and its decrements are served by
+  // the 64-byte line (atomics at about 25 G lines/s), so 4 bytes an edge halve their
+  // number against interleaved pairs
+  int32_t* sup;
+  int32_t* stamp;
   int32_t* truss;
   int32_t* alist[2];
   FrontierQueue fq[2];
@@ -214,14 +219,6 @@ template <typename T>
 __device__ __forceinline__ void stc(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ int2 ldc2(const int2* p) {
-  const unsigned long long x = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-  return make_int2((int)(uint32_t)x, (int)(uint32_t)(x >> 32));
-}
-__device__ __forceinline__ int ldc_stamp(const int2* p) { return ldc(&p->y); }
-__device__ __forceinline__ void stc_stamp(int2* p, int v) { stc(&p->y, v); }
-
 // wait until this lane's global loads, stores and atomics have completed
 __device__ __forceinline__ void mem_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -575,7 +572,7 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTab
 #pragma unroll
   for (int q = 0; q < NI; ++q) {
     ok[q] = ok[q] && w[q] != W.b[x[q]];
-    if (ok[q]) s1[q] = ldc_stamp(&P.sr[e1[q]]);
+    if (ok[q]) s1[q] = ldc(&P.stamp[e1[q]]);
   }
 #pragma unroll
   for (int q = 0; q < NI; ++q) ok[q] = ok[q] && !removed_at(s1[q], r);
@@ -625,7 +622,7 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTab
   }
 #pragma unroll
   for (int q = 0; q < NI; ++q)
-    if (ok[q]) s2[q] = ldc_stamp(&P.sr[e2[q]]);
+    if (ok[q]) s2[q] = ldc(&P.stamp[e2[q]]);
   // the triangle is destroyed now unless an edge is removed, and it belongs
   // to its frontier edge of smallest id; each other edge not in F_r loses one
   bool d1[NI], d2[NI];
@@ -638,19 +635,19 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTab
     d2[q] = live && s2[q] != r;
     old1[q] = 0;
     old2[q] = 0;
-    if (d1[q]) old1[q] = atomicSub(&P.sr[e1[q]].x, 1);
-    if (d2[q]) old2[q] = atomicSub(&P.sr[e2[q]].x, 1);
+    if (d1[q]) old1[q] = atomicSub(&P.sup[e1[q]], 1);
+    if (d2[q]) old2[q] = atomicSub(&P.sup[e2[q]], 1);
   }
   if (!sparse) return;
 #pragma unroll
   for (int q = 0; q < NI; ++q) {
     if (d1[q] && old1[q] == l + 1) {
-      stc_stamp(&P.sr[e1[q]], r + 1);
+      stc(&P.stamp[e1[q]], r + 1);
       P.truss[e1[q]] = k;
       f1[q] = e1[q];
     }
     if (d2[q] && old2[q] == l + 1) {
-      stc_stamp(&P.sr[e2[q]], r + 1);
+      stc(&P.stamp[e2[q]], r + 1);
       P.truss[e2[q]] = k;
       f2[q] = e2[q];
     }
@@ -1036,7 +1033,7 @@ __device__ __forceinline__ void peel_body() {
       for (int64_t base = (int64_t)blockIdx.x * kT * SU; base < cnt; base += (int64_t)gridDim.x * kT * SU) {
         const int64_t i0 = base + (int64_t)tid * SU;
         int32_t e[SU];
-        int2 sv[SU];
+        int sv[SU], sk[SU];
         bool live[SU], take[SU];
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
@@ -1045,18 +1042,22 @@ __device__ __forceinline__ void peel_body() {
         }
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
-          sv[u] = make_int2(0, 1);
-          if (i0 + u < cnt) sv[u] = ldc2(&P.sr[e[u]]);
+          sv[u] = 0;
+          sk[u] = 1;
+          if (i0 + u < cnt) {
+            sk[u] = ldc(&P.stamp[e[u]]);
+            sv[u] = ldc(&P.sup[e[u]]);
+          }
         }
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
-          live[u] = sv[u].y == 0;
+          live[u] = sk[u] == 0;
           take[u] = false;
           if (live[u]) {
-            mins = sv[u].x < mins ? sv[u].x : mins;
-            take[u] = sv[u].x <= kt - 2;
+            mins = sv[u] < mins ? sv[u] : mins;
+            take[u] = sv[u] <= kt - 2;
             if (take[u]) {
-              stc_stamp(&P.sr[e[u]], stamp);
+              stc(&P.stamp[e[u]], stamp);
               P.truss[e[u]] = kt;
               const int du = P.vinfo[P.eu[e[u]]].len, dv = P.vinfo[P.ev[e[u]]].len;
               wsum += (unsigned long long)(du < dv ? du : dv);
@@ -1089,10 +1090,9 @@ __device__ __forceinline__ void peel_body() {
         int32_t e[1] = {0};
         if (i < cnt) {
           e[0] = ldc(&A[i]);
-          const int2 sv = ldc2(&P.sr[e[0]]);
-          take[0] = sv.y == 0 && sv.x <= l;
+          take[0] = ldc(&P.stamp[e[0]]) == 0 && ldc(&P.sup[e[0]]) <= l;
           if (take[0]) {
-            stc_stamp(&P.sr[e[0]], stamp);
+            stc(&P.stamp[e[0]], stamp);
             P.truss[e[0]] = k;
             if (phase == PH_START) {
               const int du = P.vinfo[P.eu[e[0]]].len, dv = P.vinfo[P.ev[e[0]]].len;
@@ -1236,15 +1236,15 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8)))
 
 // One bit per edge, set when the edge is removed: the liveness test of the
 // row compaction reads this bitmap (m/8 bytes, cache-resident) instead of
-// one scattered support/stamp pair per row entry.
-__global__ void __launch_bounds__(256) k_dead_bits(const int2* __restrict__ sr, int64_t m,
+// one scattered stamp per row entry.
+__global__ void __launch_bounds__(256) k_dead_bits(const int32_t* __restrict__ stamp, int64_t m,
                                                    unsigned long long* __restrict__ dead) {
   const int lane = lane_id();
   const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
   for (int64_t base = gw * kWave; base < m; base += nw * kWave) {
     const int64_t e = base + lane;
-    const unsigned long long bits = ballot(e < m && sr[e].y != 0);
+    const unsigned long long bits = ballot(e < m && stamp[e] != 0);
     if (lane == 0) dead[base / kWave] = bits;
   }
 }
@@ -1431,7 +1431,7 @@ size_t peel_workspace(const DevGraph& dg, Arena& a) {
   return a.used;
 }
 
-int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_canon, Arena& a, PeelResult* res,
+int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp, int32_t* truss_canon, Arena& a, PeelResult* res,
          hipStream_t s, truss_trace* trace) {
   PeelLayout L;
   carve(dg, a, L);
@@ -1472,7 +1472,8 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
   P.vinfo = L.vinfo;
   P.eu = dg.eu;
   P.ev = dg.ev;
-  P.sr = sr;
+  P.sup = sup;
+  P.stamp = stamp;
   P.truss = truss_canon;
   for (int i = 0; i < 2; ++i) {
     P.alist[i] = L.alist[i];
@@ -1506,7 +1507,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int2* sr, int32_t* truss_cano
       if (hipEventElapsedTime(&t, ev0, ev1) == hipSuccess) kernel_ms += t;
     }
     if (h.abort || h.err || h.phase != PH_COMPACT) break;
-    hipLaunchKernelGGL(k_dead_bits, dim3(4096), dim3(256), 0, s, sr, dg.m, L.dead);
+    hipLaunchKernelGGL(k_dead_bits, dim3(4096), dim3(256), 0, s, stamp, dg.m, L.dead);
     hipLaunchKernelGGL(k_compact, dim3(2048), dim3(256), 0, s, dg.col, dg.seid, L.vinfo, dg.n, L.dead, L.ctl);
   }
   if (ev0) (void)hipEventDestroy(ev0);

@@ -162,11 +162,13 @@ __global__ void __launch_bounds__(kBins * kWave) k_sup_decide(SupCtl* ctl, int64
   }
 }
 
-// sup(e) in edge-id order, round stamp 0, from the counts by oriented position
+// sup(e) in edge-id order from the counts by oriented position, and round stamps 0
 __global__ void k_sup_finish(const int32_t* __restrict__ supo, const int32_t* __restrict__ oeid, int64_t m,
-                             int2* __restrict__ sr) {
+                             int32_t* __restrict__ sup, int32_t* __restrict__ stamp) {
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j < m) sr[oeid[j]] = make_int2(supo[j], 0);
+  if (j >= m) return;
+  sup[oeid[j]] = supo[j];
+  if (stamp) stamp[j] = 0;
 }
 
 // ---- the hash method: N+(a) in an LDS hash table, the (b, c) pairs walked by
@@ -719,7 +721,7 @@ size_t support_workspace(const DevGraph& dg, Arena& a) {
   return a.used;
 }
 
-int compute_support(const DevGraph& dg, const SupPlan& plan, int2* sr, Arena& a, hipStream_t s,
+int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32_t* stamp, Arena& a, hipStream_t s,
                     truss_trace* trace) {
   SupLayout L;
   carve(dg, a, L);
@@ -756,7 +758,7 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int2* sr, Arena& a,
     hipLaunchKernelGGL(k_sup_merge, dim3(b == 0 ? gw : gb), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b, L.ctl,
                        L.supo);
   }
-  hipLaunchKernelGGL(k_sup_finish, dim3(grid_for(m)), dim3(kT), 0, s, L.supo, dg.oeid, m, sr);
+  hipLaunchKernelGGL(k_sup_finish, dim3(grid_for(m)), dim3(kT), 0, s, L.supo, dg.oeid, m, sup, stamp);
   if (timed) (void)hipEventRecord(ev[kBins], s);
   TRUSS_HIP(hipGetLastError());
   if (trace) {
