@@ -421,7 +421,20 @@ __device__ void search_rows(const int* nb, const int* pre, const int* offj, cons
   }
 }
 
-// bin 0, hash: a wavefront per vertex, vertices fetched kFetch0 at a time
+// How the workers of a grid share a bin's list: worker w starts with entries
+// [w * step, (w + 1) * step) and draws further ones from ctl->fetch only while
+// the list is longer than one share each.  An empty bin costs no atomic (1024
+// workgroups drawing from an empty list took 31 us: same-address atomics are
+// served one after another).
+struct ListShare {
+  int first, step, count, workers;
+  __device__ __forceinline__ bool shared() const { return (long long)workers * step < count; }
+};
+
+// bin 0, hash: a wavefront per vertex, up to kFetch0 vertices at a time -- fewer
+// on a short list, so that every wavefront gets some: shares of 16 of a list of
+// 16 K vertices left seven of eight wavefronts idle (support of the R-MAT graph of
+// 1.2 M edges 3.1 -> 0.86 ms)
 constexpr int kFetch0 = 16;
 __global__ void __launch_bounds__(kT) k_sup_hash_wave(const int64_t* __restrict__ orow,
                                                       const int32_t* __restrict__ ocol,
@@ -441,12 +454,14 @@ __global__ void __launch_bounds__(kT) k_sup_hash_wave(const int64_t* __restrict_
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[0]);
   WalkTabs T{s_pre[w], s_offj[w], s_wi[w], s_tab[w], s_cnt[w], s_own[w]};
-  for (;;) {
-    int first = 0;
-    if (lane == 0) first = atomicAdd(&ctl->fetch[0], kFetch0);
-    first = __shfl(first, 0, kWave);
-    if (first >= count) break;
-    const int last = first + kFetch0 < count ? first + kFetch0 : count;
+  ListShare L;
+  L.count = count;
+  L.workers = (int)gridDim.x * W;
+  L.step = count / (4 * L.workers);
+  L.step = L.step < 1 ? 1 : L.step > kFetch0 ? kFetch0 : L.step;
+  L.first = ((int)blockIdx.x * W + w) * L.step;
+  for (int first = L.first; first < count;) {
+    const int last = first + L.step < count ? first + L.step : count;
     for (int idx = first; idx < last; ++idx) {
       const int32_t a = vlist[count - 1 - idx];  // the bin's list backwards: see k_sup_bin
       const int64_t base = orow[a];
@@ -464,6 +479,9 @@ __global__ void __launch_bounds__(kT) k_sup_hash_wave(const int64_t* __restrict_
       }
       wave_sync();
     }
+    if (!L.shared()) break;
+    if (lane == 0) first = L.workers * L.step + atomicAdd(&ctl->fetch[0], L.step);
+    first = __shfl(first, 0, kWave);
   }
 }
 
@@ -489,15 +507,10 @@ __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8, 8))
   const int w = threadIdx.x / kWave;
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
   WalkTabs T{s_pre, s_offj, s_wi, s_tab, s_cnt, s_own[w]};
-  for (;;) {
-    if (threadIdx.x == 0) {
-      s_idx = atomicAdd(&ctl->fetch[bin], 1);
-      s_nrev = 0;
-    }
+  const ListShare L{(int)blockIdx.x, 1, count, (int)gridDim.x};
+  for (int idx = L.first; idx < count;) {
+    if (threadIdx.x == 0) s_nrev = 0;
     __syncthreads();
-    const int idx = s_idx;
-    __syncthreads();
-    if (idx >= count) break;
     const int32_t a = vlist[(int64_t)bin * n + (count - 1 - idx)];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
@@ -513,6 +526,10 @@ __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8, 8))
       const int cc = s_cnt[i];
       if (cc) atomicAdd(&supo[base + i], cc);
     }
+    if (!L.shared()) break;
+    if (threadIdx.x == 0) s_idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    __syncthreads();
+    idx = s_idx;
     __syncthreads();
   }
 }
@@ -532,11 +549,8 @@ __global__ void __launch_bounds__(kT) k_sup_wave_bs(const int64_t* __restrict__ 
   if (ctl->act[0] != MODE) return;
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[0]);
-  for (;;) {
-    int idx = 0;
-    if (lane == 0) idx = atomicAdd(&ctl->fetch[0], 1);
-    idx = __shfl(idx, 0, kWave);
-    if (idx >= count) break;
+  const ListShare L{(int)blockIdx.x * W + w, 1, count, (int)gridDim.x * W};
+  for (int idx = L.first; idx < count;) {
     const int32_t a = vlist[idx];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
@@ -581,6 +595,9 @@ __global__ void __launch_bounds__(kT) k_sup_wave_bs(const int64_t* __restrict__ 
       if (cc) atomicAdd(&supo[base + lane], cc);
     }
     wave_sync();
+    if (!L.shared()) break;
+    if (lane == 0) idx = L.workers + atomicAdd(&ctl->fetch[0], 1);
+    idx = __shfl(idx, 0, kWave);
   }
 }
 
@@ -596,12 +613,8 @@ __global__ void __launch_bounds__(kT) k_sup_chunked(const int64_t* __restrict__ 
   __shared__ int s_idx;
   if (ctl->act[bin] != kBsearch) return;
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
-  for (;;) {
-    if (threadIdx.x == 0) s_idx = atomicAdd(&ctl->fetch[bin], 1);
-    __syncthreads();
-    const int idx = s_idx;
-    __syncthreads();
-    if (idx >= count) break;
+  const ListShare L{(int)blockIdx.x, 1, count, (int)gridDim.x};
+  for (int idx = L.first; idx < count;) {
     const int32_t a = vlist[(int64_t)bin * n + idx];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
@@ -649,6 +662,11 @@ __global__ void __launch_bounds__(kT) k_sup_chunked(const int64_t* __restrict__ 
       if (valid && s_cnt[threadIdx.x]) atomicAdd(&supo[base + i], s_cnt[threadIdx.x]);
       __syncthreads();
     }
+    if (!L.shared()) break;
+    if (threadIdx.x == 0) s_idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    __syncthreads();
+    idx = s_idx;
+    __syncthreads();
   }
 }
 
@@ -660,11 +678,9 @@ __global__ void __launch_bounds__(kT) k_sup_merge(const int64_t* __restrict__ or
   if (ctl->act[bin] != kMerge) return;
   const int lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
-  for (;;) {
-    int idx = 0;
-    if (lane == 0) idx = atomicAdd(&ctl->fetch[bin], 1);
-    idx = __shfl(idx, 0, kWave);
-    if (idx >= count) break;
+  constexpr int W = kT / kWave;
+  const ListShare L{(int)blockIdx.x * W + (int)(threadIdx.x / kWave), 1, count, (int)gridDim.x * W};
+  for (int idx = L.first; idx < count;) {
     const int32_t a = vlist[(int64_t)bin * n + idx];
     const int64_t base = orow[a], end = orow[a + 1];
     for (int64_t e0 = base; e0 < end; e0 += kWave) {
@@ -690,6 +706,9 @@ __global__ void __launch_bounds__(kT) k_sup_merge(const int64_t* __restrict__ or
       }
       if (cnt) atomicAdd(&supo[i], cnt);
     }
+    if (!L.shared()) break;
+    if (lane == 0) idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    idx = __shfl(idx, 0, kWave);
   }
 }
 
@@ -740,23 +759,43 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
     if (hipEventCreate(&ev[b]) != hipSuccess) timed = false;
   // persistent-style grids: workers fetch vertices from the bin lists
   const unsigned gw = 256 * 8, gb = 256 * 4, g2 = 256;
+  // Which methods a bin may take: one where it is known before the launch
+  // (forced, or the plain or heuristic scheduler), any where the network
+  // decides on the device.  A vertex with d out-neighbours, all of them of
+  // at least its degree, needs d (d + 1) / 2 edges, so on small graphs the bins of large
+  // d are empty and get no kernels.
+  auto may = [&](int b, int method) {
+    int only = -1;
+    if (plan.force >= 0) only = plan.force;
+    else if (plan.sched == TRUSS_SCHED_PLAIN) only = kMerge;
+    else if (plan.sched != TRUSS_SCHED_LEARNED || plan.model == nullptr) only = b == kBins - 1 ? kBsearch : kHash;
+    if (only == kHash && b == kBins - 1) only = kBsearch;
+    return only < 0 || only == method;
+  };
+  const int64_t dlo[kBins] = {2, kWaveMax + 1, kBlockMax1 + 1, kBlockMax2 + 1};
   for (int b = 0; b < kBins; ++b) {
     if (timed) (void)hipEventRecord(ev[b], s);
-    if (b == 0) {
-      hipLaunchKernelGGL(k_sup_hash_wave, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
-      hipLaunchKernelGGL(k_sup_wave_bs, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
-    } else if (b == 1) {
-      hipLaunchKernelGGL((k_sup_hash_block<kBlockMax1, kHashT1>), dim3(gb), dim3(kHashT1), 0, s, dg.orow, dg.ocol, n,
-                         L.vlist, 1, L.ctl, L.supo);
-    } else if (b == 2) {
-      hipLaunchKernelGGL((k_sup_hash_block<kBlockMax2, kHashT2>), dim3(g2), dim3(kHashT2), 0, s, dg.orow, dg.ocol,
-                         n, L.vlist, 2, L.ctl, L.supo);
+    if (m < dlo[b] * (dlo[b] + 1) / 2) continue;
+    if (may(b, kHash)) {
+      if (b == 0)
+        hipLaunchKernelGGL(k_sup_hash_wave, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
+      else if (b == 1)
+        hipLaunchKernelGGL((k_sup_hash_block<kBlockMax1, kHashT1>), dim3(gb), dim3(kHashT1), 0, s, dg.orow, dg.ocol,
+                           n, L.vlist, 1, L.ctl, L.supo);
+      else if (b == 2)
+        hipLaunchKernelGGL((k_sup_hash_block<kBlockMax2, kHashT2>), dim3(g2), dim3(kHashT2), 0, s, dg.orow, dg.ocol,
+                           n, L.vlist, 2, L.ctl, L.supo);
     }
-    if (b > 0)
-      hipLaunchKernelGGL(k_sup_chunked, dim3(b == 1 ? gb : g2), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b,
-                         L.ctl, L.supo);
-    hipLaunchKernelGGL(k_sup_merge, dim3(b == 0 ? gw : gb), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b, L.ctl,
-                       L.supo);
+    if (may(b, kBsearch)) {
+      if (b == 0)
+        hipLaunchKernelGGL(k_sup_wave_bs, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
+      else
+        hipLaunchKernelGGL(k_sup_chunked, dim3(b == 1 ? gb : g2), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b,
+                           L.ctl, L.supo);
+    }
+    if (may(b, kMerge))
+      hipLaunchKernelGGL(k_sup_merge, dim3(b == 0 ? gw : gb), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b, L.ctl,
+                         L.supo);
   }
   hipLaunchKernelGGL(k_sup_finish, dim3(grid_for(m)), dim3(kT), 0, s, L.supo, dg.oeid, m, sup, stamp);
   if (timed) (void)hipEventRecord(ev[kBins], s);
