@@ -91,6 +91,112 @@ __device__ __forceinline__ int wave_append(int* counter, bool want) {
   return base + rank_below(m);
 }
 
+// ---- persistent kernels: coherent accesses and the grid barrier -----------------
+// The L2 caches of the XCDs are not coherent with each other, and an
+// agent-scope fence writes back and invalidates a whole L2.  So what one phase
+// of a persistent kernel writes and another workgroup reads later is accessed with
+// agent-scope relaxed atomics, and each lane waits for its own memory
+// operations before its workgroup arrives at the barrier; no fences.
+template <typename T>
+__device__ __forceinline__ T ldc(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void stc(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// wait until this lane's global loads, stores and atomics have completed
+__device__ __forceinline__ void mem_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ unsigned long long scalar64(unsigned long long x) {
+  return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+         (unsigned)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+constexpr int kGridGroups = 8;  // arrival groups (workgroup id mod 8: one per XCD under round-robin dispatch)
+constexpr int kPubMax = 8;
+constexpr int kPubBits = 48;    // value bits of a published word
+
+struct GridBarrier {
+  alignas(256) unsigned count;                       // groups arrived at all barriers so far
+  alignas(256) unsigned long long pub[kPubMax];      // published words
+  alignas(256) unsigned grp[kGridGroups][32];        // workgroups arrived so far, per group (a 128-byte line each)
+  alignas(128) int abort;                            // set when a wait has timed out
+};
+
+__device__ __forceinline__ void grid_barrier_init(GridBarrier* b) {
+  b->count = 0;
+  for (int i = 0; i < kPubMax; ++i) b->pub[i] = 0ULL;  // tag 0: the first barrier waits for 1
+  for (int g = 0; g < kGridGroups; ++g) b->grp[g][0] = 0;
+  b->abort = 0;
+}
+
+// Barrier over the grid, whose workgroups must all be resident.  The first
+// wavefront of the last workgroup to arrive runs control(release), which decides
+// the next phase and calls release(word) with the word its lane publishes (lanes
+// below NPUB; kPubBits bits) as soon as that is known; what it stores
+// afterwards is complete before this workgroup's next arrival.  Each published
+// word carries the low 16 bits of the generation above its value and the
+// others poll the words themselves, so the release takes one store and one
+// load instead of state, flag and state again.  The arrival counters only
+// grow, so none has to be reset.  gen: barriers passed, including this one;
+// pub: NPUB words of LDS, on return the published values.  Returns false if the
+// wait timed out; the kernel then winds down.
+template <int NPUB, typename Control>
+__device__ __forceinline__ bool grid_barrier(GridBarrier* b, unsigned gen, unsigned long long* pub, Control control) {
+  static_assert(NPUB <= kPubMax, "published words");
+  __shared__ int s_ok;
+  mem_wait();
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    const int lane = lane_id();
+    // two-level arrival: the last workgroup of a group arrives for the group
+    int last = 0;
+    if (lane == 0) {
+      const unsigned g = blockIdx.x % kGridGroups;
+      const unsigned gsize = (gridDim.x - g + kGridGroups - 1) / kGridGroups;
+      const unsigned ngroups = gridDim.x < (unsigned)kGridGroups ? gridDim.x : (unsigned)kGridGroups;
+      const unsigned pg = __hip_atomic_fetch_add(&b->grp[g][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (pg + 1 == gen * gsize) {
+        const unsigned prev = __hip_atomic_fetch_add(&b->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = prev + 1 == gen * ngroups ? 1 : 0;
+      }
+    }
+    last = __builtin_amdgcn_readfirstlane(last);
+    const unsigned long long want = (unsigned long long)(gen & 0xffffu);
+    int ok = 1;
+    if (last) {
+      control([&](unsigned long long word) {
+        if (lane < NPUB) {
+          stc(&b->pub[lane], (want << kPubBits) | word);
+          pub[lane] = word;
+        }
+      });
+    } else {
+      const uint64_t t0 = wall_clock64();
+      unsigned long long x = 0;
+      for (int spin = 1;; ++spin) {
+        x = ldc(&b->pub[lane < NPUB ? lane : 0]);
+        if (ballot((x >> kPubBits) != want) == 0) break;
+        __builtin_amdgcn_s_sleep(1);
+        if ((spin & 63) != 0) continue;
+        // 100 MHz constant clock: give up after 30 s
+        const bool late = wall_clock64() - t0 > 3000000000ULL;
+        if (late && lane == 0) stc(&b->abort, 1);
+        if (__builtin_amdgcn_readfirstlane(late || ldc(&b->abort) != 0 ? 1 : 0)) {
+          ok = 0;
+          break;
+        }
+      }
+      if (lane < NPUB) pub[lane] = x & ((1ULL << kPubBits) - 1ULL);
+    }
+    if (lane == 0) s_ok = ok;
+  }
+  __syncthreads();
+  return s_ok != 0;
+}
+
 // ---- ordering of vertices for the orientation --------------------------------
 // u precedes v iff (deg u, u) < (deg v, v); edges point from earlier to later.
 __device__ __forceinline__ bool vertex_before(int64_t du, int u, int64_t dv, int v) {

@@ -3,15 +3,20 @@
 // (Table 6: the k_max-truss against the c_max-core).
 //
 // Core numbers peel vertices level by level, like the edges of Algorithm 2:
-// level c takes every live vertex of degree <= c (core number c); removing a
-// taken vertex lowers the degree of each live neighbour by one, and a
-// neighbour whose degree falls from c+1 to c is taken in the next sub-round
-// of the same level.  Taken vertices are not decremented again, so each live
-// vertex loses exactly its edges to taken vertices.  An empty level jumps to
-// the smallest live degree.  Each level start and each sub-round is one
-// launch of the same step kernel (a thread per vertex at a level start, a
-// wavefront per taken vertex in a sub-round); the step's last workgroup
-// decides the next step, so launches are queued without host round trips.
+// level c takes every live vertex of degree <= c (core number c), and removing
+// a taken vertex lowers the degree of each of its neighbours by one; a live
+// neighbour whose degree falls from c+1 to c is taken in the same level.  The
+// order of the removals inside a level does not matter, so a taken vertex may be
+// processed at any time: vertices are claimed by a compare-and-swap of their
+// core number, the level start and the decrements race for them freely, and a
+// workgroup goes on with the vertices it has claimed itself, from LDS, until it
+// has walked kBudget entries; only then does it hand the rest to the grid through
+// a queue.  An empty level jumps to the smallest live degree.
+//
+// All levels run in one persistent kernel, one workgroup per compute unit: what
+// bounds it is the number of grid barriers (about 5 us each) and the chain of
+// dependent accesses of a level.  R-MAT 20 (c_max 611): 832 kernel launches with a
+// fence in every workgroup took 30 ms, this one kernel 5.5.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -22,28 +27,40 @@ namespace {
 constexpr int kT = 256;
 constexpr int kIntMax = 0x7fffffff;
 
-// The peeling runs as a sequence of identical launches (steps) of one kernel;
-// the state below says what a step does.  The last workgroup to finish a step
-// decides the next one, so launches follow each other without a host round
-// trip; the host checks for the end every kStepsPerCheck launches.
-enum CorePhase : int { kStart = 0, kRound = 1, kDone = 2 };
+constexpr int kCoreT = 1024;
+constexpr int kCoreWaves = kCoreT / kWave;
+constexpr int kCoreNI = 4;         // row entries in flight per thread
+constexpr int kCoreList = 4096;    // claimed vertices held in LDS
+constexpr int kBudget = 16384;     // row entries a workgroup walks beyond its own level start in a phase
 
-struct CoreState {
-  int phase;  // kStart: take live vertices of degree <= level; kRound: remove the queue's vertices
-  int level;
-  int cur;    // queue holding the current frontier
-  int qn;     // its length (kRound)
-  int cmax;
-  int steps;
-  // counters of the running step, cleared by the workgroup that decides
-  int next;   // vertices appended by this step
-  int alive;  // kStart: live vertices left
-  int minv;   // kStart: their smallest degree
-  unsigned arrived;
+enum CorePhase : int { kLevel = 0, kRound = 1, kDone = 2 };
+enum CorePub : int { kPubFlags = 0, kPubLevel = 1, kPubHead = 2, kPubTail = 3, kPubCnt = 4, kCorePub = 5 };
+
+struct CoreCounts {  // one phase's counters, by arrival group (a line each) where many workgroups add
+  alignas(128) int minv[kGridGroups][32];   // smallest degree of a live vertex left
+  alignas(128) int taken[kGridGroups][32];  // vertices claimed
+  alignas(128) int list;                    // entries of the compacted live list
 };
 
-constexpr unsigned kStepBlocks = 1024;
-constexpr int kStepsPerCheck = 16;
+struct alignas(256) CoreCtl {
+  GridBarrier bar;
+  CoreCounts w[2];
+  alignas(128) int tail;  // entries of the queue; a vertex enters it at most once
+  alignas(128) int dead;  // vertices claimed so far
+  int cmax;
+  int phase;
+};
+
+struct CoreArgs {
+  const int64_t* row_ptr;
+  const int32_t* col;
+  int32_t* deg;
+  int32_t* core;
+  int32_t n;
+  int32_t* queue;    // n
+  int32_t* list[2];  // live lists of n entries, or null: every level looks at all vertices
+  CoreCtl* ctl;
+};
 
 inline unsigned blocks(int64_t n) {
   const int64_t b = (n + kT - 1) / kT;
@@ -51,137 +68,298 @@ inline unsigned blocks(int64_t n) {
 }
 
 __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ deg,
-                            int32_t* __restrict__ core, CoreState* st) {
+                            int32_t* __restrict__ core, CoreCtl* c) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v < n) {
     deg[v] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
     core[v] = -1;
   }
   if (v == 0) {
-    st->phase = kStart;
-    st->level = 0;
-    st->cur = 0;
-    st->qn = 0;
-    st->cmax = 0;
-    st->steps = 0;
-    st->next = 0;
-    st->alive = 0;
-    st->minv = kIntMax;
-    st->arrived = 0;
+    grid_barrier_init(&c->bar);
+    for (int i = 0; i < 2; ++i) {
+      for (int g = 0; g < kGridGroups; ++g) {
+        c->w[i].minv[g][0] = kIntMax;
+        c->w[i].taken[g][0] = 0;
+      }
+      c->w[i].list = 0;
+    }
+    c->tail = 0;
+    c->dead = 0;
+    c->cmax = 0;
+    c->phase = kLevel;
   }
 }
 
-__global__ void __launch_bounds__(kT) k_core_step(const int64_t* __restrict__ row_ptr,
-                                                  const int32_t* __restrict__ col, int32_t* __restrict__ deg,
-                                                  int32_t* __restrict__ core, int32_t n, int32_t* __restrict__ q0,
-                                                  int32_t* __restrict__ q1, CoreState* st) {
-  __shared__ int s_min[kT / kWave], s_cnt[kT / kWave];
-  __shared__ int s_last;
-  const int phase = st->phase;  // written by an earlier launch
-  if (phase == kDone) return;
-  const int level = st->level, cur = st->cur;
-  int32_t* qc = cur ? q1 : q0;
-  int32_t* qx = cur ? q0 : q1;
-  const int lane = lane_id();
-  if (phase == kStart) {
-    // live vertices of degree <= level are taken (core number = level)
-    int dmin = kIntMax, alive = 0;
-    for (int64_t v0 = (int64_t)blockIdx.x * kT; v0 < n; v0 += (int64_t)gridDim.x * kT) {
-      const int64_t v = v0 + threadIdx.x;
-      bool take = false;
-      if (v < n && core[v] < 0) {
-        const int d = deg[v];
-        if (d <= level) {
-          take = true;
-          core[v] = level;
-        } else {
-          dmin = d < dmin ? d : dmin;
-          alive += 1;
+// A workgroup's claimed vertices (LDS): one list being walked, one being filled.
+struct CoreLds {
+  int list[2][kCoreList];
+  int cnt[2];
+  uint32_t pre[kCoreT];
+  uint32_t base[kCoreT];
+  int tmp[kCoreWaves];
+  int at;
+  unsigned long long pub[kCorePub];
+};
+
+__device__ __forceinline__ bool claim(int32_t* core, int level) { return atomicCAS(core, -1, level) == -1; }
+
+// v (if want) into the list being filled, into the queue when that is full
+__device__ __forceinline__ void core_push(const CoreArgs& P, CoreLds& L, int to, bool want, int32_t v) {
+  const uint64_t m = ballot(want);
+  if (m == 0) return;
+  const int leader = __builtin_ctzll(m), n = __popcll(m);
+  int at = 0;
+  if (lane_id() == leader) at = atomicAdd(&L.cnt[to], n);
+  at = __shfl(at, leader, kWave) + rank_below(m);
+  const bool over = want && at >= kCoreList;
+  if (want && !over) L.list[to][at] = v;
+  const uint64_t mo = ballot(over);
+  if (mo) {
+    const int lo = __builtin_ctzll(mo);
+    int q = 0;
+    if (lane_id() == lo) q = atomicAdd(&P.ctl->tail, __popcll(mo));
+    q = __shfl(q, lo, kWave) + rank_below(mo);
+    if (over) stc(&P.queue[q], v);
+  }
+}
+
+// Walks the rows of the vertices in list `from` (cnt of them) and claims into the
+// other list.  Returns the row entries walked.
+__device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from, int cnt, int level, int& taken) {
+  const int tid = threadIdx.x, wv = tid / kWave;
+  int total = 0;
+  for (int c0 = 0; c0 < cnt; c0 += kCoreT) {
+    int len = 0;
+    uint32_t base = 0;
+    if (c0 + tid < cnt) {
+      const int32_t v = L.list[from][c0 + tid];
+      const int64_t rb = P.row_ptr[v];
+      base = (uint32_t)rb;  // 2m < 2^32
+      len = (int)(P.row_ptr[v + 1] - rb);
+    }
+    const int n = cnt - c0 < kCoreT ? cnt - c0 : kCoreT;
+    // distinct rows of fewer than 2^32 entries in all: 32-bit sums suffice
+    const uint32_t inc = wave_inclusive_sum((uint32_t)len);
+    __syncthreads();
+    if (lane_id() == kWave - 1) L.tmp[wv] = (int)inc;
+    __syncthreads();
+    uint32_t off = 0, W = 0;
+#pragma unroll 4
+    for (int q = 0; q < kCoreWaves; ++q) {
+      if (q < wv) off += (uint32_t)L.tmp[q];
+      W += (uint32_t)L.tmp[q];
+    }
+    L.pre[tid] = off + inc - (uint32_t)len;
+    L.base[tid] = base;
+    __syncthreads();
+    int top = 1;
+    while (2 * top < n) top <<= 1;
+    for (int64_t t0 = 0; t0 < W; t0 += kCoreNI * kCoreT) {
+      int x[kCoreNI], u[kCoreNI], k[kCoreNI];
+      bool ok[kCoreNI];
+#pragma unroll
+      for (int q = 0; q < kCoreNI; ++q) x[q] = 0;
+      for (int st = top; st > 0; st >>= 1) {
+#pragma unroll
+        for (int q = 0; q < kCoreNI; ++q) {
+          const int y = x[q] + st;
+          if (y < n && L.pre[y] <= t0 + q * kCoreT + tid) x[q] = y;
         }
       }
-      const int pos = wave_append(&st->next, take);
-      if (take) qc[pos] = (int32_t)v;
-    }
-    dmin = wave_min(dmin);
-    alive = wave_sum(alive);
-    const int w = threadIdx.x / kWave;
-    if (lane == 0) {
-      s_min[w] = dmin;
-      s_cnt[w] = alive;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int x = 0, y = kIntMax;
-      for (int i = 0; i < kT / kWave; ++i) {
-        x += s_cnt[i];
-        y = s_min[i] < y ? s_min[i] : y;
+#pragma unroll
+      for (int q = 0; q < kCoreNI; ++q) {
+        const int64_t t = t0 + q * kCoreT + tid;
+        ok[q] = t < W;
+        u[q] = ok[q] ? P.col[L.base[x[q]] + ((uint32_t)t - L.pre[x[q]])] : 0;
       }
-      if (x) atomicAdd(&st->alive, x);
-      if (y != kIntMax) atomicMin(&st->minv, y);
+#pragma unroll
+      for (int q = 0; q < kCoreNI; ++q) k[q] = ok[q] ? ldc(&P.core[u[q]]) : 0;
+#pragma unroll
+      for (int q = 0; q < kCoreNI; ++q) {
+        ok[q] = ok[q] && k[q] < 0;
+        k[q] = ok[q] ? atomicSub(&P.deg[u[q]], 1) : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < kCoreNI; ++q) {
+        const bool got = ok[q] && k[q] == level + 1 && claim(&P.core[u[q]], level);
+        taken += __popcll(ballot(got));
+        core_push(P, L, from ^ 1, got, u[q]);
+      }
     }
-  } else {
-    // every queued vertex removes its edges to live vertices; a neighbour
-    // whose degree falls from level + 1 to level joins the next queue
-    const int qn = st->qn;
-    const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t i = gw; i < qn; i += nw) {
-      const int32_t v = qc[i];
-      const int64_t rb = row_ptr[v], re = row_ptr[v + 1];
-      for (int64_t j0 = rb; j0 < re; j0 += kWave) {
-        const int64_t j = j0 + lane;
-        bool take = false;
-        int32_t u = 0;
-        if (j < re) {
-          u = col[j];
-          if (__hip_atomic_load(&core[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0) {
-            const int old = atomicSub(&deg[u], 1);
-            if (old == level + 1) {
-              __hip_atomic_store(&core[u], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              take = true;
+    total = W < (uint32_t)(kIntMax - total) ? total + (int)W : kIntMax;
+    __syncthreads();
+  }
+  return total;
+}
+
+// Walks list 0 and then, in turn, what has been claimed meanwhile, as long as the
+// entries walked beyond the first list stay below kBudget; hands the rest to
+// the queue.  Every thread of the workgroup calls it; both lists are empty on return.
+__device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int level, int& spent, int& taken) {
+  int from = 0;
+  bool first = true;
+  for (;;) {
+    __syncthreads();
+    const int cnt = L.cnt[from] < kCoreList ? L.cnt[from] : kCoreList;
+    __syncthreads();
+    if (cnt == 0) break;
+    if (!first && spent >= kBudget) {
+      if (threadIdx.x == 0) L.at = atomicAdd(&P.ctl->tail, cnt);
+      __syncthreads();
+      for (int i = threadIdx.x; i < cnt; i += kCoreT) stc(&P.queue[L.at + i], L.list[from][i]);
+      __syncthreads();
+      if (threadIdx.x == 0) L.cnt[from] = 0;
+      __syncthreads();
+      break;
+    }
+    if (threadIdx.x == 0) L.cnt[from ^ 1] = 0;
+    __syncthreads();
+    const int w = core_walk(P, L, from, cnt, level, taken);
+    if (!first) spent = spent < kIntMax - w ? spent + w : kIntMax;
+    first = false;
+    if (threadIdx.x == 0) L.cnt[from] = 0;
+    from ^= 1;
+  }
+  if (threadIdx.x == 0) L.cnt[0] = L.cnt[1] = 0;
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
+  __shared__ CoreLds L;
+  CoreCtl* const c = P.ctl;
+  const int tid = threadIdx.x, lane = lane_id();
+  const unsigned g = blockIdx.x % kGridGroups;
+  if (tid < 2) L.cnt[tid] = 0;
+  __syncthreads();
+  int phase = kLevel, level = 0, head = 0, tail = 0;
+  int cnt = P.n;         // entries of the live list
+  int cur = 0;           // which list
+  bool ids = true;       // the list is 0..n-1
+  bool compact = false;  // write the next list in this level
+  for (unsigned gen = 1;; ++gen) {
+    CoreCounts* const w = &c->w[(gen - 1) & 1];
+    int taken = 0, spent = 0, mins = kIntMax;
+    if (phase == kLevel) {
+      for (int64_t i0 = (int64_t)blockIdx.x * kCoreT; i0 < cnt; i0 += (int64_t)gridDim.x * kCoreT) {
+        const int64_t i = i0 + tid;
+        int32_t v = 0;
+        bool keep = false, got = false;
+        if (i < cnt) {
+          v = ids ? (int32_t)i : ldc(&P.list[cur][i]);
+          const int k = ldc(&P.core[v]), d = ldc(&P.deg[v]);
+          if (k < 0) {
+            if (d <= level) {
+              got = claim(&P.core[v], level);
+            } else {
+              keep = true;
+              mins = d < mins ? d : mins;
             }
           }
         }
-        const int pos = wave_append(&st->next, take);
-        if (take) qx[pos] = u;
-      }
-    }
-  }
-  // the last workgroup of the step decides the next one
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    s_last = atomicAdd(&st->arrived, 1u) == gridDim.x - 1;
-  }
-  __syncthreads();
-  if (s_last && threadIdx.x == 0) {
-    __threadfence();
-    const int next = __hip_atomic_load(&st->next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (phase == kStart) {
-      if (next == 0) {
-        if (__hip_atomic_load(&st->alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
-          st->phase = kDone;
-        } else {
-          // no vertex at this level: the next level is the smallest live degree
-          st->level = __hip_atomic_load(&st->minv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        taken += __popcll(ballot(got));
+        core_push(P, L, 0, got, v);
+        if (compact) {
+          const uint64_t m = ballot(keep);
+          if (lane == 0) L.tmp[tid / kWave] = __popcll(m);
+          __syncthreads();
+          int before = 0, all = 0;
+#pragma unroll 4
+          for (int q = 0; q < kCoreWaves; ++q) {
+            if (q < tid / kWave) before += L.tmp[q];
+            all += L.tmp[q];
+          }
+          if (tid == 0 && all) L.at = atomicAdd(&w->list, all);
+          __syncthreads();
+          if (keep) stc(&P.list[cur ^ 1][L.at + before + rank_below(m)], v);
         }
-      } else {
-        st->cmax = level;
-        st->qn = next;
-        st->phase = kRound;
+        __syncthreads();
+        const int held = L.cnt[0];
+        __syncthreads();  // every thread has read it before the next append
+        if (held > kCoreList - kCoreT) core_drain(P, L, level, spent, taken);
       }
-    } else if (next == 0) {
-      st->level = level + 1;
-      st->phase = kStart;
+      core_drain(P, L, level, spent, taken);
     } else {
-      st->cur = cur ^ 1;
-      st->qn = next;
+      // the queue's vertices [head, tail), spread over the workgroups
+      const int per = (tail - head + (int)gridDim.x - 1) / (int)gridDim.x;
+      const int64_t q0 = (int64_t)head + (int64_t)blockIdx.x * per;
+      const int64_t q1 = q0 + per < tail ? q0 + per : tail;
+      for (int64_t i0 = q0; i0 < q1; i0 += kCoreList) {
+        const int n = (int)(q1 - i0 < kCoreList ? q1 - i0 : kCoreList);
+        for (int i = tid; i < n; i += kCoreT) L.list[0][i] = ldc(&P.queue[i0 + i]);
+        if (tid == 0) L.cnt[0] = n;
+        core_drain(P, L, level, spent, taken);
+      }
     }
-    st->next = 0;
-    st->alive = 0;
-    st->minv = kIntMax;
-    st->steps += 1;
-    st->arrived = 0;
+    // smallest live degree seen, vertices claimed (taken is the same in a wavefront's lanes)
+    mins = wave_min(mins);
+    if (lane == 0) L.tmp[tid / kWave] = mins;
+    __syncthreads();
+    if (tid == 0) {
+      for (int q = 1; q < kCoreWaves; ++q) mins = L.tmp[q] < mins ? L.tmp[q] : mins;
+      if (mins != kIntMax) atomicMin(&w->minv[g][0], mins);
+    }
+    __syncthreads();
+    if (lane == 0) L.tmp[tid / kWave] = taken;
+    __syncthreads();
+    if (tid == 0) {
+      for (int q = 1; q < kCoreWaves; ++q) taken += L.tmp[q];
+      if (taken) atomicAdd(&w->taken[g][0], taken);
+    }
+    const bool ok = grid_barrier<kCorePub>(&c->bar, gen, L.pub, [&](auto release) {
+      const int q = lane < kGridGroups ? lane : 0;
+      const int mv = ldc(&w->minv[q][0]), tk = lane < kGridGroups ? ldc(&w->taken[q][0]) : 0;
+      const int tl = ldc(&c->tail), ll = ldc(&w->list);
+      int dead = ldc(&c->dead), cmax = ldc(&c->cmax);
+      const int m_all = wave_min(mv), t_all = wave_sum(tk);
+      dead += t_all;
+      if (t_all > 0) cmax = level;
+      int ncnt = cnt, ncur = cur, nids = ids ? 1 : 0, nphase = phase, nlevel = level;
+      if (phase == kLevel && compact) {
+        ncnt = ll;
+        ncur = cur ^ 1;
+        nids = 0;
+      }
+      if (tl > tail) {
+        nphase = kRound;
+      } else if (phase == kLevel && t_all == 0) {
+        // nothing left the graph in this level: the smallest live degree is exact
+        nlevel = m_all;
+        if (m_all == kIntMax) nphase = kDone;
+      } else {
+        nphase = kLevel;
+        nlevel = level + 1;
+      }
+      // a new list once a fifth of this one is dead
+      const bool comp = P.list[0] != nullptr && (long long)(P.n - dead) * 5 < (long long)ncnt * 4;
+      unsigned long long word = (unsigned)ncnt;
+      if (lane == kPubFlags) word = (unsigned)(nphase | (ncur << 2) | (nids << 3) | ((comp ? 1 : 0) << 4));
+      if (lane == kPubLevel) word = (unsigned)nlevel;
+      if (lane == kPubHead) word = (unsigned)tail;
+      if (lane == kPubTail) word = (unsigned)tl;
+      release(word);
+      if (lane < kGridGroups) {
+        stc(&w->minv[lane][0], kIntMax);
+        stc(&w->taken[lane][0], 0);
+      }
+      if (lane == 0) {
+        stc(&w->list, 0);
+        stc(&c->dead, dead);
+        stc(&c->cmax, cmax);
+        stc(&c->phase, nphase);
+      }
+    });
+    if (!ok) break;
+    const unsigned f = (unsigned)scalar64(L.pub[kPubFlags]);
+    phase = (int)(f & 3u);
+    cur = (int)(f >> 2) & 1;
+    ids = ((f >> 3) & 1u) != 0;
+    compact = ((f >> 4) & 1u) != 0;
+    level = (int)scalar64(L.pub[kPubLevel]);
+    head = (int)scalar64(L.pub[kPubHead]);
+    tail = (int)scalar64(L.pub[kPubTail]);
+    cnt = (int)scalar64(L.pub[kPubCnt]);
+    if (phase == kDone) break;
+    __syncthreads();
   }
 }
 
@@ -238,42 +416,50 @@ __global__ void __launch_bounds__(1024) k_cc_reduce(const int32_t* __restrict__ 
 }  // namespace
 
 size_t core_workspace(int32_t n, Arena& a) {
-  a.take<int32_t>((size_t)n + 1);
-  a.take<int32_t>((size_t)n + 1);
-  a.take<int32_t>((size_t)n + 1);
-  a.take<CoreState>(1);
+  for (int i = 0; i < 3; ++i) a.take<int32_t>((size_t)n + 1);
+  a.take<CoreCtl>(1);
   return a.used;
 }
 
 int compute_core_numbers(const DevGraph& dg, int32_t* core, int32_t* cmax_out, Arena& a, hipStream_t s) {
-  int32_t* deg = a.take<int32_t>((size_t)dg.n + 1);
-  int32_t* q0 = a.take<int32_t>((size_t)dg.n + 1);
-  int32_t* q1 = a.take<int32_t>((size_t)dg.n + 1);
-  CoreState* st = a.take<CoreState>(1);
+  CoreArgs P;
+  P.deg = a.take<int32_t>((size_t)dg.n + 1);
+  P.queue = a.take<int32_t>((size_t)dg.n + 1);
+  P.list[0] = a.take<int32_t>((size_t)dg.n + 1);
+  P.list[1] = nullptr;
+  P.ctl = a.take<CoreCtl>(1);
   if (a.overflow()) return TRUSS_E_WORKSPACE;
+  // the second live list lies in what the build leaves unused; on a graph of
+  // almost only isolated vertices that is too little, and no lists are kept
+  if (dg.tmp_bytes >= sizeof(int32_t) * ((size_t)dg.n + 1)) P.list[1] = static_cast<int32_t*>(dg.tmp);
+  else P.list[0] = nullptr;
   *cmax_out = 0;
   if (dg.n == 0) return TRUSS_OK;
-  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, deg, core, st);
-  // a level with takes costs its start, at most one empty start before it and
-  // at most one sub-round per vertex taken: at most 3n + 1 steps in all (a
-  // guard against a stuck loop)
-  const long long max_steps = 4LL * dg.n + 2 * kStepsPerCheck;
-  CoreState h;
-  for (long long launched = 0;;) {
-    for (int i = 0; i < kStepsPerCheck; ++i)
-      hipLaunchKernelGGL(k_core_step, dim3(kStepBlocks), dim3(kT), 0, s, dg.row_ptr, dg.col, deg, core, dg.n, q0,
-                         q1, st);
-    launched += kStepsPerCheck;
-    TRUSS_HIP(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
-    TRUSS_HIP(hipStreamSynchronize(s));
-    if (h.phase == kDone) break;
-    if (launched > max_steps) {
-      set_last_error("core numbers did not finish within %lld steps", max_steps);
-      return TRUSS_E_INTERNAL;
-    }
+  P.row_ptr = dg.row_ptr;
+  P.col = dg.col;
+  P.core = core;
+  P.n = dg.n;
+  int dev = 0, cus = 0, occ = 0;
+  TRUSS_HIP(hipGetDevice(&dev));
+  TRUSS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  TRUSS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void*)k_core, kCoreT, 0));
+  if (occ < 1 || cus < 1) {  // the grid barrier needs every workgroup resident
+    set_last_error("core number kernel does not fit on a compute unit");
+    return TRUSS_E_DEVICE;
   }
+  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, P.deg, core, P.ctl);
+  hipLaunchKernelGGL(k_core, dim3((unsigned)cus), dim3(kCoreT), 0, s, P);
   TRUSS_HIP(hipGetLastError());
-  *cmax_out = h.cmax;
+  int aborted = 0;
+  int res[2] = {0, 0};  // cmax, phase
+  TRUSS_HIP(hipMemcpyAsync(&aborted, &P.ctl->bar.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+  TRUSS_HIP(hipMemcpyAsync(res, &P.ctl->cmax, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+  TRUSS_HIP(hipStreamSynchronize(s));
+  if (aborted || res[1] != kDone) {
+    set_last_error("core number kernel barrier timed out");
+    return TRUSS_E_INTERNAL;
+  }
+  *cmax_out = res[0];
   return TRUSS_OK;
 }
 

@@ -42,14 +42,11 @@
 // The kernel returns to the host only to compact the rows (a separate kernel)
 // or when every edge is removed.
 //
-// Memory coherence: the L2 caches of the XCDs are not coherent with each
-// other, and an agent-scope fence writes back and invalidates a whole L2.  The
-// barrier therefore uses no fences: every value that one phase writes and a
+// Memory coherence (see grid_barrier): every value that one phase writes and a
 // later phase of another workgroup reads (queues, live lists, round stamps,
-// supports, pieces) is written and read with agent-scope relaxed atomics, which
-// go to the coherent level, and each lane waits for its outstanding memory
-// operations before its workgroup arrives.  Adjacency rows, offsets and row
-// lengths are immutable inside a launch and use ordinary cached loads.
+// supports) is written and read with agent-scope relaxed atomics.  Adjacency
+// rows, offsets and row lengths are immutable inside a launch and use ordinary
+// cached loads.
 //
 // Each level runs in one of four ways, decided when its first frontier is
 // known: the frontier mode (SPARSE enqueues an edge the moment its support
@@ -98,8 +95,6 @@ enum Phase : int {
   PH_DONE = 6
 };
 
-constexpr int kGroups = 8;  // barrier arrival groups (workgroup id mod 8: one per XCD under round-robin dispatch)
-
 // Working counters of one phase, each on its own 128-byte line.  Two sets
 // alternate from phase to phase: the control step that reads one resets it
 // for the phase after the next, so the release of the next phase need not
@@ -112,19 +107,11 @@ struct alignas(128) PhaseCounts {
   alignas(128) unsigned long long fwork;   // level start: sum over F_0 of the shorter live row
 };
 
-// What the workgroups need of the control state in a phase, released by the
-// control step as kPub words of which each carries the low 16 bits of the
-// barrier's generation above its value: a workgroup polls the words themselves,
-// so the release takes one store and one load instead of state, flag and
-// state again.
+// what the workgroups need of the control state in a phase (published words)
 enum Pub : int { PUB_FLAGS = 0, PUB_K = 1, PUB_R = 2, PUB_UNITS = 3, PUB_ACNT = 4, kPub = 5 };
-constexpr int kPubBits = 48;
 
 struct alignas(256) PeelCtl {
-  unsigned bar_count;          // groups arrived at all barriers so far
-  unsigned pad0[63];
-  unsigned long long pub[kPub];
-  alignas(256) unsigned grp_count[kGroups][32];  // workgroups arrived at all barriers so far, per group (a 128-byte line each)
+  GridBarrier bar;
   PhaseCounts w[2];
   alignas(128) unsigned long long w_work;
   alignas(128) unsigned bar_gen;  // barriers passed before this launch
@@ -149,7 +136,6 @@ struct alignas(256) PeelCtl {
   unsigned long long t_last;            // wall clock at the previous barrier
   unsigned long long t_phase[8];        // time spent per phase (100 MHz ticks)
   int err;
-  int abort;
   int launches;
   // scheduling
   int probe;               // membership probe of the current level: 0 row hash table, 1 binary search
@@ -210,18 +196,6 @@ struct PeelArgs {
   int tr_cap;
 };
 
-// ---- coherent (agent-scope relaxed) accesses ---------------------------------------
-template <typename T>
-__device__ __forceinline__ T ldc(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void stc(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// wait until this lane's global loads, stores and atomics have completed
-__device__ __forceinline__ void mem_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 __device__ __forceinline__ int hist_bin(long long q) {
   return q <= 1 ? 0 : q <= 16 ? 1 : q <= 256 ? 2 : q <= 4096 ? 3 : q <= 65536 ? 4 : 5;
 }
@@ -252,11 +226,7 @@ __device__ __forceinline__ unsigned long long pub_word(const PhaseState& s, int 
     default: return (unsigned)s.acnt;
   }
 }
-__device__ __forceinline__ unsigned long long scalar64(unsigned long long x) {
-  return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
-         (unsigned)__builtin_amdgcn_readfirstlane((int)x);
-}
-// from the words (tags cleared) in LDS; the same in all lanes
+// from the published words in LDS; the same in all lanes
 __device__ __forceinline__ PhaseState phase_state(const unsigned long long* pub) {
   PhaseState s;
   const unsigned long long f = scalar64(pub[PUB_FLAGS]);
@@ -288,7 +258,9 @@ __device__ __forceinline__ int heuristic_action(const float* x) {
 // lanes; the lanes evaluate the scheduler's network together (one hidden unit
 // each).  st: the state of the phase that has ended, on return that of the
 // next one; gen: barriers passed including this one.
-__device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, PhaseState& st, unsigned gen, int shift) {
+template <typename Release>
+__device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, PhaseState& st, unsigned gen, int shift,
+                                             Release release) {
   const bool lead = lane_id() == 0;
   PhaseCounts* const w = &c->w[(gen - 1) & 1];
   int phase = st.phase;
@@ -441,8 +413,7 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
   st.r = r;
   st.acnt = acnt;
   st.acur = acur;
-  const unsigned long long tag = (unsigned long long)(gen & 0xffffu) << kPubBits;
-  if (lane_id() < kPub) stc(&c->pub[lane_id()], tag | pub_word(st, lane_id()));
+  release(pub_word(st, lane_id()));
   if (!lead) return;
   if (failed) stc(&c->err, (int)TRUSS_E_INTERNAL);
   if (t_last != 0) stc(&c->t_phase[phase_in], t_ph + (now - t_last));
@@ -475,61 +446,13 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
   stc(&c->phase, phase);
 }
 
-// Grid barrier without cache maintenance (see the coherence note above); the
-// first wavefront of the last workgroup to arrive runs control_step, whose
-// release ends the wait of the others.  The arrival counters only grow, so
-// none has to be reset before the next barrier.  st (published state, the
-// same in all threads) and pub (kPub words of LDS): on return those of the next
-// phase.  gen: barriers passed, including this one.  Returns false if the
-// wait timed out, and the kernel then winds down.
+// The grid barrier between two phases; on return st is the state of the next one.
 __device__ __forceinline__ bool phase_barrier(PeelCtl* c, const PeelArgs& P, PhaseState& st, unsigned gen, int shift,
                                               unsigned long long* pub) {
-  __shared__ int s_ok;
-  mem_wait();
-  __syncthreads();
-  if (threadIdx.x < kWave) {
-    const int lane = lane_id();
-    // two-level arrival: the last workgroup of a group arrives for the group
-    int last = 0;
-    if (lane == 0) {
-      const unsigned g = blockIdx.x % kGroups;
-      const unsigned gsize = (gridDim.x - g + kGroups - 1) / kGroups;
-      const unsigned ngroups = gridDim.x < (unsigned)kGroups ? gridDim.x : (unsigned)kGroups;
-      const unsigned pg = __hip_atomic_fetch_add(&c->grp_count[g][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (pg + 1 == gen * gsize) {
-        const unsigned prev = __hip_atomic_fetch_add(&c->bar_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = prev + 1 == gen * ngroups ? 1 : 0;
-      }
-    }
-    last = __builtin_amdgcn_readfirstlane(last);
-    int ok = 1;
-    if (last) {
-      control_step(c, P, st, gen, shift);
-      if (lane < kPub) pub[lane] = pub_word(st, lane);
-    } else {
-      const unsigned long long want = (unsigned long long)(gen & 0xffffu);
-      const uint64_t t0 = wall_clock64();
-      unsigned long long x = 0;
-      for (int spin = 1;; ++spin) {
-        x = ldc(&c->pub[lane < kPub ? lane : 0]);
-        if (ballot((x >> kPubBits) != want) == 0) break;
-        __builtin_amdgcn_s_sleep(1);
-        if ((spin & 63) != 0) continue;
-        // 100 MHz constant clock: give up after 30 s
-        const bool late = wall_clock64() - t0 > 3000000000ULL;
-        if (late && lane == 0) stc(&c->abort, 1);
-        if (__builtin_amdgcn_readfirstlane(late || ldc(&c->abort) != 0 ? 1 : 0)) {
-          ok = 0;
-          break;
-        }
-      }
-      if (lane < kPub) pub[lane] = x & ((1ULL << kPubBits) - 1ULL);
-    }
-    if (lane == 0) s_ok = ok;
-  }
-  __syncthreads();
+  const bool ok = grid_barrier<kPub>(&c->bar, gen, pub,
+                                     [&](auto release) { control_step(c, P, st, gen, shift, release); });
   st = phase_state(pub);
-  return s_ok != 0;
+  return ok;
 }
 
 __device__ __forceinline__ bool removed_at(int rnd, int r) { return rnd != 0 && rnd < r; }
@@ -1332,10 +1255,8 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     if (w) atomicAdd(&c->wbound, w);
   }
   if (i == 0) {
-    c->bar_count = 0;
+    grid_barrier_init(&c->bar);
     c->bar_gen = 0;
-    for (int g = 0; g < kGroups; ++g) c->grp_count[g][0] = 0;
-    for (int i = 0; i < kPub; ++i) c->pub[i] = 0ULL;  // tag 0: the first barrier waits for 1
     for (int i = 0; i < 2; ++i) {
       c->w[i].fetch = 0;
       c->w[i].q = 0ULL;
@@ -1364,7 +1285,6 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     c->t_last = 0;
     for (int b = 0; b < 8; ++b) c->t_phase[b] = 0;
     c->err = 0;
-    c->abort = 0;
     c->launches = 0;
     c->probe = 0;
     c->sched = sched;
@@ -1506,7 +1426,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
       float t = 0.f;
       if (hipEventElapsedTime(&t, ev0, ev1) == hipSuccess) kernel_ms += t;
     }
-    if (h.abort || h.err || h.phase != PH_COMPACT) break;
+    if (h.bar.abort || h.err || h.phase != PH_COMPACT) break;
     hipLaunchKernelGGL(k_dead_bits, dim3(4096), dim3(256), 0, s, stamp, dg.m, L.dead);
     hipLaunchKernelGGL(k_compact, dim3(2048), dim3(256), 0, s, dg.col, dg.seid, L.vinfo, dg.n, L.dead, L.ctl);
   }
@@ -1522,7 +1442,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   res->heavy_rounds = h.heavy_rounds;
   for (int b = 0; b < kHistBins; ++b) res->hist[b] = h.hist[b];
   for (int b = 0; b < 6; ++b) res->phase_ms[b] = (double)h.t_phase[b] * 1e-5;
-  if (h.abort) {
+  if (h.bar.abort) {
     set_last_error("peeling kernel barrier timed out");
     return TRUSS_E_INTERNAL;
   }
