@@ -278,7 +278,10 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
   Timer tm(stats != nullptr && timed, s);
   tm.mark(0);
   DevGraph dg;
-  rc = build_graph(g, a, dg, p.d_err, s, true);
+  rc = build_graph(g, a, dg, p.d_err, s, true,
+                   mode == kModeSupport ? 0
+                   : mode == kModeBound ? kBuildRows | kBuildIds
+                                        : kBuildRows | kBuildIds | kBuildTables);
   if (rc) return rc;
   tm.mark(1);
   p.sup = a.take<int32_t>((size_t)g->m + 1);
@@ -478,11 +481,11 @@ int run_topdown(const truss_graph* g, int32_t t, int32_t* out, int32_t* kmin_out
   Timer tm(stats != nullptr, s);
   tm.mark(0);
   DevGraph dg;
-  rc = build_graph(g, a, dg, p.d_err, s);
+  rc = build_graph(g, a, dg, p.d_err, s, true, kBuildRows | kBuildIds);
   if (rc) return rc;
   p.sup = a.take<int32_t>((size_t)g->m + 1);
   p.stamp = a.take<int32_t>((size_t)g->m + 1);
-  p.truss_canon = g->fmt == TRUSS_FMT_EDGES ? a.take<int32_t>((size_t)g->m + 1) : nullptr;
+  p.truss_canon = a.take<int32_t>((size_t)g->m + 1);
   take_bound(g, a, p);
   rc = compute_support(dg, sp, p.sup, nullptr, a, s, nullptr);
   if (rc) return rc;
@@ -629,7 +632,7 @@ int run_cohen(const truss_graph* g, int32_t* out, truss_stats* stats, void* ws, 
   Timer tm(stats != nullptr, s);
   tm.mark(0);
   DevGraph dg;
-  if ((rc = build_graph(g, a, dg, d_err, s))) return rc;
+  if ((rc = build_graph(g, a, dg, d_err, s, false, kBuildRows | kBuildIds))) return rc;
   tm.mark(1);
   int2* sr = a.take<int2>((size_t)g->m + 1);
   int32_t* tc = a.take<int32_t>((size_t)g->m + 1);
@@ -682,7 +685,7 @@ int run_core(const truss_graph* g, int32_t* core_out, int32_t* cmax_out, void* w
   a.cap = ws_bytes;
   int* d_err = a.take<int>(64);
   DevGraph dg;
-  rc = build_graph(g, a, dg, d_err, s);
+  rc = build_graph(g, a, dg, d_err, s, false, kBuildRows);
   if (rc) return rc;
   int32_t cmax = 0;
   rc = compute_core_numbers(dg, core_out, &cmax, a, s);
@@ -842,7 +845,7 @@ int run_cohesion(const truss_graph* g, const truss_options* opts, truss_cohesion
   r.cap = b.region_bytes;
   int* d_err = r.take<int>(64);
   DevGraph dg;
-  if ((rc = build_graph(g, r, dg, d_err, s))) return rc;
+  if ((rc = build_graph(g, r, dg, d_err, s, false, kBuildRows | kBuildIds))) return rc;
   int32_t cmax = 0;
   if ((rc = compute_core_numbers(dg, b.core, &cmax, r, s))) return rc;
   int cnt[2] = {0, 0};

@@ -28,12 +28,11 @@ inline int bits_for(int64_t n) {
 
 __device__ __forceinline__ void report(int* err, int code) { atomicMin(err, code); }
 
-__global__ void k_init_err(int* err) { *err = kNoErr; }
-
-template <typename T>
-__global__ void k_fill(T* p, int64_t n, T v) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
+// the error word, and counters of n + 1 entries (nullable) cleared
+__global__ void k_build_init(int* err, int32_t* __restrict__ deg, int64_t n) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *err = kNoErr;
+  if (!deg) return;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n; i += (int64_t)gridDim.x * blockDim.x) deg[i] = 0;
 }
 
 // ---- row hash tables (the membership test of Algorithm 2) -----------------------------------
@@ -60,6 +59,7 @@ __global__ void k_rtab_clear(int2* __restrict__ rtab, const int64_t* __restrict_
 
 __device__ __forceinline__ void rtab_put(int2* __restrict__ rtab, const int64_t* __restrict__ rtoff, int32_t v,
                                          int32_t w, int32_t e) {
+  if (!rtab) return;
   const int64_t off = rtoff[v];
   const int lg = row_table_lg(rtoff[v + 1] - off);
   const uint32_t mask = (1u << lg) - 1u;
@@ -67,17 +67,6 @@ __device__ __forceinline__ void rtab_put(int2* __restrict__ rtab, const int64_t*
   // neighbours are distinct and the table is at most half full: a free slot is found
   while (atomicCAS(&rtab[off + h].x, -1, w) != -1) h = (h + 1) & mask;
   rtab[off + h].y = e;
-}
-
-// a thread per edge (u, v) inserts v into u's table and u into v's table (CSR
-// input used as it is; the sorted builds insert while placing the row entries)
-__global__ void k_rtab_insert(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t m,
-                              const int64_t* __restrict__ rtoff, int2* __restrict__ rtab) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m) return;
-  const int32_t u = eu[e], v = ev[e];
-  rtab_put(rtab, rtoff, u, v, (int32_t)e);
-  rtab_put(rtab, rtoff, v, u, (int32_t)e);
 }
 
 // capacity bound: 2^ceil(log2(2d)) < 4d for d >= 1, so all tables fit in 8m slots
@@ -99,18 +88,23 @@ __global__ void k_canon(const int32_t* __restrict__ src, const int32_t* __restri
   val[i] = (int32_t)i;
 }
 
-__device__ __forceinline__ int64_t deg_of(const int64_t* __restrict__ rp, int32_t v) { return rp[v + 1] - rp[v]; }
-
+// and, for the rows, the larger endpoint and the edge id as sort key and value
 __global__ void k_edges_from_keys(const uint64_t* __restrict__ key, const int32_t* __restrict__ val, int64_t m,
                                   int vb, int32_t* __restrict__ eu, int32_t* __restrict__ ev,
-                                  int32_t* __restrict__ perm, int* err) {
+                                  int32_t* __restrict__ perm, uint32_t* __restrict__ tkey,
+                                  int32_t* __restrict__ tval, int* err) {
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
   uint64_t k = key[e];
   if (e > 0 && key[e - 1] == k) report(err, kErrDup);
   eu[e] = (int32_t)(k >> vb);
-  ev[e] = (int32_t)(k & ((1ULL << vb) - 1));
+  const int32_t v = (int32_t)(k & ((1ULL << vb) - 1));
+  ev[e] = v;
   perm[e] = val[e];
+  if (tkey) {
+    tkey[e] = (uint32_t)v;
+    tval[e] = (int32_t)e;
+  }
 }
 
 // Row offsets without counters: the canonical edges are sorted by their
@@ -118,14 +112,16 @@ __global__ void k_edges_from_keys(const uint64_t* __restrict__ key, const int32_
 // uppre[x] / lowpre[x] = edges whose smaller / larger endpoint is below x
 // are lower bounds in those arrays; row x of the symmetric CSR starts at
 // uppre[x] + lowpre[x] and holds its lower neighbours, then its upper ones.
+// (lo_v null: uppre alone.)
 __global__ void k_row_bounds(const int32_t* __restrict__ eu, const int32_t* __restrict__ lo_v, int64_t m, int32_t n,
                              int64_t* __restrict__ uppre, int64_t* __restrict__ lowpre,
                              int64_t* __restrict__ row_ptr) {
   const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (x > n) return;
   const int64_t a = lower_bound_i32<int64_t>(eu, 0, m, (int)x);
-  const int64_t b = lower_bound_i32<int64_t>(lo_v, 0, m, (int)x);
   uppre[x] = a;
+  if (!lo_v) return;
+  const int64_t b = lower_bound_i32<int64_t>(lo_v, 0, m, (int)x);
   lowpre[x] = b;
   row_ptr[x] = a + b;
 }
@@ -135,7 +131,7 @@ __global__ void k_row_bounds(const int32_t* __restrict__ eu, const int32_t* __re
 // (the threads of a block share u, so their inserts land in one table)
 __global__ void k_sym_upper(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t m,
                             const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ lowpre,
-                            int32_t* __restrict__ col, int32_t* __restrict__ seid, int32_t* __restrict__ kf,
+                            int32_t* __restrict__ col, int32_t* __restrict__ seid,
                             const int64_t* __restrict__ rtoff, int2* __restrict__ rtab) {
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
@@ -143,16 +139,7 @@ __global__ void k_sym_upper(const int32_t* __restrict__ eu, const int32_t* __res
   int64_t pos = lowpre[u + 1] + e;
   col[pos] = v;
   seid[pos] = (int32_t)e;
-  kf[pos] = vertex_before(deg_of(row_ptr, u), u, deg_of(row_ptr, v), v) ? 1 : 0;
   rtab_put(rtab, rtoff, u, v, (int32_t)e);
-}
-
-__global__ void k_copy_ev(const int32_t* __restrict__ ev, int64_t m, uint32_t* __restrict__ tkey,
-                          int32_t* __restrict__ tval) {
-  int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m) return;
-  tkey[e] = (uint32_t)ev[e];
-  tval[e] = (int32_t)e;
 }
 
 // lower entry of edge tval[t] = (u, v) with v = tkey[t]: the head of v's row,
@@ -161,8 +148,8 @@ __global__ void k_copy_ev(const int32_t* __restrict__ ev, int64_t m, uint32_t* _
 __global__ void k_sym_lower(const uint32_t* __restrict__ tkey, const int32_t* __restrict__ tval, int64_t m,
                             const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ uppre,
                             const int32_t* __restrict__ eu, int32_t* __restrict__ col,
-                            int32_t* __restrict__ seid, int32_t* __restrict__ kf,
-                            const int64_t* __restrict__ rtoff, int2* __restrict__ rtab) {
+                            int32_t* __restrict__ seid, const int64_t* __restrict__ rtoff,
+                            int2* __restrict__ rtab) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= m) return;
   int32_t e = tval[t];
@@ -171,7 +158,6 @@ __global__ void k_sym_lower(const uint32_t* __restrict__ tkey, const int32_t* __
   int64_t pos = uppre[v] + t;
   col[pos] = u;
   seid[pos] = e;
-  kf[pos] = vertex_before(deg_of(row_ptr, v), v, deg_of(row_ptr, u), u) ? 1 : 0;
   rtab_put(rtab, rtoff, v, u, e);
 }
 
@@ -196,15 +182,15 @@ __global__ void k_edge_degrees(const int32_t* __restrict__ src, const int32_t* _
   atomicAdd(&deg[v], 1);
 }
 
-// sort keys (degree, id) of the vertices; degrees from the CSR offsets or from deg
+// sort keys of the vertices: the degree, from the CSR offsets or from deg; in id
+// order, so that a stable sort ranks by (degree, id)
 __global__ void k_degree_keys(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ deg, int32_t n, int vb,
-                              uint64_t* __restrict__ key, int32_t* __restrict__ val) {
+                              uint32_t* __restrict__ key, int32_t* __restrict__ val) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v >= n) return;
   int64_t d = row_ptr ? row_ptr[v + 1] - row_ptr[v] : deg[v];
   const int64_t dmax = (1LL << vb) - 1;  // a simple graph has d < n <= 2^vb; larger only on invalid input
-  d = d < 0 ? 0 : d > dmax ? dmax : d;
-  key[v] = ((uint64_t)d << vb) | (uint64_t)v;
+  key[v] = (uint32_t)(d < 0 ? 0 : d > dmax ? dmax : d);
   val[v] = (int32_t)v;
 }
 
@@ -213,13 +199,20 @@ __global__ void k_ranks(const int32_t* __restrict__ order, int32_t n, int32_t* _
   if (i < n) rank[order[i]] = (int32_t)i;
 }
 
-// canonical keys of the relabelled edges (ids already checked)
-__global__ void k_canon_relabel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m, int vb,
+// Canonical keys of the relabelled edges.  The input may still turn out to be
+// invalid (its errors are read once, when the build is done): a pair with an id
+// out of range or beyond the *valid pairs there are (nullable) gets key 0, so
+// that everything built from the keys stays in bounds.
+__global__ void k_canon_relabel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m,
+                                const int64_t* __restrict__ valid, int32_t n, int vb,
                                 const int32_t* __restrict__ rank, uint64_t* __restrict__ key,
                                 int32_t* __restrict__ val) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= m) return;
-  const int32_t u = rank[src[i]], v = rank[dst[i]];
+  const bool in = !valid || i < *valid;
+  const int32_t s = in ? src[i] : -1, d = in ? dst[i] : -1;
+  const bool ok = s >= 0 && s < n && d >= 0 && d < n;
+  const int32_t u = ok ? rank[s] : 0, v = ok ? rank[d] : 0;
   const uint64_t a = (uint64_t)(u < v ? u : v), b = (uint64_t)(u < v ? v : u);
   key[i] = (a << vb) | b;
   val[i] = (int32_t)i;
@@ -266,7 +259,7 @@ __global__ void k_csr_check(const int64_t* __restrict__ row_ptr, const int32_t* 
 }
 
 __global__ void k_csr_upper(const int32_t* __restrict__ col, const int32_t* __restrict__ rowid,
-                            const int64_t* __restrict__ upos, int64_t m2, int32_t* __restrict__ colcopy,
+                            const int64_t* __restrict__ upos, int64_t m2, int64_t m, int32_t* __restrict__ colcopy,
                             int32_t* __restrict__ seid, int32_t* __restrict__ eu, int32_t* __restrict__ ev) {
   int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (j >= m2) return;
@@ -277,14 +270,16 @@ __global__ void k_csr_upper(const int32_t* __restrict__ col, const int32_t* __re
   }
   if (w > v) {
     const int64_t e = upos[j];
-    eu[e] = v;
-    ev[e] = w;
+    if (e < m) {  // more than m upper entries: an asymmetric input, reported by k_check_total
+      eu[e] = v;
+      ev[e] = w;
+    }
   }
 }
 
 __global__ void k_csr_lower(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                             const int32_t* __restrict__ rowid, const int64_t* __restrict__ upos, int64_t m2,
-                            int32_t* __restrict__ seid, int32_t* __restrict__ kf, int* err) {
+                            int32_t* __restrict__ seid, int* err) {
   int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (j >= m2) return;
   const int32_t v = rowid[j], w = col[j];
@@ -292,49 +287,37 @@ __global__ void k_csr_lower(const int64_t* __restrict__ row_ptr, const int32_t* 
     const int64_t lo = row_ptr[w], hi = row_ptr[w + 1];
     const int64_t p = lower_bound_i32<int64_t>(col, lo, hi, v);
     if (p >= hi || col[p] != v) report(err, kErrAsym);
-    else seid[j] = (int32_t)upos[p];
+    else if (seid) seid[j] = (int32_t)upos[p];
   }
-  kf[j] = vertex_before(deg_of(row_ptr, v), v, deg_of(row_ptr, w), w) ? 1 : 0;
 }
 
 // Symmetry of a CSR input built through the relabelled path: the graph was
 // built from the upper entries alone (m of them, no repeats), so the input is
 // symmetric iff every lower entry (v, w), w < v, is an edge of that graph --
-// looked up in the row table of v's new id.
+// looked up in the row table of v's new id or, where no tables are built, in
+// the sorted out-neighbours of the smaller new id.
 __global__ void k_csr_sym_check(const int32_t* __restrict__ col_in, const int32_t* __restrict__ rowid, int64_t m2,
-                                const int32_t* __restrict__ rank, const int2* __restrict__ rtab,
-                                const int64_t* __restrict__ rtoff, int* err) {
+                                int32_t n, const int32_t* __restrict__ rank, const int2* __restrict__ rtab,
+                                const int64_t* __restrict__ rtoff, const int64_t* __restrict__ orow,
+                                const int32_t* __restrict__ ocol, int* err) {
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (j >= m2) return;
   const int32_t v = rowid[j], w = col_in[j];
-  if (w >= v) return;
-  const int32_t x = rank[v];
-  const int64_t off = rtoff[x], slots = rtoff[x + 1] - off;
-  if (slots == 0 || row_lookup(rtab, off, row_table_lg(slots), rank[w]) < 0) report(err, kErrAsym);
+  if (w >= v || w < 0) return;  // (an id out of range is reported by k_csr_check)
+  const int32_t x = rank[v], y = rank[w];
+  if (rtab) {
+    const int64_t off = rtoff[x], slots = rtoff[x + 1] - off;
+    if (slots == 0 || row_lookup(rtab, off, row_table_lg(slots), y) < 0) report(err, kErrAsym);
+  } else {
+    const int32_t a = x < y ? x : y, b = x < y ? y : x;
+    const int64_t end = orow[a + 1];
+    const int64_t p = lower_bound_i32<int64_t>(ocol, orow[a], end, b);
+    if (p >= end || ocol[p] != b) report(err, kErrAsym);
+  }
 }
 
 __global__ void k_check_total(const int64_t* __restrict__ upos, int64_t m2, int64_t m, int* err) {
   if (upos[m2] != m) report(err, kErrAsym);
-}
-
-// ---- orientation ------------------------------------------------------------------------
-
-__global__ void k_orow(const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ opos, int32_t n,
-                       int64_t* __restrict__ orow) {
-  int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (v <= n) orow[v] = opos[row_ptr[v]];
-}
-
-__global__ void k_ocsr(const int32_t* __restrict__ col, const int32_t* __restrict__ seid,
-                       const int32_t* __restrict__ kf, const int64_t* __restrict__ opos, int64_t m2,
-                       int32_t* __restrict__ ocol, int32_t* __restrict__ oeid) {
-  int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= m2) return;
-  if (kf[j]) {
-    const int64_t p = opos[j];
-    ocol[p] = col[j];
-    oeid[p] = seid[j];
-  }
 }
 
 int read_err(const int* d_err, hipStream_t s) {
@@ -357,13 +340,13 @@ int read_err(const int* d_err, hipStream_t s) {
 // buffers of the build, laid out identically for the size query and the run
 struct Layout {
   // resident
-  int32_t *col, *seid, *eu, *ev, *perm, *ocol, *oeid;
+  int32_t *col, *seid, *eu, *ev, *perm;
   int64_t *row_ptr, *orow;
   // temporaries
   uint64_t *key, *key_alt;
   int32_t *val, *val_alt;
   int64_t *uppre, *lowpre;
-  int32_t *rowid, *kf;
+  int32_t *rowid, *uf;
   int64_t *opos;
   int32_t *rtmp;
   int64_t *stmp;
@@ -385,8 +368,6 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
   L.seid = a.take<int32_t>(m2 + 1);
   L.eu = a.take<int32_t>(m + 1);
   L.ev = a.take<int32_t>(m + 1);
-  L.ocol = a.take<int32_t>(m + 1);
-  L.oeid = a.take<int32_t>(m + 1);
   L.orow = a.take<int64_t>(n + 1);
   L.perm = edges ? a.take<int32_t>(m + 1) : nullptr;
   L.rtab = a.take<int2>((size_t)rtab_capacity(m));
@@ -395,7 +376,7 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
   L.row_ptr = edges ? a.take<int64_t>(n + 1) : nullptr;
   // temporaries: free once the build has returned (DevGraph::tmp)
   L.tmp_at = a.used;
-  L.kf = a.take<int32_t>(m2 + 1);
+  L.uf = a.take<int32_t>(m2 + 1);
   L.opos = a.take<int64_t>(m2 + 1);
   L.stmp = a.take<int64_t>(scan_tmp_elems(m2 + 1) + scan_tmp_elems(n + 1));
   if (edges) {
@@ -431,9 +412,10 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
 
 // ranks of the vertices in (degree, id) order; degrees from row_ptr, else from deg
 void degree_ranks(const int64_t* row_ptr, const int32_t* deg, int32_t n, int vb, Layout& L, hipStream_t s) {
-  hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, deg, n, vb, L.vkey,
-                     L.vval);
-  const bool alt = radix_sort_u64(L.vkey, L.vval, L.vkey_alt, L.vval_alt, n, 2 * vb, L.vtmp, s);
+  uint32_t* key = reinterpret_cast<uint32_t*>(L.vkey);
+  uint32_t* key_alt = reinterpret_cast<uint32_t*>(L.vkey_alt);
+  hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, deg, n, vb, key, L.vval);
+  const bool alt = radix_sort_u32(key, L.vval, key_alt, L.vval_alt, n, vb, L.vtmp, s);
   hipLaunchKernelGGL(k_ranks, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, alt ? L.vval_alt : L.vval, n, L.rank);
 }
 
@@ -446,33 +428,38 @@ void table_layout(const int64_t* row_ptr, int32_t n, int64_t m, Layout& L, hipSt
                      L.rtoff, n, cap);
 }
 
-// symmetric CSR, canonical edges, perm and the row tables from the unsorted
-// canonical keys in L.key / L.val (val: the caller's index of each edge)
-int rows_from_keys(int32_t n, int64_t m, int vb, Layout& L, int* d_err, hipStream_t s) {
+// canonical edges and perm, and by `needs` the symmetric rows and their tables,
+// from the unsorted canonical keys in L.key / L.val (val: the caller's index of
+// each edge).
+void rows_from_keys(int32_t n, int64_t m, int vb, Layout& L, int needs, int* d_err, hipStream_t s) {
   if (radix_sort_u64(L.key, L.val, L.key_alt, L.val_alt, m, 2 * vb, L.rtmp, s)) {
     std::swap(L.key, L.key_alt);
     std::swap(L.val, L.val_alt);
   }
+  const bool rows = (needs & kBuildRows) != 0;
+  uint32_t* tkey = reinterpret_cast<uint32_t*>(L.key_alt);
+  uint32_t* tkey_alt = reinterpret_cast<uint32_t*>(L.key);
   hipLaunchKernelGGL(k_edges_from_keys, dim3(grid_for(m)), dim3(kT), 0, s, L.key, L.val, m, vb, L.eu, L.ev, L.perm,
-                     d_err);
-  const int rc = read_err(d_err, s);
-  if (rc) return rc;
-  // the canonical order, stably sorted by the larger endpoint (lower halves of the rows)
-  uint32_t* tkey = reinterpret_cast<uint32_t*>(L.key);
-  uint32_t* tkey_alt = reinterpret_cast<uint32_t*>(L.key_alt);
-  hipLaunchKernelGGL(k_copy_ev, dim3(grid_for(m)), dim3(kT), 0, s, L.ev, m, tkey, L.val);
-  if (radix_sort_u32(tkey, L.val, tkey_alt, L.val_alt, m, vb, L.rtmp, s)) {
-    std::swap(tkey, tkey_alt);
-    std::swap(L.val, L.val_alt);
+                     rows ? tkey : nullptr, L.val_alt, d_err);
+  const int32_t* lo_v = nullptr;
+  if (rows) {
+    // the canonical order, stably sorted by the larger endpoint (lower halves of the rows)
+    if (radix_sort_u32(tkey, L.val_alt, tkey_alt, L.val, m, vb, L.rtmp, s)) std::swap(tkey, tkey_alt);
+    else std::swap(L.val, L.val_alt);
+    lo_v = reinterpret_cast<const int32_t*>(tkey);
   }
-  hipLaunchKernelGGL(k_row_bounds, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, L.eu,
-                     reinterpret_cast<const int32_t*>(tkey), m, n, L.uppre, L.lowpre, L.row_ptr);
-  table_layout(L.row_ptr, n, m, L, s);
+  hipLaunchKernelGGL(k_row_bounds, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, L.eu, lo_v, m, n, L.uppre,
+                     L.lowpre, L.row_ptr);
+  if (!rows) return;
+  int2* rtab = nullptr;
+  if (needs & kBuildTables) {
+    table_layout(L.row_ptr, n, m, L, s);
+    rtab = L.rtab;
+  }
   hipLaunchKernelGGL(k_sym_upper, dim3(grid_for(m)), dim3(kT), 0, s, L.eu, L.ev, m, L.row_ptr, L.lowpre, L.col,
-                     L.seid, L.kf, L.rtoff, L.rtab);
+                     L.seid, L.rtoff, rtab);
   hipLaunchKernelGGL(k_sym_lower, dim3(grid_for(m)), dim3(kT), 0, s, tkey, L.val, m, L.row_ptr, L.uppre, L.eu,
-                     L.col, L.seid, L.kf, L.rtoff, L.rtab);
-  return TRUSS_OK;
+                     L.col, L.seid, L.rtoff, rtab);
 }
 
 }  // namespace
@@ -484,7 +471,61 @@ size_t build_workspace(const truss_graph* g, Arena& a, bool relabel, size_t* tmp
   return a.used;
 }
 
-int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel) {
+// Renumbered graph: the canonical edges are sorted by (smaller new id, larger new
+// id) and new ids rank the degrees, so the oriented CSR is the edge list itself
+// (entry j is edge j, its row offsets uppre).  The input's errors are read once,
+// at the end (and, for CSR input, those of row_ptr at the start: the entries are
+// found through it).
+static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int vb, int* d_err, hipStream_t s,
+                            int needs) {
+  const int32_t n = g->n;
+  const int64_t m = g->m, m2 = 2 * m;
+  const bool edges = g->fmt == TRUSS_FMT_EDGES;
+  L.uppre = L.orow;  // kept
+  const unsigned gn = grid_for((int64_t)n + 1) < 4096 ? grid_for((int64_t)n + 1) : 4096;
+  hipLaunchKernelGGL(k_build_init, dim3(gn), dim3(kT), 0, s, d_err, edges ? L.vdeg : nullptr, (int64_t)n);
+  const int64_t* valid = nullptr;
+  const int32_t *src = g->src, *dst = g->dst;
+  if (edges) {
+    hipLaunchKernelGGL(k_edge_degrees, dim3(grid_for(m)), dim3(kT), 0, s, src, dst, m, n, L.vdeg, d_err);
+    degree_ranks(nullptr, L.vdeg, n, vb, L, s);
+  } else {
+    hipLaunchKernelGGL(k_rowptr_check, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n, m2, d_err);
+    const int rc = read_err(d_err, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_rowid, dim3(grid_for((int64_t)n * kWave > 0 ? (int64_t)n * kWave : 1)), dim3(kT), 0, s,
+                       g->row_ptr, n, L.rowid);
+    hipLaunchKernelGGL(k_csr_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->row_ptr, g->col, n, m2, L.rowid, L.uf,
+                       d_err);
+    scan_exclusive_i32_to_i64(L.uf, L.opos, m2, L.stmp, s);
+    hipLaunchKernelGGL(k_check_total, dim3(1), dim3(1), 0, s, L.opos, m2, m, d_err);
+    // the upper entries, renamed, go through the edge-list build; perm then maps
+    // each edge to its canonical CSR position
+    hipLaunchKernelGGL(k_csr_upper, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, L.opos, m2, m,
+                       (int32_t*)nullptr, L.seid, L.eu, L.ev);
+    src = L.eu;
+    dst = L.ev;
+    valid = L.opos + m2;
+    degree_ranks(g->row_ptr, nullptr, n, vb, L, s);
+  }
+  hipLaunchKernelGGL(k_canon_relabel, dim3(grid_for(m)), dim3(kT), 0, s, src, dst, m, valid, n, vb, L.rank, L.key,
+                     L.val);
+  rows_from_keys(n, m, vb, L, needs, d_err, s);
+  const bool tables = (needs & kBuildTables) != 0;
+  if (!edges && m2 > 0)
+    hipLaunchKernelGGL(k_csr_sym_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, m2, n, L.rank,
+                       tables ? L.rtab : nullptr, L.rtoff, L.uppre, L.ev, d_err);
+  TRUSS_HIP(hipGetLastError());
+  const int rc = read_err(d_err, s);
+  if (rc) return rc;
+  dg.orow = L.orow;
+  dg.ocol = L.ev;
+  dg.row_ptr = L.row_ptr;
+  dg.perm = L.perm;
+  return TRUSS_OK;
+}
+
+int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel, int needs) {
   Layout L;
   carve(g, relabel, a, L);
   if (a.overflow()) return TRUSS_E_WORKSPACE;
@@ -495,87 +536,45 @@ int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStr
   dg.m = m;
   dg.tmp = a.base + L.tmp_at;
   dg.tmp_bytes = L.tmp_bytes;
-  hipLaunchKernelGGL(k_init_err, dim3(1), dim3(1), 0, s, d_err);
-
-  if (g->fmt == TRUSS_FMT_EDGES) {
-    int rc;
-    if (relabel) {
-      hipLaunchKernelGGL(k_fill<int32_t>, dim3(grid_for(n + 1)), dim3(kT), 0, s, L.vdeg, (int64_t)n + 1, 0);
-      hipLaunchKernelGGL(k_edge_degrees, dim3(grid_for(m)), dim3(kT), 0, s, g->src, g->dst, m, n, L.vdeg, d_err);
-      if ((rc = read_err(d_err, s))) return rc;
-      degree_ranks(nullptr, L.vdeg, n, vb, L, s);
-      hipLaunchKernelGGL(k_canon_relabel, dim3(grid_for(m)), dim3(kT), 0, s, g->src, g->dst, m, vb, L.rank, L.key,
-                         L.val);
-    } else {
-      hipLaunchKernelGGL(k_canon, dim3(grid_for(m)), dim3(kT), 0, s, g->src, g->dst, m, n, vb, L.key, L.val, d_err);
-      if ((rc = read_err(d_err, s))) return rc;
-    }
-    if ((rc = rows_from_keys(n, m, vb, L, d_err, s))) return rc;
-    dg.row_ptr = L.row_ptr;
-    dg.perm = L.perm;
-  } else {
-    hipLaunchKernelGGL(k_rowptr_check, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n, m2, d_err);
-    int rc = read_err(d_err, s);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_rowid, dim3(grid_for((int64_t)n * kWave > 0 ? (int64_t)n * kWave : 1)), dim3(kT), 0, s,
-                       g->row_ptr, n, L.rowid);
-    int32_t* uf = L.kf;  // upper flags, later reused for orientation flags
-    hipLaunchKernelGGL(k_csr_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->row_ptr, g->col, n, m2, L.rowid, uf,
-                       d_err);
-    rc = read_err(d_err, s);
-    if (rc) return rc;
-    int64_t* upos = L.opos;
-    scan_exclusive_i32_to_i64(uf, upos, m2, L.stmp, s);
-    hipLaunchKernelGGL(k_check_total, dim3(1), dim3(1), 0, s, upos, m2, m, d_err);
-    rc = read_err(d_err, s);
-    if (rc) return rc;
-    // canonical edges; the entries themselves are kept only when the input rows are used as they are
-    hipLaunchKernelGGL(k_csr_upper, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, upos, m2,
-                       relabel ? nullptr : L.col, L.seid, L.eu, L.ev);
-    if (relabel) {
-      // the canonical edges (the upper entries), renamed, go through the
-      // edge-list build; perm then maps each edge to its canonical CSR
-      // position.  Symmetry is checked on the row tables at the end.
-      degree_ranks(g->row_ptr, nullptr, n, vb, L, s);
-      hipLaunchKernelGGL(k_canon_relabel, dim3(grid_for(m)), dim3(kT), 0, s, L.eu, L.ev, m, vb, L.rank, L.key,
-                         L.val);
-      if ((rc = rows_from_keys(n, m, vb, L, d_err, s))) return rc;
-      dg.row_ptr = L.row_ptr;
-      dg.perm = L.perm;
-    } else {
-      hipLaunchKernelGGL(k_csr_lower, dim3(grid_for(m2)), dim3(kT), 0, s, g->row_ptr, g->col, L.rowid, upos, m2,
-                         L.seid, L.kf, d_err);
-      if ((rc = read_err(d_err, s))) return rc;
-      dg.row_ptr = g->row_ptr;
-      dg.perm = nullptr;
-    }
-  }
-  // oriented CSR: stable compaction of the symmetric rows by the orientation flag
-  scan_exclusive_i32_to_i64(L.kf, L.opos, m2, L.stmp, s);
-  hipLaunchKernelGGL(k_orow, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, dg.row_ptr, L.opos, n, L.orow);
-  hipLaunchKernelGGL(k_ocsr, dim3(grid_for(m2)), dim3(kT), 0, s, L.col, L.seid, L.kf, L.opos, m2, L.ocol, L.oeid);
-  TRUSS_HIP(hipGetLastError());
   dg.col = L.col;
   dg.seid = L.seid;
   dg.eu = L.eu;
   dg.ev = L.ev;
-  dg.orow = L.orow;
-  dg.ocol = L.ocol;
-  dg.oeid = L.oeid;
-  // row hash tables for the membership tests of peeling (the sorted builds
-  // filled them while placing the row entries)
-  if (dg.perm == nullptr) {
-    table_layout(dg.row_ptr, n, m, L, s);
-    if (m > 0) hipLaunchKernelGGL(k_rtab_insert, dim3(grid_for(m)), dim3(kT), 0, s, L.eu, L.ev, m, L.rtoff, L.rtab);
-  }
-  TRUSS_HIP(hipGetLastError());
   dg.rtab = L.rtab;
   dg.rtoff = L.rtoff;
-  if (relabel && g->fmt == TRUSS_FMT_CSR && m2 > 0) {
-    hipLaunchKernelGGL(k_csr_sym_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, m2, L.rank, L.rtab,
-                       L.rtoff, d_err);
-    return read_err(d_err, s);
+  if (relabel) return build_relabelled(g, L, dg, vb, d_err, s, needs);
+
+  hipLaunchKernelGGL(k_build_init, dim3(1), dim3(1), 0, s, d_err, (int32_t*)nullptr, (int64_t)0);
+  int rc;
+  if (g->fmt == TRUSS_FMT_EDGES) {
+    hipLaunchKernelGGL(k_canon, dim3(grid_for(m)), dim3(kT), 0, s, g->src, g->dst, m, n, vb, L.key, L.val, d_err);
+    rows_from_keys(n, m, vb, L, needs, d_err, s);
+    if ((rc = read_err(d_err, s))) return rc;
+    dg.row_ptr = L.row_ptr;
+    dg.perm = L.perm;
+  } else {
+    hipLaunchKernelGGL(k_rowptr_check, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n, m2, d_err);
+    if ((rc = read_err(d_err, s))) return rc;
+    hipLaunchKernelGGL(k_rowid, dim3(grid_for((int64_t)n * kWave > 0 ? (int64_t)n * kWave : 1)), dim3(kT), 0, s,
+                       g->row_ptr, n, L.rowid);
+    hipLaunchKernelGGL(k_csr_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->row_ptr, g->col, n, m2, L.rowid, L.uf,
+                       d_err);
+    int64_t* upos = L.opos;
+    scan_exclusive_i32_to_i64(L.uf, upos, m2, L.stmp, s);
+    hipLaunchKernelGGL(k_check_total, dim3(1), dim3(1), 0, s, upos, m2, m, d_err);
+    if ((rc = read_err(d_err, s))) return rc;
+    const bool own = needs != kBuildRows;  // rows alone: the input's are used as they are
+    if (own)
+      hipLaunchKernelGGL(k_csr_upper, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, upos, m2, m, L.col, L.seid,
+                         L.eu, L.ev);
+    hipLaunchKernelGGL(k_csr_lower, dim3(grid_for(m2)), dim3(kT), 0, s, g->row_ptr, g->col, L.rowid, upos, m2,
+                       own ? L.seid : nullptr, d_err);
+    if ((rc = read_err(d_err, s))) return rc;
+    dg.row_ptr = g->row_ptr;
+    dg.perm = nullptr;
+    if (!own) dg.col = const_cast<int32_t*>(g->col);  // read only
   }
+  TRUSS_HIP(hipGetLastError());
   return TRUSS_OK;
 }
 

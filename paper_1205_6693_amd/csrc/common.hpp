@@ -197,12 +197,7 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, unsigned gen, unsig
   return s_ok != 0;
 }
 
-// ---- ordering of vertices for the orientation --------------------------------
-// u precedes v iff (deg u, u) < (deg v, v); edges point from earlier to later.
-__device__ __forceinline__ bool vertex_before(int64_t du, int u, int64_t dv, int v) {
-  return du < dv || (du == dv && u < v);
-}
-
+// ---- searches in sorted rows ----------------------------------------------------
 // lower_bound of `key` in the sorted range a[lo, hi)
 template <typename IdxT>
 __device__ __forceinline__ IdxT lower_bound_i32(const int* __restrict__ a, IdxT lo, IdxT hi, int key) {

@@ -60,10 +60,9 @@ struct DevGraph {
   int32_t* seid = nullptr;           // 2m edge id of each CSR entry
   int32_t* eu = nullptr;             // m smaller-id endpoint
   int32_t* ev = nullptr;             // m larger-id endpoint
-  int64_t* orow = nullptr;           // n+1 oriented CSR offsets
-  int32_t* ocol = nullptr;           // m out-neighbours, ascending
-  int32_t* oeid = nullptr;           // m edge ids of oriented entries
-  int32_t* perm = nullptr;           // m canonical edge -> input index (EDGES only)
+  int64_t* orow = nullptr;           // n+1 oriented CSR offsets (relabelled builds)
+  int32_t* ocol = nullptr;           // m out-neighbours, ascending; entry j is edge j
+  int32_t* perm = nullptr;           // m built edge -> caller's edge (null: the same)
   int2* rtab = nullptr;               // row hash tables (neighbour, edge id), back to back
   const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two)
   void* tmp = nullptr;               // the build's temporaries, free for later phases once it has returned
@@ -78,7 +77,14 @@ struct BuildBufs;
 // vertex ids back out of dg
 // tmp_bytes (nullable): bytes of the temporaries that later phases may use (DevGraph::tmp)
 size_t build_workspace(const truss_graph* g, Arena& a, bool relabel = false, size_t* tmp_bytes = nullptr);
-int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel = false);
+// What a caller reads of the built graph beyond n, m and perm; the rest is not
+// built.  Relabelled builds always give the canonical edges and the oriented CSR.
+enum : int {
+  kBuildRows = 1,   // row_ptr, col (alone, without relabelling, on CSR input: the input's own)
+  kBuildIds = 2,    // with kBuildRows: seid, eu, ev
+  kBuildTables = 4  // with both, relabelled: rtab, rtoff
+};
+int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel, int needs);
 
 // Scheduling of the exact methods (the scheduler never changes results).
 struct SupPlan {

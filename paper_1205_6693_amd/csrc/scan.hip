@@ -71,7 +71,9 @@ __global__ void __launch_bounds__(1024) k_scan_partials(OutT* __restrict__ parti
 
 template <typename InT, typename OutT>
 __global__ void __launch_bounds__(kScanThreads) k_scan_apply(const InT* __restrict__ in, OutT* __restrict__ out,
-                                                              int64_t n, const OutT* __restrict__ partial) {
+                                                              int64_t n, const OutT* __restrict__ partial,
+                                                              int64_t ntiles) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partial[ntiles];
   __shared__ OutT tile[kTile + kTile / 32];
   __shared__ OutT wt[kScanThreads / kWave];
   const int64_t base = (int64_t)blockIdx.x * kTile;
@@ -106,9 +108,23 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(const InT* __restri
   }
 }
 
-template <typename OutT>
-__global__ void k_store_total(OutT* out, int64_t n, const OutT* partial, int64_t ntiles) {
-  out[n] = partial[ntiles];
+// The whole scan in one workgroup, for up to kOneBlock elements: three launches
+// would take longer than the work.
+constexpr int kOneThreads = 1024, kOneItems = 16;
+constexpr int64_t kOneBlock = kOneThreads * kOneItems;
+template <typename InT, typename OutT>
+__global__ void __launch_bounds__(kOneThreads) k_scan_one(const InT* __restrict__ in, OutT* __restrict__ out, int n) {
+  __shared__ OutT wt[kOneThreads / kWave];
+  OutT carry = 0;
+  for (int base = 0; base < n; base += kOneThreads) {
+    const int i = base + (int)threadIdx.x;
+    const OutT x = i < n ? (OutT)in[i] : (OutT)0;
+    OutT total;
+    const OutT ex = block_exclusive_sum(x, wt, &total);
+    if (i < n) out[i] = carry + ex;
+    carry += total;
+  }
+  if (threadIdx.x == 0) out[n] = carry;
 }
 
 template <typename OutT>
@@ -120,11 +136,14 @@ void scan_impl(const InT* in, OutT* out, int64_t n, OutT* tmp, hipStream_t s) {
     hipLaunchKernelGGL(k_zero1<OutT>, dim3(1), dim3(1), 0, s, out);
     return;
   }
+  if (n <= kOneBlock) {
+    hipLaunchKernelGGL((k_scan_one<InT, OutT>), dim3(1), dim3(kOneThreads), 0, s, in, out, (int)n);
+    return;
+  }
   const int64_t ntiles = (n + kTile - 1) / kTile;
   hipLaunchKernelGGL((k_scan_reduce<InT, OutT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tmp);
   hipLaunchKernelGGL(k_scan_partials<OutT>, dim3(1), dim3(1024), 0, s, tmp, ntiles);
-  hipLaunchKernelGGL((k_scan_apply<InT, OutT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, out, n, tmp);
-  hipLaunchKernelGGL(k_store_total<OutT>, dim3(1), dim3(1), 0, s, out, n, tmp, ntiles);
+  hipLaunchKernelGGL((k_scan_apply<InT, OutT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, out, n, tmp, ntiles);
 }
 
 // ---- radix sort -------------------------------------------------------------------
@@ -159,13 +178,27 @@ __global__ void __launch_bounds__(kRadixThreads) k_rs_hist(const K* __restrict__
 // prefix over the wavefronts places every element.
 template <typename K>
 __global__ void __launch_bounds__(kRadixThreads) k_rs_scatter(const K* __restrict__ keys, const int32_t* __restrict__ vals,
-                                                               int64_t n, int shift, const int32_t* __restrict__ offs,
-                                                               int64_t ntiles, K* __restrict__ keys_out,
+                                                               int64_t n, int shift, const int32_t* __restrict__ counts,
+                                                               const int32_t* __restrict__ offs, int64_t ntiles,
+                                                               K* __restrict__ keys_out,
                                                                int32_t* __restrict__ vals_out) {
   __shared__ int run[256];
   __shared__ int wcnt[kRadixWaves][256];
   const int w = threadIdx.x / kWave, lane = lane_id();
-  run[threadIdx.x] = offs[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+  if (offs) {
+    run[threadIdx.x] = offs[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+  } else {
+    // few tiles: this tile's offsets straight from the counts, thread t for digit t
+    __shared__ int s_scan[kRadixWaves];
+    int before = 0, all = 0;
+    for (int q = 0; q < (int)ntiles; ++q) {
+      const int c = counts[(int64_t)threadIdx.x * ntiles + q];
+      before += q < (int)blockIdx.x ? c : 0;
+      all += c;
+    }
+    int total;
+    run[threadIdx.x] = block_exclusive_sum(all, s_scan, &total) + before;
+  }
   for (int q = 0; q < kRadixWaves; ++q) wcnt[q][threadIdx.x] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * kRadixTile + (int64_t)w * kWave * kRadixItems;
@@ -217,6 +250,11 @@ __global__ void __launch_bounds__(kRadixThreads) k_rs_scatter(const K* __restric
   }
 }
 
+// Up to this many tiles every scatter workgroup sums the tile counts itself
+// (64 tiles: 16 K counts, 64 KB from the L2), which saves the scan's launches; with
+// more, each workgroup would read more than its own tile.
+constexpr int64_t kFewTiles = 64;
+
 template <typename K>
 bool radix_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int64_t n, int bits,
                 int32_t* tmp, hipStream_t s) {
@@ -231,9 +269,9 @@ bool radix_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int64_t 
   int32_t* vout = vals_alt;
   for (int shift = 0; shift < bits; shift += 8) {
     hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, n, shift, counts, ntiles);
-    scan_impl<int32_t, int32_t>(counts, offs, 256 * ntiles, stmp, s);
-    hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, vin, n, shift, offs,
-                       ntiles, kout, vout);
+    if (ntiles > kFewTiles) scan_impl<int32_t, int32_t>(counts, offs, 256 * ntiles, stmp, s);
+    hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, vin, n, shift, counts,
+                       ntiles > kFewTiles ? offs : nullptr, ntiles, kout, vout);
     K* tk = kin; kin = kout; kout = tk;
     int32_t* tv = vin; vin = vout; vout = tv;
   }

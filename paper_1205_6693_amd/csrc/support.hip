@@ -22,7 +22,7 @@
 // position j of ocol counts into supo[j]): the pairs (b, c) a wavefront walks
 // sit at consecutive positions of N+(b), so their increments land on the same
 // few lines, and the per-vertex flushes of the (a, b), (a, c) counts are
-// contiguous.  One pass at the end moves supo into edge-id order.
+// contiguous.  Position j is edge j, so supo is the result.
 #include "common.hpp"
 #include "internal.hpp"
 #include "mlp.hpp"
@@ -55,9 +55,13 @@ struct SupCtl {
   float feat[kBins][kSupF];                  // the decision's features
 };
 
-__global__ void k_sup_zero(int32_t* __restrict__ supo, int64_t m, SupCtl* ctl) {
+// supports and, for the peeling, round stamps cleared
+__global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ stamp, int64_t m, SupCtl* ctl) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < m) supo[i] = 0;
+  if (i < m) {
+    supo[i] = 0;
+    if (stamp) stamp[i] = 0;
+  }
   if (i < kBins) {
     ctl->cnt[i] = 0;
     ctl->fetch[i] = 0;
@@ -160,15 +164,6 @@ __global__ void __launch_bounds__(kBins * kWave) k_sup_decide(SupCtl* ctl, int64
     ctl->act[b] = act;
     for (int i = 0; i < kSupF; ++i) ctl->feat[b][i] = x[i];
   }
-}
-
-// sup(e) in edge-id order from the counts by oriented position, and round stamps 0
-__global__ void k_sup_finish(const int32_t* __restrict__ supo, const int32_t* __restrict__ oeid, int64_t m,
-                             int32_t* __restrict__ sup, int32_t* __restrict__ stamp) {
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= m) return;
-  sup[oeid[j]] = supo[j];
-  if (stamp) stamp[j] = 0;
 }
 
 // ---- the hash method: N+(a) in an LDS hash table, the (b, c) pairs walked by
@@ -720,13 +715,11 @@ inline unsigned grid_for(int64_t n) {
 struct SupLayout {
   SupCtl* ctl;
   int32_t* vlist;
-  int32_t* supo;  // counts by oriented position
 };
 
 void carve(const DevGraph& dg, Arena& a, SupLayout& L) {
   L.ctl = a.take<SupCtl>(1);
   L.vlist = a.take<int32_t>((size_t)kBins * (dg.n + 1));
-  L.supo = a.take<int32_t>((size_t)dg.m + 1);
 }
 
 // workgroup sizes of the hash kernels of bins 1 and 2
@@ -747,7 +740,7 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
   if (a.overflow()) return TRUSS_E_WORKSPACE;
   const int64_t m = dg.m;
   const int32_t n = dg.n;
-  hipLaunchKernelGGL(k_sup_zero, dim3(grid_for(m > kBins ? m : kBins)), dim3(kT), 0, s, L.supo, m, L.ctl);
+  hipLaunchKernelGGL(k_sup_zero, dim3(grid_for(m > kBins ? m : kBins)), dim3(kT), 0, s, sup, stamp, m, L.ctl);
   if (m == 0) return TRUSS_OK;
   hipLaunchKernelGGL(k_sup_bin, dim3((unsigned)((n + kBinT - 1) / kBinT > 0 ? (n + kBinT - 1) / kBinT : 1)),
                      dim3(kBinT), 0, s, dg.orow, n, L.vlist, L.ctl);
@@ -778,26 +771,25 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
     if (m < dlo[b] * (dlo[b] + 1) / 2) continue;
     if (may(b, kHash)) {
       if (b == 0)
-        hipLaunchKernelGGL(k_sup_hash_wave, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
+        hipLaunchKernelGGL(k_sup_hash_wave, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, sup);
       else if (b == 1)
         hipLaunchKernelGGL((k_sup_hash_block<kBlockMax1, kHashT1>), dim3(gb), dim3(kHashT1), 0, s, dg.orow, dg.ocol,
-                           n, L.vlist, 1, L.ctl, L.supo);
+                           n, L.vlist, 1, L.ctl, sup);
       else if (b == 2)
         hipLaunchKernelGGL((k_sup_hash_block<kBlockMax2, kHashT2>), dim3(g2), dim3(kHashT2), 0, s, dg.orow, dg.ocol,
-                           n, L.vlist, 2, L.ctl, L.supo);
+                           n, L.vlist, 2, L.ctl, sup);
     }
     if (may(b, kBsearch)) {
       if (b == 0)
-        hipLaunchKernelGGL(k_sup_wave_bs, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, L.supo);
+        hipLaunchKernelGGL(k_sup_wave_bs, dim3(gw), dim3(kT), 0, s, dg.orow, dg.ocol, L.vlist, L.ctl, sup);
       else
         hipLaunchKernelGGL(k_sup_chunked, dim3(b == 1 ? gb : g2), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b,
-                           L.ctl, L.supo);
+                           L.ctl, sup);
     }
     if (may(b, kMerge))
       hipLaunchKernelGGL(k_sup_merge, dim3(b == 0 ? gw : gb), dim3(kT), 0, s, dg.orow, dg.ocol, n, L.vlist, b, L.ctl,
-                         L.supo);
+                         sup);
   }
-  hipLaunchKernelGGL(k_sup_finish, dim3(grid_for(m)), dim3(kT), 0, s, L.supo, dg.oeid, m, sup, stamp);
   if (timed) (void)hipEventRecord(ev[kBins], s);
   TRUSS_HIP(hipGetLastError());
   if (trace) {
