@@ -196,7 +196,8 @@ int truss_decompose(const truss_graph *g, int32_t *truss_out, const truss_option
  * graph is validated as an edge list; the failing graph of smallest index
  * decides the returned code (the other graphs' outputs are then unspecified).
  * The workspace holds the offsets, a scratch slot per concurrent workgroup
- * (about 8 bytes per vertex and 48 per edge of the largest batched graph, for
+ * (about 8 bytes per vertex and 48 per edge of the largest batched graph; 16
+ * and 50 where that has at most 2^13 vertices and 2^18 edges; for
  * up to four workgroups per compute unit) and the device-wide path's workspace
  * for the largest remaining graph. */
 int truss_batch_workspace_size(int32_t num_graphs, const int64_t *vtx_off, const int64_t *edge_off,

@@ -37,18 +37,20 @@ constexpr int64_t kBatchMaxM = 1 << 21;  // larger graphs take the device-wide p
 constexpr int64_t kBatchMaxN = 1 << 22;
 
 struct BatchCtl {
-  int next;        // queue head
+  int next;        // queue head (general kernel)
   int err_g;       // smallest failing graph index
   int kmax;
-  int pad;
+  int next_compact;  // queue head (compact kernel)
   unsigned long long levels, subrounds, triangles3;
   unsigned long long sup_work, peel_work;  // row entries walked (support, peeling)
   unsigned long long t_phase[3];            // workgroup time in CSR build, support, peeling (10 ns ticks)
 };
 
 struct BatchArgs {
-  int G;                   // graphs in the queue
-  const int32_t* order;    // queue: graph ids, largest first
+  int G;                   // graphs in the general kernel's queue
+  const int32_t* order;    // that queue: graph ids, largest first
+  int Gc;                  // the same of the compact kernel
+  const int32_t* order_c;
   const int64_t* vo;       // G+1 vertex offsets (device copy)
   const int64_t* eo;       // G+1 edge offsets (device copy)
   const int32_t* src;
@@ -704,6 +706,717 @@ __global__ void __launch_bounds__(T) k_batch(BatchArgs A) {
   }
 }
 
+// ---- compact graphs: up to 2^13 vertices and 2^18 edges --------------------------------------
+//
+// The same method with everything small: a row entry is one word (neighbour id in
+// 13 bits, edge id in 18), the membership test looks the neighbour up in a
+// hash table of such words per vertex, and what the walks ask of every edge they meet --
+// removed? in this round's frontier? -- are two bitmaps in LDS.  A walked entry then
+// costs two dependent loads (row, table) where the general path makes four and a
+// binary search.  Vertices are renumbered by (degree, id), so the out-neighbours
+// that triangle listing walks are the tail of the sorted row, every triangle is
+// found once instead of three times, and an edge's id is its place among the
+// out-neighbours of all vertices in order (perm maps it to the input), so that
+// the counts of neighbouring entries share lines.  Rows are sorted by setting
+// their neighbours' bits in a bitmap of all ids and counting the bits below:
+// linear in the row, where comparing all pairs took a tenth of the batch.
+//
+// What bounds a walk here is instruction issue (16 wavefronts a compute unit, some
+// 4 cycles a walked entry and unit) and, with all units busy, the 128-byte
+// lines the tables of hubs draw.  1024 graphs of up to 8192 vertices and 262 K edges:
+// 388 ms with the general kernel, whose longest graphs alone took 350, against 90
+// (tables probed slot by slot 115, by buckets of four 98; with the starts of the
+// walks searched for every entry 98).
+constexpr int kCN = 1 << 13, kCM = 1 << 18;
+constexpr int kIdBits = 18, kNbShift = 19;
+constexpr uint32_t kIdMask = (1u << kIdBits) - 1u;
+constexpr uint32_t kNoSlot = 0xffffffffu;   // its id field is no edge's (ids are below 2^18)
+constexpr int kBits = kCN / 32;             // words of a bitmap over the vertices
+constexpr int kMaxOut = 1024;               // out-degrees are at most sqrt(2 m) < 725
+
+struct CompactSlot {
+  uint32_t *rp, *len, *tab, *up;  // row offset, live length, table (offset << 4 | log2 slots), first edge id
+  uint32_t* rows;                 // 2m words, rows sorted by neighbour
+  uint32_t* slots;                // 6m words: tables of buckets of 4 (before that the unsorted rows)
+  int32_t* sup;                   // (before that the edge ids by input position)
+  uint32_t *live, *gone;          // (smaller end << 18 | edge) live; in order of removal
+  int32_t* perm;                  // edge -> input position
+  uint16_t* ev;                   // larger end
+};
+
+__host__ __device__ inline size_t compact_bytes(int64_t n, int64_t m) {
+  return 4 * align256((size_t)(n + 1) * 4) + align256((size_t)(2 * m + 1) * 4) + align256((size_t)(6 * m + 1) * 4) +
+         4 * align256((size_t)(m + 1) * 4) + align256((size_t)(m + 1) * 2);
+}
+
+__device__ inline CompactSlot compact_at(char* p, int n, int m) {
+  const size_t nb = align256((size_t)(n + 1) * 4), mb = align256((size_t)(m + 1) * 4);
+  CompactSlot S;
+  S.rp = (uint32_t*)p;
+  S.len = (uint32_t*)(p += nb);
+  S.tab = (uint32_t*)(p += nb);
+  S.up = (uint32_t*)(p += nb);
+  S.rows = (uint32_t*)(p += nb);
+  S.slots = (uint32_t*)(p += align256((size_t)(2 * m + 1) * 4));
+  S.sup = (int32_t*)(p += align256((size_t)(6 * m + 1) * 4));
+  S.live = (uint32_t*)(p += mb);
+  S.gone = (uint32_t*)(p += mb);
+  S.perm = (int32_t*)(p += mb);
+  S.ev = (uint16_t*)(p += mb);
+  return S;
+}
+
+template <typename T>
+__device__ __forceinline__ T ldg(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// LDS of the three stages, one over the other, in the kernel's dynamic LDS.
+struct BuildLds {
+  uint32_t key[kCN];      // (degree << 13 | old id) sorted, then row cursors
+  uint16_t rank[kCN];     // old id -> new id
+  uint32_t half[kCN / 2]; // 16-bit counters: degrees by old id, then out-degrees by new id
+};
+struct WaveLds {  // a wavefront's row as a bitmap, with the bits below each word
+  uint32_t bits[kBits];
+  uint16_t below[kBits];
+  uint32_t cnt[kMaxOut / 2];  // 16-bit counters by position among the out-neighbours
+  int pre[kWave];
+  int st[kWave];
+};
+template <int T>
+struct PeelLds {
+  uint32_t pre[T + 1], eb[T], base[T], tab[T];  // eb: (b << 18 | edge)
+  int own[T];
+  // followed by the two bitmaps
+};
+template <int T>
+__host__ __device__ inline size_t compact_lds(int64_t n, int64_t m) {
+  (void)n;
+  const size_t build = sizeof(BuildLds), wave = sizeof(WaveLds) * (T / kWave);
+  const size_t peel = sizeof(PeelLds<T>) + 2 * (((size_t)m + 31) / 32 + 1) * 4;
+  const size_t a = build > wave ? build : wave;
+  return a > peel ? a : peel;
+}
+
+template <int T>
+struct CompactCtl {  // static LDS
+  int tmp[T / kWave + 2];
+  int err, next, g, cnt, qn, minv;
+};
+
+// inclusive sum over the workgroup; *total
+template <int T>
+__device__ __forceinline__ int block_scan32(int v, int* tmp, int* total) {
+  const int w = threadIdx.x / kWave;
+  const int inc = wave_inclusive_sum(v);
+  if (lane_id() == kWave - 1) tmp[w] = inc;
+  __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll 4
+  for (int q = 0; q < T / kWave; ++q) {
+    const int x = tmp[q];
+    if (q < w) base += x;
+    all += x;
+  }
+  __syncthreads();
+  *total = all;
+  return base + inc;
+}
+
+__device__ __forceinline__ int half_add(uint32_t* h, int i, int v) {  // 16-bit counter i; the value before
+  const uint32_t old = atomicAdd(&h[i >> 1], (uint32_t)v << (16 * (i & 1)));
+  return (int)(old >> (16 * (i & 1))) & 0xffff;
+}
+__device__ __forceinline__ int half_get(const uint32_t* h, int i) { return (int)(h[i >> 1] >> (16 * (i & 1))) & 0xffff; }
+
+// bits set below each word of a wavefront's bitmap
+__device__ __forceinline__ void count_below(WaveLds& W) {
+  const int lane = lane_id();
+  uint32_t b[kBits / kWave];
+  int c = 0;
+#pragma unroll
+  for (int i = 0; i < kBits / kWave; ++i) {
+    b[i] = W.bits[lane * (kBits / kWave) + i];
+    c += __popc(b[i]);
+  }
+  int run = wave_inclusive_sum(c) - c;
+#pragma unroll
+  for (int i = 0; i < kBits / kWave; ++i) {
+    W.below[lane * (kBits / kWave) + i] = (uint16_t)run;
+    run += __popc(b[i]);
+  }
+}
+__device__ __forceinline__ int rank_in(const WaveLds& W, int w) {
+  return W.below[w >> 5] + __popc(W.bits[w >> 5] & ((1u << (w & 31)) - 1u));
+}
+
+// first slot of the bucket of w in a table of 2^lg slots (lg >= 2); a bucket is
+// filled from its first slot on and runs over into the next
+__device__ __forceinline__ uint32_t bucket_of(int w, int lg) {
+  return lg == 2 ? 0u : (((uint32_t)w * 2654435769u) >> (32 - (lg - 2))) << 2;
+}
+
+template <int T, int NI>
+__device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* lds, CompactCtl<T>& C) {
+  const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+  const int n = (int)(A.vo[g + 1] - A.vo[g]);
+  const int m = (int)(A.eo[g + 1] - A.eo[g]);
+  const int32_t* src = A.src + A.eo[g];
+  const int32_t* dst = A.dst + A.eo[g];
+  int32_t* out = A.out + A.eo[g];
+  if (m == 0) {
+    if (tid == 0) A.gerr[g] = 0;
+    return;
+  }
+  const CompactSlot S = compact_at(scratch, n, m);
+  const unsigned long long t0 = wall_clock64();
+  // ---- build --------------------------------------------------------------------------------
+  BuildLds& B = *reinterpret_cast<BuildLds*>(lds);
+  int np = 1;
+  while (np < n) np <<= 1;
+  for (int x = tid; x < (n + 1) / 2; x += T) B.half[x] = 0u;
+  if (tid == 0) C.err = kNoErr;
+  __syncthreads();
+  // degrees; range and self-loop checks (Section 2: simple graphs).  Repeated
+  // pairs may push a 16-bit count over, but never past its word: a count
+  // stops mattering once it reaches n, which only repeats can do.
+  for (int i = tid; i < m; i += T) {
+    const int u = src[i], v = dst[i];
+    int e = 0;
+    if (u < 0 || u >= n || v < 0 || v >= n) e = kErrRange;
+    else if (u == v) e = kErrSelfloop;
+    if (e) {
+      atomicMin(&C.err, e);
+      continue;
+    }
+    if (half_add(B.half, u, 1) >= n || half_add(B.half, v, 1) >= n) atomicMin(&C.err, kErrDup);
+  }
+  __syncthreads();
+  if (C.err < kErrDup) {
+    if (tid == 0) {
+      A.gerr[g] = -C.err;
+      atomicMin(&A.ctl->err_g, g);
+    }
+    return;
+  }
+  if (C.err != kNoErr) {  // a degree above n - 1: some pair is repeated
+    if (tid == 0) {
+      A.gerr[g] = -kErrDup;
+      atomicMin(&A.ctl->err_g, g);
+    }
+    return;
+  }
+  // new ids by (degree, id): bitonic sort of the keys
+  for (int x = tid; x < np; x += T) B.key[x] = x < n ? ((uint32_t)half_get(B.half, x) << 13) | (uint32_t)x : 0xffffffffu;
+  __syncthreads();
+  for (int k = 2; k <= np; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int x = tid; x < np / 2; x += T) {
+        const int lo = ((x & ~(j - 1)) << 1) | (x & (j - 1)), hi = lo | j;
+        const uint32_t a = B.key[lo], b = B.key[hi];
+        if ((a > b) == ((lo & k) == 0)) {
+          B.key[lo] = b;
+          B.key[hi] = a;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (int x = tid; x < n; x += T) B.rank[B.key[x] & (kCN - 1)] = (uint16_t)x;
+  for (int x = tid; x < (n + 1) / 2; x += T) B.half[x] = 0u;
+  __syncthreads();
+  for (int i = tid; i < m; i += T) {
+    const int x = B.rank[src[i]], y = B.rank[dst[i]];
+    half_add(B.half, x < y ? x : y, 1);
+  }
+  __syncthreads();
+  // row offsets, first edge ids, tables; the keys become row cursors
+  {
+    int row0 = 0, up0 = 0, tab0 = 0;
+    for (int x0 = 0; x0 < n; x0 += T) {
+      const int x = x0 + tid;
+      const int d = x < n ? (int)(B.key[x] >> 13) : 0;
+      const int u = x < n ? half_get(B.half, x) : 0;
+      int lg = 2;
+      while ((1 << lg) < d + (d + 1) / 2) ++lg;  // 1.5 d slots or more, at least a bucket, fewer than 3 d
+      const int sz = d > 1 ? 1 << lg : 0;        // the only neighbour of a vertex is never looked up
+      int td, tu, tt;
+      const int id = block_scan32<T>(d, C.tmp, &td);
+      const int iu = block_scan32<T>(u, C.tmp, &tu);
+      const int it = block_scan32<T>(sz, C.tmp, &tt);
+      if (x < n) {
+        S.rp[x] = (uint32_t)(row0 + id - d);
+        S.len[x] = (uint32_t)d;
+        S.up[x] = (uint32_t)(up0 + iu - u);
+        S.tab[x] = ((uint32_t)(tab0 + it - sz) << 4) | (uint32_t)lg;
+        B.key[x] = (uint32_t)(row0 + id - d);
+      }
+      row0 += td;
+      up0 += tu;
+      tab0 += tt;
+    }
+    if (tid == 0) {
+      S.rp[n] = (uint32_t)row0;
+      S.tab[n] = (uint32_t)tab0;  // slots in all
+      S.up[n] = (uint32_t)up0;
+    }
+  }
+  __syncthreads();
+  // every edge into both rows, unordered: (neighbour, input position)
+  for (int i = tid; i < m; i += T) {
+    const uint32_t x = B.rank[src[i]], y = B.rank[dst[i]];
+    S.slots[atomicAdd(&B.key[x], 1u)] = (y << kNbShift) | (uint32_t)i;
+    S.slots[atomicAdd(&B.key[y], 1u)] = (x << kNbShift) | (uint32_t)i;
+  }
+  if (tid == 0) C.next = 0;
+  __syncthreads();
+  // rows sorted through a bitmap; the edge ids of the upper entries by input position
+  WaveLds& W = reinterpret_cast<WaveLds*>(lds)[wv];
+  for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
+  wave_sync();
+  for (;;) {
+    int x = 0;
+    if (lane == 0) x = n - 1 - atomicAdd(&C.next, 1);  // long rows first
+    x = __shfl(x, 0, kWave);
+    if (x < 0) break;
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    if (d == 0) continue;
+    for (int j = lane; j < d; j += kWave) {
+      const int w = (int)(ldg(&S.slots[base + j]) >> kNbShift);
+      if (atomicOr(&W.bits[w >> 5], 1u << (w & 31)) >> (w & 31) & 1u) atomicMin(&C.err, kErrDup);
+    }
+    wave_sync();
+    count_below(W);
+    wave_sync();
+    const int up = (int)ldg(&S.up[x]), low = d - ((int)ldg(&S.up[x + 1]) - up);
+    for (int j = lane; j < d; j += kWave) {
+      const uint32_t v = ldg(&S.slots[base + j]);
+      const int r = rank_in(W, (int)(v >> kNbShift));
+      S.rows[base + r] = v;
+      if (r >= low) {
+        const int id = up + r - low, i = (int)(v & kIdMask);
+        if (id < m) {  // (repeated pairs, reported below, can leave ranks that do not fit)
+          S.sup[i] = id;
+          S.perm[id] = i;
+          S.ev[id] = (uint16_t)(v >> kNbShift);
+          S.live[id] = ((uint32_t)x << kIdBits) | (uint32_t)id;
+        }
+      }
+    }
+    wave_sync();
+    for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
+    wave_sync();
+  }
+  __syncthreads();
+  if (C.err != kNoErr) {
+    if (tid == 0) {
+      A.gerr[g] = -C.err;
+      atomicMin(&A.ctl->err_g, g);
+    }
+    return;
+  }
+  // the entries' edge ids; cleared tables
+  {
+    for (int i = tid; i < (int)ldg(&S.tab[n]); i += T) S.slots[i] = kNoSlot;
+    for (int j = tid; j < 2 * m; j += T) {
+      const uint32_t v = ldg(&S.rows[j]);
+      S.rows[j] = (v & ~((1u << kNbShift) - 1u)) | (uint32_t)ldg(&S.sup[v & kIdMask]);
+    }
+  }
+  if (tid == 0) C.next = 0;
+  __syncthreads();
+  for (int i = tid; i < m; i += T) S.sup[i] = 0;
+  for (;;) {
+    int x = 0;
+    if (lane == 0) x = n - 1 - atomicAdd(&C.next, 1);
+    x = __shfl(x, 0, kWave);
+    if (x < 0) break;
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    if (d < 2) continue;
+    const uint32_t tb = ldg(&S.tab[x]);
+    const int lg = (int)(tb & 15);
+    uint32_t* t = S.slots + (tb >> 4);
+    const uint32_t mask = (1u << lg) - 1u;
+    for (int j = lane; j < d; j += kWave) {
+      const uint32_t v = ldg(&S.rows[base + j]);
+      uint32_t h = bucket_of((int)(v >> kNbShift), lg);
+      while (atomicCAS(&t[h], kNoSlot, v) != kNoSlot) h = (h + 1) & mask;  // at most 2/3 full
+    }
+  }
+  __syncthreads();  // every wavefront has seen the end of the list
+  if (tid == 0) C.next = 0;
+  __syncthreads();
+  const unsigned long long t1 = wall_clock64();
+  // ---- support (each triangle once, from its lowest vertex) --------------------------------------
+  unsigned long long tri = 0, wsup = 0, wpeel = 0;
+  for (int i = lane; i < kMaxOut / 2; i += kWave) W.cnt[i] = 0u;
+  wave_sync();
+  for (;;) {
+    int a = 0;
+    if (lane == 0) a = n - 1 - atomicAdd(&C.next, 1);
+    a = __shfl(a, 0, kWave);
+    if (a < 0) break;
+    const int ua = (int)ldg(&S.up[a]), da = (int)ldg(&S.up[a + 1]) - ua;
+    if (da < 2) continue;
+    const int oa = (int)ldg(&S.rp[a + 1]) - da;  // the out-neighbours end the row
+    for (int j = lane; j < da; j += kWave) {
+      const int w = (int)(ldg(&S.rows[oa + j]) >> kNbShift);
+      atomicOr(&W.bits[w >> 5], 1u << (w & 31));
+    }
+    wave_sync();
+    count_below(W);
+    wave_sync();
+    for (int c0 = 0; c0 < da; c0 += kWave) {
+      int ob = 0, db = 0;
+      if (c0 + lane < da) {
+        const int b = (int)(ldg(&S.rows[oa + c0 + lane]) >> kNbShift);
+        db = (int)ldg(&S.up[b + 1]) - (int)ldg(&S.up[b]);
+        ob = (int)ldg(&S.rp[b + 1]) - db;
+      }
+      const int inc = wave_inclusive_sum(db);
+      const int tot = __shfl(inc, kWave - 1, kWave);
+      W.pre[lane] = inc - db;
+      W.st[lane] = ob - (inc - db);
+      wave_sync();
+      wsup += lane == 0 ? (unsigned long long)tot : 0ULL;
+      constexpr int U = 4;  // windows of 64 pairs in flight
+      for (int q0 = 0; q0 < tot; q0 += U * kWave) {
+        int k[U];
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = 0;
+#pragma unroll
+        for (int st = kWave / 2; st > 0; st >>= 1) {
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (W.pre[k[u] + st] <= q0 + u * kWave + lane) k[u] += st;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int t = q0 + u * kWave + lane;
+          v[u] = t < tot ? ldg(&S.rows[W.st[k[u]] + t]) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c = (int)(v[u] >> kNbShift);
+          const bool hit = q0 + u * kWave + lane < tot && (W.bits[c >> 5] >> (c & 31) & 1u);
+          if (hit) {
+            tri += 1;
+            half_add(W.cnt, c0 + k[u], 1);
+            half_add(W.cnt, rank_in(W, c), 1);
+            atomicAdd(&S.sup[v[u] & kIdMask], 1);
+          }
+        }
+      }
+      wave_sync();
+    }
+    for (int j = lane; j < da; j += kWave) {
+      const int c = half_get(W.cnt, j);
+      if (c) atomicAdd(&S.sup[ua + j], c);
+    }
+    wave_sync();
+    for (int j = lane; j < (da + 1) / 2; j += kWave) W.cnt[j] = 0u;
+    for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
+    wave_sync();
+  }
+  __syncthreads();
+  const unsigned long long t2 = wall_clock64();
+  // ---- peeling, level by level (Algorithm 2, level-synchronous) ------------------------------------
+  PeelLds<T>& L = *reinterpret_cast<PeelLds<T>*>(lds);
+  const int words = (m + 31) / 32;
+  uint32_t* removed = reinterpret_cast<uint32_t*>(&L + 1);  // removed in an earlier round
+  uint32_t* front = removed + words + 1;                    // in this round's frontier
+  for (int i = tid; i < words; i += T) {
+    removed[i] = 0u;
+    front[i] = 0u;
+  }
+  auto bit = [](const uint32_t* b, int e) { return (b[e >> 5] >> (e & 31) & 1u) != 0; };
+  int acnt = m, csr_live = m, k = 1, levels = 0, subrounds = 0;
+  int head = 0, tail = 0;  // S.gone[head, tail): the frontier
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) {
+      C.cnt = 0;
+      C.minv = kIntMax;
+      C.qn = 0;
+    }
+    __syncthreads();
+    // live list of the level (in place: a step's entries are written below
+    // where the next step reads), its minimum support, and at once the live
+    // edges with sup <= k-1: the frontier F_0 of level k+1.  If none is taken,
+    // the minimum is at least k and the next level is min + 2.
+    const int kt = k + 1;
+    int mins = kIntMax;
+    for (int q0 = 0; q0 < acnt; q0 += kSweepNI * T) {
+      uint32_t v[kSweepNI];
+      int sv[kSweepNI];
+      bool live[kSweepNI], take[kSweepNI];
+#pragma unroll
+      for (int q = 0; q < kSweepNI; ++q) {
+        const int t = q0 + q * T + tid;
+        live[q] = t < acnt;
+        v[q] = live[q] ? ldg(&S.live[t]) : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kSweepNI; ++q) {
+        live[q] = live[q] && !bit(removed, (int)(v[q] & kIdMask));
+        sv[q] = live[q] ? ldc(&S.sup[v[q] & kIdMask]) : kIntMax;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kSweepNI; ++q) {
+        take[q] = live[q] && sv[q] <= kt - 2;
+        mins = sv[q] < mins ? sv[q] : mins;
+        if (take[q]) out[ldg(&S.perm[v[q] & kIdMask])] = kt;
+        const int pos = lds_append(&C.cnt, live[q]);
+        if (live[q]) S.live[pos] = v[q];
+        const int qp = lds_append(&C.qn, take[q]);
+        if (take[q]) S.gone[tail + qp] = v[q];
+      }
+    }
+    mins = wave_min(mins);
+    if (lane == 0 && mins != kIntMax) atomicMin(&C.minv, mins);
+    __syncthreads();
+    acnt = C.cnt;
+    if (acnt == 0) break;
+    ++levels;
+    if (C.qn > 0) {
+      k = kt;
+    } else {
+      k = C.minv + 2;
+      __syncthreads();
+      for (int q0 = 0; q0 < acnt; q0 += T) {
+        const int t = q0 + tid;
+        bool take = false;
+        uint32_t v = 0;
+        if (t < acnt) {
+          v = ldg(&S.live[t]);
+          take = ldc(&S.sup[v & kIdMask]) <= k - 2;
+          if (take) out[ldg(&S.perm[v & kIdMask])] = k;
+        }
+        const int qp = lds_append(&C.qn, take);
+        if (take) S.gone[tail + qp] = v;
+      }
+      __syncthreads();
+    }
+    const int l = k - 2;
+    head = tail;
+    tail += C.qn;
+    const int level_head = head;
+    __syncthreads();
+    while (head < tail) {
+      ++subrounds;
+      if (tid == 0) C.qn = 0;
+      for (int i = head + tid; i < tail; i += T) {
+        const int e = (int)(ldg(&S.gone[i]) & kIdMask);
+        atomicOr(&front[e >> 5], 1u << (e & 31));
+      }
+      __syncthreads();
+      // frontier edges in chunks of T; the chunk's walks (shorter live row of
+      // each edge) are laid end to end and every thread takes NI entries of
+      // the flattened range at a time, so long and short walks share the lanes
+      for (int c0 = head; c0 < tail; c0 += T) {
+        const int i = c0 + tid;
+        int la = 0;
+        if (i < tail) {
+          const uint32_t f = ldg(&S.gone[i]);
+          const int e = (int)(f & kIdMask), u = (int)(f >> kIdBits), v = (int)ldg(&S.ev[e]);
+          const int du = (int)ldg(&S.len[u]), dv = (int)ldg(&S.len[v]);
+          const bool walk_u = du < dv || (du == dv && u < v);
+          const int a = walk_u ? u : v, b = walk_u ? v : u;
+          la = walk_u ? du : dv;
+          L.eb[tid] = ((uint32_t)b << kIdBits) | (uint32_t)e;
+          L.base[tid] = ((uint32_t)a << kNbShift) | ldg(&S.rp[a]);  // rp < 2m <= 2^19
+          L.tab[tid] = ldg(&S.tab[b]);
+        }
+        wpeel += (unsigned long long)la;
+        int tot;
+        const int inc = block_scan32<T>(la, C.tmp, &tot);
+        L.pre[tid] = (uint32_t)(inc - la);
+        __syncthreads();
+        const int nrec = tail - c0 < T ? tail - c0 : T;
+        // A wavefront walks a contiguous stretch, NI windows of 64 entries at a
+        // time, so the record of its first entry is known from the window
+        // before; where walks start inside a window each marks its first entry
+        // and a maximum scan gives every lane its record.  (A search of the
+        // starts for every entry took a third of the walk's instructions.)
+        const int wins = ((tot + kWave - 1) / kWave + T / kWave - 1) / (T / kWave);
+        const int lo = wv * wins * kWave, hi = lo + wins * kWave < tot ? lo + wins * kWave : tot;
+        int kc = 0;
+        if (lo < hi) {
+          int y = nrec - 1;
+          while (kc < y) {
+            const int mid = (kc + y + 1) >> 1;
+            if ((int)L.pre[mid] <= lo) kc = mid; else y = mid - 1;
+          }
+        }
+        int* own = L.own + wv * kWave;
+        for (int q0 = lo; q0 < hi; q0 += NI * kWave) {
+          int x[NI], e1[NI], e2[NI], w[NI];
+          uint32_t v[NI];
+          bool ok[NI];
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const int tq = q0 + q * kWave;
+            x[q] = kc;
+            if (kc + 1 < nrec && (int)L.pre[kc + 1] < tq + kWave) {
+              const int idx = kc + 1 + lane;
+              const int p = idx < nrec ? (int)L.pre[idx] : kIntMax;
+              own[lane] = -1;
+              wave_sync();
+              if (p < tq + kWave) own[p - tq] = idx;  // walks after kc's start at or after tq
+              wave_sync();
+              int o = own[lane];
+              o = wave_incl_max(o > kc ? o : kc);
+              x[q] = o;
+              kc = __builtin_amdgcn_readlane(o, kWave - 1);
+              wave_sync();
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const int t = q0 + q * kWave + lane;
+            ok[q] = t < hi;
+            v[q] = ok[q] ? ldg(&S.rows[(L.base[x[q]] & ((1u << kNbShift) - 1u)) + (uint32_t)(t - (int)L.pre[x[q]])]) : 0u;
+          }
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            w[q] = (int)(v[q] >> kNbShift);
+            e1[q] = (int)(v[q] & kIdMask);
+            ok[q] = ok[q] && w[q] != (int)(L.eb[x[q]] >> kIdBits) && !bit(removed, e1[q]);
+          }
+          // the second other edge: b's table, the first buckets of all lookups in
+          // flight together; a bucket with an empty slot ends the search
+          uint32_t h[NI];
+          uint4 sl[NI];
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const uint32_t tb = L.tab[x[q]];
+            h[q] = bucket_of(w[q], (int)(tb & 15));
+            sl[q] = ok[q] ? *reinterpret_cast<const uint4*>(&S.slots[(tb >> 4) + h[q]])
+                          : make_uint4(kNoSlot, kNoSlot, kNoSlot, kNoSlot);
+          }
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const uint32_t tb = L.tab[x[q]];
+            const uint32_t mask = (1u << (tb & 15)) - 1u, key = (uint32_t)w[q] << kNbShift;
+            uint32_t f = kNoSlot;
+            if (ok[q]) {
+              for (;;) {
+                // w's word differs from its key in the id alone; an empty slot
+                // has the bit between the two set
+                if ((sl[q].x ^ key) <= kIdMask) f = sl[q].x;
+                if ((sl[q].y ^ key) <= kIdMask) f = sl[q].y;
+                if ((sl[q].z ^ key) <= kIdMask) f = sl[q].z;
+                if ((sl[q].w ^ key) <= kIdMask) f = sl[q].w;
+                if (f != kNoSlot || sl[q].w == kNoSlot) break;
+                h[q] = (h[q] + 4) & mask;
+                sl[q] = *reinterpret_cast<const uint4*>(&S.slots[(tb >> 4) + h[q]]);
+              }
+            }
+            e2[q] = (int)(f & kIdMask);
+            if (ok[q]) ok[q] = f != kNoSlot && !bit(removed, e2[q]);
+          }
+          // the triangle belongs to its frontier edge of smallest id; each
+          // other edge not in F_r loses one
+          bool d1[NI], d2[NI];
+          int o1[NI], o2[NI];
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const int e = (int)(L.eb[x[q]] & kIdMask);
+            const bool f1 = ok[q] && bit(front, e1[q]), f2 = ok[q] && bit(front, e2[q]);
+            const bool mine = ok[q] && !(f1 && e1[q] < e) && !(f2 && e2[q] < e);
+            d1[q] = mine && !f1;
+            d2[q] = mine && !f2;
+            o1[q] = d1[q] ? atomicSub(&S.sup[e1[q]], 1) : 0;
+            o2[q] = d2[q] ? atomicSub(&S.sup[e2[q]], 1) : 0;
+          }
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            const bool c1 = d1[q] && o1[q] == l + 1, c2 = d2[q] && o2[q] == l + 1;
+            if (ballot(c1 || c2) == 0) continue;
+            const int a = (int)(L.base[x[q]] >> kNbShift), b = (int)(L.eb[x[q]] >> kIdBits);
+            const int p1 = lds_append(&C.qn, c1);
+            if (c1) {
+              S.gone[tail + p1] = ((uint32_t)(a < w[q] ? a : w[q]) << kIdBits) | (uint32_t)e1[q];
+              out[ldg(&S.perm[e1[q]])] = k;
+            }
+            const int p2 = lds_append(&C.qn, c2);
+            if (c2) {
+              S.gone[tail + p2] = ((uint32_t)(b < w[q] ? b : w[q]) << kIdBits) | (uint32_t)e2[q];
+              out[ldg(&S.perm[e2[q]])] = k;
+            }
+          }
+        }
+        __syncthreads();  // the chunk tables are reused by the next chunk
+      }
+      for (int i = head + tid; i < tail; i += T) {
+        const int e = (int)(ldg(&S.gone[i]) & kIdMask);
+        atomicOr(&removed[e >> 5], 1u << (e & 31));
+        atomicAnd(&front[e >> 5], ~(1u << (e & 31)));
+      }
+      head = tail;
+      tail += C.qn;
+      __syncthreads();
+    }
+    if (2 * (acnt - (tail - level_head)) < csr_live) {
+      // drop removed entries from the rows once the live edge count has halved
+      // (stable, so rows stay sorted; a wavefront per row)
+      csr_live = acnt - (tail - level_head);
+      for (int x = wv; x < n; x += T / kWave) {
+        const int base = (int)ldg(&S.rp[x]), len = (int)ldg(&S.len[x]);
+        int wpos = 0;
+        for (int c0 = 0; c0 < len; c0 += kWave) {
+          const int j = c0 + lane;
+          const uint32_t v = j < len ? ldg(&S.rows[base + j]) : 0u;
+          const bool keep = j < len && !bit(removed, (int)(v & kIdMask));
+          const uint64_t km = ballot(keep);
+          wave_sync();
+          if (keep) S.rows[base + wpos + rank_below(km)] = v;
+          wpos += __popcll(km);
+          wave_sync();
+        }
+        if (lane == 0) S.len[x] = (uint32_t)wpos;
+      }
+      __syncthreads();
+    }
+  }
+  // per-graph totals
+  tri = wave_sum(tri);
+  wsup = wave_sum(wsup);
+  wpeel = wave_sum(wpeel);
+  if (lane == 0) {
+    if (tri) atomicAdd(&A.ctl->triangles3, 3 * tri);
+    if (wsup) atomicAdd(&A.ctl->sup_work, wsup);
+    if (wpeel) atomicAdd(&A.ctl->peel_work, wpeel);
+  }
+  if (tid == 0) {
+    const unsigned long long t3 = wall_clock64();
+    atomicAdd(&A.ctl->t_phase[0], t1 - t0);
+    atomicAdd(&A.ctl->t_phase[1], t2 - t1);
+    atomicAdd(&A.ctl->t_phase[2], t3 - t2);
+    A.gerr[g] = 0;
+    atomicMax(&A.ctl->kmax, k);
+    atomicAdd(&A.ctl->levels, (unsigned long long)levels);
+    atomicAdd(&A.ctl->subrounds, (unsigned long long)subrounds);
+  }
+}
+
+template <int T, int NI>
+__global__ void __launch_bounds__(T) k_batch_compact(BatchArgs A) {
+  extern __shared__ __align__(16) char lds[];
+  __shared__ CompactCtl<T> C;
+  for (;;) {
+    if (threadIdx.x == 0) C.g = atomicAdd(&A.ctl->next_compact, 1);
+    __syncthreads();
+    const int gi = C.g;
+    if (gi >= A.Gc) break;
+    process_compact<T, NI>(A, A.order_c[gi], A.scratch + (size_t)blockIdx.x * A.slot_bytes, lds, C);
+    __syncthreads();
+  }
+}
+
 // gerr = 1 (not run) for every graph; counters cleared.  A fill kernel rather
 // than a memset, so that the plan's graph holds kernels only.
 __global__ void k_batch_init(BatchCtl* c, int32_t* gerr, int G) {
@@ -711,6 +1424,7 @@ __global__ void k_batch_init(BatchCtl* c, int32_t* gerr, int G) {
   if (i < G) gerr[i] = 1;
   if (i == 0) {
     c->next = 0;
+    c->next_compact = 0;
     c->err_g = kIntMax;
     c->kmax = 0;
     c->levels = 0;
@@ -734,6 +1448,19 @@ BatchKernel batch_kernel(int T, int NI) {
   return nullptr;
 }
 
+BatchKernel compact_kernel(int T, int NI, int64_t n, int64_t m, size_t* lds) {
+#define TRUSS_BK(t, g)                 \
+  if (T == t && NI == g) {             \
+    *lds = compact_lds<t>(n, m);       \
+    return &k_batch_compact<t, g>;     \
+  }
+  TRUSS_BK(256, 1) TRUSS_BK(256, 2) TRUSS_BK(256, 4)
+  TRUSS_BK(512, 1) TRUSS_BK(512, 2) TRUSS_BK(512, 4)
+  TRUSS_BK(1024, 1) TRUSS_BK(1024, 2) TRUSS_BK(1024, 4)
+#undef TRUSS_BK
+  return nullptr;
+}
+
 constexpr int kDefaultT = 1024, kDefaultG = 2;
 
 int device_cus() {
@@ -743,11 +1470,12 @@ int device_cus() {
   return cus;
 }
 
-// The batch split: graphs for the persistent kernel (largest first) and graphs
-// for the device-wide path; scratch shapes.
+// The batch split: graphs for the two persistent kernels (largest first) and
+// graphs for the device-wide path; scratch shapes.
 struct BatchSplit {
-  std::vector<int32_t> order, big;
-  int64_t max_n = 0, max_m = 0;
+  std::vector<int32_t> order, compact, big;
+  int64_t max_n = 0, max_m = 0;    // general kernel
+  int64_t max_cn = 0, max_cm = 0;  // compact kernel
   int slots = 0;
   size_t slot_bytes = 0, big_ws = 0;
 };
@@ -769,7 +1497,11 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
       set_last_error("graph %d has more than INT32_MAX edges", i);
       return TRUSS_E_TOOBIG;
     }
-    if (m <= kBatchMaxM && n <= kBatchMaxN) {
+    if (m <= kCM && n <= kCN) {
+      B.compact.push_back(i);
+      B.max_cn = std::max(B.max_cn, n);
+      B.max_cm = std::max(B.max_cm, m);
+    } else if (m <= kBatchMaxM && n <= kBatchMaxN) {
       B.order.push_back(i);
       B.max_n = std::max(B.max_n, n);
       B.max_m = std::max(B.max_m, m);
@@ -787,11 +1519,14 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
       B.big_ws = std::max(B.big_ws, b);
     }
   }
-  std::stable_sort(B.order.begin(), B.order.end(),
-                   [&](int32_t a, int32_t b) { return eo[a + 1] - eo[a] > eo[b + 1] - eo[b]; });
+  auto larger = [&](int32_t a, int32_t b) { return eo[a + 1] - eo[a] > eo[b + 1] - eo[b]; };
+  std::stable_sort(B.order.begin(), B.order.end(), larger);
+  std::stable_sort(B.compact.begin(), B.compact.end(), larger);
+  // the kernels run one after the other over the same slots
   const int maxslots = 4 * device_cus();
-  B.slots = (int)std::min<int64_t>((int64_t)B.order.size(), maxslots);
-  B.slot_bytes = slot_bytes_for(B.max_n, B.max_m);
+  B.slots = (int)std::min<int64_t>((int64_t)std::max(B.order.size(), B.compact.size()), maxslots);
+  if (!B.order.empty()) B.slot_bytes = slot_bytes_for(B.max_n, B.max_m);
+  if (!B.compact.empty()) B.slot_bytes = std::max(B.slot_bytes, compact_bytes(B.max_cn, B.max_cm));
   return TRUSS_OK;
 }
 
@@ -828,10 +1563,11 @@ int check_cfg(int T, int G) {
   return TRUSS_OK;
 }
 
-int launch_batch(const BatchArgs& A, int T, int G, int slots, hipStream_t s) {
-  BatchKernel k = batch_kernel(T, G);
+int launch_one(const BatchArgs& A, BatchKernel k, int T, size_t lds, int slots, hipStream_t s) {
   int occ = 0;
-  TRUSS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void*)k, T, 0));
+  if (lds > 0)
+    TRUSS_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  TRUSS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void*)k, T, lds));
   if (occ < 1) {
     set_last_error("batch kernel does not fit on a compute unit");
     return TRUSS_E_DEVICE;
@@ -839,7 +1575,19 @@ int launch_batch(const BatchArgs& A, int T, int G, int slots, hipStream_t s) {
   const int grid = std::max(1, std::min(slots, occ * device_cus()));
   BatchArgs a = A;
   void* args[] = {&a};
-  TRUSS_HIP(hipLaunchKernel((const void*)k, dim3(grid), dim3(T), args, 0, s));
+  TRUSS_HIP(hipLaunchKernel((const void*)k, dim3(grid), dim3(T), args, lds, s));
+  return TRUSS_OK;
+}
+
+// The kernels of the queues that hold graphs (A.G, A.Gc); B for the shapes.
+int launch_batch(const BatchArgs& A, const BatchSplit& B, int T, int G, hipStream_t s) {
+  if (A.Gc > 0) {
+    size_t lds = 0;
+    BatchKernel k = compact_kernel(T, G, B.max_cn, B.max_cm, &lds);
+    const int rc = launch_one(A, k, T, lds, std::min(A.Gc, B.slots), s);
+    if (rc) return rc;
+  }
+  if (A.G > 0) return launch_one(A, batch_kernel(T, G), T, 0, std::min(A.G, B.slots), s);
   return TRUSS_OK;
 }
 
@@ -965,11 +1713,14 @@ int plan_build(int32_t G, const int64_t* vo, const int64_t* eo, const int32_t* s
   p->src = src;
   p->dst = dst;
   p->out = out;
-  const int Q = (int)p->split.order.size();
+  // one device array: the general queue, then the compact one
+  std::vector<int32_t> queue(p->split.order);
+  queue.insert(queue.end(), p->split.compact.begin(), p->split.compact.end());
+  const int Q = (int)queue.size();
   if (G > 0) {
     if (hipMemcpyAsync(p->lay.vo, vo, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(p->lay.eo, eo, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
-        (Q > 0 && hipMemcpyAsync(p->lay.order, p->split.order.data(), sizeof(int32_t) * Q, hipMemcpyHostToDevice,
+        (Q > 0 && hipMemcpyAsync(p->lay.order, queue.data(), sizeof(int32_t) * Q, hipMemcpyHostToDevice,
                                  s) != hipSuccess) ||
         hipStreamSynchronize(s) != hipSuccess) {
       set_last_error("copying the batch offsets failed");
@@ -978,8 +1729,10 @@ int plan_build(int32_t G, const int64_t* vo, const int64_t* eo, const int32_t* s
     }
   }
   BatchArgs& A = p->args;
-  A.G = Q;
+  A.G = (int)p->split.order.size();
   A.order = p->lay.order;
+  A.Gc = (int)p->split.compact.size();
+  A.order_c = p->lay.order + p->split.order.size();
   A.vo = p->lay.vo;
   A.eo = p->lay.eo;
   A.src = src;
@@ -1004,7 +1757,7 @@ int plan_build(int32_t G, const int64_t* vo, const int64_t* eo, const int32_t* s
     if (!rc) {
       hipLaunchKernelGGL(k_batch_init, dim3((unsigned)((G + 256) / 256)), dim3(256), 0, cs, p->lay.ctl, p->lay.gerr,
                          G);
-      if (Q > 0) rc = launch_batch(A, p->T, p->Gl, p->split.slots, cs);
+      if (Q > 0) rc = launch_batch(A, p->split, p->T, p->Gl, cs);
       hipGraph_t gr = nullptr;
       if (hipStreamEndCapture(cs, &gr) != hipSuccess || !gr) rc = rc ? rc : TRUSS_E_DEVICE;
       p->graph = gr;
@@ -1098,12 +1851,16 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   truss_batch_plan* p = nullptr;
   int rc = plan_build(num_graphs, vtx_off, edge_off, src, dst, truss_out, opts, ws, ws_bytes, s, false, &p);
   if (rc) return rc;
-  // a stratified sample of the queue: every stride-th graph in size order
-  const std::vector<int32_t>& q = p->split.order;
+  // a stratified sample of each queue: every stride-th graph in size order
   const int want = 512;
+  const size_t all = p->split.order.size() + p->split.compact.size();
+  const size_t stride = all > (size_t)want ? all / want : 1;
+  auto pick = [&](const std::vector<int32_t>& q, std::vector<int32_t>& to) {
+    for (size_t i = 0; i < q.size(); i += stride) to.push_back(q[i]);
+    return (int)((q.size() + stride - 1) / stride);
+  };
   std::vector<int32_t> sample;
-  const size_t stride = q.size() > (size_t)want ? q.size() / want : 1;
-  for (size_t i = 0; i < q.size(); i += stride) sample.push_back(q[i]);
+  const int sg = pick(p->split.order, sample), sc = pick(p->split.compact, sample);
   *best_block = kDefaultT;
   *best_ilp = kDefaultG;
   if (best_ms) *best_ms = 0.f;
@@ -1114,16 +1871,18 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   hipEvent_t e0 = nullptr, e1 = nullptr;
   TRUSS_HIP(hipEventCreate(&e0));
   TRUSS_HIP(hipEventCreate(&e1));
-  // time one shape on the first `count` queue entries (order already on the device)
-  auto time_shape = [&](int T, int Gl, int count, int reps, float* ms) -> int {
+  // time one shape on the queues on the device: gen general graphs, then cmp compact ones
+  auto time_shape = [&](int T, int Gl, int gen, int cmp, int reps, float* ms) -> int {
     BatchArgs A = p->args;
-    A.G = count;
+    A.G = gen;
+    A.Gc = cmp;
+    A.order_c = A.order + gen;
     float t = 0.f;
     for (int rep = 0; rep < reps; ++rep) {
       hipLaunchKernelGGL(k_batch_init, dim3((unsigned)((num_graphs + 256) / 256)), dim3(256), 0, s, p->lay.ctl,
                          p->lay.gerr, num_graphs);
       (void)hipEventRecord(e0, s);
-      int r = launch_batch(A, T, Gl, (int)std::min<size_t>((size_t)count, (size_t)p->split.slots), s);
+      int r = launch_batch(A, p->split, T, Gl, s);
       if (r) return r;
       (void)hipEventRecord(e1, s);
       if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&t, e0, e1) != hipSuccess)
@@ -1140,18 +1899,21 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   for (int ti = 0; ti < 3 && !rc; ++ti)
     for (int gi = 0; gi < 3 && !rc; ++gi) {
       float t = 0.f;
-      rc = time_shape(Ts[ti], Gs[gi], (int)sample.size(), 2, &t);
+      rc = time_shape(Ts[ti], Gs[gi], sg, sc, 2, &t);
       if (!rc) cands.push_back({t, Ts[ti], Gs[gi]});
     }
-  // stage 2: the three fastest on the whole queue, where the largest graphs
+  // stage 2: the three fastest on the whole queues, where the largest graphs
   // (which set the tail) count at their full weight
   float best = -1.f;
   if (!rc) {
     std::sort(cands.begin(), cands.end(), [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
-    TRUSS_HIP(hipMemcpyAsync(p->lay.order, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice, s));
+    std::vector<int32_t> queue(p->split.order);
+    queue.insert(queue.end(), p->split.compact.begin(), p->split.compact.end());
+    TRUSS_HIP(hipMemcpyAsync(p->lay.order, queue.data(), sizeof(int32_t) * queue.size(), hipMemcpyHostToDevice, s));
+    TRUSS_HIP(hipStreamSynchronize(s));  // queue leaves scope
     for (size_t c = 0; c < cands.size() && c < 3 && !rc; ++c) {
       float t = 0.f;
-      rc = time_shape(cands[c].T, cands[c].G, (int)q.size(), 1, &t);
+      rc = time_shape(cands[c].T, cands[c].G, (int)p->split.order.size(), (int)p->split.compact.size(), 1, &t);
       if (!rc && (best < 0.f || t < best)) {
         best = t;
         *best_block = cands[c].T;

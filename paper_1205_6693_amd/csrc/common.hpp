@@ -67,6 +67,26 @@ __device__ __forceinline__ T wave_max(T x) {
   return x;
 }
 
+// Inclusive maximum over the lanes 0..lane (DPP row shifts within rows of 16,
+// then the row broadcasts 15 and 31 of the gfx9 wave64 scan).
+__device__ __forceinline__ int wave_incl_max(int x) {
+  constexpr int lo = (int)0x80000000;
+  int y;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x = y > x ? y : x;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x = y > x ? y : x;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x = y > x ? y : x;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x = y > x ? y : x;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  x = y > x ? y : x;
+  y = __builtin_amdgcn_update_dpp(lo, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  x = y > x ? y : x;
+  return x;
+}
+
 // first lane (lowest id) of a non-empty mask broadcasts `x`
 template <typename T>
 __device__ __forceinline__ T wave_bcast(T x, int src) {

@@ -199,26 +199,6 @@ __device__ __forceinline__ int tab_find(const int2* tab, int32_t key) {
   }
 }
 
-// Inclusive maximum over the lanes 0..lane (DPP row shifts within rows of 16,
-// then the row broadcasts 15 and 31 of the gfx9 wave64 scan).
-__device__ __forceinline__ int wave_incl_max(int x) {
-  constexpr int lo = (int)0x80000000;
-  int y;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x = y > x ? y : x;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x = y > x ? y : x;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x = y > x ? y : x;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x = y > x ? y : x;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
-  x = y > x ? y : x;
-  y = __builtin_amdgcn_update_dpp(lo, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
-  x = y > x ? y : x;
-  return x;
-}
-
 // One wavefront walks pairs [lo, hi) of a vertex's flattened list, 64 pairs
 // (one per lane) a window.  Every lane needs the row of its pair.  Inside a
 // row (the common case: most pairs lie in long rows) that is the row in
