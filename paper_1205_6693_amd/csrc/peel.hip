@@ -70,9 +70,16 @@ constexpr int kWaves = kT / kWave;
 constexpr int kIntMax = 0x7fffffff;
 constexpr int kHistBins = 6;
 constexpr long long kCompactNum = 8, kCompactDen = 10;  // row compaction threshold
-constexpr int kStageA = 8192;  // LDS staging of live-list appends (entries)
-constexpr int kStageQ = 2048;  // LDS staging of frontier-queue appends
-static_assert(4 * kT <= kStageA && 2 * kT <= kStageQ, "sweep staging capacity");
+constexpr int kStageQ = 16384;  // LDS staging of a list phase's frontier (entries)
+
+// The support of an edge that has joined a frontier is set to kGone, so that the
+// list phases tell live edges by their support alone.  Later decrements (fewer than
+// the edge has triangles) leave it above kGoneMin; the supports out of reach that
+// frozen edges start with (2^29) lie below.
+constexpr int kGone = 1 << 30, kGoneMin = 3 << 28;
+
+// The live list is written anew in a sweep once a quarter of its edges are gone.
+constexpr long long kListNum = 3, kListDen = 4;
 
 // A round's walks, laid end to end in queue order, are cut into parts of equal
 // length: one a workgroup while that length lies between kMinChunk and kPartMax
@@ -86,7 +93,7 @@ constexpr int kMinChunk = 64;  // entries of the smallest part: one a lane of on
 constexpr long long kPartMax = 16384;
 
 enum Phase : int {
-  PH_SWEEP = 0,    // compact the live-edge list, minimum live support
+  PH_SWEEP = 0,    // minimum live support and the next level's first frontier
   PH_START = 1,    // level start: collect live edges with sup <= k-2
   PH_PROC = 2,     // destroy the triangles of F_r
   PH_UNUSED = 3,
@@ -102,7 +109,7 @@ enum Phase : int {
 struct alignas(128) PhaseCounts {
   alignas(128) int fetch;                  // parts of the round drawn
   alignas(128) unsigned long long q;       // next frontier: (walk units << qbits) | edges
-  alignas(128) int alive;                  // live-list length
+  alignas(128) int alive;                  // entries of the list being written
   alignas(128) int minsup;                 // minimum live support
   alignas(128) unsigned long long fwork;   // level start: sum over F_0 of the shorter live row
 };
@@ -121,13 +128,15 @@ struct alignas(256) PeelCtl {
   int r;
   int qlen;
   unsigned long long qunits;  // walk units of the round
-  int acnt;
-  int acur;
-  int first;
+  int acnt;     // length of the live list
+  int acur;     // which list
+  int first;    // the list is still all edges, in order
+  int compact;  // the next sweep writes a new list
   int mode;
   int kmax;
   int levels;
   long long removed_level;
+  long long removed;      // edges of the finished levels
   long long csr_live;
   long long subrounds;
   long long heavy_rounds;
@@ -212,14 +221,15 @@ __device__ __forceinline__ int walk_shift(unsigned long long wbound, int64_t m, 
 
 // The published state of a phase.
 struct PhaseState {
-  int phase, acur, mode, probe, first, qlen, k, r, acnt;
+  int phase, acur, mode, probe, first, compact, qlen, k, r, acnt;
   unsigned long long units;
 };
 __device__ __forceinline__ unsigned long long pub_word(const PhaseState& s, int i) {
   switch (i) {
     case PUB_FLAGS:
-      return (unsigned long long)(unsigned)(s.phase | (s.acur << 3) | (s.mode << 4) | (s.probe << 6) | (s.first << 7)) |
-             ((unsigned long long)(unsigned)s.qlen << 8);
+      return (unsigned long long)(unsigned)(s.phase | (s.acur << 3) | (s.mode << 4) | (s.probe << 6) | (s.first << 7) |
+                                           (s.compact << 8)) |
+             ((unsigned long long)(unsigned)s.qlen << 9);
     case PUB_K: return (unsigned)s.k;
     case PUB_R: return (unsigned)s.r;
     case PUB_UNITS: return s.units;
@@ -235,7 +245,8 @@ __device__ __forceinline__ PhaseState phase_state(const unsigned long long* pub)
   s.mode = (int)(f >> 4) & 3;
   s.probe = (int)(f >> 6) & 1;
   s.first = (int)(f >> 7) & 1;
-  s.qlen = (int)(f >> 8);
+  s.compact = (int)(f >> 8) & 1;
+  s.qlen = (int)(f >> 9);
   s.k = (int)scalar64(pub[PUB_K]);
   s.r = (int)scalar64(pub[PUB_R]);
   s.acnt = (int)scalar64(pub[PUB_ACNT]);
@@ -272,6 +283,7 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
   const unsigned long long qunits_in = st.units;
   int levels = ldc(&c->levels);
   long long removed_level = ldc(&c->removed_level);
+  long long removed = ldc(&c->removed);
   long long csr_live = ldc(&c->csr_live);
   long long subrounds = ldc(&c->subrounds);
   long long heavy_rounds = ldc(&c->heavy_rounds);
@@ -315,7 +327,10 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
       prev_sub = subrounds - lvl_sub0;
       // compact the rows when the live count has dropped below kCompactNum /
       // kCompactDen of the entries they hold
-      const long long alive_after = (long long)acnt - removed_level;
+      removed += removed_level;
+      removed_level = 0;
+      const long long alive_after = P.m - removed;
+      st.compact = alive_after * kListDen < (long long)acnt * kListNum ? 1 : 0;
       if (alive_after > 0 && alive_after * kCompactDen < csr_live * kCompactNum) {
         csr_live = alive_after;
         phase = PH_COMPACT;
@@ -328,7 +343,7 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
   // levels chose; then the level's first round
   auto start_level = [&]() {
         float x[kPeelF];
-        const float live = (float)acnt, f0 = (float)w_qlen, wk = (float)w_fwork;
+        const float live = (float)(P.m - removed), f0 = (float)w_qlen, wk = (float)w_fwork;
         x[0] = log2f(1.f + live);
         x[1] = log2f(1.f + f0);
         x[2] = f0 / (live > 1.f ? live : 1.f);
@@ -366,10 +381,12 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
       // of level k+1 (stamped r+1); it is the level's F_0 unless empty, which
       // happens exactly when the minimum live support is at least k, so that
       // the next level is min + 2 and needs its own start phase
-      acnt = w_alive;
-      acur ^= 1;
-      st.first = 0;
-      if (w_alive == 0 || (stop_level > 0 && (w_qlen > 0 ? k + 1 : w_minsup + 2) > stop_level)) {
+      if (st.compact) {
+        acnt = w_alive;
+        acur ^= 1;
+        st.first = 0;
+      }
+      if (removed == P.m || (stop_level > 0 && (w_qlen > 0 ? k + 1 : w_minsup + 2) > stop_level)) {
         phase = PH_DONE;
         break;
       }
@@ -431,12 +448,14 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
   stc(&c->acnt, acnt);
   stc(&c->acur, acur);
   stc(&c->first, st.first);
+  stc(&c->compact, st.compact);
   stc(&c->mode, st.mode);
   stc(&c->probe, st.probe);
   stc(&c->qlen, st.qlen);
   stc(&c->qunits, st.units);
   stc(&c->levels, levels);
   stc(&c->removed_level, removed_level);
+  stc(&c->removed, removed);
   stc(&c->csr_live, csr_live);
   stc(&c->subrounds, subrounds);
   stc(&c->heavy_rounds, heavy_rounds);
@@ -566,11 +585,13 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTab
   for (int q = 0; q < NI; ++q) {
     if (d1[q] && old1[q] == l + 1) {
       stc(&P.stamp[e1[q]], r + 1);
+      stc(&P.sup[e1[q]], kGone);
       P.truss[e1[q]] = k;
       f1[q] = e1[q];
     }
     if (d2[q] && old2[q] == l + 1) {
       stc(&P.stamp[e2[q]], r + 1);
+      stc(&P.sup[e2[q]], kGone);
       P.truss[e2[q]] = k;
       f2[q] = e2[q];
     }
@@ -719,37 +740,12 @@ __device__ __forceinline__ void wq_push(WaveQueue& wq, int32_t f, int32_t u, int
   wq.cnt += __popcll(m);
 }
 
-// Appends of a whole workgroup gathered in LDS and written to a global list in
-// bulk, so that the list's counter sees one atomic per flush rather than one
-// per 1024 entries.  Every thread of the workgroup calls append() and flush().
-struct StagedList {
-  int* buf;       // LDS, cap entries
-  int cap;
-  int* fill;      // LDS: entries held
-  int* base;      // LDS: list position of a flush
-  int* counter;   // global list length
-  int32_t* out;   // global list
-};
-
-__device__ __forceinline__ void staged_flush(StagedList& L) {
-  __syncthreads();
-  const int n = *L.fill;
-  if (n == 0) return;
-  if (threadIdx.x == 0) *L.base = atomicAdd(L.counter, n);
-  __syncthreads();
-  const int b = *L.base;
-  for (int i = threadIdx.x; i < n; i += kT) stc(&L.out[b + i], L.buf[i]);
-  __syncthreads();
-  if (threadIdx.x == 0) *L.fill = 0;
-  __syncthreads();
-}
-
-// The same for a frontier queue: a flush appends the walk records of the
-// staged edges, one atomic per kT of them.  tmp: kWaves entries of LDS.
+// Frontier edges of a list phase gathered in LDS; a flush appends their walk
+// records, one atomic per kT of them.  Every thread of the workgroup calls
+// flush().  tmp: kWaves entries of LDS.
 struct StagedQueue {
-  int* buf;
-  int cap;
-  int* fill;
+  int* buf;   // LDS, kStageQ entries
+  int* fill;  // LDS: entries held
   unsigned long long* tmp;
   QueueOut out;
 };
@@ -792,39 +788,6 @@ __device__ __forceinline__ void staged_flush(const PeelArgs& P, StagedQueue& L) 
   __syncthreads();
 }
 
-__device__ __forceinline__ void staged_flush(const PeelArgs&, StagedList& L) { staged_flush(L); }
-
-// U candidate entries per thread (vals[u] kept where want[u]) into a staged
-// list or queue; a thread's kept entries stay in order and follow the
-// previous thread's.  U * kT must not exceed the LDS capacity.  tmp: kWaves
-// ints of LDS.
-template <int U, typename Staged>
-__device__ __forceinline__ void staged_append_n(const PeelArgs& P, Staged& L, const bool (&want)[U],
-                                                const int32_t (&vals)[U], int* tmp) {
-  const int lane = lane_id(), w = threadIdx.x / kWave;
-  int cnt = 0;
-#pragma unroll
-  for (int u = 0; u < U; ++u) cnt += want[u] ? 1 : 0;
-  const int incl = wave_inclusive_sum(cnt);
-  if (lane == kWave - 1) tmp[w] = incl;
-  __syncthreads();
-  int wbase = 0, tot = 0;
-#pragma unroll 4
-  for (int q = 0; q < kWaves; ++q) {
-    const int x = tmp[q];
-    if (q < w) wbase += x;
-    tot += x;
-  }
-  if (*L.fill + tot > L.cap) staged_flush(P, L);
-  int pos = *L.fill + wbase + incl - cnt;
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (want[u]) L.buf[pos++] = vals[u];
-  __syncthreads();
-  if (threadIdx.x == 0) *L.fill += tot;
-  __syncthreads();
-}
-
 // minimum over the workgroup into *dst (one atomic per workgroup); tmp: kWaves ints
 __device__ __forceinline__ void block_min_to(int x, int* tmp, int* dst) {
   x = wave_min(x);
@@ -852,6 +815,24 @@ __device__ __forceinline__ void block_sum_to(unsigned long long x, unsigned long
   __syncthreads();
 }
 
+// Block-wide inclusive prefix sum of one int per thread; total in *total; tmp: kWaves ints of LDS.
+__device__ __forceinline__ int block_inclusive_sum(int x, int* tmp, int* total) {
+  const int w = threadIdx.x / kWave;
+  const int inc = wave_inclusive_sum(x);
+  if (lane_id() == kWave - 1) tmp[w] = inc;
+  __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll 4
+  for (int q = 0; q < kWaves; ++q) {
+    const int v = tmp[q];
+    if (q < w) base += v;
+    all += v;
+  }
+  *total = all;
+  __syncthreads();
+  return base + inc;
+}
+
 // Number of threads of the workgroup with `p` set; tmp: kWaves ints of LDS.
 __device__ __forceinline__ int block_count(bool p, int* tmp) {
   const uint64_t m = ballot(p);
@@ -877,18 +858,17 @@ __device__ __forceinline__ int block_count2(bool p, bool q, int* tmp) {
   return n;
 }
 
-// NI: walk entries in flight per thread; SU (2 or 4): live-list entries per
-// thread and step of the level sweep
+// NI: walk entries in flight per thread; SU: live-list entries per thread and
+// step of the list phases
 template <int NI, int SU>
 __device__ __forceinline__ void peel_body() {
-  static_assert(SU == 2 || SU == 4, "sweep step");
+  static_assert(2 * SU * kT <= kStageQ, "a step's frontier fits beside the last one's");
   // the walking phase and the list phases use the same LDS
   struct RoundLds {
     WalkTabs W;
     int qe[kWaves][kWq], qu[kWaves][kWq], qv[kWaves][kWq];
   };
   struct ListLds {
-    int a[kStageA];
     int q[kStageQ];
   };
   __shared__ union {
@@ -898,13 +878,10 @@ __device__ __forceinline__ void peel_body() {
   __shared__ int s_tmp[kWaves + 2];
   __shared__ int s_part;
   __shared__ unsigned long long s_w64[kWaves];
-  __shared__ int s_fill[4];
+  __shared__ int s_fill, s_list;
   KernArgs ka = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
   PeelCtl* const c = ((const PeelArgs*)ka)->ctl;
-  if (threadIdx.x == 0) {
-    s_fill[0] = 0;
-    s_fill[2] = 0;
-  }
+  if (threadIdx.x == 0) s_fill = 0;
   __syncthreads();
   const int tid = threadIdx.x;
   const int wv = tid / kWave;
@@ -921,6 +898,7 @@ __device__ __forceinline__ void peel_body() {
   st.mode = ldc(&c->mode);
   st.probe = ldc(&c->probe);
   st.first = ldc(&c->first);
+  st.compact = ldc(&c->compact);
   st.qlen = 0;
   st.k = ldc(&c->k);
   st.r = ldc(&c->r);
@@ -939,94 +917,93 @@ __device__ __forceinline__ void peel_body() {
     const int r = st.r;
     const int acur = st.acur;
     PhaseCounts* const cw = &c->w[gen & 1];
-    if (phase == PH_SWEEP) {
-      // live-edge list of the new level and its minimum support; the live
-      // edges with sup <= k-1 are taken at once as the frontier of level k+1
-      // (the control step keeps them only if that level is not skipped, in
-      // which case none is taken)
-      const int first = st.first;
-      const int64_t cnt = first ? P.m : (int64_t)st.acnt;
-      const int32_t* A = P.alist[acur];
-      StagedList LA{S.l.a, kStageA, &s_fill[0], &s_fill[1], &cw->alive, P.alist[acur ^ 1]};
-      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[(r + 1) & 1], &cw->q, qbits, shift}};
-      const int kt = k + 1, stamp = r + 1;
-      int mins = kIntMax;
-      unsigned long long wsum = 0;
-      // SU consecutive list entries a thread, their loads in flight together
-      for (int64_t base = (int64_t)blockIdx.x * kT * SU; base < cnt; base += (int64_t)gridDim.x * kT * SU) {
-        const int64_t i0 = base + (int64_t)tid * SU;
-        int32_t e[SU];
-        int sv[SU], sk[SU];
-        bool live[SU], take[SU];
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-          e[u] = 0;
-          if (i0 + u < cnt) e[u] = first ? (int32_t)(i0 + u) : ldc(&A[i0 + u]);
-        }
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-          sv[u] = 0;
-          sk[u] = 1;
-          if (i0 + u < cnt) {
-            sk[u] = ldc(&P.stamp[e[u]]);
-            sv[u] = ldc(&P.sup[e[u]]);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-          live[u] = sk[u] == 0;
-          take[u] = false;
-          if (live[u]) {
-            mins = sv[u] < mins ? sv[u] : mins;
-            take[u] = sv[u] <= kt - 2;
-            if (take[u]) {
-              stc(&P.stamp[e[u]], stamp);
-              P.truss[e[u]] = kt;
-              const int du = P.vinfo[P.eu[e[u]]].len, dv = P.vinfo[P.ev[e[u]]].len;
-              wsum += (unsigned long long)(du < dv ? du : dv);
-            }
-          }
-        }
-        staged_append_n<SU>(P, LA, live, e, s_tmp);
-        // the frontier stage holds two entries a thread per append
-#pragma unroll
-        for (int h = 0; h < SU; h += 2) {
-          const bool th[2] = {take[h], take[h + 1]};
-          const int32_t eh[2] = {e[h], e[h + 1]};
-          staged_append_n<2>(P, LQ, th, eh, s_tmp);
-        }
-      }
-      staged_flush(LA);
-      staged_flush(P, LQ);
-      block_min_to(mins, s_tmp, &cw->minsup);
-      block_sum_to(wsum, s_w64, &cw->fwork);
-    } else if (phase == PH_START || phase == PH_DENSE) {
-      // collect live edges with sup <= k-2 (level start after a skip, or dense re-scan)
-      const int64_t cnt = st.acnt;
-      const int32_t* A = P.alist[acur];
+    if (phase != PH_PROC) {
+      // Sweep: the minimum live support, and at once the live edges with
+      // sup <= k-1 as the frontier of level k+1 (the control step keeps them only
+      // if that level is not skipped, in which case none is taken); with
+      // compact set the live edges are also written as the new list.  Level start
+      // after a skip, or dense re-scan: the live edges with sup <= k-2.
+      const bool sweep = phase == PH_SWEEP;
+      const int kt = sweep ? k + 1 : k;
       const int stamp = phase == PH_START ? r : r + 1;
-      StagedQueue LQ{S.l.q, kStageQ, &s_fill[2], s_w64, QueueOut{P.fq[stamp & 1], &cw->q, qbits, shift}};
-      unsigned long long wsum = 0;  // level start: shorter live row over the frontier
-      for (int64_t base = (int64_t)blockIdx.x * kT; base < cnt; base += (int64_t)gridDim.x * kT) {
-        const int64_t i = base + tid;
-        bool take[1] = {false};
-        int32_t e[1] = {0};
-        if (i < cnt) {
-          e[0] = ldc(&A[i]);
-          take[0] = ldc(&P.stamp[e[0]]) == 0 && ldc(&P.sup[e[0]]) <= l;
-          if (take[0]) {
-            stc(&P.stamp[e[0]], stamp);
-            P.truss[e[0]] = k;
-            if (phase == PH_START) {
-              const int du = P.vinfo[P.eu[e[0]]].len, dv = P.vinfo[P.ev[e[0]]].len;
+      const bool ids = st.first != 0, write = sweep && st.compact != 0;
+      const int64_t cnt = ids ? P.m : (int64_t)st.acnt;
+      const int32_t* A = P.alist[acur];
+      int32_t* const B = P.alist[acur ^ 1];
+      StagedQueue LQ{S.l.q, &s_fill, s_w64, QueueOut{P.fq[stamp & 1], &cw->q, qbits, shift}};
+      int mins = kIntMax;
+      unsigned long long wsum = 0;  // shorter live row over the frontier
+      // SU list entries a thread, their loads in flight together; the few that
+      // are taken (or written to the new list) are read again afterwards, so
+      // that only their bits are held.  What bounds a sweep is the lines of sup
+      // that sparse lists touch; SU of 2, 4 and 8 measured 57.6, 67.5 and 77.1 ms
+      // of sweeps on R-MAT 23 (the list written anew in every sweep, with stamps
+      // read as well: 74.4), since larger steps leave workgroups idle on the
+      // shorter lists.
+      for (int64_t base = (int64_t)blockIdx.x * kT * SU; base < cnt; base += (int64_t)gridDim.x * kT * SU) {
+        unsigned live = 0, taken = 0;
+        {
+          int32_t e[SU];
+          int sv[SU];
+#pragma unroll
+          for (int u = 0; u < SU; ++u) {
+            const int64_t i = base + u * kT + tid;
+            e[u] = i < cnt ? (ids ? (int32_t)i : ldc(&A[i])) : -1;
+          }
+#pragma unroll
+          for (int u = 0; u < SU; ++u) sv[u] = e[u] >= 0 ? ldc(&P.sup[e[u]]) : kGone;
+#pragma unroll
+          for (int u = 0; u < SU; ++u) {
+            if (sv[u] < kGoneMin) {
+              mins = sv[u] < mins ? sv[u] : mins;
+              live |= 1u << u;
+              if (sv[u] <= kt - 2) taken |= 1u << u;
+            }
+          }
+        }
+        if (ballot(taken != 0)) {
+#pragma unroll 1
+          for (int u = 0; u < SU; ++u) {
+            const bool take = (taken >> u & 1u) != 0;
+            const uint64_t m = ballot(take);
+            if (m == 0) continue;
+            int at = 0;
+            if (lane_id() == 0) at = atomicAdd(&s_fill, __popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (take) {
+              const int64_t i = base + u * kT + tid;
+              const int32_t e = ids ? (int32_t)i : ldc(&A[i]);
+              S.l.q[at + rank_below(m)] = e;
+              stc(&P.stamp[e], stamp);
+              stc(&P.sup[e], kGone);
+              P.truss[e] = kt;
+              const int du = P.vinfo[P.eu[e]].len, dv = P.vinfo[P.ev[e]].len;
               wsum += (unsigned long long)(du < dv ? du : dv);
             }
           }
         }
-        staged_append_n<1>(P, LQ, take, e, s_tmp);
+        if (write) {
+          int total;
+          const int keep = __popc(live);
+          const int inc = block_inclusive_sum(keep, s_tmp, &total);
+          if (tid == 0) s_list = atomicAdd(&cw->alive, total);
+          __syncthreads();
+          int at = s_list + inc - keep;
+#pragma unroll 1
+          for (int u = 0; u < SU; ++u) {
+            if (!(live >> u & 1u)) continue;
+            const int64_t i = base + u * kT + tid;
+            stc(&B[at++], ids ? (int32_t)i : ldc(&A[i]));
+          }
+        }
+        __syncthreads();
+        const int held = s_fill;
+        __syncthreads();  // every thread has read it before the next append
+        if (held > kStageQ - SU * kT) staged_flush(P, LQ);
       }
       staged_flush(P, LQ);
-      if (phase == PH_START) block_sum_to(wsum, s_w64, &cw->fwork);
+      if (sweep) block_min_to(mins, s_tmp, &cw->minsup);
+      if (phase != PH_DENSE) block_sum_to(wsum, s_w64, &cw->fwork);
     } else if (phase == PH_PROC) {
       // The round's walks, laid end to end, in parts of equal length (see
       // kMinChunk): every workgroup finds the record its part starts in by a
@@ -1152,7 +1129,7 @@ __device__ __forceinline__ void peel_body() {
 // per thread, or two workgroups per compute unit (registers capped for eight
 // wavefronts per SIMD) with two entries per thread, which hides more latency
 // when walks are long.  All state lives in global memory between launches.
-__global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<4, 4>(); }
+__global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<4, 2>(); }
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) k_peel_wide(PeelArgs) {
   peel_body<2, 2>();
 }
@@ -1273,10 +1250,12 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     c->acnt = (int)m;
     c->acur = 0;
     c->first = 1;
+    c->compact = 0;
     c->mode = TRUSS_PEEL_SPARSE;
     c->kmax = 0;
     c->levels = 0;
     c->removed_level = 0;
+    c->removed = 0;
     c->csr_live = m;
     c->subrounds = 0;
     c->heavy_rounds = 0;
