@@ -17,10 +17,11 @@ thread_local char g_last_error[512] = "";
 
 constexpr int kT = 256;
 
+// (nothing is written for an invalid input, here and below)
 __global__ void k_scatter_out(const int32_t* __restrict__ val, const int32_t* __restrict__ perm, int64_t m,
-                              int32_t* __restrict__ out) {
+                              int32_t* __restrict__ out, const RunHead* head) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e < m) out[perm ? perm[e] : e] = val[e];
+  if (e < m && head->err == kNoErr) out[perm ? perm[e] : e] = val[e];
 }
 
 // x summed over the workgroup into *total, one atomic each.  Same-address
@@ -39,17 +40,16 @@ __device__ __forceinline__ void block_total(unsigned long long x, unsigned long 
 }
 
 __global__ void __launch_bounds__(kT) k_scatter_sup(const int32_t* __restrict__ sup, const int32_t* __restrict__ perm, int64_t m,
-                              int32_t* __restrict__ out, unsigned long long* total) {
+                              int32_t* __restrict__ out, RunHead* head) {
+  if (head->err != kNoErr) return;
   unsigned long long x = 0;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
     const int s = sup[e];
     out[perm ? perm[e] : e] = s;
     x += (unsigned long long)s;
   }
-  block_total(x, total);
+  block_total(x, &head->sup_total);
 }
-
-__global__ void k_zero_u64(unsigned long long* p) { *p = 0; }
 
 // supports out of reach of every level for edges that must not be peeled
 constexpr int kFrozenSup = 1 << 29;
@@ -62,13 +62,6 @@ __global__ void k_freeze(int32_t* __restrict__ sup, const int32_t* __restrict__ 
 __global__ void k_fill_i32(int32_t* __restrict__ x, int64_t m, int32_t v) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < m) x[i] = v;
-}
-
-__global__ void __launch_bounds__(kT) k_sum_sup(const int32_t* __restrict__ sup, int64_t m, unsigned long long* total) {
-  unsigned long long x = 0;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
-    x += (unsigned long long)sup[e];
-  block_total(x, total);
 }
 
 inline unsigned grid_for(int64_t n) {
@@ -123,6 +116,24 @@ bool model_parts(const float* model, int64_t nfloats, const float** peel_part, c
                  hipStream_t s) {
   if (!model) return false;
   if (nfloats > 0 && nfloats < 4) return false;
+  // a model of stated length comes over whole, in one copy
+  constexpr int64_t kWhole = 4096;
+  if (nfloats > 0 && nfloats <= kWhole) {
+    float w[kWhole];
+    if (hipMemcpyAsync(w, model, sizeof(float) * (size_t)nfloats, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
+    if (hipStreamSynchronize(s) != hipSuccess) return false;
+    auto part = [&](const float* h, int F, int O) {
+      return h[0] == kModelTag && h[1] == (float)F && h[3] == (float)O && h[2] >= 1.f && h[2] <= (float)kMlpMaxH &&
+             h[2] == (float)(int)h[2];
+    };
+    if (!part(w, kPeelF, kPeelA)) return false;
+    const int off = model_part_floats(kPeelF, (int)w[2], kPeelA);
+    if ((int64_t)off + 4 > nfloats || !part(w + off, kSupF, kSupA)) return false;
+    if ((int64_t)off + model_part_floats(kSupF, (int)w[off + 2], kSupA) != nfloats) return false;
+    *peel_part = model;
+    *sup_part = model + off;
+    return true;
+  }
   float h[4];
   if (hipMemcpyAsync(h, model, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess) return false;
   if (hipStreamSynchronize(s) != hipSuccess) return false;
@@ -176,9 +187,10 @@ void resolve(const truss_options* in, SupPlan* sp, PeelPlan* pp, int* fallback, 
   pp->shape = o.peel_shape;
 }
 
+RunHead* take_head(Arena& a) { return reinterpret_cast<RunHead*>(a.take<int>(64)); }
+
 struct Plan {
-  int* d_err = nullptr;
-  unsigned long long* d_total = nullptr;
+  RunHead* head = nullptr;
   int32_t *sup = nullptr, *stamp = nullptr;
   int32_t* truss_canon = nullptr;
   int32_t *h = nullptr, *ch = nullptr, *psi = nullptr;  // upper bound (Procedure 6)
@@ -195,8 +207,7 @@ void take_bound(const truss_graph* g, Arena& a, Plan& p) {
 
 // One layout for size queries and runs: header, build, per-edge state, support, peel.
 void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
-  p.d_err = a.take<int>(64);
-  p.d_total = a.take<unsigned long long>(8);
+  p.head = take_head(a);
   size_t tmp_bytes = 0;
   build_workspace(g, a, true, &tmp_bytes);
   p.sup = a.take<int32_t>((size_t)g->m + 1);
@@ -268,8 +279,7 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
   a.base = static_cast<char*>(ws);
   a.cap = ws_bytes;
   Plan p;
-  p.d_err = a.take<int>(64);
-  p.d_total = a.take<unsigned long long>(8);
+  p.head = take_head(a);
   SupPlan sp;
   PeelPlan pp;
   int fallback = 0;
@@ -278,10 +288,11 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
   Timer tm(stats != nullptr && timed, s);
   tm.mark(0);
   DevGraph dg;
-  rc = build_graph(g, a, dg, p.d_err, s, true,
+  rc = build_graph(g, a, dg, p.head, s, true,
                    mode == kModeSupport ? 0
                    : mode == kModeBound ? kBuildRows | kBuildIds
-                                        : kBuildRows | kBuildIds | kBuildTables);
+                                        : kBuildRows | kBuildIds | kBuildTables,
+                   true);
   if (rc) return rc;
   tm.mark(1);
   p.sup = a.take<int32_t>((size_t)g->m + 1);
@@ -292,46 +303,47 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
   if (rc) return rc;
   tm.mark(2);
   PeelResult pr;
-  unsigned long long tot = 0;
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, p.d_total);
-  if (mode == kModeBound) {
-    // the counters of long rows live in the (unused) peeling region
-    int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
-    if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
-    compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
-    if (g->m > 0)
-      hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, p.psi, dg.perm, g->m, out);
-    TRUSS_HIP(hipGetLastError());
-    TRUSS_HIP(hipStreamSynchronize(s));
-    tm.mark(3);
-  } else if (mode == kModeSupport) {
-    if (g->m > 0)
-      hipLaunchKernelGGL(k_scatter_sup, dim3(sum_grid(g->m)), dim3(kT), 0, s, p.sup, dg.perm, g->m, out, p.d_total);
-    TRUSS_HIP(hipMemcpyAsync(&tot, p.d_total, sizeof(tot), hipMemcpyDeviceToHost, s));
-    TRUSS_HIP(hipStreamSynchronize(s));
-    if (triangles) *triangles = (int64_t)(tot / 3);
-    tm.mark(3);
-  } else {
-    if (stats && g->m > 0) hipLaunchKernelGGL(k_sum_sup, dim3(sum_grid(g->m)), dim3(kT), 0, s, p.sup, g->m, p.d_total);
-    int32_t* tc = dg.perm ? p.truss_canon : out;
+  if (mode == kModeDecompose) {
     if (sub && g->m > 0) {
       if (sub->sup_out)
         hipLaunchKernelGGL(k_scatter_sup, dim3(sum_grid(g->m)), dim3(kT), 0, s, p.sup, dg.perm, g->m, sub->sup_out,
-                           p.d_total);
+                           p.head);
       if (sub->frozen)
         hipLaunchKernelGGL(k_freeze, dim3(grid_for(g->m)), dim3(kT), 0, s, p.sup, dg.perm, sub->frozen, g->m);
-      if (sub->stop_level > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, g->m, 0);
+      if (sub->stop_level > 0)
+        hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(g->m)), dim3(kT), 0, s, p.truss_canon, g->m, 0);
       pp.first_level = sub->first_level;
       pp.stop_level = sub->stop_level;
     }
-    rc = peel(dg, pp, p.sup, p.stamp, tc, a, &pr, s, trace);
+    pp.head = p.head;
+    pp.sum = stats != nullptr;
+    pp.perm = dg.perm;
+    pp.out = out;
+    pp.done = tm.on ? tm.ev[3] : nullptr;
+    rc = peel(dg, pp, p.sup, p.stamp, p.truss_canon, a, &pr, s, trace);
     if (rc) return rc;
-    if (dg.perm && g->m > 0)
-      hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, dg.perm, g->m, out);
-    tm.mark(3);
+    if (g->m == 0) {
+      tm.mark(3);
+      TRUSS_HIP(hipStreamSynchronize(s));
+    }
+  } else {
+    if (mode == kModeBound) {
+      // the counters of long rows live in the (unused) peeling region
+      int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
+      if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
+      compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
+      if (g->m > 0)
+        hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, p.psi, dg.perm, g->m, out, p.head);
+    } else if (g->m > 0) {
+      hipLaunchKernelGGL(k_scatter_sup, dim3(sum_grid(g->m)), dim3(kT), 0, s, p.sup, dg.perm, g->m, out, p.head);
+    }
     TRUSS_HIP(hipGetLastError());
-    if (stats) TRUSS_HIP(hipMemcpyAsync(&tot, p.d_total, sizeof(tot), hipMemcpyDeviceToHost, s));
+    tm.mark(3);
+    RunHead h;
+    TRUSS_HIP(hipMemcpyAsync(&h, p.head, sizeof(h), hipMemcpyDeviceToHost, s));
     TRUSS_HIP(hipStreamSynchronize(s));
+    if (h.err != kNoErr) return input_error(h.err);
+    if (triangles) *triangles = (int64_t)(h.sup_total / 3);
   }
   if (stats) {
     memset(stats, 0, sizeof(*stats));
@@ -346,7 +358,7 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
     stats->ms_peel = tm.ms(2, 3);
     stats->ms_total = tm.ms(0, 3);
     stats->sched_fallback = fallback;
-    stats->triangles = (int64_t)(tot / 3);
+    stats->triangles = (int64_t)(pr.sup_total / 3);
     stats->launches = pr.launches;
     stats->heavy_rounds = pr.heavy_rounds;
     for (int b = 0; b < 6; ++b) stats->frontier_hist[b] = pr.hist[b];
@@ -472,8 +484,7 @@ int run_topdown(const truss_graph* g, int32_t t, int32_t* out, int32_t* kmin_out
   a.base = static_cast<char*>(ws);
   a.cap = ws_bytes;
   Plan p;
-  p.d_err = a.take<int>(64);
-  p.d_total = a.take<unsigned long long>(8);
+  p.head = take_head(a);
   SupPlan sp;
   PeelPlan pp;
   int fallback = 0;
@@ -481,7 +492,7 @@ int run_topdown(const truss_graph* g, int32_t t, int32_t* out, int32_t* kmin_out
   Timer tm(stats != nullptr, s);
   tm.mark(0);
   DevGraph dg;
-  rc = build_graph(g, a, dg, p.d_err, s, true, kBuildRows | kBuildIds);
+  rc = build_graph(g, a, dg, p.head, s, true, kBuildRows | kBuildIds);
   if (rc) return rc;
   p.sup = a.take<int32_t>((size_t)g->m + 1);
   p.stamp = a.take<int32_t>((size_t)g->m + 1);
@@ -628,18 +639,18 @@ int run_cohen(const truss_graph* g, int32_t* out, truss_stats* stats, void* ws, 
   Arena a;
   a.base = static_cast<char*>(ws);
   a.cap = ws_bytes;
-  int* d_err = a.take<int>(64);
+  RunHead* head = take_head(a);
   Timer tm(stats != nullptr, s);
   tm.mark(0);
   DevGraph dg;
-  if ((rc = build_graph(g, a, dg, d_err, s, false, kBuildRows | kBuildIds))) return rc;
+  if ((rc = build_graph(g, a, dg, head, s, false, kBuildRows | kBuildIds))) return rc;
   tm.mark(1);
   int2* sr = a.take<int2>((size_t)g->m + 1);
   int32_t* tc = a.take<int32_t>((size_t)g->m + 1);
   CohenResult cr;
   if ((rc = cohen_decompose(dg, sr, g->fmt == TRUSS_FMT_EDGES ? tc : out, a, &cr, s))) return rc;
   if (g->fmt == TRUSS_FMT_EDGES && g->m > 0)
-    hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, dg.perm, g->m, out);
+    hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, tc, dg.perm, g->m, out, head);
   tm.mark(2);
   TRUSS_HIP(hipGetLastError());
   TRUSS_HIP(hipStreamSynchronize(s));
@@ -683,9 +694,9 @@ int run_core(const truss_graph* g, int32_t* core_out, int32_t* cmax_out, void* w
   Arena a;
   a.base = static_cast<char*>(ws);
   a.cap = ws_bytes;
-  int* d_err = a.take<int>(64);
+  RunHead* head = take_head(a);
   DevGraph dg;
-  rc = build_graph(g, a, dg, d_err, s, false, kBuildRows);
+  rc = build_graph(g, a, dg, head, s, false, kBuildRows);
   if (rc) return rc;
   int32_t cmax = 0;
   rc = compute_core_numbers(dg, core_out, &cmax, a, s);
@@ -843,9 +854,9 @@ int run_cohesion(const truss_graph* g, const truss_options* opts, truss_cohesion
   Arena r;
   r.base = b.region;
   r.cap = b.region_bytes;
-  int* d_err = r.take<int>(64);
+  RunHead* head = take_head(r);
   DevGraph dg;
-  if ((rc = build_graph(g, r, dg, d_err, s, false, kBuildRows | kBuildIds))) return rc;
+  if ((rc = build_graph(g, r, dg, head, s, false, kBuildRows | kBuildIds))) return rc;
   int32_t cmax = 0;
   if ((rc = compute_core_numbers(dg, b.core, &cmax, r, s))) return rc;
   int cnt[2] = {0, 0};

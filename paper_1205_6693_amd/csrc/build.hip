@@ -28,9 +28,13 @@ inline int bits_for(int64_t n) {
 
 __device__ __forceinline__ void report(int* err, int code) { atomicMin(err, code); }
 
-// the error word, and counters of n + 1 entries (nullable) cleared
-__global__ void k_build_init(int* err, int32_t* __restrict__ deg, int64_t n) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *err = kNoErr;
+// the head, and counters of n + 1 entries (nullable) cleared
+__global__ void k_build_init(RunHead* head, int32_t* __restrict__ deg, int64_t n) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    head->err = kNoErr;
+    head->sup_total = 0ULL;
+    head->wbound = 0ULL;
+  }
   if (!deg) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n; i += (int64_t)gridDim.x * blockDim.x) deg[i] = 0;
 }
@@ -182,6 +186,30 @@ __global__ void k_edge_degrees(const int32_t* __restrict__ src, const int32_t* _
   atomicAdd(&deg[v], 1);
 }
 
+// The same for up to kLdsVerts vertices, counted in LDS first: device atomics are
+// served at about 27 G a second (lines of 16 counters at a time where a wavefront's
+// are neighbours), and 400 K edges on 16 K vertices took 32 us of them.
+constexpr int kLdsVerts = 16384, kLdsDegT = 1024;
+__global__ void __launch_bounds__(kLdsDegT) k_edge_degrees_lds(const int32_t* __restrict__ src,
+                                                               const int32_t* __restrict__ dst, int64_t m, int32_t n,
+                                                               int32_t* __restrict__ deg, int* err) {
+  __shared__ int cnt[kLdsVerts];
+  for (int x = threadIdx.x; x < n; x += kLdsDegT) cnt[x] = 0;
+  __syncthreads();
+  for (int64_t i = blockIdx.x * (int64_t)kLdsDegT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kLdsDegT) {
+    const int32_t u = src[i], v = dst[i];
+    if (u < 0 || u >= n || v < 0 || v >= n) report(err, kErrRange);
+    else if (u == v) report(err, kErrSelfloop);
+    else {
+      atomicAdd(&cnt[u], 1);
+      atomicAdd(&cnt[v], 1);
+    }
+  }
+  __syncthreads();
+  for (int x = threadIdx.x; x < n; x += kLdsDegT)
+    if (cnt[x]) atomicAdd(&deg[x], cnt[x]);
+}
+
 // sort keys of the vertices: the degree, from the CSR offsets or from deg; in id
 // order, so that a stable sort ranks by (degree, id)
 __global__ void k_degree_keys(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ deg, int32_t n, int vb,
@@ -324,17 +352,7 @@ int read_err(const int* d_err, hipStream_t s) {
   int h = kNoErr;
   TRUSS_HIP(hipMemcpyAsync(&h, d_err, sizeof(int), hipMemcpyDeviceToHost, s));
   TRUSS_HIP(hipStreamSynchronize(s));
-  if (h == kNoErr) return TRUSS_OK;
-  switch (h) {
-    case kErrRowptr: set_last_error("CSR row_ptr is not a valid offset array for 2m entries"); break;
-    case kErrRange: set_last_error("vertex id outside [0, n)"); break;
-    case kErrSelfloop: set_last_error("self-loop in input (simple graphs only)"); break;
-    case kErrUnsorted: set_last_error("CSR row not strictly ascending"); break;
-    case kErrDup: set_last_error("edge listed more than once"); break;
-    case kErrAsym: set_last_error("CSR is not symmetric"); break;
-    default: set_last_error("validation failed (%d)", h); break;
-  }
-  return -h;
+  return input_error(h);
 }
 
 // buffers of the build, laid out identically for the size query and the run
@@ -464,6 +482,20 @@ void rows_from_keys(int32_t n, int64_t m, int vb, Layout& L, int needs, int* d_e
 
 }  // namespace
 
+int input_error(int h) {
+  if (h == kNoErr) return TRUSS_OK;
+  switch (h) {
+    case kErrRowptr: set_last_error("CSR row_ptr is not a valid offset array for 2m entries"); break;
+    case kErrRange: set_last_error("vertex id outside [0, n)"); break;
+    case kErrSelfloop: set_last_error("self-loop in input (simple graphs only)"); break;
+    case kErrUnsorted: set_last_error("CSR row not strictly ascending"); break;
+    case kErrDup: set_last_error("edge listed more than once"); break;
+    case kErrAsym: set_last_error("CSR is not symmetric"); break;
+    default: set_last_error("validation failed (%d)", h); break;
+  }
+  return -h;
+}
+
 size_t build_workspace(const truss_graph* g, Arena& a, bool relabel, size_t* tmp_bytes) {
   Layout L;
   carve(g, relabel, a, L);
@@ -474,20 +506,26 @@ size_t build_workspace(const truss_graph* g, Arena& a, bool relabel, size_t* tmp
 // Renumbered graph: the canonical edges are sorted by (smaller new id, larger new
 // id) and new ids rank the degrees, so the oriented CSR is the edge list itself
 // (entry j is edge j, its row offsets uppre).  The input's errors are read once,
-// at the end (and, for CSR input, those of row_ptr at the start: the entries are
-// found through it).
-static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int vb, int* d_err, hipStream_t s,
-                            int needs) {
+// at the end or with the caller's results (and, for CSR input, those of row_ptr at
+// the start: the entries are found through it).
+static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int vb, RunHead* head, hipStream_t s,
+                            int needs, bool defer) {
+  int* const d_err = &head->err;
   const int32_t n = g->n;
   const int64_t m = g->m, m2 = 2 * m;
   const bool edges = g->fmt == TRUSS_FMT_EDGES;
   L.uppre = L.orow;  // kept
   const unsigned gn = grid_for((int64_t)n + 1) < 4096 ? grid_for((int64_t)n + 1) : 4096;
-  hipLaunchKernelGGL(k_build_init, dim3(gn), dim3(kT), 0, s, d_err, edges ? L.vdeg : nullptr, (int64_t)n);
+  hipLaunchKernelGGL(k_build_init, dim3(gn), dim3(kT), 0, s, head, edges ? L.vdeg : nullptr, (int64_t)n);
   const int64_t* valid = nullptr;
   const int32_t *src = g->src, *dst = g->dst;
   if (edges) {
-    hipLaunchKernelGGL(k_edge_degrees, dim3(grid_for(m)), dim3(kT), 0, s, src, dst, m, n, L.vdeg, d_err);
+    const int64_t share = 8 * (int64_t)(n > kLdsDegT ? n : kLdsDegT);  // edges that pay for a workgroup's counters
+    if (n <= kLdsVerts && m >= share)
+      hipLaunchKernelGGL(k_edge_degrees_lds, dim3((unsigned)(m / share < 256 ? m / share : 256)), dim3(kLdsDegT), 0, s,
+                         src, dst, m, n, L.vdeg, d_err);
+    else
+      hipLaunchKernelGGL(k_edge_degrees, dim3(grid_for(m)), dim3(kT), 0, s, src, dst, m, n, L.vdeg, d_err);
     degree_ranks(nullptr, L.vdeg, n, vb, L, s);
   } else {
     hipLaunchKernelGGL(k_rowptr_check, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n, m2, d_err);
@@ -516,8 +554,10 @@ static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int v
     hipLaunchKernelGGL(k_csr_sym_check, dim3(grid_for(m2)), dim3(kT), 0, s, g->col, L.rowid, m2, n, L.rank,
                        tables ? L.rtab : nullptr, L.rtoff, L.uppre, L.ev, d_err);
   TRUSS_HIP(hipGetLastError());
-  const int rc = read_err(d_err, s);
-  if (rc) return rc;
+  if (!defer) {
+    const int rc = read_err(d_err, s);
+    if (rc) return rc;
+  }
   dg.orow = L.orow;
   dg.ocol = L.ev;
   dg.row_ptr = L.row_ptr;
@@ -525,7 +565,8 @@ static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int v
   return TRUSS_OK;
 }
 
-int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel, int needs) {
+int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, RunHead* head, hipStream_t s, bool relabel, int needs,
+                bool defer) {
   Layout L;
   carve(g, relabel, a, L);
   if (a.overflow()) return TRUSS_E_WORKSPACE;
@@ -534,6 +575,8 @@ int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStr
   const int vb = bits_for(n) > 0 ? bits_for(n) : 1;
   dg.n = n;
   dg.m = m;
+  // no id is in range, and there is no row that could hold the pairs meanwhile
+  if (g->fmt == TRUSS_FMT_EDGES && n == 0 && m > 0) return input_error(kErrRange);
   dg.tmp = a.base + L.tmp_at;
   dg.tmp_bytes = L.tmp_bytes;
   dg.col = L.col;
@@ -542,9 +585,10 @@ int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStr
   dg.ev = L.ev;
   dg.rtab = L.rtab;
   dg.rtoff = L.rtoff;
-  if (relabel) return build_relabelled(g, L, dg, vb, d_err, s, needs);
+  if (relabel) return build_relabelled(g, L, dg, vb, head, s, needs, defer);
 
-  hipLaunchKernelGGL(k_build_init, dim3(1), dim3(1), 0, s, d_err, (int32_t*)nullptr, (int64_t)0);
+  int* const d_err = &head->err;
+  hipLaunchKernelGGL(k_build_init, dim3(1), dim3(1), 0, s, head, (int32_t*)nullptr, (int64_t)0);
   int rc;
   if (g->fmt == TRUSS_FMT_EDGES) {
     hipLaunchKernelGGL(k_canon, dim3(grid_for(m)), dim3(kT), 0, s, g->src, g->dst, m, n, vb, L.key, L.val, d_err);

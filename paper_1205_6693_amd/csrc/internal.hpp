@@ -69,6 +69,14 @@ struct DevGraph {
   size_t tmp_bytes = 0;
 };
 
+// Words at the head of a call's workspace (256 bytes are taken), cleared by the build.
+struct RunHead {
+  int err;  // smallest error magnitude found in the input, kNoErr if none
+  int pad;
+  unsigned long long sup_total;  // sum of the supports
+  unsigned long long wbound;     // peeling: bound on the entries of one round's walks
+};
+
 // Build: validation + canonical edge ids + symmetric and oriented CSR.
 // Returns TRUSS_OK or a TRUSS_E_* code; syncs on the stream for the checks.
 struct BuildBufs;
@@ -84,7 +92,12 @@ enum : int {
   kBuildIds = 2,    // with kBuildRows: seid, eu, ev
   kBuildTables = 4  // with both, relabelled: rtab, rtoff
 };
-int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, int* d_err, hipStream_t s, bool relabel, int needs);
+// With defer (relabelled builds only) the errors found in the entries are left in
+// head->err for the caller to read with its results: what is built from an invalid
+// input stays in bounds in every later phase.
+int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, RunHead* head, hipStream_t s, bool relabel, int needs,
+                bool defer = false);
+int input_error(int err);  // head->err as a return code (message set)
 
 // Scheduling of the exact methods (the scheduler never changes results).
 struct SupPlan {
@@ -103,6 +116,11 @@ struct PeelPlan {
   int first_level = 2;  // the first level peeled takes every live edge with sup <= first_level - 2
   int stop_level = 0;   // > 0: stop once the next level would exceed it (later edges keep no truss number)
   bool timed = true;    // time the kernel's launches with HIP events
+  RunHead* head = nullptr;         // (device) an input error found there ends the peeling at its start
+  bool sum = false;                // sum the supports (PeelResult::sup_total)
+  const int32_t* perm = nullptr;   // the truss numbers go to out[perm[e]]
+  int32_t* out = nullptr;
+  hipEvent_t done = nullptr;       // recorded behind the output (nullable)
 };
 
 // Support: sup[e] for every canonical edge; stamp[e] = 0 (round stamps of the peeling, nullable).
@@ -111,7 +129,8 @@ size_t support_workspace(const DevGraph& dg, Arena& a);
 int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32_t* stamp, Arena& a, hipStream_t s,
                     truss_trace* trace);
 
-// Peeling: truss[e] for every canonical edge; sup holds the supports and stamp zeros on entry.
+// Peeling: truss[e] for every canonical edge, scattered to plan.out; sup holds
+// the supports and stamp zeros on entry.  The stream has synchronised on return.
 struct PeelResult {
   int32_t kmax = 0, levels = 0;
   int64_t subrounds = 0, work = 0;
@@ -119,6 +138,7 @@ struct PeelResult {
   int64_t heavy_rounds = 0;
   int64_t hist[6] = {0, 0, 0, 0, 0, 0};
   double phase_ms[6] = {0, 0, 0, 0, 0, 0};
+  unsigned long long sup_total = 0;
   double kernel_ms = 0;  // time inside the persistent peeling kernel (all launches)
 };
 size_t peel_workspace(const DevGraph& dg, Arena& a);

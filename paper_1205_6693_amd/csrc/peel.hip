@@ -70,6 +70,10 @@ constexpr int kWaves = kT / kWave;
 constexpr int kIntMax = 0x7fffffff;
 constexpr int kHistBins = 6;
 constexpr long long kCompactNum = 8, kCompactDen = 10;  // row compaction threshold
+// Rows that hold fewer edges are not compacted any more: the way through the host
+// costs some 60 us, more than walking the removed entries to the end does
+// (G(2000, 0.01), 20 K edges: the call 0.47 -> 0.36 ms, with the waits below).
+constexpr long long kCompactMin = 1 << 15;
 constexpr int kStageQ = 16384;  // LDS staging of a list phase's frontier (entries)
 
 // The support of an edge that has joined a frontier is set to kGone, so that the
@@ -152,7 +156,8 @@ struct alignas(256) PeelCtl {
   int fix_bits, fix_vals;  // action bits fixed by the options
   int m_edges;
   int qbits;               // bits of the edge count in w_q
-  unsigned long long wbound;  // bound on the entries of one round's walks
+  int input_err;           // RunHead::err when the peeling began
+  unsigned long long sup_total;
   int stop_level;          // > 0: no level above it is started
   long long lvl_sub0;      // sub-rounds before the current level
   long long prev_sub;      // sub-rounds of the previous level
@@ -198,6 +203,7 @@ struct PeelArgs {
   FrontierQueue fq[2];
   const int2* rtab;           // row hash tables
   PeelCtl* ctl;
+  const RunHead* head;
   const float* model;         // peeling model part (learned scheduler), or null
   float* tr_feat;             // per-level trace (tr_cap rows), or null
   float* tr_ms;
@@ -331,7 +337,7 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
       removed_level = 0;
       const long long alive_after = P.m - removed;
       st.compact = alive_after * kListDen < (long long)acnt * kListNum ? 1 : 0;
-      if (alive_after > 0 && alive_after * kCompactDen < csr_live * kCompactNum) {
+      if (csr_live >= kCompactMin && alive_after > 0 && alive_after * kCompactDen < csr_live * kCompactNum) {
         csr_live = alive_after;
         phase = PH_COMPACT;
       } else {
@@ -886,7 +892,8 @@ __device__ __forceinline__ void peel_body() {
   const int tid = threadIdx.x;
   const int wv = tid / kWave;
   const int qbits = ldc(&c->qbits);
-  const int shift = walk_shift(ldc(&c->wbound), ((const PeelArgs*)ka)->m, qbits);
+  const int shift = walk_shift(((const PeelArgs*)ka)->head->wbound, ((const PeelArgs*)ka)->m, qbits);
+  if (blockIdx.x == 0 && threadIdx.x == 0) stc(&c->sup_total, ((const PeelArgs*)ka)->head->sup_total);
   unsigned long long my_work = 0;  // entries walked by this wavefront
 
   __shared__ unsigned long long s_pub[kPub];
@@ -1202,18 +1209,23 @@ __global__ void __launch_bounds__(256) k_compact(int32_t* __restrict__ col,
   }
 }
 
-// The vertices' walk records and the control block; wbound (zeroed before)
-// receives the sum of the shorter row over all edges: with the ids ranked by
-// degree an edge's shorter row is that of its first endpoint in the
-// orientation, so the sum is that of out-degree times degree.
+// The vertices' walk records and the control block.  head->wbound receives the sum
+// of the shorter row over all edges: with the ids ranked by degree an edge's
+// shorter row is that of its first endpoint in the orientation, so the sum is
+// that of out-degree times degree.  head->sup_total receives the sum of the
+// supports (sup nullable).
 __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __restrict__ row_ptr,
                                                    const int64_t* __restrict__ orow, const int64_t* __restrict__ rtoff,
                                                    VInfo* __restrict__ vinfo, int32_t n, int64_t m,
                                                    long long max_subrounds, int sched, int fix_bits, int fix_vals,
-                                                   int qbits, int first_level, int stop_level) {
+                                                   int qbits, int first_level, int stop_level,
+                                                   const int32_t* __restrict__ sup, RunHead* head) {
+  __shared__ unsigned long long s_s[4];
   __shared__ unsigned long long s_w[4];
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  unsigned long long wsum = 0;
+  unsigned long long wsum = 0, ssum = 0;
+  if (sup)
+    for (int64_t e = i; e < m; e += (int64_t)gridDim.x * blockDim.x) ssum += (unsigned long long)sup[e];
   if (i < n) {
     const int64_t rb = row_ptr[i], d = row_ptr[i + 1] - rb;
     const int64_t to = rtoff[i], slots = rtoff[i + 1] - to;
@@ -1225,11 +1237,16 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     wsum = (unsigned long long)(orow[i + 1] - orow[i]) * (unsigned long long)d;
   }
   wsum = wave_sum(wsum);
-  if (lane_id() == 0) s_w[threadIdx.x / kWave] = wsum;
+  ssum = wave_sum(ssum);
+  if (lane_id() == 0) {
+    s_w[threadIdx.x / kWave] = wsum;
+    s_s[threadIdx.x / kWave] = ssum;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned long long w = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-    if (w) atomicAdd(&c->wbound, w);
+    const unsigned long long w = s_w[0] + s_w[1] + s_w[2] + s_w[3], t = s_s[0] + s_s[1] + s_s[2] + s_s[3];
+    if (w) atomicAdd(&head->wbound, w);
+    if (t) atomicAdd(&head->sup_total, t);
   }
   if (i == 0) {
     grid_barrier_init(&c->bar);
@@ -1242,7 +1259,9 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
       c->w[i].fwork = 0ULL;
     }
     c->w_work = 0ULL;
-    c->phase = PH_SWEEP;
+    c->input_err = head->err;
+    c->sup_total = 0ULL;
+    c->phase = head->err == kNoErr ? PH_SWEEP : PH_DONE;
     c->k = first_level - 1;  // the first sweep takes the frontier of level first_level
     c->r = 0;
     c->qlen = 0;
@@ -1278,7 +1297,12 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
   }
 }
 
-__global__ void k_zero_bound(PeelCtl* c) { c->wbound = 0ULL; }
+// truss numbers in the caller's order (nothing for an invalid input)
+__global__ void __launch_bounds__(256) k_peel_out(const int32_t* __restrict__ truss, const int32_t* __restrict__ perm,
+                                                  int64_t m, int32_t* __restrict__ out, const PeelCtl* c) {
+  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (e < m && c->input_err == kNoErr) out[perm[e]] = truss[e];
+}
 
 struct PeelLayout {
   PeelCtl* ctl;
@@ -1340,10 +1364,14 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   const long long maxsr = plan.max_subrounds;
   int qbits = 1;
   while ((dg.m >> qbits) != 0) ++qbits;  // a frontier holds up to m edges
-  hipLaunchKernelGGL(k_zero_bound, dim3(1), dim3(1), 0, s, L.ctl);
-  hipLaunchKernelGGL(k_peel_init, dim3((unsigned)(((int64_t)(dg.n > 0 ? dg.n : 1) + 255) / 256)), dim3(256), 0, s,
+  // a thread a vertex; with the sum of the supports at least up to 1024 workgroups
+  int64_t init = ((int64_t)(dg.n > 0 ? dg.n : 1) + 255) / 256;
+  const int64_t for_sum = (dg.m + 255) / 256 < 1024 ? (dg.m + 255) / 256 : 1024;
+  if (plan.sum && init < for_sum) init = for_sum;
+  hipLaunchKernelGGL(k_peel_init, dim3((unsigned)init), dim3(256), 0, s,
                      L.ctl, dg.row_ptr, dg.orow, dg.rtoff, L.vinfo, dg.n, dg.m, maxsr, plan.sched, plan.fix_bits,
-                     plan.fix_vals, qbits, plan.first_level < 2 ? 2 : plan.first_level, plan.stop_level);
+                     plan.fix_vals, qbits, plan.first_level < 2 ? 2 : plan.first_level, plan.stop_level,
+                     plan.sum ? sup : nullptr, plan.head);
   if (g_peel_blocks == 0) {
     int dev = 0, cus = 0, occ = 0;
     TRUSS_HIP(hipGetDevice(&dev));
@@ -1380,12 +1408,21 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   }
   P.rtab = dg.rtab;
   P.ctl = L.ctl;
+  P.head = plan.head;
   P.model = plan.sched == TRUSS_SCHED_LEARNED ? plan.model : nullptr;
   P.tr_cap = trace && trace->level_feat && trace->level_ms && trace->level_action ? trace->level_cap : 0;
   P.tr_feat = P.tr_cap > 0 ? trace->level_feat : nullptr;
   P.tr_ms = P.tr_cap > 0 ? trace->level_ms : nullptr;
   P.tr_act = P.tr_cap > 0 ? trace->level_action : nullptr;
   PeelCtl h;
+  // below kCompactMin edges the kernel never returns for a compaction, so the
+  // output can follow it without asking
+  const bool once = dg.m < kCompactMin;
+  auto output = [&]() {
+    hipLaunchKernelGGL(k_peel_out, dim3((unsigned)((dg.m + 255) / 256)), dim3(256), 0, s, truss_canon, plan.perm, dg.m,
+                       plan.out, L.ctl);
+    if (plan.done) (void)hipEventRecord(plan.done, s);
+  };
   int launches = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   const bool timed = plan.timed && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess;
@@ -1399,6 +1436,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
     TRUSS_HIP(hipGetLastError());
     if (timed) (void)hipEventRecord(ev1, s);
     ++launches;
+    if (once) output();
     TRUSS_HIP(hipMemcpyAsync(&h, L.ctl, sizeof(PeelCtl), hipMemcpyDeviceToHost, s));
     TRUSS_HIP(hipStreamSynchronize(s));
     if (timed) {
@@ -1411,6 +1449,13 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   }
   if (ev0) (void)hipEventDestroy(ev0);
   if (ev1) (void)hipEventDestroy(ev1);
+  if (h.input_err != kNoErr) return input_error(h.input_err);
+  if (!once && !h.bar.abort && !h.err && h.phase == PH_DONE) {
+    output();
+    TRUSS_HIP(hipStreamSynchronize(s));
+  }
+  TRUSS_HIP(hipGetLastError());
+  res->sup_total = h.sup_total;
   res->kernel_ms = kernel_ms;
   if (trace) trace->levels = h.levels < P.tr_cap ? h.levels : P.tr_cap;
   res->kmax = h.kmax;

@@ -55,8 +55,10 @@ struct SupCtl {
   float feat[kBins][kSupF];                  // the decision's features
 };
 
-// supports and, for the peeling, round stamps cleared
-__global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ stamp, int64_t m, SupCtl* ctl) {
+// supports and, for the peeling, round stamps cleared; act: the bins' methods
+// where they are known before the launch (two bits a bin)
+__global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ stamp, int64_t m, SupCtl* ctl,
+                           unsigned act) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < m) {
     supo[i] = 0;
@@ -65,7 +67,7 @@ __global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ sta
   if (i < kBins) {
     ctl->cnt[i] = 0;
     ctl->fetch[i] = 0;
-    ctl->act[i] = 0;
+    ctl->act[i] = (int)(act >> (2 * i)) & 3;
     ctl->sd[i] = 0ULL;
     ctl->sd2[i] = 0ULL;
   }
@@ -268,34 +270,44 @@ __device__ void walk_pairs(const WalkTabs& W, int nrows, int lo, int hi, const i
       continue;
     }
     // rows start inside the window: settle row kc's count, then find each
-    // lane's row
+    // lane's row, for kU windows before their loads go out together
     if (lane == 0 && acc && kc >= 0) atomicAdd(&W.cnt[W.wi[kc]], acc);
     acc = 0;
-    const int idx = kc + 1 + lane;
-    const int p = idx < nrows ? W.pre[idx] : 0x7fffffff;
-    wave_sync();
-    W.own[lane] = -1;
-    wave_sync();
-    if (p < t0 + kWave) W.own[p - t0] = idx;  // rows after kc start at or after t0
-    wave_sync();
-    int o = W.own[lane];
-    o = o > kc ? o : kc;
-    o = wave_incl_max(o);
-    o = o < 0 ? 0 : o >= nrows ? nrows - 1 : o;
-    const int t = t0 + lane;
-    if (t < hi) {
-      const int64_t j = (int64_t)W.offj[o] + t;
-      const int pos = tab_find<LOGTAB>(W.tab, ocol[j]);
+    int o[kU];
+    int32_t c[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int tu = t0 + u * kWave;
+      int x = kc;
+      if (nx < tu + kWave) {
+        const int idx = kc + 1 + lane;
+        const int p = idx < nrows ? W.pre[idx] : 0x7fffffff;
+        wave_sync();
+        W.own[lane] = -1;
+        wave_sync();
+        if (p < tu + kWave) W.own[p - tu] = idx;  // rows after kc start at or after tu
+        wave_sync();
+        x = W.own[lane];
+        x = wave_incl_max(x > kc ? x : kc);
+        kc = __shfl(x, kWave - 1, kWave);
+        nx = kc + 1 < nrows ? W.pre[kc + 1] : 0x7fffffff;
+      }
+      o[u] = x < 0 ? 0 : x >= nrows ? nrows - 1 : x;
+      const int t = tu + lane;
+      c[u] = t < hi ? ocol[(int64_t)W.offj[o[u]] + t] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      if (c[u] < 0) continue;
+      const int pos = tab_find<LOGTAB>(W.tab, c[u]);
       if (pos >= 0) {
         atomicAdd(&W.cnt[pos], 1);
-        atomicAdd(&supo[j], 1);
-        atomicAdd(&W.cnt[W.wi[o]], 1);
+        atomicAdd(&supo[(int64_t)W.offj[o[u]] + t0 + u * kWave + lane], 1);
+        atomicAdd(&W.cnt[W.wi[o[u]]], 1);
       }
     }
-    kc = __shfl(o, kWave - 1, kWave);
-    nx = kc + 1 < nrows ? W.pre[kc + 1] : 0x7fffffff;
-    oj = W.offj[kc];
-    t0 += kWave;
+    oj = kc >= 0 ? W.offj[kc] : 0;
+    t0 += kU * kWave;
   }
   if (lane == 0 && acc && kc >= 0) atomicAdd(&W.cnt[W.wi[kc]], acc);
 }
@@ -720,31 +732,34 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
   if (a.overflow()) return TRUSS_E_WORKSPACE;
   const int64_t m = dg.m;
   const int32_t n = dg.n;
-  hipLaunchKernelGGL(k_sup_zero, dim3(grid_for(m > kBins ? m : kBins)), dim3(kT), 0, s, sup, stamp, m, L.ctl);
+  // The method of a bin where it is known before the launch (forced, or the plain
+  // or heuristic scheduler), -1 where the network decides on the device.
+  auto known = [&](int b) {
+    int method = b == kBins - 1 ? kBsearch : kHash;
+    if (plan.force >= 0) method = plan.force;
+    else if (plan.sched == TRUSS_SCHED_PLAIN) method = kMerge;
+    else if (plan.sched == TRUSS_SCHED_LEARNED && plan.model != nullptr) return -1;
+    return method == kHash && b == kBins - 1 ? (int)kBsearch : method;
+  };
+  unsigned act = 0;
+  for (int b = 0; b < kBins; ++b) act |= (unsigned)(known(b) < 0 ? 0 : known(b)) << (2 * b);
+  hipLaunchKernelGGL(k_sup_zero, dim3(grid_for(m > kBins ? m : kBins)), dim3(kT), 0, s, sup, stamp, m, L.ctl, act);
   if (m == 0) return TRUSS_OK;
   hipLaunchKernelGGL(k_sup_bin, dim3((unsigned)((n + kBinT - 1) / kBinT > 0 ? (n + kBinT - 1) / kBinT : 1)),
                      dim3(kBinT), 0, s, dg.orow, n, L.vlist, L.ctl);
-  hipLaunchKernelGGL(k_sup_decide, dim3(1), dim3(kBins * kWave), 0, s, L.ctl, m, plan.sched, plan.force,
-                     plan.model);
+  if (trace || known(0) < 0)  // (a trace wants the decision's features)
+    hipLaunchKernelGGL(k_sup_decide, dim3(1), dim3(kBins * kWave), 0, s, L.ctl, m, plan.sched, plan.force,
+                       plan.model);
   hipEvent_t ev[kBins + 1] = {};
   bool timed = trace != nullptr;
   for (int b = 0; timed && b <= kBins; ++b)
     if (hipEventCreate(&ev[b]) != hipSuccess) timed = false;
   // persistent-style grids: workers fetch vertices from the bin lists
   const unsigned gw = 256 * 8, gb = 256 * 4, g2 = 256;
-  // Which methods a bin may take: one where it is known before the launch
-  // (forced, or the plain or heuristic scheduler), any where the network
-  // decides on the device.  A vertex with d out-neighbours, all of them of
-  // at least its degree, needs d (d + 1) / 2 edges, so on small graphs the bins of large
-  // d are empty and get no kernels.
-  auto may = [&](int b, int method) {
-    int only = -1;
-    if (plan.force >= 0) only = plan.force;
-    else if (plan.sched == TRUSS_SCHED_PLAIN) only = kMerge;
-    else if (plan.sched != TRUSS_SCHED_LEARNED || plan.model == nullptr) only = b == kBins - 1 ? kBsearch : kHash;
-    if (only == kHash && b == kBins - 1) only = kBsearch;
-    return only < 0 || only == method;
-  };
+  // A vertex with d out-neighbours, all of them of at least its degree, needs
+  // d (d + 1) / 2 edges, so on small graphs the bins of large d are empty and get
+  // no kernels.
+  auto may = [&](int b, int method) { return known(b) == method || (known(b) < 0 && !(method == kHash && b == kBins - 1)); };
   const int64_t dlo[kBins] = {2, kWaveMax + 1, kBlockMax1 + 1, kBlockMax2 + 1};
   for (int b = 0; b < kBins; ++b) {
     if (timed) (void)hipEventRecord(ev[b], s);
