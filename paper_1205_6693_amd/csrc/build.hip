@@ -174,40 +174,42 @@ __global__ void k_sym_lower(const uint32_t* __restrict__ tkey, const int32_t* __
 // the caller's edge (input pair, or canonical CSR position), so outputs keep
 // the caller's order.
 
-// edge-list input: range and self-loop checks, degrees over the valid pairs
-__global__ void k_edge_degrees(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m,
-                               int32_t n, int32_t* __restrict__ deg, int* err) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const int32_t u = src[i], v = dst[i];
-  if (u < 0 || u >= n || v < 0 || v >= n) { report(err, kErrRange); return; }
-  if (u == v) { report(err, kErrSelfloop); return; }
-  atomicAdd(&deg[u], 1);
-  atomicAdd(&deg[v], 1);
-}
-
-// The same for up to kLdsVerts vertices, counted in LDS first: device atomics are
-// served at about 27 G a second (lines of 16 counters at a time where a wavefront's
-// are neighbours), and 400 K edges on 16 K vertices took 32 us of them.
-constexpr int kLdsVerts = 16384, kLdsDegT = 1024;
-__global__ void __launch_bounds__(kLdsDegT) k_edge_degrees_lds(const int32_t* __restrict__ src,
-                                                               const int32_t* __restrict__ dst, int64_t m, int32_t n,
-                                                               int32_t* __restrict__ deg, int* err) {
-  __shared__ int cnt[kLdsVerts];
-  for (int x = threadIdx.x; x < n; x += kLdsDegT) cnt[x] = 0;
+// Edge-list input: range and self-loop checks, degrees over the valid pairs.
+// A workgroup counts in an LDS table first, one counter a slot, claimed by the
+// first vertex that hashes there (another one counts in memory at once): device
+// atomics are served at some 27 G a second, and those on one address at one per
+// 17 ns, so a hub's count cost 185 us of an R-MAT graph of 592 K edges.
+constexpr int kDegT = 1024, kDegSlots = 8192;
+__global__ void __launch_bounds__(kDegT) k_edge_degrees(const int32_t* __restrict__ src,
+                                                        const int32_t* __restrict__ dst, int64_t m, int32_t n,
+                                                        int32_t* __restrict__ deg, int* err) {
+  __shared__ int owner[kDegSlots], cnt[kDegSlots];
+  for (int x = threadIdx.x; x < kDegSlots; x += kDegT) {
+    owner[x] = -1;
+    cnt[x] = 0;
+  }
   __syncthreads();
-  for (int64_t i = blockIdx.x * (int64_t)kLdsDegT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kLdsDegT) {
+  auto count = [&](int32_t v) {
+    const int h = (int)((uint32_t)v % kDegSlots);
+    int o = owner[h];
+    if (o < 0) o = atomicCAS(&owner[h], -1, v);
+    if (o < 0 || o == v) atomicAdd(&cnt[h], 1);
+    else atomicAdd(&deg[v], 1);
+  };
+  for (int64_t i = blockIdx.x * (int64_t)kDegT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kDegT) {
     const int32_t u = src[i], v = dst[i];
-    if (u < 0 || u >= n || v < 0 || v >= n) report(err, kErrRange);
-    else if (u == v) report(err, kErrSelfloop);
-    else {
-      atomicAdd(&cnt[u], 1);
-      atomicAdd(&cnt[v], 1);
+    if (u < 0 || u >= n || v < 0 || v >= n) {
+      report(err, kErrRange);
+    } else if (u == v) {
+      report(err, kErrSelfloop);
+    } else {
+      count(u);
+      count(v);
     }
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < n; x += kLdsDegT)
-    if (cnt[x]) atomicAdd(&deg[x], cnt[x]);
+  for (int x = threadIdx.x; x < kDegSlots; x += kDegT)
+    if (cnt[x]) atomicAdd(&deg[owner[x]], cnt[x]);
 }
 
 // sort keys of the vertices: the degree, from the CSR offsets or from deg; in id
@@ -520,12 +522,9 @@ static int build_relabelled(const truss_graph* g, Layout& L, DevGraph& dg, int v
   const int64_t* valid = nullptr;
   const int32_t *src = g->src, *dst = g->dst;
   if (edges) {
-    const int64_t share = 8 * (int64_t)(n > kLdsDegT ? n : kLdsDegT);  // edges that pay for a workgroup's counters
-    if (n <= kLdsVerts && m >= share)
-      hipLaunchKernelGGL(k_edge_degrees_lds, dim3((unsigned)(m / share < 256 ? m / share : 256)), dim3(kLdsDegT), 0, s,
-                         src, dst, m, n, L.vdeg, d_err);
-    else
-      hipLaunchKernelGGL(k_edge_degrees, dim3(grid_for(m)), dim3(kT), 0, s, src, dst, m, n, L.vdeg, d_err);
+    const int64_t groups = (m + 4 * kDegT - 1) / (4 * kDegT);
+    hipLaunchKernelGGL(k_edge_degrees, dim3((unsigned)(groups < 1 ? 1 : groups > 2048 ? 2048 : groups)), dim3(kDegT), 0,
+                       s, src, dst, m, n, L.vdeg, d_err);
     degree_ranks(nullptr, L.vdeg, n, vb, L, s);
   } else {
     hipLaunchKernelGGL(k_rowptr_check, dim3(grid_for((int64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n, m2, d_err);

@@ -155,7 +155,8 @@ constexpr int kRadixWaves = kRadixThreads / kWave;
 
 template <typename K>
 __global__ void __launch_bounds__(kRadixThreads) k_rs_hist(const K* __restrict__ keys, int64_t n, int shift,
-                                                            int32_t* __restrict__ counts, int64_t ntiles) {
+                                                            int32_t* __restrict__ counts, int64_t ntiles,
+                                                            bool by_tile) {
   __shared__ int hist[256];
   hist[threadIdx.x] = 0;
   __syncthreads();
@@ -166,7 +167,8 @@ __global__ void __launch_bounds__(kRadixThreads) k_rs_hist(const K* __restrict__
     if (i < n) atomicAdd(&hist[(int)((keys[i] >> shift) & 255)], 1);
   }
   __syncthreads();
-  counts[(int64_t)threadIdx.x * ntiles + blockIdx.x] = hist[threadIdx.x];
+  counts[by_tile ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)threadIdx.x * ntiles + blockIdx.x] =
+      hist[threadIdx.x];
 }
 
 // Stable scatter of one tile.  Wavefront w owns the tile's elements
@@ -191,9 +193,9 @@ __global__ void __launch_bounds__(kRadixThreads) k_rs_scatter(const K* __restric
     // few tiles: this tile's offsets straight from the counts, thread t for digit t
     __shared__ int s_scan[kRadixWaves];
     int before = 0, all = 0;
-#pragma unroll 8
+#pragma unroll 16
     for (int q = 0; q < (int)ntiles; ++q) {
-      const int c = counts[(int64_t)threadIdx.x * ntiles + q];
+      const int c = counts[q * 256 + (int)threadIdx.x];  // by tile
       before += q < (int)blockIdx.x ? c : 0;
       all += c;
     }
@@ -269,7 +271,8 @@ bool radix_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int64_t 
   K* kout = keys_alt;
   int32_t* vout = vals_alt;
   for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, n, shift, counts, ntiles);
+    hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, n, shift, counts, ntiles,
+                       ntiles <= kFewTiles);
     if (ntiles > kFewTiles) scan_impl<int32_t, int32_t>(counts, offs, 256 * ntiles, stmp, s);
     hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)ntiles), dim3(kRadixThreads), 0, s, kin, vin, n, shift, counts,
                        ntiles > kFewTiles ? offs : nullptr, ntiles, kout, vout);

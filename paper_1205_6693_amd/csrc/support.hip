@@ -47,9 +47,11 @@ __device__ __forceinline__ uint32_t hslot(int32_t c, int logsz) {
   return ((uint32_t)c * 2654435769u) >> (32 - logsz);
 }
 
+constexpr int kFetchGroups = 16;  // draw counters per bin
+
 struct SupCtl {
+  alignas(128) int fetch[kBins][kFetchGroups][32];  // draws of each group of workers (a 128-byte line each)
   int cnt[kBins];    // vertices per bin
-  int fetch[kBins];  // next vertex of the bin to take
   int act[kBins];    // method chosen for the bin
   unsigned long long sd[kBins], sd2[kBins];  // sum of d+ and of d+^2 over the bin
   float feat[kBins][kSupF];                  // the decision's features
@@ -66,7 +68,7 @@ __global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ sta
   }
   if (i < kBins) {
     ctl->cnt[i] = 0;
-    ctl->fetch[i] = 0;
+    for (int g = 0; g < kFetchGroups; ++g) ctl->fetch[i][g][0] = 0;
     ctl->act[i] = (int)(act >> (2 * i)) & 3;
     ctl->sd[i] = 0ULL;
     ctl->sd2[i] = 0ULL;
@@ -408,14 +410,30 @@ __device__ void search_rows(const int* nb, const int* pre, const int* offj, cons
   }
 }
 
-// How the workers of a grid share a bin's list: worker w starts with entries
-// [w * step, (w + 1) * step) and draws further ones from ctl->fetch only while
-// the list is longer than one share each.  An empty bin costs no atomic (1024
-// workgroups drawing from an empty list took 31 us: same-address atomics are
-// served one after another).
+// How the workers of a grid share a bin's list.  The list is dealt out to
+// kFetchGroups groups of workers, entry i to group i mod kFetchGroups; worker w of a
+// group starts with its entries [w * step, (w + 1) * step) and draws further ones
+// from the group's counter, only while the group's entries are more than one share
+// each.  Same-address atomics are served one after another (12-17 ns), so with one
+// counter for all the draws bounded short walks (16 K vertices of 25 out-neighbours:
+// 187 us of draws), and workgroups that drew from an empty list took 31 us to find out.
 struct ListShare {
-  int first, step, count, workers;
+  int group, step, count, workers;  // count, workers: of the group
+  int* fetch;
+  int first;
+  // worker of workers (a multiple of kFetchGroups) on a list of n entries of bin b; most: largest step
+  __device__ __forceinline__ ListShare(SupCtl* ctl, int b, int worker, int of, int n, int most) {
+    group = worker % kFetchGroups;
+    workers = of / kFetchGroups;
+    count = n / kFetchGroups + (group < n % kFetchGroups ? 1 : 0);
+    step = count / (4 * workers);
+    step = step < 1 ? 1 : step > most ? most : step;
+    fetch = &ctl->fetch[b][group][0];
+    first = worker / kFetchGroups * step;
+  }
   __device__ __forceinline__ bool shared() const { return (long long)workers * step < count; }
+  __device__ __forceinline__ int draw() const { return workers * step + atomicAdd(fetch, step); }
+  __device__ __forceinline__ int entry(int j) const { return group + kFetchGroups * j; }
 };
 
 // bin 0, hash: a wavefront per vertex, up to kFetch0 vertices at a time -- fewer
@@ -441,16 +459,11 @@ __global__ void __launch_bounds__(kT) k_sup_hash_wave(const int64_t* __restrict_
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[0]);
   WalkTabs T{s_pre[w], s_offj[w], s_wi[w], s_tab[w], s_cnt[w], s_own[w]};
-  ListShare L;
-  L.count = count;
-  L.workers = (int)gridDim.x * W;
-  L.step = count / (4 * L.workers);
-  L.step = L.step < 1 ? 1 : L.step > kFetch0 ? kFetch0 : L.step;
-  L.first = ((int)blockIdx.x * W + w) * L.step;
-  for (int first = L.first; first < count;) {
-    const int last = first + L.step < count ? first + L.step : count;
+  const ListShare L(ctl, 0, (int)blockIdx.x * W + w, (int)gridDim.x * W, count, kFetch0);
+  for (int first = L.first; first < L.count;) {
+    const int last = first + L.step < L.count ? first + L.step : L.count;
     for (int idx = first; idx < last; ++idx) {
-      const int32_t a = vlist[count - 1 - idx];  // the bin's list backwards: see k_sup_bin
+      const int32_t a = vlist[count - 1 - L.entry(idx)];  // the bin's list backwards: see k_sup_bin
       const int64_t base = orow[a];
       const int d = (int)(orow[a + 1] - base);
       if (lane == 0) s_nrev[w] = 0;
@@ -467,7 +480,7 @@ __global__ void __launch_bounds__(kT) k_sup_hash_wave(const int64_t* __restrict_
       wave_sync();
     }
     if (!L.shared()) break;
-    if (lane == 0) first = L.workers * L.step + atomicAdd(&ctl->fetch[0], L.step);
+    if (lane == 0) first = L.draw();
     first = __shfl(first, 0, kWave);
   }
 }
@@ -494,11 +507,11 @@ __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8, 8))
   const int w = threadIdx.x / kWave;
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
   WalkTabs T{s_pre, s_offj, s_wi, s_tab, s_cnt, s_own[w]};
-  const ListShare L{(int)blockIdx.x, 1, count, (int)gridDim.x};
-  for (int idx = L.first; idx < count;) {
+  const ListShare L(ctl, bin, (int)blockIdx.x, (int)gridDim.x, count, 1);
+  for (int idx = L.first; idx < L.count;) {
     if (threadIdx.x == 0) s_nrev = 0;
     __syncthreads();
-    const int32_t a = vlist[(int64_t)bin * n + (count - 1 - idx)];
+    const int32_t a = vlist[(int64_t)bin * n + (count - 1 - L.entry(idx))];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
     const int nrows = stage_rows<LOGTAB, NTH, MAXD>(orow, ocol, base, d, s_tab, s_nb, s_pre, s_offj, s_wi, s_cnt,
@@ -514,7 +527,7 @@ __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8, 8))
       if (cc) atomicAdd(&supo[base + i], cc);
     }
     if (!L.shared()) break;
-    if (threadIdx.x == 0) s_idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    if (threadIdx.x == 0) s_idx = L.draw();
     __syncthreads();
     idx = s_idx;
     __syncthreads();
@@ -536,9 +549,9 @@ __global__ void __launch_bounds__(kT) k_sup_wave_bs(const int64_t* __restrict__ 
   if (ctl->act[0] != MODE) return;
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[0]);
-  const ListShare L{(int)blockIdx.x * W + w, 1, count, (int)gridDim.x * W};
-  for (int idx = L.first; idx < count;) {
-    const int32_t a = vlist[idx];
+  const ListShare L(ctl, 0, (int)blockIdx.x * W + w, (int)gridDim.x * W, count, 1);
+  for (int idx = L.first; idx < L.count;) {
+    const int32_t a = vlist[L.entry(idx)];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
     const bool valid = lane < d;
@@ -583,7 +596,7 @@ __global__ void __launch_bounds__(kT) k_sup_wave_bs(const int64_t* __restrict__ 
     }
     wave_sync();
     if (!L.shared()) break;
-    if (lane == 0) idx = L.workers + atomicAdd(&ctl->fetch[0], 1);
+    if (lane == 0) idx = L.draw();
     idx = __shfl(idx, 0, kWave);
   }
 }
@@ -600,9 +613,9 @@ __global__ void __launch_bounds__(kT) k_sup_chunked(const int64_t* __restrict__ 
   __shared__ int s_idx;
   if (ctl->act[bin] != kBsearch) return;
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
-  const ListShare L{(int)blockIdx.x, 1, count, (int)gridDim.x};
-  for (int idx = L.first; idx < count;) {
-    const int32_t a = vlist[(int64_t)bin * n + idx];
+  const ListShare L(ctl, bin, (int)blockIdx.x, (int)gridDim.x, count, 1);
+  for (int idx = L.first; idx < L.count;) {
+    const int32_t a = vlist[(int64_t)bin * n + L.entry(idx)];
     const int64_t base = orow[a];
     const int d = (int)(orow[a + 1] - base);
     for (int c0 = 0; c0 < d; c0 += kT) {
@@ -650,7 +663,7 @@ __global__ void __launch_bounds__(kT) k_sup_chunked(const int64_t* __restrict__ 
       __syncthreads();
     }
     if (!L.shared()) break;
-    if (threadIdx.x == 0) s_idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    if (threadIdx.x == 0) s_idx = L.draw();
     __syncthreads();
     idx = s_idx;
     __syncthreads();
@@ -666,9 +679,9 @@ __global__ void __launch_bounds__(kT) k_sup_merge(const int64_t* __restrict__ or
   const int lane = lane_id();
   const int count = atomic_load_relaxed(&ctl->cnt[bin]);
   constexpr int W = kT / kWave;
-  const ListShare L{(int)blockIdx.x * W + (int)(threadIdx.x / kWave), 1, count, (int)gridDim.x * W};
-  for (int idx = L.first; idx < count;) {
-    const int32_t a = vlist[(int64_t)bin * n + idx];
+  const ListShare L(ctl, bin, (int)blockIdx.x * W + (int)(threadIdx.x / kWave), (int)gridDim.x * W, count, 1);
+  for (int idx = L.first; idx < L.count;) {
+    const int32_t a = vlist[(int64_t)bin * n + L.entry(idx)];
     const int64_t base = orow[a], end = orow[a + 1];
     for (int64_t e0 = base; e0 < end; e0 += kWave) {
       const int64_t i = e0 + lane;
@@ -694,7 +707,7 @@ __global__ void __launch_bounds__(kT) k_sup_merge(const int64_t* __restrict__ or
       if (cnt) atomicAdd(&supo[i], cnt);
     }
     if (!L.shared()) break;
-    if (lane == 0) idx = L.workers + atomicAdd(&ctl->fetch[bin], 1);
+    if (lane == 0) idx = L.draw();
     idx = __shfl(idx, 0, kWave);
   }
 }
@@ -755,7 +768,7 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
   for (int b = 0; timed && b <= kBins; ++b)
     if (hipEventCreate(&ev[b]) != hipSuccess) timed = false;
   // persistent-style grids: workers fetch vertices from the bin lists
-  const unsigned gw = 256 * 8, gb = 256 * 4, g2 = 256;
+  const unsigned gw = 256 * 8, gb = 256 * 4, g2 = 256;  // multiples of kFetchGroups
   // A vertex with d out-neighbours, all of them of at least its degree, needs
   // d (d + 1) / 2 edges, so on small graphs the bins of large d are empty and get
   // no kernels.
