@@ -41,14 +41,14 @@ __global__ void k_build_init(RunHead* head, int32_t* __restrict__ deg, int64_t n
 
 // ---- row hash tables (the membership test of Algorithm 2) -----------------------------------
 
-// slots of v's table: the power of two >= 2 deg(v) (0 for an isolated vertex)
+// slots of v's table: the power of two >= 2 deg(v), at least a bucket of four (0 for an isolated vertex)
 __global__ void k_rtab_sizes(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ tsz) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v >= n) return;
   const int64_t d = row_ptr[v + 1] - row_ptr[v];
   int64_t sz = 0;
   if (d > 0) {
-    sz = 2;
+    sz = 4;
     while (sz < 2 * d) sz <<= 1;
   }
   tsz[v] = (int32_t)sz;
@@ -67,13 +67,18 @@ __device__ __forceinline__ void rtab_put(int2* __restrict__ rtab, const int64_t*
   const int64_t off = rtoff[v];
   const int lg = row_table_lg(rtoff[v + 1] - off);
   const uint32_t mask = (1u << lg) - 1u;
-  uint32_t h = row_slot(w, lg);
+  const uint32_t h = row_slot(w, lg);
   // neighbours are distinct and the table is at most half full: a free slot is found
-  while (atomicCAS(&rtab[off + h].x, -1, w) != -1) h = (h + 1) & mask;
-  rtab[off + h].y = e;
+  // the home bucket's slots, its home half first, then the next buckets'
+  for (uint32_t p = 0;; ++p) {
+    const int64_t at = off + (((h + (p & ~3u)) & mask) ^ (p & 3u));
+    if (atomicCAS(&rtab[at].x, -1, w) != -1) continue;
+    rtab[at].y = e;
+    return;
+  }
 }
 
-// capacity bound: 2^ceil(log2(2d)) < 4d for d >= 1, so all tables fit in 8m slots
+// capacity bound: max(4, 2^ceil(log2(2d))) <= 4d for d >= 1, so all tables fit in 8m slots
 inline int64_t rtab_capacity(int64_t m) { return 8 * m + 2; }
 
 // ---- edge-list input ----------------------------------------------------------------
@@ -337,7 +342,7 @@ __global__ void k_csr_sym_check(const int32_t* __restrict__ col_in, const int32_
   const int32_t x = rank[v], y = rank[w];
   if (rtab) {
     const int64_t off = rtoff[x], slots = rtoff[x + 1] - off;
-    if (slots == 0 || row_lookup(rtab, off, row_table_lg(slots), y) < 0) report(err, kErrAsym);
+    if (slots == 0 || row_lookup(rtab + off, row_table_lg(slots), y) < 0) report(err, kErrAsym);
   } else {
     const int32_t a = x < y ? x : y, b = x < y ? y : x;
     const int64_t end = orow[a + 1];

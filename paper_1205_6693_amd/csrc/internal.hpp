@@ -64,7 +64,7 @@ struct DevGraph {
   int32_t* ocol = nullptr;           // m out-neighbours, ascending; entry j is edge j
   int32_t* perm = nullptr;           // m built edge -> caller's edge (null: the same)
   int2* rtab = nullptr;               // row hash tables (neighbour, edge id), back to back
-  const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two)
+  const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two, at least 4)
   void* tmp = nullptr;               // the build's temporaries, free for later phases once it has returned
   size_t tmp_bytes = 0;
 };

@@ -494,9 +494,11 @@ struct WalkTabs {
 // NI adjacency entries of walks, one step at a time for all of them so that
 // their memory accesses are in flight together.  Entry q is position j[q] of
 // the row walked for the frontier record x[q] of W (edge e = (a, b)), valid if
-// ok[q].  Outputs the (up to two) edges per entry whose support crossed
+// ok[q].  HALF: a lookup reads the other half of a bucket only when the home half
+// does not settle it, which costs short rounds a hop through memory and saves
+// long ones accesses.  Outputs the (up to two) edges per entry whose support crossed
 // k-1 -> k-2 and must be enqueued: f1 = (a, w) and f2 = (b, w).
-template <int NI>
+template <int NI, bool HALF>
 __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTabs& W, const int (&x)[NI],
                                                 const uint32_t (&j)[NI], bool (&ok)[NI], int r, int l, int k,
                                                 bool sparse, int probe, int32_t (&w)[NI], int32_t (&f1)[NI],
@@ -530,31 +532,43 @@ __device__ __forceinline__ void process_entries(const PeelArgs& P, const WalkTab
   if (probe == 0) {
     const int2* tb[NI];
     uint32_t h[NI], mask[NI];
-    int2 sl[NI];
+    int4 sa[NI], sb[NI];
 #pragma unroll
-    for (int q = 0; q < NI; ++q) {  // the first slots of all lookups in flight together
+    for (int q = 0; q < NI; ++q) {  // the home buckets of all lookups in flight together
       tb[q] = P.rtab;
       h[q] = 0;
       mask[q] = 0;
-      sl[q] = make_int2(-1, 0);
+      sa[q] = make_int4(-1, 0, -1, 0);
+      sb[q] = sa[q];
       if (ok[q]) {
         const unsigned long long tab = W.tab[x[q]];
         const int lg = (int)(tab & 63);
         tb[q] = P.rtab + (tab >> 6);
         mask[q] = (1u << lg) - 1u;
-        h[q] = row_slot(w[q], lg);
-        sl[q] = tb[q][h[q]];
+        h[q] = row_slot(w[q], lg) & ~1u;
+        sa[q] = *(const int4*)(tb[q] + h[q]);
+        if (!HALF) sb[q] = *(const int4*)(tb[q] + (h[q] ^ 2u));
       }
     }
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
       if (!ok[q]) continue;
-      while (sl[q].x != w[q] && sl[q].x >= 0) {
-        h[q] = (h[q] + 1) & mask[q];
-        sl[q] = tb[q][h[q]];
+      for (;;) {
+        const int4 a = sa[q];
+        if (HALF) {
+          e2[q] = half_find(a, w[q]);
+          if (e2[q] >= 0 || half_open(a)) break;
+          sb[q] = *(const int4*)(tb[q] + (h[q] ^ 2u));
+        }
+        const int4 b = sb[q];
+        if (!HALF) e2[q] = half_find(a, w[q]);
+        if (e2[q] < 0) e2[q] = half_find(b, w[q]);
+        if (e2[q] >= 0 || half_open(a) || half_open(b)) break;
+        h[q] = (h[q] + 4) & mask[q];
+        sa[q] = *(const int4*)(tb[q] + h[q]);
+        if (!HALF) sb[q] = *(const int4*)(tb[q] + (h[q] ^ 2u));
       }
-      e2[q] = sl[q].y;
-      ok[q] = sl[q].x == w[q];
+      ok[q] = e2[q] >= 0;
     }
   } else {
 #pragma unroll
@@ -866,7 +880,7 @@ __device__ __forceinline__ int block_count2(bool p, bool q, int* tmp) {
 
 // NI: walk entries in flight per thread; SU: live-list entries per thread and
 // step of the list phases
-template <int NI, int SU>
+template <int NI, int SU, bool HALF>
 __device__ __forceinline__ void peel_body() {
   static_assert(2 * SU * kT <= kStageQ, "a step's frontier fits beside the last one's");
   // the walking phase and the list phases use the same LDS
@@ -1105,7 +1119,7 @@ __device__ __forceinline__ void peel_body() {
               j[q] = W.base[x_[q]] + (uint32_t)off;
               my_work += __popcll(ballot(ok[q]));
             }
-            process_entries<NI>(P, W, x_, j, ok, r, l, k, sparse, probe, w, f1, f2);
+            process_entries<NI, HALF>(P, W, x_, j, ok, r, l, k, sparse, probe, w, f1, f2);
             if (sparse) {
 #pragma unroll
               for (int q = 0; q < NI; ++q) {
@@ -1132,13 +1146,17 @@ __device__ __forceinline__ void peel_body() {
 }
 
 // The persistent peeling kernel in two shapes over the same state machine:
-// one 1024-thread workgroup per compute unit with four walk entries in flight
+// one 1024-thread workgroup per compute unit with two walk entries in flight
 // per thread, or two workgroups per compute unit (registers capped for eight
-// wavefronts per SIMD) with two entries per thread, which hides more latency
-// when walks are long.  All state lives in global memory between launches.
-__global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<4, 2>(); }
+// wavefronts per SIMD) with one entry per thread, which hides more latency
+// when walks are long.  Entries per thread, measured: narrow 1 / 2 / 3 / 4: 13.2 / 13.3 /
+// 13.8 / 14.3 ms on R-MAT of 1.2 M edges, 90.7 / 83.5 / 85.7 / 87.2 on 15.7 M; wide
+// 1 / 2: 1173 / 1202 ms on R-MAT 23, where two spill.  Buckets read by halves / at once:
+// narrow 86.4 / 83.8 ms on 15.7 M edges, wide 1173 / 1224 on R-MAT 23.  All state lives in global
+// memory between launches.
+__global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<2, 2, false>(); }
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) k_peel_wide(PeelArgs) {
-  peel_body<2, 2>();
+  peel_body<1, 2, true>();
 }
 
 // One bit per edge, set when the edge is removed: the liveness test of the
@@ -1343,7 +1361,8 @@ int g_peel_wide_blocks = -1;  // grid of k_peel_wide (two per compute unit), 0 i
 // TRUSS_SHAPE_AUTO takes the wide shape from this many edges on: there its
 // extra wavefronts hide the latency of long walks in every launch, while on
 // smaller graphs the shorter rounds favour the narrow shape (fewer workgroups
-// at each barrier, more entries in flight per thread).
+// at each barrier, more entries in flight per thread; 1173 against 1470 ms on
+// R-MAT 23, 129 M edges).
 constexpr long long kWideMinEdges = 1LL << 27;
 
 }  // namespace
