@@ -97,9 +97,9 @@ typedef struct truss_graph {
 #define TRUSS_PROBE_BSEARCH 2 /* binary search of the other endpoint's sorted row  */
 
 /* Shape of the persistent peeling kernel (a tuning choice; results are the
- * same): one 1024-thread workgroup per compute unit with four walk entries in
- * flight per thread, or two workgroups per compute unit with two entries per
- * thread (more wavefronts to hide memory latency).  AUTO takes the wide shape
+ * same): one 1024-thread workgroup per compute unit (fewer on small graphs) with
+ * two walk entries in flight per thread, or two workgroups per compute unit with
+ * one entry per thread (more wavefronts to hide memory latency).  AUTO takes the wide shape
  * for graphs of at least 2^27 edges, where it measured faster. */
 #define TRUSS_SHAPE_AUTO 0
 #define TRUSS_SHAPE_NARROW 1

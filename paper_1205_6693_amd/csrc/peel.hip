@@ -30,7 +30,7 @@
 // 36 and 73 us (R-MAT of 15.7 M edges: rounds 110.8 -> 86.4 ms of a call).
 //
 // The level loop runs in a persistent kernel, one 1024-thread workgroup per
-// compute unit.  The grid is never larger than the number of workgroups the
+// compute unit (fewer on small graphs).  The grid is never larger than the number of workgroups the
 // device holds at once (one per compute unit, checked against the occupancy
 // of the kernel before the first launch), so every workgroup is resident and
 // the grid barrier can complete; the launch is an ordinary one on the
@@ -1370,7 +1370,7 @@ int g_peel_wide_blocks = -1;  // grid of k_peel_wide (two per compute unit), 0 i
 // extra wavefronts hide the latency of long walks in every launch, while on
 // smaller graphs the shorter rounds favour the narrow shape (fewer workgroups
 // at each barrier, more entries in flight per thread; 1173 against 1470 ms on
-// R-MAT 23, 129 M edges).
+// R-MAT 23, 161 M edges).
 constexpr long long kWideMinEdges = 1LL << 27;
 
 }  // namespace
