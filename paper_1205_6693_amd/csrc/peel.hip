@@ -82,8 +82,11 @@ constexpr int kStageQ = 16384;  // LDS staging of a list phase's frontier (entri
 // frozen edges start with (2^29) lie below.
 constexpr int kGone = 1 << 30, kGoneMin = 3 << 28;
 
-// The live list is written anew in a sweep once a quarter of its edges are gone.
-constexpr long long kListNum = 3, kListDen = 4;
+// The live list is written anew in a sweep once half of its edges are gone: a sweep
+// reads 4 bytes of list and a line of supports per some edges, a rewrite takes a
+// block scan and an atomic per step.  At 3/4, 1/2, 1/3 and 1/4 left: sweeps 5.48, 4.77,
+// 5.06 and 4.99 ms on R-MAT of 15.7 M edges, 57.4, 48.2, 52.0 ms (3/4 to 1/3) on R-MAT 23.
+constexpr long long kListNum = 1, kListDen = 2;
 
 // A round's walks, laid end to end in queue order, are cut into parts of equal
 // length: one a workgroup while that length lies between kMinChunk and kPartMax
