@@ -16,7 +16,7 @@
 // by its triangle walk: walk the adjacency row of the endpoint with the shorter live row,
 // and look each neighbour w up in the other endpoint's row (hash table or
 // binary search).  Deleted edges are only marked (Section 3.1); the rows are compacted
-// in place whenever the live edge count has fallen below 80 % of their entries.
+// in place whenever the live edge count has fallen below 70 % of their entries.
 //
 // What bounds a round is a chain of dependent memory accesses (about 0.7 us
 // each at the coherent level) up to some 10^6 walk entries, and memory
@@ -69,7 +69,11 @@ constexpr int kT = 1024;
 constexpr int kWaves = kT / kWave;
 constexpr int kIntMax = 0x7fffffff;
 constexpr int kHistBins = 6;
-constexpr long long kCompactNum = 8, kCompactDen = 10;  // row compaction threshold
+// Rows are compacted when the live entries fall to kCompactNum / kCompactDen of those
+// they hold.  With 0.85 / 0.8 / 0.75 / 0.7 (the list as below): 13.7, 13.4, 13.2 and 13.0 ms
+// a call on R-MAT of 1.2 M edges, - / 83.5 / 82.9 / 83.0 on 15.7 M, - / 84.6 / 83.5 / 83.3
+// on Chung-Lu of 15.5 M, 1162 / 1145 / 1152 / 1141 on R-MAT 23.
+constexpr long long kCompactNum = 7, kCompactDen = 10;
 // Rows that hold fewer edges are not compacted any more: the way through the host
 // costs some 60 us, more than walking the removed entries to the end does
 // (G(2000, 0.01), 20 K edges: the call 0.47 -> 0.36 ms, with the waits below).
