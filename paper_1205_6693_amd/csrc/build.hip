@@ -97,7 +97,10 @@ __global__ void k_canon(const int32_t* __restrict__ src, const int32_t* __restri
   val[i] = (int32_t)i;
 }
 
-// and, for the rows, the larger endpoint and the edge id as sort key and value
+// and, for the rows, the larger endpoint and the edge id as sort key and value.
+// Repeats count only in an input without errors so far: pairs that have been
+// set to key 0 repeat that key, and a CSR with too few upper entries is asymmetric
+// (a larger code than a repeat's, so it would be hidden).
 __global__ void k_edges_from_keys(const uint64_t* __restrict__ key, const int32_t* __restrict__ val, int64_t m,
                                   int vb, int32_t* __restrict__ eu, int32_t* __restrict__ ev,
                                   int32_t* __restrict__ perm, uint32_t* __restrict__ tkey,
@@ -105,7 +108,7 @@ __global__ void k_edges_from_keys(const uint64_t* __restrict__ key, const int32_
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
   uint64_t k = key[e];
-  if (e > 0 && key[e - 1] == k) report(err, kErrDup);
+  if (e > 0 && key[e - 1] == k && *err == kNoErr) report(err, kErrDup);
   eu[e] = (int32_t)(k >> vb);
   const int32_t v = (int32_t)(k & ((1ULL << vb) - 1));
   ev[e] = v;
