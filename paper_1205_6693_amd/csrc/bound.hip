@@ -30,7 +30,8 @@ __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)
 // scan from the top finds the largest y with at least y supports >= y.
 __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ seid,
                                                const int32_t* __restrict__ sup, int32_t n, int32_t* __restrict__ h,
-                                               int32_t* __restrict__ ch, int32_t* __restrict__ hs) {
+                                               int32_t* __restrict__ ch, int32_t* __restrict__ hs, const int* err) {
+  if (invalid(err)) return;
   const int lane = lane_id();
   const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
@@ -84,9 +85,10 @@ __global__ void __launch_bounds__(kT) k_hindex(const int64_t* __restrict__ row_p
 
 __global__ void __launch_bounds__(kT) k_psi(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                                             const int32_t* __restrict__ sup, const int32_t* __restrict__ h,
-                                            const int32_t* __restrict__ ch, int64_t m, int32_t* __restrict__ psi) {
+                                            const int32_t* __restrict__ ch, int64_t m, int32_t* __restrict__ psi,
+                                            const int* err) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m) return;
+  if (e >= m || invalid(err)) return;
   const int s = sup[e];
   const int u = eu[e], v = ev[e];
   const int hu = h[u], hv = h[v];
@@ -103,9 +105,9 @@ void compute_upper_bound(const DevGraph& dg, const int32_t* sup, int32_t* h, int
                          hipStream_t s) {
   if (dg.m == 0) return;
   const unsigned gw = 256 * 8;
-  hipLaunchKernelGGL(k_hindex, dim3(gw), dim3(kT), 0, s, dg.row_ptr, dg.seid, sup, dg.n, h, ch, hs);
+  hipLaunchKernelGGL(k_hindex, dim3(gw), dim3(kT), 0, s, dg.row_ptr, dg.seid, sup, dg.n, h, ch, hs, dg.err);
   const int64_t b = (dg.m + kT - 1) / kT;
-  hipLaunchKernelGGL(k_psi, dim3((unsigned)b), dim3(kT), 0, s, dg.eu, dg.ev, sup, h, ch, dg.m, psi);
+  hipLaunchKernelGGL(k_psi, dim3((unsigned)b), dim3(kT), 0, s, dg.eu, dg.ev, sup, h, ch, dg.m, psi, dg.err);
 }
 
 }  // namespace truss

@@ -41,11 +41,12 @@ __global__ void k_build_init(RunHead* head, int32_t* __restrict__ deg, int64_t n
 
 // ---- row hash tables (the membership test of Algorithm 2) -----------------------------------
 
-// slots of v's table: the power of two >= 2 deg(v), at least a bucket of four (0 for an isolated vertex)
-__global__ void k_rtab_sizes(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ tsz) {
+// slots of v's table: the power of two >= 2 deg(v), at least a bucket of four (0 for an
+// isolated vertex, and throughout for an invalid input)
+__global__ void k_rtab_sizes(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ tsz, const int* err) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v >= n) return;
-  const int64_t d = row_ptr[v + 1] - row_ptr[v];
+  const int64_t d = invalid(err) ? 0 : row_ptr[v + 1] - row_ptr[v];
   int64_t sz = 0;
   if (d > 0) {
     sz = 4;
@@ -108,7 +109,7 @@ __global__ void k_edges_from_keys(const uint64_t* __restrict__ key, const int32_
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
   uint64_t k = key[e];
-  if (e > 0 && key[e - 1] == k && *err == kNoErr) report(err, kErrDup);
+  if (e > 0 && key[e - 1] == k && !invalid(err)) report(err, kErrDup);
   eu[e] = (int32_t)(k >> vb);
   const int32_t v = (int32_t)(k & ((1ULL << vb) - 1));
   ev[e] = v;
@@ -144,9 +145,9 @@ __global__ void k_row_bounds(const int32_t* __restrict__ eu, const int32_t* __re
 __global__ void k_sym_upper(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t m,
                             const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ lowpre,
                             int32_t* __restrict__ col, int32_t* __restrict__ seid,
-                            const int64_t* __restrict__ rtoff, int2* __restrict__ rtab) {
+                            const int64_t* __restrict__ rtoff, int2* __restrict__ rtab, const int* err) {
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m) return;
+  if (e >= m || invalid(err)) return;
   int32_t u = eu[e], v = ev[e];
   int64_t pos = lowpre[u + 1] + e;
   col[pos] = v;
@@ -161,9 +162,9 @@ __global__ void k_sym_lower(const uint32_t* __restrict__ tkey, const int32_t* __
                             const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ uppre,
                             const int32_t* __restrict__ eu, int32_t* __restrict__ col,
                             int32_t* __restrict__ seid, const int64_t* __restrict__ rtoff,
-                            int2* __restrict__ rtab) {
+                            int2* __restrict__ rtab, const int* err) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m) return;
+  if (t >= m || invalid(err)) return;
   int32_t e = tval[t];
   int32_t v = (int32_t)tkey[t];
   int32_t u = eu[e];
@@ -240,7 +241,7 @@ __global__ void k_ranks(const int32_t* __restrict__ order, int32_t n, int32_t* _
 // Canonical keys of the relabelled edges.  The input may still turn out to be
 // invalid (its errors are read once, when the build is done): a pair with an id
 // out of range or beyond the *valid pairs there are (nullable) gets key 0, so
-// that everything built from the keys stays in bounds.
+// that the keys can be sorted and searched like any others.
 __global__ void k_canon_relabel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t m,
                                 const int64_t* __restrict__ valid, int32_t n, int vb,
                                 const int32_t* __restrict__ rank, uint64_t* __restrict__ key,
@@ -339,7 +340,7 @@ __global__ void k_csr_sym_check(const int32_t* __restrict__ col_in, const int32_
                                 const int64_t* __restrict__ rtoff, const int64_t* __restrict__ orow,
                                 const int32_t* __restrict__ ocol, int* err) {
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= m2) return;
+  if (j >= m2 || invalid(err)) return;
   const int32_t v = rowid[j], w = col_in[j];
   if (w >= v || w < 0) return;  // (an id out of range is reported by k_csr_check)
   const int32_t x = rank[v], y = rank[w];
@@ -448,8 +449,8 @@ void degree_ranks(const int64_t* row_ptr, const int32_t* deg, int32_t n, int vb,
 }
 
 // sizes, offsets and cleared slots of the row tables for the rows at row_ptr
-void table_layout(const int64_t* row_ptr, int32_t n, int64_t m, Layout& L, hipStream_t s) {
-  hipLaunchKernelGGL(k_rtab_sizes, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, n, L.tsz);
+void table_layout(const int64_t* row_ptr, int32_t n, int64_t m, Layout& L, const int* d_err, hipStream_t s) {
+  hipLaunchKernelGGL(k_rtab_sizes, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, n, L.tsz, d_err);
   scan_exclusive_i32_to_i64(L.tsz, L.rtoff, n, L.stmp, s);
   const int64_t cap = rtab_capacity(m);
   hipLaunchKernelGGL(k_rtab_clear, dim3(grid_for(cap) < 65536 ? grid_for(cap) : 65536), dim3(kT), 0, s, L.rtab,
@@ -481,13 +482,13 @@ void rows_from_keys(int32_t n, int64_t m, int vb, Layout& L, int needs, int* d_e
   if (!rows) return;
   int2* rtab = nullptr;
   if (needs & kBuildTables) {
-    table_layout(L.row_ptr, n, m, L, s);
+    table_layout(L.row_ptr, n, m, L, d_err, s);
     rtab = L.rtab;
   }
   hipLaunchKernelGGL(k_sym_upper, dim3(grid_for(m)), dim3(kT), 0, s, L.eu, L.ev, m, L.row_ptr, L.lowpre, L.col,
-                     L.seid, L.rtoff, rtab);
+                     L.seid, L.rtoff, rtab, d_err);
   hipLaunchKernelGGL(k_sym_lower, dim3(grid_for(m)), dim3(kT), 0, s, tkey, L.val, m, L.row_ptr, L.uppre, L.eu,
-                     L.col, L.seid, L.rtoff, rtab);
+                     L.col, L.seid, L.rtoff, rtab, d_err);
 }
 
 }  // namespace
@@ -592,6 +593,7 @@ int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, RunHead* head, hip
   dg.ev = L.ev;
   dg.rtab = L.rtab;
   dg.rtoff = L.rtoff;
+  dg.err = &head->err;
   if (relabel) return build_relabelled(g, L, dg, vb, head, s, needs, defer);
 
   int* const d_err = &head->err;

@@ -15,6 +15,11 @@ enum : int {
 };
 constexpr int kNoErr = 0x7fffffff;
 
+// Whether an earlier kernel has found the input invalid (err: RunHead::err): one
+// word, the same in all lanes.  Kernels that walk rows or tables test it first,
+// as an invalid input may hold one edge any number of times.
+__device__ __forceinline__ bool invalid(const int* err) { return *err != kNoErr; }
+
 // ---- bump allocator over the caller's workspace --------------------------------
 struct Arena {
   char* base = nullptr;
@@ -65,6 +70,7 @@ struct DevGraph {
   int32_t* perm = nullptr;           // m built edge -> caller's edge (null: the same)
   int2* rtab = nullptr;               // row hash tables (neighbour, edge id), back to back
   const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two, at least 4)
+  const int* err = nullptr;          // RunHead::err, for the kernels that test it (see invalid)
   void* tmp = nullptr;               // the build's temporaries, free for later phases once it has returned
   size_t tmp_bytes = 0;
 };
@@ -93,8 +99,10 @@ enum : int {
   kBuildTables = 4  // with both, relabelled: rtab, rtoff
 };
 // With defer (relabelled builds only) the errors found in the entries are left in
-// head->err for the caller to read with its results: what is built from an invalid
-// input stays in bounds in every later phase.
+// head->err for the caller to read with its results.  Every later kernel that
+// follows the graph's structure tests that word first and does nothing for an
+// invalid input: all bad pairs have become the same edge by then, whose rows, tables
+// and triangles would take time quadratic in their number.
 int build_graph(const truss_graph* g, Arena& a, DevGraph& dg, RunHead* head, hipStream_t s, bool relabel, int needs,
                 bool defer = false);
 int input_error(int err);  // head->err as a return code (message set)
@@ -145,7 +153,8 @@ size_t peel_workspace(const DevGraph& dg, Arena& a);
 int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp, int32_t* truss_canon, Arena& a,
          PeelResult* res, hipStream_t s, truss_trace* trace);
 
-// Upper bound psi(e) (Procedure 6) for every canonical edge from the supports.
+// Upper bound psi(e) (Procedure 6) for every canonical edge from the supports
+// (nothing for an invalid input).
 // h, ch: n entries of scratch each; psi: m entries; hs: 2m + n + 1 entries.
 void compute_upper_bound(const DevGraph& dg, const int32_t* sup, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
                          hipStream_t s);

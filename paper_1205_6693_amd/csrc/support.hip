@@ -79,10 +79,12 @@ __global__ void k_sup_zero(int32_t* __restrict__ supo, int32_t* __restrict__ sta
 // gathered per wavefront, then per workgroup, so each bin counter sees one
 // atomic per workgroup.  A bin's list comes out roughly in id order; with ids
 // ranked by degree, the hash kernels take it backwards, so the vertices with
-// the most pairs start first and the short ones fill the tail.
+// the most pairs start first and the short ones fill the tail.  An invalid input
+// (see build_graph's defer) leaves the bins empty, so that no kernel below has
+// anything to walk.
 constexpr int kBinT = 1024;
 __global__ void __launch_bounds__(kBinT) k_sup_bin(const int64_t* __restrict__ orow, int32_t n,
-                                                   int32_t* __restrict__ vlist, SupCtl* ctl) {
+                                                   int32_t* __restrict__ vlist, SupCtl* ctl, const int* err) {
   __shared__ int s_c[kBins], s_base[kBins];
   __shared__ unsigned long long s_d[kBins], s_d2[kBins];
   if (threadIdx.x < kBins) {
@@ -93,7 +95,7 @@ __global__ void __launch_bounds__(kBinT) k_sup_bin(const int64_t* __restrict__ o
   __syncthreads();
   const int64_t a = blockIdx.x * (int64_t)kBinT + threadIdx.x;
   int d = 0;
-  if (a < n) d = (int)(orow[a + 1] - orow[a]);
+  if (a < n && !invalid(err)) d = (int)(orow[a + 1] - orow[a]);
   int bin = -1;
   if (d >= 2) bin = d <= kWaveMax ? 0 : d <= kBlockMax1 ? 1 : d <= kBlockMax2 ? 2 : 3;
   int local = 0;
@@ -759,7 +761,7 @@ int compute_support(const DevGraph& dg, const SupPlan& plan, int32_t* sup, int32
   hipLaunchKernelGGL(k_sup_zero, dim3(grid_for(m > kBins ? m : kBins)), dim3(kT), 0, s, sup, stamp, m, L.ctl, act);
   if (m == 0) return TRUSS_OK;
   hipLaunchKernelGGL(k_sup_bin, dim3((unsigned)((n + kBinT - 1) / kBinT > 0 ? (n + kBinT - 1) / kBinT : 1)),
-                     dim3(kBinT), 0, s, dg.orow, n, L.vlist, L.ctl);
+                     dim3(kBinT), 0, s, dg.orow, n, L.vlist, L.ctl, dg.err);
   if (trace || known(0) < 0)  // (a trace wants the decision's features)
     hipLaunchKernelGGL(k_sup_decide, dim3(1), dim3(kBins * kWave), 0, s, L.ctl, m, plan.sched, plan.force,
                        plan.model);
