@@ -223,6 +223,17 @@ void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   peel_workspace(dg, a);
 }
 
+// The counters of the upper bound's long rows (2m + n + 1), in the build's temporaries:
+// those hold 2m + 1 and n + 1 eight-byte entries and more besides (relabelled builds).
+int bound_counters(const DevGraph& dg, int32_t** hs) {
+  if (dg.tmp_bytes < sizeof(int32_t) * (size_t)(2 * dg.m + dg.n + 1)) {
+    set_last_error("workspace too small for the upper bound");
+    return TRUSS_E_WORKSPACE;
+  }
+  *hs = static_cast<int32_t*>(dg.tmp);
+  return TRUSS_OK;
+}
+
 struct Timer {
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   bool on = false;
@@ -328,9 +339,8 @@ int run_single(const truss_graph* g, Mode mode, int32_t* out, int64_t* triangles
     }
   } else {
     if (mode == kModeBound) {
-      // the counters of long rows live in the (unused) peeling region
-      int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
-      if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
+      int32_t* hs = nullptr;
+      if ((rc = bound_counters(dg, &hs))) return rc;
       compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
       if (g->m > 0)
         hipLaunchKernelGGL(k_scatter_out, dim3(grid_for(g->m)), dim3(kT), 0, s, p.psi, dg.perm, g->m, out, p.head);
@@ -501,8 +511,8 @@ int run_topdown(const truss_graph* g, int32_t t, int32_t* out, int32_t* kmin_out
   rc = compute_support(dg, sp, p.sup, nullptr, a, s, nullptr);
   if (rc) return rc;
   {
-    int32_t* hs = a.take<int32_t>((size_t)(2 * g->m + g->n + 1));
-    if (a.overflow()) { set_last_error("workspace too small for the upper bound"); return TRUSS_E_WORKSPACE; }
+    int32_t* hs = nullptr;
+    if ((rc = bound_counters(dg, &hs))) return rc;
     compute_upper_bound(dg, p.sup, p.h, p.ch, p.psi, hs, s);
   }
   // the top-down region follows the whole single-graph layout
