@@ -208,8 +208,7 @@ void take_bound(const truss_graph* g, Arena& a, Plan& p) {
 // One layout for size queries and runs: header, build, per-edge state, support, peel.
 void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   p.head = take_head(a);
-  size_t tmp_bytes = 0;
-  build_workspace(g, a, true, &tmp_bytes);
+  build_workspace(g, a, true);
   p.sup = a.take<int32_t>((size_t)g->m + 1);
   p.stamp = a.take<int32_t>((size_t)g->m + 1);
   p.truss_canon = a.take<int32_t>((size_t)g->m + 1);
@@ -218,7 +217,6 @@ void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
   dg.n = g->n;
   dg.m = g->m;
   if (dg_for_sizes) dg = *dg_for_sizes;
-  dg.tmp_bytes = tmp_bytes;
   support_workspace(dg, a);
   peel_workspace(dg, a);
 }

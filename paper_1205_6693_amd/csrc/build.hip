@@ -436,6 +436,9 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
     L.vkey = L.vkey_alt = nullptr;
     L.vval = L.vval_alt = L.vtmp = L.rank = L.vdeg = nullptr;
   }
+  // what the peeling keeps there goes in whole: placed by what happens to fit, the
+  // workspace would shrink where n or m grows a little
+  if (relabel && a.used - L.tmp_at < peel_record_bytes(n, m)) a.used = L.tmp_at + peel_record_bytes(n, m);
   L.tmp_bytes = a.used - L.tmp_at;
 }
 
@@ -507,10 +510,9 @@ int input_error(int h) {
   return -h;
 }
 
-size_t build_workspace(const truss_graph* g, Arena& a, bool relabel, size_t* tmp_bytes) {
+size_t build_workspace(const truss_graph* g, Arena& a, bool relabel) {
   Layout L;
   carve(g, relabel, a, L);
-  if (tmp_bytes) *tmp_bytes = L.tmp_bytes;
   return a.used;
 }
 

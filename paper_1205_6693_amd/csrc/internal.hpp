@@ -71,7 +71,9 @@ struct DevGraph {
   int2* rtab = nullptr;               // row hash tables (neighbour, edge id), back to back
   const int64_t* rtoff = nullptr;    // n+1 offsets of the tables in rtab (slots; sizes are powers of two, at least 4)
   const int* err = nullptr;          // RunHead::err, for the kernels that test it (see invalid)
-  void* tmp = nullptr;               // the build's temporaries, free for later phases once it has returned
+  // The build's temporaries, free for later phases once it has returned; a relabelled
+  // build's hold at least peel_record_bytes.
+  void* tmp = nullptr;
   size_t tmp_bytes = 0;
 };
 
@@ -89,8 +91,7 @@ struct BuildBufs;
 // relabel: vertices renumbered by (degree, id) inside the build (dg.perm then
 // always maps the build's edges to the caller's); off where the caller reads
 // vertex ids back out of dg
-// tmp_bytes (nullable): bytes of the temporaries that later phases may use (DevGraph::tmp)
-size_t build_workspace(const truss_graph* g, Arena& a, bool relabel = false, size_t* tmp_bytes = nullptr);
+size_t build_workspace(const truss_graph* g, Arena& a, bool relabel = false);
 // What a caller reads of the built graph beyond n, m and perm; the rest is not
 // built.  Relabelled builds always give the canonical edges and the oriented CSR.
 enum : int {
@@ -149,6 +150,9 @@ struct PeelResult {
   unsigned long long sup_total = 0;
   double kernel_ms = 0;  // time inside the persistent peeling kernel (all launches)
 };
+// The arena holds the control block and the live lists; the records of the frontiers and
+// vertices and the removed-edge bitmap (peel_record_bytes) lie in dg.tmp.
+size_t peel_record_bytes(int32_t n, int64_t m);
 size_t peel_workspace(const DevGraph& dg, Arena& a);
 int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp, int32_t* truss_canon, Arena& a,
          PeelResult* res, hipStream_t s, truss_trace* trace);

@@ -55,8 +55,6 @@
 // hash table, or a binary search of the other endpoint's sorted row).  The scheduler
 // (plain, a fixed heuristic, or the learned network evaluated by the control
 // wavefront) only picks among these exact methods.
-#include <type_traits>
-
 #include "common.hpp"
 #include "internal.hpp"
 #include "mlp.hpp"
@@ -1337,29 +1335,21 @@ struct PeelLayout {
   unsigned long long* dead;  // removed-edge bitmap for the row compaction
 };
 
-// The records of the frontier queues and the vertices lie in what the build
-// leaves unused (dg.tmp) as far as that reaches, the rest in the arena.
-void carve(const DevGraph& dg, Arena& a, PeelLayout& L) {
-  const int64_t m = dg.m;
-  Arena t;
-  t.base = static_cast<char*>(dg.tmp);
-  t.cap = dg.tmp_bytes;
-  t.counting = a.counting;
-  auto place = [&](auto* type, size_t count) {
-    using T = std::remove_pointer_t<decltype(type)>;
-    const size_t bytes = (count * sizeof(T) + 255) & ~size_t(255);
-    return t.used + bytes <= t.cap ? t.take<T>(count) : a.take<T>(count);
-  };
+void carve(int64_t m, Arena& a, PeelLayout& L) {
   L.ctl = a.take<PeelCtl>(1);
   for (int i = 0; i < 2; ++i) L.alist[i] = a.take<int32_t>(m + 1);
-  L.vinfo = place((VInfo*)nullptr, (size_t)dg.n + 1);
+}
+
+// what lies in the build's temporaries
+void carve_records(int32_t n, int64_t m, Arena& t, PeelLayout& L) {
+  L.vinfo = t.take<VInfo>((size_t)n + 1);
   for (int i = 0; i < 2; ++i) {
-    L.fq[i].pre = place((unsigned long long*)nullptr, (size_t)m + 1);
-    L.fq[i].eb = place((unsigned long long*)nullptr, (size_t)m + 1);
-    L.fq[i].ab = place((unsigned long long*)nullptr, (size_t)m + 1);
-    L.fq[i].tab = place((unsigned long long*)nullptr, (size_t)m + 1);
+    L.fq[i].pre = t.take<unsigned long long>((size_t)m + 1);
+    L.fq[i].eb = t.take<unsigned long long>((size_t)m + 1);
+    L.fq[i].ab = t.take<unsigned long long>((size_t)m + 1);
+    L.fq[i].tab = t.take<unsigned long long>((size_t)m + 1);
   }
-  L.dead = place((unsigned long long*)nullptr, (size_t)(m / kWave + 2));
+  L.dead = t.take<unsigned long long>((size_t)(m / kWave + 2));
 }
 
 // Small graphs take one workgroup per kGridEdges edges, at least kGridMin: fewer start
@@ -1384,15 +1374,27 @@ constexpr long long kWideMinEdges = 1LL << 27;
 
 size_t peel_workspace(const DevGraph& dg, Arena& a) {
   PeelLayout L;
-  carve(dg, a, L);
+  carve(dg.m, a, L);
   return a.used;
+}
+
+size_t peel_record_bytes(int32_t n, int64_t m) {
+  PeelLayout L;
+  Arena t;
+  t.counting = true;
+  carve_records(n, m, t, L);
+  return t.used;
 }
 
 int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp, int32_t* truss_canon, Arena& a, PeelResult* res,
          hipStream_t s, truss_trace* trace) {
   PeelLayout L;
-  carve(dg, a, L);
-  if (a.overflow()) return TRUSS_E_WORKSPACE;
+  carve(dg.m, a, L);
+  Arena t;
+  t.base = static_cast<char*>(dg.tmp);
+  t.cap = dg.tmp_bytes;
+  carve_records(dg.n, dg.m, t, L);
+  if (a.overflow() || t.overflow()) return TRUSS_E_WORKSPACE;
   *res = PeelResult();
   if (dg.m == 0) return TRUSS_OK;
   const long long maxsr = plan.max_subrounds;
