@@ -1320,11 +1320,13 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
   }
 }
 
-// truss numbers in the caller's order (nothing for an invalid input)
+// truss numbers in the caller's order (nothing for an invalid input or a peeling
+// that did not come to its end)
 __global__ void __launch_bounds__(256) k_peel_out(const int32_t* __restrict__ truss, const int32_t* __restrict__ perm,
                                                   int64_t m, int32_t* __restrict__ out, const PeelCtl* c) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e < m && c->input_err == kNoErr) out[perm[e]] = truss[e];
+  const bool done = c->input_err == kNoErr && c->err == 0 && c->bar.abort == 0 && c->phase == PH_DONE;
+  if (e < m && done) out[perm[e]] = truss[e];
 }
 
 struct PeelLayout {
@@ -1457,7 +1459,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   P.tr_act = P.tr_cap > 0 ? trace->level_action : nullptr;
   PeelCtl h;
   // below kCompactMin edges the kernel never returns for a compaction, so the
-  // output can follow it without asking
+  // output can follow it without asking (k_peel_out looks at how it ended)
   const bool once = dg.m < kCompactMin;
   auto output = [&]() {
     hipLaunchKernelGGL(k_peel_out, dim3((unsigned)((dg.m + 255) / 256)), dim3(256), 0, s, truss_canon, plan.perm, dg.m,
@@ -1491,7 +1493,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
   if (ev0) (void)hipEventDestroy(ev0);
   if (ev1) (void)hipEventDestroy(ev1);
   if (h.input_err != kNoErr) return input_error(h.input_err);
-  if (!once && !h.bar.abort && !h.err && h.phase == PH_DONE) {
+  if (!once) {
     output();
     TRUSS_HIP(hipStreamSynchronize(s));
   }
