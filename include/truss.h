@@ -272,7 +272,7 @@ int truss_cohen(const truss_graph *g, int32_t *truss_out, truss_stats *stats, vo
  * vertices).  core_out (device) int32[n], indexed by vertex id in both
  * formats; *cmax_out (host, nullable) = max core(v).  The graph is validated
  * as for truss_decompose.  Workspace from truss_core_workspace_size; the
- * call synchronises the stream (the host steps the peeling levels). */
+ * call synchronises the stream. */
 int truss_core_workspace_size(const truss_graph *g, size_t *bytes);
 int truss_core_numbers(const truss_graph *g, int32_t *core_out, int32_t *cmax_out, void *ws, size_t ws_bytes,
                        void *stream);

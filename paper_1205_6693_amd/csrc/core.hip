@@ -17,6 +17,14 @@
 // bounds it is the number of grid barriers (about 5 us each) and the chain of
 // dependent accesses of a level.  R-MAT 20 (c_max 611): 832 kernel launches with a
 // fence in every workgroup took 30 ms, this one kernel 5.5.
+//
+// Its barriers need every workgroup resident, which the device alone can not
+// promise: beside another persistent kernel (a second call of this one, a
+// peeling) on another stream or of another process, each could hold part of the
+// compute units and wait for the rest.  So the grid first agrees on
+// whether all of it is there, within kAdmitTicks; if not, it ends without having
+// changed anything, and the levels are stepped by ordinary launches, which
+// finish beside anything.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -36,6 +44,11 @@ constexpr int kBudget = 16384;     // row entries a workgroup walks beyond its o
 enum CorePhase : int { kLevel = 0, kRound = 1, kDone = 2 };
 enum CorePub : int { kPubFlags = 0, kPubLevel = 1, kPubHead = 2, kPubTail = 3, kPubCnt = 4, kCorePub = 5 };
 
+enum CoreAdmit : int { kUndecided = 0, kAdmitted = 1, kRefused = 2 };
+// Longest wait for the rest of the grid, in ticks of the 100 MHz clock (0.5 ms): a grid
+// alone on the device is complete within some 20 us.
+constexpr unsigned long long kAdmitTicks = 50000;
+
 struct CoreCounts {  // one phase's counters, by arrival group (a line each) where many workgroups add
   alignas(128) int minv[kGridGroups][32];   // smallest degree of a live vertex left
   alignas(128) int taken[kGridGroups][32];  // vertices claimed
@@ -49,7 +62,31 @@ struct alignas(256) CoreCtl {
   alignas(128) int dead;  // vertices claimed so far
   int cmax;
   int phase;
+  int admit;  // CoreAdmit, changed once
+  alignas(128) unsigned arrived;  // workgroups that have asked for admission
 };
+
+// The stepped form: a sequence of identical launches of one kernel; the state says
+// what a step does.  The last workgroup to finish a step decides the next one, so
+// launches follow each other without a host round trip; the host checks for
+// the end every kStepsPerCheck launches.
+enum StepPhase : int { kStart = 0, kTake = 1, kEnd = 2 };
+
+struct CoreState {
+  int phase;  // kStart: take live vertices of degree <= level; kTake: remove the queue's vertices
+  int level;
+  int cur;    // queue holding the current frontier
+  int qn;     // its length (kTake)
+  int cmax;
+  // counters of the running step, cleared by the workgroup that decides
+  int next;   // vertices appended by this step
+  int alive;  // kStart: live vertices left
+  int minv;   // kStart: their smallest degree
+  unsigned arrived;
+};
+
+constexpr unsigned kStepBlocks = 1024;
+constexpr int kStepsPerCheck = 16;
 
 struct CoreArgs {
   const int64_t* row_ptr;
@@ -68,7 +105,7 @@ inline unsigned blocks(int64_t n) {
 }
 
 __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ deg,
-                            int32_t* __restrict__ core, CoreCtl* c) {
+                            int32_t* __restrict__ core, CoreCtl* c, CoreState* st) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v < n) {
     deg[v] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
@@ -87,7 +124,30 @@ __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int3
     c->dead = 0;
     c->cmax = 0;
     c->phase = kLevel;
+    c->admit = kUndecided;
+    c->arrived = 0;
+    *st = CoreState{kStart, 0, 0, 0, 0, 0, 0, kIntMax, 0u};
   }
+}
+
+// Whether the whole grid is resident, the same answer for every workgroup: the last
+// one to arrive says yes, one that has waited too long says no, and the first to
+// change the word decides.  A workgroup that starts after a no reads it and ends.
+__device__ __forceinline__ bool core_admitted(CoreCtl* c) {
+  __shared__ int s_yes;
+  if (threadIdx.x == 0) {
+    if (ldc(&c->admit) == kUndecided) {
+      if (atomicAdd(&c->arrived, 1u) + 1 == gridDim.x) atomicCAS(&c->admit, kUndecided, kAdmitted);
+      const uint64_t t0 = wall_clock64();
+      while (ldc(&c->admit) == kUndecided) {
+        __builtin_amdgcn_s_sleep(1);
+        if (wall_clock64() - t0 > kAdmitTicks) atomicCAS(&c->admit, kUndecided, kRefused);
+      }
+    }
+    s_yes = ldc(&c->admit) == kAdmitted ? 1 : 0;
+  }
+  __syncthreads();
+  return s_yes != 0;
 }
 
 // A workgroup's claimed vertices (LDS): one list being walked, one being filled.
@@ -227,6 +287,7 @@ __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int le
 __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
   __shared__ CoreLds L;
   CoreCtl* const c = P.ctl;
+  if (!core_admitted(c)) return;
   const int tid = threadIdx.x, lane = lane_id();
   const unsigned g = blockIdx.x % kGridGroups;
   if (tid < 2) L.cnt[tid] = 0;
@@ -363,6 +424,119 @@ __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
   }
 }
 
+__global__ void __launch_bounds__(kT) k_core_step(const int64_t* __restrict__ row_ptr,
+                                                  const int32_t* __restrict__ col, int32_t* __restrict__ deg,
+                                                  int32_t* __restrict__ core, int32_t n, int32_t* __restrict__ q0,
+                                                  int32_t* __restrict__ q1, CoreState* st) {
+  __shared__ int s_min[kT / kWave], s_cnt[kT / kWave];
+  __shared__ int s_last;
+  const int phase = st->phase;  // written by an earlier launch
+  if (phase == kEnd) return;
+  const int level = st->level, cur = st->cur;
+  int32_t* qc = cur ? q1 : q0;
+  int32_t* qx = cur ? q0 : q1;
+  const int lane = lane_id();
+  if (phase == kStart) {
+    // live vertices of degree <= level are taken (core number = level)
+    int dmin = kIntMax, alive = 0;
+    for (int64_t v0 = (int64_t)blockIdx.x * kT; v0 < n; v0 += (int64_t)gridDim.x * kT) {
+      const int64_t v = v0 + threadIdx.x;
+      bool take = false;
+      if (v < n && core[v] < 0) {
+        const int d = deg[v];
+        if (d <= level) {
+          take = true;
+          core[v] = level;
+        } else {
+          dmin = d < dmin ? d : dmin;
+          alive += 1;
+        }
+      }
+      const int pos = wave_append(&st->next, take);
+      if (take) qc[pos] = (int32_t)v;
+    }
+    dmin = wave_min(dmin);
+    alive = wave_sum(alive);
+    const int w = threadIdx.x / kWave;
+    if (lane == 0) {
+      s_min[w] = dmin;
+      s_cnt[w] = alive;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int x = 0, y = kIntMax;
+      for (int i = 0; i < kT / kWave; ++i) {
+        x += s_cnt[i];
+        y = s_min[i] < y ? s_min[i] : y;
+      }
+      if (x) atomicAdd(&st->alive, x);
+      if (y != kIntMax) atomicMin(&st->minv, y);
+    }
+  } else {
+    // every queued vertex removes its edges to live vertices; a neighbour
+    // whose degree falls from level + 1 to level joins the next queue
+    const int qn = st->qn;
+    const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
+    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    for (int64_t i = gw; i < qn; i += nw) {
+      const int32_t v = qc[i];
+      const int64_t rb = row_ptr[v], re = row_ptr[v + 1];
+      for (int64_t j0 = rb; j0 < re; j0 += kWave) {
+        const int64_t j = j0 + lane;
+        bool take = false;
+        int32_t u = 0;
+        if (j < re) {
+          u = col[j];
+          if (__hip_atomic_load(&core[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0) {
+            const int old = atomicSub(&deg[u], 1);
+            if (old == level + 1) {
+              __hip_atomic_store(&core[u], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              take = true;
+            }
+          }
+        }
+        const int pos = wave_append(&st->next, take);
+        if (take) qx[pos] = u;
+      }
+    }
+  }
+  // the last workgroup of the step decides the next one
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    s_last = atomicAdd(&st->arrived, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (s_last && threadIdx.x == 0) {
+    __threadfence();
+    const int next = __hip_atomic_load(&st->next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (phase == kStart) {
+      if (next == 0) {
+        if (__hip_atomic_load(&st->alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+          st->phase = kEnd;
+        } else {
+          // no vertex at this level: the next level is the smallest live degree
+          st->level = __hip_atomic_load(&st->minv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else {
+        st->cmax = level;
+        st->qn = next;
+        st->phase = kTake;
+      }
+    } else if (next == 0) {
+      st->level = level + 1;
+      st->phase = kStart;
+    } else {
+      st->cur = cur ^ 1;
+      st->qn = next;
+    }
+    st->next = 0;
+    st->alive = 0;
+    st->minv = kIntMax;
+    st->arrived = 0;
+  }
+}
+
 // per-vertex degree and triangle sums over a subgraph's edges (sup = support
 // of each subgraph edge inside the subgraph)
 __global__ void k_vertex_sums(const int32_t* __restrict__ su, const int32_t* __restrict__ sv,
@@ -418,16 +592,44 @@ __global__ void __launch_bounds__(1024) k_cc_reduce(const int32_t* __restrict__ 
 size_t core_workspace(int32_t n, Arena& a) {
   for (int i = 0; i < 3; ++i) a.take<int32_t>((size_t)n + 1);
   a.take<CoreCtl>(1);
+  a.take<CoreState>(1);
   return a.used;
+}
+
+// The levels by ordinary launches, from the state that k_core_init has set.
+static int core_steps(const CoreArgs& P, int32_t* q0, int32_t* q1, CoreState* st, int32_t* cmax_out, hipStream_t s) {
+  // a level with takes costs its start, at most one empty start before it and
+  // at most one sub-round per vertex taken: at most 3n + 1 steps in all (a
+  // guard against a stuck loop)
+  const long long max_steps = 4LL * P.n + 2 * kStepsPerCheck;
+  CoreState h;
+  for (long long launched = 0;;) {
+    for (int i = 0; i < kStepsPerCheck; ++i)
+      hipLaunchKernelGGL(k_core_step, dim3(kStepBlocks), dim3(kT), 0, s, P.row_ptr, P.col, P.deg, P.core, P.n, q0, q1,
+                         st);
+    TRUSS_HIP(hipGetLastError());
+    launched += kStepsPerCheck;
+    TRUSS_HIP(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
+    TRUSS_HIP(hipStreamSynchronize(s));
+    if (h.phase == kEnd) break;
+    if (launched > max_steps) {
+      set_last_error("core numbers did not finish within %lld steps", max_steps);
+      return TRUSS_E_INTERNAL;
+    }
+  }
+  *cmax_out = h.cmax;
+  return TRUSS_OK;
 }
 
 int compute_core_numbers(const DevGraph& dg, int32_t* core, int32_t* cmax_out, Arena& a, hipStream_t s) {
   CoreArgs P;
   P.deg = a.take<int32_t>((size_t)dg.n + 1);
   P.queue = a.take<int32_t>((size_t)dg.n + 1);
-  P.list[0] = a.take<int32_t>((size_t)dg.n + 1);
+  int32_t* const second = a.take<int32_t>((size_t)dg.n + 1);  // live list, or the steps' second queue
+  P.list[0] = second;
   P.list[1] = nullptr;
   P.ctl = a.take<CoreCtl>(1);
+  CoreState* const st = a.take<CoreState>(1);
   if (a.overflow()) return TRUSS_E_WORKSPACE;
   // the second live list lies in what the build leaves unused; on a graph of
   // almost only isolated vertices that is too little, and no lists are kept
@@ -443,18 +645,16 @@ int compute_core_numbers(const DevGraph& dg, int32_t* core, int32_t* cmax_out, A
   TRUSS_HIP(hipGetDevice(&dev));
   TRUSS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   TRUSS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void*)k_core, kCoreT, 0));
-  if (occ < 1 || cus < 1) {  // the grid barrier needs every workgroup resident
-    set_last_error("core number kernel does not fit on a compute unit");
-    return TRUSS_E_DEVICE;
-  }
-  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, P.deg, core, P.ctl);
+  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, P.deg, core, P.ctl, st);
+  if (occ < 1 || cus < 1) return core_steps(P, P.queue, second, st, cmax_out, s);
   hipLaunchKernelGGL(k_core, dim3((unsigned)cus), dim3(kCoreT), 0, s, P);
   TRUSS_HIP(hipGetLastError());
   int aborted = 0;
-  int res[2] = {0, 0};  // cmax, phase
+  int res[3] = {0, 0, 0};  // cmax, phase, admit
   TRUSS_HIP(hipMemcpyAsync(&aborted, &P.ctl->bar.abort, sizeof(int), hipMemcpyDeviceToHost, s));
-  TRUSS_HIP(hipMemcpyAsync(res, &P.ctl->cmax, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+  TRUSS_HIP(hipMemcpyAsync(res, &P.ctl->cmax, sizeof(res), hipMemcpyDeviceToHost, s));
   TRUSS_HIP(hipStreamSynchronize(s));
+  if (res[2] != kAdmitted) return core_steps(P, P.queue, second, st, cmax_out, s);
   if (aborted || res[1] != kDone) {
     set_last_error("core number kernel barrier timed out");
     return TRUSS_E_INTERNAL;

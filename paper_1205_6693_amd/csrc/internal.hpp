@@ -163,8 +163,7 @@ int peel(const DevGraph& dg, const PeelPlan& plan, int32_t* sup, int32_t* stamp,
 void compute_upper_bound(const DevGraph& dg, const int32_t* sup, int32_t* h, int32_t* ch, int32_t* psi, int32_t* hs,
                          hipStream_t s);
 
-// Core numbers of every vertex (k-cores); syncs the stream once per peeling
-// step.  core: n entries.  Workspace: core_workspace(n) after the build's.
+// Core numbers of every vertex (k-cores); syncs the stream.  core: n entries.  Workspace: core_workspace(n) after the build's.
 size_t core_workspace(int32_t n, Arena& a);
 int compute_core_numbers(const DevGraph& dg, int32_t* core, int32_t* cmax_out, Arena& a, hipStream_t s);
 // Vertices of degree > 0 in the subgraph given by ms edges (su, sv) and
