@@ -1522,11 +1522,14 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
   auto larger = [&](int32_t a, int32_t b) { return eo[a + 1] - eo[a] > eo[b + 1] - eo[b]; };
   std::stable_sort(B.order.begin(), B.order.end(), larger);
   std::stable_sort(B.compact.begin(), B.compact.end(), larger);
-  // the kernels run one after the other over the same slots
+  // The kernels run one after the other over the same slots.  Their number and size come
+  // from all batched graphs whichever kernel takes them, so that the workspace grows
+  // with the graphs also where one of them passes from one kernel to the other.
   const int maxslots = 4 * device_cus();
-  B.slots = (int)std::min<int64_t>((int64_t)std::max(B.order.size(), B.compact.size()), maxslots);
-  if (!B.order.empty()) B.slot_bytes = slot_bytes_for(B.max_n, B.max_m);
-  if (!B.compact.empty()) B.slot_bytes = std::max(B.slot_bytes, compact_bytes(B.max_cn, B.max_cm));
+  B.slots = (int)std::min<int64_t>((int64_t)(B.order.size() + B.compact.size()), maxslots);
+  const int64_t max_n = std::max(B.max_n, B.max_cn), max_m = std::max(B.max_m, B.max_cm);
+  B.slot_bytes = std::max(slot_bytes_for(max_n, max_m),
+                          compact_bytes(std::min<int64_t>(max_n, kCN), std::min<int64_t>(max_m, kCM)));
   return TRUSS_OK;
 }
 
