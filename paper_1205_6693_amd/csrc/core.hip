@@ -39,7 +39,9 @@ constexpr int kCoreT = 1024;
 constexpr int kCoreWaves = kCoreT / kWave;
 constexpr int kCoreNI = 4;         // row entries in flight per thread
 constexpr int kCoreList = 4096;    // claimed vertices held in LDS
-constexpr int kBudget = 16384;     // row entries a workgroup walks beyond its own level start in a phase
+// Row entries that a workgroup walks in a phase for the vertices of its part of a level
+// start, and as many again for those it claims on the way; the others go to the grid.
+constexpr int kBudget = 16384;
 
 enum CorePhase : int { kLevel = 0, kRound = 1, kDone = 2 };
 enum CorePub : int { kPubFlags = 0, kPubLevel = 1, kPubHead = 2, kPubTail = 3, kPubCnt = 4, kCorePub = 5 };
@@ -184,10 +186,13 @@ __device__ __forceinline__ void core_push(const CoreArgs& P, CoreLds& L, int to,
 }
 
 // Walks the rows of the vertices in list `from` (cnt of them) and claims into the
-// other list.  Returns the row entries walked.
-__device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from, int cnt, int level, int& taken) {
+// other list, up to the kCoreT vertices whose rows would pass `room` entries (kIntMax:
+// all).  Returns the row entries walked; done: the vertices walked.
+__device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from, int cnt, int level, int room,
+                                         int& done, int& taken) {
   const int tid = threadIdx.x, wv = tid / kWave;
   int total = 0;
+  done = 0;
   for (int c0 = 0; c0 < cnt; c0 += kCoreT) {
     int len = 0;
     uint32_t base = 0;
@@ -209,6 +214,8 @@ __device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from
       if (q < wv) off += (uint32_t)L.tmp[q];
       W += (uint32_t)L.tmp[q];
     }
+    if (room != kIntMax && W > (uint32_t)(room - total)) break;
+    done = c0 + n;
     L.pre[tid] = off + inc - (uint32_t)len;
     L.base[tid] = base;
     __syncthreads();
@@ -253,9 +260,13 @@ __device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from
 }
 
 // Walks list 0 and then, in turn, what has been claimed meanwhile, as long as the
-// entries walked beyond the first list stay below kBudget; hands the rest to
-// the queue.  Every thread of the workgroup calls it; both lists are empty on return.
-__device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int level, int& spent, int& taken) {
+// entries stay within kBudget; hands the rest to the queue.  must: list 0 is
+// walked whatever its length (it comes from the queue, cut into equal shares).  A
+// level start's list is cut like the others: where one level takes a whole dense
+// graph, two workgroups would walk all its rows (K_2000: the call 2.4 ms, handed
+// over 0.29).  Every thread of the workgroup calls it; both lists are empty on return.
+__device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int level, bool must, int& spent,
+                                           int& taken) {
   int from = 0;
   bool first = true;
   for (;;) {
@@ -263,19 +274,18 @@ __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int le
     const int cnt = L.cnt[from] < kCoreList ? L.cnt[from] : kCoreList;
     __syncthreads();
     if (cnt == 0) break;
-    if (!first && spent >= kBudget) {
-      if (threadIdx.x == 0) L.at = atomicAdd(&P.ctl->tail, cnt);
-      __syncthreads();
-      for (int i = threadIdx.x; i < cnt; i += kCoreT) stc(&P.queue[L.at + i], L.list[from][i]);
-      __syncthreads();
-      if (threadIdx.x == 0) L.cnt[from] = 0;
-      __syncthreads();
-      break;
-    }
     if (threadIdx.x == 0) L.cnt[from ^ 1] = 0;
     __syncthreads();
-    const int w = core_walk(P, L, from, cnt, level, taken);
-    if (!first) spent = spent < kIntMax - w ? spent + w : kIntMax;
+    const int room = !first ? kBudget - spent : must ? kIntMax : kBudget;
+    int done;
+    const int w = core_walk(P, L, from, cnt, level, room, done, taken);
+    if (done < cnt) {
+      if (threadIdx.x == 0) L.at = atomicAdd(&P.ctl->tail, cnt - done);
+      __syncthreads();
+      for (int i = done + threadIdx.x; i < cnt; i += kCoreT) stc(&P.queue[L.at + i - done], L.list[from][i]);
+      __syncthreads();
+    }
+    if (!first) spent += w;  // at most kBudget
     first = false;
     if (threadIdx.x == 0) L.cnt[from] = 0;
     from ^= 1;
@@ -336,9 +346,9 @@ __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
         __syncthreads();
         const int held = L.cnt[0];
         __syncthreads();  // every thread has read it before the next append
-        if (held > kCoreList - kCoreT) core_drain(P, L, level, spent, taken);
+        if (held > kCoreList - kCoreT) core_drain(P, L, level, false, spent, taken);
       }
-      core_drain(P, L, level, spent, taken);
+      core_drain(P, L, level, false, spent, taken);
     } else {
       // the queue's vertices [head, tail), spread over the workgroups
       const int per = (tail - head + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -348,7 +358,7 @@ __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
         const int n = (int)(q1 - i0 < kCoreList ? q1 - i0 : kCoreList);
         for (int i = tid; i < n; i += kCoreT) L.list[0][i] = ldc(&P.queue[i0 + i]);
         if (tid == 0) L.cnt[0] = n;
-        core_drain(P, L, level, spent, taken);
+        core_drain(P, L, level, true, spent, taken);
       }
     }
     // smallest live degree seen, vertices claimed (taken is the same in a wavefront's lanes)
