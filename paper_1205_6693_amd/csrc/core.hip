@@ -21,10 +21,9 @@
 // Its barriers need every workgroup resident, which the device alone can not
 // promise: beside another persistent kernel (a second call of this one, a
 // peeling) on another stream or of another process, each could hold part of the
-// compute units and wait for the rest.  So the grid first agrees on
-// whether all of it is there, within kAdmitTicks; if not, it ends without having
-// changed anything, and the levels are stepped by ordinary launches, which
-// finish beside anything.
+// compute units and wait for the rest.  So the grid agrees, before its first
+// barrier, on whether all of it is there within kAdmitTicks; if not, it ends,
+// and the levels are stepped by ordinary launches, which finish beside anything.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -39,16 +38,18 @@ constexpr int kCoreT = 1024;
 constexpr int kCoreWaves = kCoreT / kWave;
 constexpr int kCoreNI = 4;         // row entries in flight per thread
 constexpr int kCoreList = 4096;    // claimed vertices held in LDS
-// Row entries that a workgroup walks in a phase for the vertices of its part of a level
-// start, and as many again for those it claims on the way; the others go to the grid.
+// A workgroup walks the vertices it has claimed itself until they come to kBudget row
+// entries in a phase, and no list of more than kListMax: it would take longer than a
+// grid barrier and the queue (kListMax 16384: a graph of 2000 vertices 0.305 -> 0.312 ms,
+// the call on a ring of 1 M vertices of degree 10 3 % slower).
 constexpr int kBudget = 16384;
+constexpr int kListMax = 65536;
 
 enum CorePhase : int { kLevel = 0, kRound = 1, kDone = 2 };
 enum CorePub : int { kPubFlags = 0, kPubLevel = 1, kPubHead = 2, kPubTail = 3, kPubCnt = 4, kCorePub = 5 };
 
 enum CoreAdmit : int { kUndecided = 0, kAdmitted = 1, kRefused = 2 };
-// Longest wait for the rest of the grid, in ticks of the 100 MHz clock (0.5 ms): a grid
-// alone on the device is complete within some 20 us.
+// Longest wait for the rest of the grid, in ticks of the 100 MHz clock (0.5 ms).
 constexpr unsigned long long kAdmitTicks = 50000;
 
 struct CoreCounts {  // one phase's counters, by arrival group (a line each) where many workgroups add
@@ -134,17 +135,19 @@ __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int3
 
 // Whether the whole grid is resident, the same answer for every workgroup: the last
 // one to arrive says yes, one that has waited too long says no, and the first to
-// change the word decides.  A workgroup that starts after a no reads it and ends.
+// change the word decides.  A workgroup arrives as it starts (core_arrive, one
+// thread) and asks after its first phase, when the others have long arrived: asked at
+// once, the answer took 8 us.
+__device__ __forceinline__ void core_arrive(CoreCtl* c) {
+  if (atomicAdd(&c->arrived, 1u) + 1 == gridDim.x) atomicCAS(&c->admit, kUndecided, kAdmitted);
+}
 __device__ __forceinline__ bool core_admitted(CoreCtl* c) {
   __shared__ int s_yes;
   if (threadIdx.x == 0) {
-    if (ldc(&c->admit) == kUndecided) {
-      if (atomicAdd(&c->arrived, 1u) + 1 == gridDim.x) atomicCAS(&c->admit, kUndecided, kAdmitted);
-      const uint64_t t0 = wall_clock64();
-      while (ldc(&c->admit) == kUndecided) {
-        __builtin_amdgcn_s_sleep(1);
-        if (wall_clock64() - t0 > kAdmitTicks) atomicCAS(&c->admit, kUndecided, kRefused);
-      }
+    const uint64_t t0 = wall_clock64();
+    while (ldc(&c->admit) == kUndecided) {
+      __builtin_amdgcn_s_sleep(1);
+      if (wall_clock64() - t0 > kAdmitTicks) atomicCAS(&c->admit, kUndecided, kRefused);
     }
     s_yes = ldc(&c->admit) == kAdmitted ? 1 : 0;
   }
@@ -259,12 +262,12 @@ __device__ __forceinline__ int core_walk(const CoreArgs& P, CoreLds& L, int from
   return total;
 }
 
-// Walks list 0 and then, in turn, what has been claimed meanwhile, as long as the
-// entries stay within kBudget; hands the rest to the queue.  must: list 0 is
-// walked whatever its length (it comes from the queue, cut into equal shares).  A
-// level start's list is cut like the others: where one level takes a whole dense
-// graph, two workgroups would walk all its rows (K_2000: the call 2.4 ms, handed
-// over 0.29).  Every thread of the workgroup calls it; both lists are empty on return.
+// Walks list 0 and then, in turn, what has been claimed meanwhile, within kBudget
+// and kListMax; hands the rest to the queue.  must: list 0 is walked whatever its
+// length (it comes from the queue, cut into equal shares, or is full, and then the
+// other workgroups' are, too).  Otherwise a level start's list is cut like the
+// others: where one level takes a whole dense graph, two workgroups would walk all
+// its rows (K_2000: the call 2.4 ms, handed over 0.29).  Every thread of the workgroup calls it; both lists are empty on return.
 __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int level, bool must, int& spent,
                                            int& taken) {
   int from = 0;
@@ -276,7 +279,7 @@ __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int le
     if (cnt == 0) break;
     if (threadIdx.x == 0) L.cnt[from ^ 1] = 0;
     __syncthreads();
-    const int room = !first ? kBudget - spent : must ? kIntMax : kBudget;
+    const int room = first && must ? kIntMax : spent < kBudget ? kListMax : 0;
     int done;
     const int w = core_walk(P, L, from, cnt, level, room, done, taken);
     if (done < cnt) {
@@ -285,7 +288,7 @@ __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int le
       for (int i = done + threadIdx.x; i < cnt; i += kCoreT) stc(&P.queue[L.at + i - done], L.list[from][i]);
       __syncthreads();
     }
-    if (!first) spent += w;  // at most kBudget
+    if (!first) spent += w;
     first = false;
     if (threadIdx.x == 0) L.cnt[from] = 0;
     from ^= 1;
@@ -297,8 +300,8 @@ __device__ __forceinline__ void core_drain(const CoreArgs& P, CoreLds& L, int le
 __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
   __shared__ CoreLds L;
   CoreCtl* const c = P.ctl;
-  if (!core_admitted(c)) return;
   const int tid = threadIdx.x, lane = lane_id();
+  if (tid == 0) core_arrive(c);
   const unsigned g = blockIdx.x % kGridGroups;
   if (tid < 2) L.cnt[tid] = 0;
   __syncthreads();
@@ -346,7 +349,7 @@ __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
         __syncthreads();
         const int held = L.cnt[0];
         __syncthreads();  // every thread has read it before the next append
-        if (held > kCoreList - kCoreT) core_drain(P, L, level, false, spent, taken);
+        if (held > kCoreList - kCoreT) core_drain(P, L, level, true, spent, taken);
       }
       core_drain(P, L, level, false, spent, taken);
     } else {
@@ -376,6 +379,7 @@ __global__ void __launch_bounds__(kCoreT) k_core(CoreArgs P) {
       for (int q = 1; q < kCoreWaves; ++q) taken += L.tmp[q];
       if (taken) atomicAdd(&w->taken[g][0], taken);
     }
+    if (gen == 1 && !core_admitted(c)) return;
     const bool ok = grid_barrier<kCorePub>(&c->bar, gen, L.pub, [&](auto release) {
       const int q = lane < kGridGroups ? lane : 0;
       const int mv = ldc(&w->minv[q][0]), tk = lane < kGridGroups ? ldc(&w->taken[q][0]) : 0;
@@ -606,8 +610,10 @@ size_t core_workspace(int32_t n, Arena& a) {
   return a.used;
 }
 
-// The levels by ordinary launches, from the state that k_core_init has set.
+// The levels by ordinary launches.
 static int core_steps(const CoreArgs& P, int32_t* q0, int32_t* q1, CoreState* st, int32_t* cmax_out, hipStream_t s) {
+  // (a refused grid may have taken vertices)
+  hipLaunchKernelGGL(k_core_init, dim3(blocks(P.n)), dim3(kT), 0, s, P.row_ptr, P.n, P.deg, P.core, P.ctl, st);
   // a level with takes costs its start, at most one empty start before it and
   // at most one sub-round per vertex taken: at most 3n + 1 steps in all (a
   // guard against a stuck loop)
@@ -655,8 +661,8 @@ int compute_core_numbers(const DevGraph& dg, int32_t* core, int32_t* cmax_out, A
   TRUSS_HIP(hipGetDevice(&dev));
   TRUSS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   TRUSS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void*)k_core, kCoreT, 0));
-  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, P.deg, core, P.ctl, st);
   if (occ < 1 || cus < 1) return core_steps(P, P.queue, second, st, cmax_out, s);
+  hipLaunchKernelGGL(k_core_init, dim3(blocks(dg.n)), dim3(kT), 0, s, dg.row_ptr, dg.n, P.deg, core, P.ctl, st);
   hipLaunchKernelGGL(k_core, dim3((unsigned)cus), dim3(kCoreT), 0, s, P);
   TRUSS_HIP(hipGetLastError());
   int aborted = 0;
