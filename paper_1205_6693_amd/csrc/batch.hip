@@ -37,20 +37,18 @@ constexpr int64_t kBatchMaxM = 1 << 21;  // larger graphs take the device-wide p
 constexpr int64_t kBatchMaxN = 1 << 22;
 
 struct BatchCtl {
-  int next;        // queue head (general kernel)
+  int next;        // queue head
   int err_g;       // smallest failing graph index
   int kmax;
-  int next_compact;  // queue head (compact kernel)
+  int pad;
   unsigned long long levels, subrounds, triangles3;
   unsigned long long sup_work, peel_work;  // row entries walked (support, peeling)
   unsigned long long t_phase[3];            // workgroup time in CSR build, support, peeling (10 ns ticks)
 };
 
 struct BatchArgs {
-  int G;                   // graphs in the general kernel's queue
-  const int32_t* order;    // that queue: graph ids, largest first
-  int Gc;                  // the same of the compact kernel
-  const int32_t* order_c;
+  int G;                   // graphs in the queue
+  const int32_t* order;    // queue: graph ids, longest first
   const int64_t* vo;       // G+1 vertex offsets (device copy)
   const int64_t* eo;       // G+1 edge offsets (device copy)
   const int32_t* src;
@@ -59,7 +57,7 @@ struct BatchArgs {
   int32_t* gerr;           // per graph status
   char* scratch;
   size_t slot_bytes;
-  int32_t max_n;
+  int32_t max_n;           // largest sizes of the graphs that process_graph takes
   int64_t max_m;
   BatchCtl* ctl;
 };
@@ -728,6 +726,7 @@ __global__ void __launch_bounds__(T) k_batch(BatchArgs A) {
 // (tables probed slot by slot 115, by buckets of four 98; with the starts of the
 // walks searched for every entry 98).
 constexpr int kCN = 1 << 13, kCM = 1 << 18;
+__host__ __device__ inline bool is_compact(int64_t n, int64_t m) { return m <= kCM && n <= kCN; }
 constexpr int kIdBits = 18, kNbShift = 19;
 constexpr uint32_t kIdMask = (1u << kIdBits) - 1u;
 constexpr uint32_t kNoSlot = 0xffffffffu;   // its id field is no edge's (ids are below 2^18)
@@ -1408,12 +1407,37 @@ __global__ void __launch_bounds__(T) k_batch_compact(BatchArgs A) {
   extern __shared__ __align__(16) char lds[];
   __shared__ CompactCtl<T> C;
   for (;;) {
-    if (threadIdx.x == 0) C.g = atomicAdd(&A.ctl->next_compact, 1);
+    if (threadIdx.x == 0) C.g = atomicAdd(&A.ctl->next, 1);
     __syncthreads();
     const int gi = C.g;
-    if (gi >= A.Gc) break;
-    process_compact<T, NI>(A, A.order_c[gi], A.scratch + (size_t)blockIdx.x * A.slot_bytes, lds, C);
+    if (gi >= A.G) break;
+    process_compact<T, NI>(A, A.order[gi], A.scratch + (size_t)blockIdx.x * A.slot_bytes, lds, C);
     __syncthreads();
+  }
+}
+
+// Graphs of both kinds from one queue, so that the small ones fill the compute units
+// that the longest large one leaves idle: one kernel after the other took 55.8 ms for
+// 300 graphs of 9000 vertices and 256 of up to 8192, where one queue takes 41.6.
+// Alone, each kind keeps its own kernel, with its own registers and LDS.  A workgroup's
+// first graph is that of its number, so that the longest ones run on
+// different XCDs (drawn, they went to the workgroups that started first, on a few XCDs:
+// 16 graphs of 290 K edges and 600 tiny ones 335 -> 365-410 ms).
+template <int T, int NI>
+__global__ void __launch_bounds__(T) k_batch_mixed(BatchArgs A) {
+  extern __shared__ __align__(16) char lds[];
+  __shared__ CompactCtl<T> C;
+  const Slot S = slot_at(A, blockIdx.x);
+  for (int gi = blockIdx.x; gi < A.G;) {
+    const int g = A.order[gi];
+    if (is_compact(A.vo[g + 1] - A.vo[g], A.eo[g + 1] - A.eo[g]))
+      process_compact<T, NI>(A, g, A.scratch + (size_t)blockIdx.x * A.slot_bytes, lds, C);
+    else
+      process_graph<T, NI>(A, S, g, *reinterpret_cast<Lds<T>*>(lds));
+    __syncthreads();
+    if (threadIdx.x == 0) C.g = (int)gridDim.x + atomicAdd(&A.ctl->next, 1);
+    __syncthreads();
+    gi = C.g;
   }
 }
 
@@ -1424,7 +1448,6 @@ __global__ void k_batch_init(BatchCtl* c, int32_t* gerr, int G) {
   if (i < G) gerr[i] = 1;
   if (i == 0) {
     c->next = 0;
-    c->next_compact = 0;
     c->err_g = kIntMax;
     c->kmax = 0;
     c->levels = 0;
@@ -1438,21 +1461,16 @@ __global__ void k_batch_init(BatchCtl* c, int32_t* gerr, int G) {
 
 using BatchKernel = void (*)(BatchArgs);
 
-BatchKernel batch_kernel(int T, int NI) {
-#define TRUSS_BK(t, g) \
-  if (T == t && NI == g) return &k_batch<t, g>;
-  TRUSS_BK(256, 1) TRUSS_BK(256, 2) TRUSS_BK(256, 4)
-  TRUSS_BK(512, 1) TRUSS_BK(512, 2) TRUSS_BK(512, 4)
-  TRUSS_BK(1024, 1) TRUSS_BK(1024, 2) TRUSS_BK(1024, 4)
-#undef TRUSS_BK
-  return nullptr;
-}
+enum Kind { kGeneral = 0, kCompact = 1, kMixed = 2 };  // what a batch holds
 
-BatchKernel compact_kernel(int T, int NI, int64_t n, int64_t m, size_t* lds) {
-#define TRUSS_BK(t, g)                 \
-  if (T == t && NI == g) {             \
-    *lds = compact_lds<t>(n, m);       \
-    return &k_batch_compact<t, g>;     \
+// the kernel for a shape (null if it is not built) and its dynamic LDS for
+// compact graphs of up to n vertices and m edges
+BatchKernel batch_kernel(int T, int NI, Kind kind, int64_t n, int64_t m, size_t* lds) {
+#define TRUSS_BK(t, g)                                                              \
+  if (T == t && NI == g) {                                                          \
+    *lds = kind == kGeneral ? 0 : compact_lds<t>(n, m);                             \
+    if (kind == kMixed && *lds < sizeof(Lds<t>)) *lds = sizeof(Lds<t>);             \
+    return kind == kGeneral ? &k_batch<t, g> : kind == kCompact ? &k_batch_compact<t, g> : &k_batch_mixed<t, g>; \
   }
   TRUSS_BK(256, 1) TRUSS_BK(256, 2) TRUSS_BK(256, 4)
   TRUSS_BK(512, 1) TRUSS_BK(512, 2) TRUSS_BK(512, 4)
@@ -1470,12 +1488,13 @@ int device_cus() {
   return cus;
 }
 
-// The batch split: graphs for the two persistent kernels (largest first) and
-// graphs for the device-wide path; scratch shapes.
+// The batch split: graphs for the persistent kernel (longest first) and graphs
+// for the device-wide path; scratch shapes.
 struct BatchSplit {
-  std::vector<int32_t> order, compact, big;
-  int64_t max_n = 0, max_m = 0;    // general kernel
-  int64_t max_cn = 0, max_cm = 0;  // compact kernel
+  std::vector<int32_t> order, big;
+  bool general = false, compact = false;  // kinds among the order
+  int64_t max_n = 0, max_m = 0;           // of each kind
+  int64_t max_cn = 0, max_cm = 0;
   int slots = 0;
   size_t slot_bytes = 0, big_ws = 0;
 };
@@ -1497,12 +1516,14 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
       set_last_error("graph %d has more than INT32_MAX edges", i);
       return TRUSS_E_TOOBIG;
     }
-    if (m <= kCM && n <= kCN) {
-      B.compact.push_back(i);
+    if (is_compact(n, m)) {
+      B.order.push_back(i);
+      B.compact = true;
       B.max_cn = std::max(B.max_cn, n);
       B.max_cm = std::max(B.max_cm, m);
     } else if (m <= kBatchMaxM && n <= kBatchMaxN) {
       B.order.push_back(i);
+      B.general = true;
       B.max_n = std::max(B.max_n, n);
       B.max_m = std::max(B.max_m, m);
     } else {
@@ -1519,14 +1540,16 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
       B.big_ws = std::max(B.big_ws, b);
     }
   }
-  auto larger = [&](int32_t a, int32_t b) { return eo[a + 1] - eo[a] > eo[b + 1] - eo[b]; };
-  std::stable_sort(B.order.begin(), B.order.end(), larger);
-  std::stable_sort(B.compact.begin(), B.compact.end(), larger);
-  // The kernels run one after the other over the same slots.  Their number and size come
-  // from all batched graphs whichever kernel takes them, so that the workspace grows
-  // with the graphs also where one of them passes from one kernel to the other.
+  // a compact graph takes about a quarter of the time of a general one of as many edges
+  auto cost = [&](int32_t g) {
+    const int64_t m = eo[g + 1] - eo[g];
+    return is_compact(vo[g + 1] - vo[g], m) ? m : 4 * m;
+  };
+  std::stable_sort(B.order.begin(), B.order.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+  // The slots' size comes from all batched graphs whatever their kind, so that the
+  // workspace grows with the graphs also where one passes from one kind to the other.
   const int maxslots = 4 * device_cus();
-  B.slots = (int)std::min<int64_t>((int64_t)(B.order.size() + B.compact.size()), maxslots);
+  B.slots = (int)std::min<int64_t>((int64_t)B.order.size(), maxslots);
   const int64_t max_n = std::max(B.max_n, B.max_cn), max_m = std::max(B.max_m, B.max_cm);
   B.slot_bytes = std::max(slot_bytes_for(max_n, max_m),
                           compact_bytes(std::min<int64_t>(max_n, kCN), std::min<int64_t>(max_m, kCM)));
@@ -1559,14 +1582,19 @@ size_t batch_layout(int32_t G, const BatchSplit& B, char* base, BatchLayout* L) 
 }
 
 int check_cfg(int T, int G) {
-  if (!batch_kernel(T, G)) {
+  size_t lds = 0;
+  if (!batch_kernel(T, G, kGeneral, 0, 0, &lds)) {
     set_last_error("batch shape %d threads x %d walk entries per thread is not built", T, G);
     return TRUSS_E_INVAL;
   }
   return TRUSS_OK;
 }
 
-int launch_one(const BatchArgs& A, BatchKernel k, int T, size_t lds, int slots, hipStream_t s) {
+// The persistent kernel over the queue, for the kinds of graphs in the batch.
+int launch_batch(const BatchArgs& A, const BatchSplit& B, int T, int G, hipStream_t s) {
+  const Kind kind = !B.compact ? kGeneral : B.general ? kMixed : kCompact;
+  size_t lds = 0;
+  const BatchKernel k = batch_kernel(T, G, kind, B.max_cn, B.max_cm, &lds);
   int occ = 0;
   if (lds > 0)
     TRUSS_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1575,22 +1603,10 @@ int launch_one(const BatchArgs& A, BatchKernel k, int T, size_t lds, int slots, 
     set_last_error("batch kernel does not fit on a compute unit");
     return TRUSS_E_DEVICE;
   }
-  const int grid = std::max(1, std::min(slots, occ * device_cus()));
+  const int grid = std::max(1, std::min(std::min(A.G, B.slots), occ * device_cus()));
   BatchArgs a = A;
   void* args[] = {&a};
   TRUSS_HIP(hipLaunchKernel((const void*)k, dim3(grid), dim3(T), args, lds, s));
-  return TRUSS_OK;
-}
-
-// The kernels of the queues that hold graphs (A.G, A.Gc); B for the shapes.
-int launch_batch(const BatchArgs& A, const BatchSplit& B, int T, int G, hipStream_t s) {
-  if (A.Gc > 0) {
-    size_t lds = 0;
-    BatchKernel k = compact_kernel(T, G, B.max_cn, B.max_cm, &lds);
-    const int rc = launch_one(A, k, T, lds, std::min(A.Gc, B.slots), s);
-    if (rc) return rc;
-  }
-  if (A.G > 0) return launch_one(A, batch_kernel(T, G), T, 0, std::min(A.G, B.slots), s);
   return TRUSS_OK;
 }
 
@@ -1716,14 +1732,11 @@ int plan_build(int32_t G, const int64_t* vo, const int64_t* eo, const int32_t* s
   p->src = src;
   p->dst = dst;
   p->out = out;
-  // one device array: the general queue, then the compact one
-  std::vector<int32_t> queue(p->split.order);
-  queue.insert(queue.end(), p->split.compact.begin(), p->split.compact.end());
-  const int Q = (int)queue.size();
+  const int Q = (int)p->split.order.size();
   if (G > 0) {
     if (hipMemcpyAsync(p->lay.vo, vo, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(p->lay.eo, eo, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
-        (Q > 0 && hipMemcpyAsync(p->lay.order, queue.data(), sizeof(int32_t) * Q, hipMemcpyHostToDevice,
+        (Q > 0 && hipMemcpyAsync(p->lay.order, p->split.order.data(), sizeof(int32_t) * Q, hipMemcpyHostToDevice,
                                  s) != hipSuccess) ||
         hipStreamSynchronize(s) != hipSuccess) {
       set_last_error("copying the batch offsets failed");
@@ -1732,10 +1745,8 @@ int plan_build(int32_t G, const int64_t* vo, const int64_t* eo, const int32_t* s
     }
   }
   BatchArgs& A = p->args;
-  A.G = (int)p->split.order.size();
+  A.G = Q;
   A.order = p->lay.order;
-  A.Gc = (int)p->split.compact.size();
-  A.order_c = p->lay.order + p->split.order.size();
   A.vo = p->lay.vo;
   A.eo = p->lay.eo;
   A.src = src;
@@ -1854,16 +1865,12 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   truss_batch_plan* p = nullptr;
   int rc = plan_build(num_graphs, vtx_off, edge_off, src, dst, truss_out, opts, ws, ws_bytes, s, false, &p);
   if (rc) return rc;
-  // a stratified sample of each queue: every stride-th graph in size order
+  // a stratified sample of the queue: every stride-th graph in its order
+  const std::vector<int32_t>& q = p->split.order;
   const int want = 512;
-  const size_t all = p->split.order.size() + p->split.compact.size();
-  const size_t stride = all > (size_t)want ? all / want : 1;
-  auto pick = [&](const std::vector<int32_t>& q, std::vector<int32_t>& to) {
-    for (size_t i = 0; i < q.size(); i += stride) to.push_back(q[i]);
-    return (int)((q.size() + stride - 1) / stride);
-  };
   std::vector<int32_t> sample;
-  const int sg = pick(p->split.order, sample), sc = pick(p->split.compact, sample);
+  const size_t stride = q.size() > (size_t)want ? q.size() / want : 1;
+  for (size_t i = 0; i < q.size(); i += stride) sample.push_back(q[i]);
   *best_block = kDefaultT;
   *best_ilp = kDefaultG;
   if (best_ms) *best_ms = 0.f;
@@ -1874,12 +1881,10 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   hipEvent_t e0 = nullptr, e1 = nullptr;
   TRUSS_HIP(hipEventCreate(&e0));
   TRUSS_HIP(hipEventCreate(&e1));
-  // time one shape on the queues on the device: gen general graphs, then cmp compact ones
-  auto time_shape = [&](int T, int Gl, int gen, int cmp, int reps, float* ms) -> int {
+  // time one shape on the first `count` queue entries (order already on the device)
+  auto time_shape = [&](int T, int Gl, int count, int reps, float* ms) -> int {
     BatchArgs A = p->args;
-    A.G = gen;
-    A.Gc = cmp;
-    A.order_c = A.order + gen;
+    A.G = count;
     float t = 0.f;
     for (int rep = 0; rep < reps; ++rep) {
       hipLaunchKernelGGL(k_batch_init, dim3((unsigned)((num_graphs + 256) / 256)), dim3(256), 0, s, p->lay.ctl,
@@ -1902,21 +1907,18 @@ int truss_batch_autotune(int32_t num_graphs, const int64_t* vtx_off, const int64
   for (int ti = 0; ti < 3 && !rc; ++ti)
     for (int gi = 0; gi < 3 && !rc; ++gi) {
       float t = 0.f;
-      rc = time_shape(Ts[ti], Gs[gi], sg, sc, 2, &t);
+      rc = time_shape(Ts[ti], Gs[gi], (int)sample.size(), 2, &t);
       if (!rc) cands.push_back({t, Ts[ti], Gs[gi]});
     }
-  // stage 2: the three fastest on the whole queues, where the largest graphs
+  // stage 2: the three fastest on the whole queue, where the largest graphs
   // (which set the tail) count at their full weight
   float best = -1.f;
   if (!rc) {
     std::sort(cands.begin(), cands.end(), [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
-    std::vector<int32_t> queue(p->split.order);
-    queue.insert(queue.end(), p->split.compact.begin(), p->split.compact.end());
-    TRUSS_HIP(hipMemcpyAsync(p->lay.order, queue.data(), sizeof(int32_t) * queue.size(), hipMemcpyHostToDevice, s));
-    TRUSS_HIP(hipStreamSynchronize(s));  // queue leaves scope
+    TRUSS_HIP(hipMemcpyAsync(p->lay.order, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice, s));
     for (size_t c = 0; c < cands.size() && c < 3 && !rc; ++c) {
       float t = 0.f;
-      rc = time_shape(cands[c].T, cands[c].G, (int)p->split.order.size(), (int)p->split.compact.size(), 1, &t);
+      rc = time_shape(cands[c].T, cands[c].G, (int)q.size(), 1, &t);
       if (!rc && (best < 0.f || t < best)) {
         best = t;
         *best_block = cands[c].T;
