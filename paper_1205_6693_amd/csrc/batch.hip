@@ -732,6 +732,13 @@ constexpr uint32_t kIdMask = (1u << kIdBits) - 1u;
 constexpr uint32_t kNoSlot = 0xffffffffu;   // its id field is no edge's (ids are below 2^18)
 constexpr int kBits = kCN / 32;             // words of a bitmap over the vertices
 constexpr int kMaxOut = 1024;               // out-degrees are at most sqrt(2 m) < 725
+// A wavefront spends some 2 us on a row however short, in each of the three passes over
+// the rows, so rows of up to kThreadRow entries are a thread's work and those of up to
+// kGroupRow a quarter wavefront's.  Ids rise with the degree, so each kind is a range of
+// ids.  G(8192, m) of mean degree 4 and 8, one graph: 2.95 and 3.75 ms by wavefronts alone,
+// 0.97 and 2.05 so (general kernel 1.80 and 2.80); of 16, 5.5 and 5.0 (5.8).
+constexpr int kThreadRow = 4, kGroupRow = 16;
+static_assert(kWave % kGroupRow == 0, "groups of lanes");
 
 struct CompactSlot {
   uint32_t *rp, *len, *tab, *up;  // row offset, live length, table (offset << 4 | log2 slots), first edge id
@@ -802,6 +809,7 @@ template <int T>
 struct CompactCtl {  // static LDS
   int tmp[T / kWave + 2];
   int err, next, g, cnt, qn, minv;
+  int nthread, ngroup;  // first row of more than kThreadRow entries, of more than kGroupRow
 };
 
 // inclusive sum over the workgroup; *total
@@ -856,6 +864,21 @@ __device__ __forceinline__ uint32_t bucket_of(int w, int lg) {
   return lg == 2 ? 0u : (((uint32_t)w * 2654435769u) >> (32 - (lg - 2))) << 2;
 }
 
+// the table slot that holds w's word, or kNoSlot: buckets of four, filled from the first
+// slot on, so one with an empty slot ends the search
+__device__ __forceinline__ uint32_t table_find(const uint32_t* slots, uint32_t tb, int w) {
+  const int lg = (int)(tb & 15);
+  const uint32_t mask = (1u << lg) - 1u, key = (uint32_t)w << kNbShift;
+  for (uint32_t h = bucket_of(w, lg);; h = (h + 4) & mask) {
+    const uint4 s = *reinterpret_cast<const uint4*>(&slots[(tb >> 4) + h]);
+    if ((s.x ^ key) <= kIdMask) return s.x;
+    if ((s.y ^ key) <= kIdMask) return s.y;
+    if ((s.z ^ key) <= kIdMask) return s.z;
+    if ((s.w ^ key) <= kIdMask) return s.w;
+    if (s.w == kNoSlot) return kNoSlot;
+  }
+}
+
 template <int T, int NI>
 __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* lds, CompactCtl<T>& C) {
   const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
@@ -875,7 +898,11 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
   int np = 1;
   while (np < n) np <<= 1;
   for (int x = tid; x < (n + 1) / 2; x += T) B.half[x] = 0u;
-  if (tid == 0) C.err = kNoErr;
+  if (tid == 0) {
+    C.err = kNoErr;
+    C.nthread = 0;
+    C.ngroup = 0;
+  }
   __syncthreads();
   // degrees; range and self-loop checks (Section 2: simple graphs).  Repeated
   // pairs may push a 16-bit count over, but never past its word: a count
@@ -940,6 +967,11 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
       int lg = 2;
       while ((1 << lg) < d + (d + 1) / 2) ++lg;  // 1.5 d slots or more, at least a bucket, fewer than 3 d
       const int sz = d > 1 ? 1 << lg : 0;        // the only neighbour of a vertex is never looked up
+      const uint64_t ofthread = ballot(x < n && d <= kThreadRow), ofgroup = ballot(x < n && d <= kGroupRow);
+      if (lane == 0) {
+        if (ofthread) atomicMax(&C.nthread, x + kWave - __builtin_clzll(ofthread));
+        if (ofgroup) atomicMax(&C.ngroup, x + kWave - __builtin_clzll(ofgroup));
+      }
       int td, tu, tt;
       const int id = block_scan32<T>(d, C.tmp, &td);
       const int iu = block_scan32<T>(u, C.tmp, &tu);
@@ -972,13 +1004,29 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
   __syncthreads();
   // rows sorted through a bitmap; the edge ids of the upper entries by input position
   WaveLds& W = reinterpret_cast<WaveLds*>(lds)[wv];
+  const int nt = C.nthread, ng = C.ngroup;  // rows [0, nt) are the threads', [nt, ng) the groups'
+  const int gl = lane % kGroupRow;          // this lane's place in its group
+  constexpr int kStep = T / kGroupRow;      // groups in the workgroup
+  const int g0 = nt + tid / kGroupRow;
+  auto place = [&](int x, int base, int r, int low, int up, uint32_t v) {
+    S.rows[base + r] = v;
+    if (r >= low) {
+      const int id = up + r - low, i = (int)(v & kIdMask);
+      if (id < m) {  // (repeated pairs, reported below, can leave ranks that do not fit)
+        S.sup[i] = id;
+        S.perm[id] = i;
+        S.ev[id] = (uint16_t)(v >> kNbShift);
+        S.live[id] = ((uint32_t)x << kIdBits) | (uint32_t)id;
+      }
+    }
+  };
   for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
   wave_sync();
   for (;;) {
     int x = 0;
     if (lane == 0) x = n - 1 - atomicAdd(&C.next, 1);  // long rows first
     x = __shfl(x, 0, kWave);
-    if (x < 0) break;
+    if (x < ng) break;
     const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
     if (d == 0) continue;
     for (int j = lane; j < d; j += kWave) {
@@ -991,21 +1039,46 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
     const int up = (int)ldg(&S.up[x]), low = d - ((int)ldg(&S.up[x + 1]) - up);
     for (int j = lane; j < d; j += kWave) {
       const uint32_t v = ldg(&S.slots[base + j]);
-      const int r = rank_in(W, (int)(v >> kNbShift));
-      S.rows[base + r] = v;
-      if (r >= low) {
-        const int id = up + r - low, i = (int)(v & kIdMask);
-        if (id < m) {  // (repeated pairs, reported below, can leave ranks that do not fit)
-          S.sup[i] = id;
-          S.perm[id] = i;
-          S.ev[id] = (uint16_t)(v >> kNbShift);
-          S.live[id] = ((uint32_t)x << kIdBits) | (uint32_t)id;
-        }
-      }
+      place(x, base, rank_in(W, (int)(v >> kNbShift)), low, up, v);
     }
     wave_sync();
     for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
     wave_sync();
+  }
+  // (the loops over the groups run as often for all lanes of a wavefront)
+  for (int x0 = g0; x0 - lane / kGroupRow < ng; x0 += kStep) {
+    const int x = x0 < ng ? x0 : ng - 1;
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    const int up = (int)ldg(&S.up[x]), low = d - ((int)ldg(&S.up[x + 1]) - up);
+    const bool in = x0 < ng && gl < d;
+    const uint32_t v = in ? ldg(&S.slots[base + gl]) : kNoSlot;
+    int r = 0, same = 0;
+#pragma unroll 4
+    for (int t = 0; t < kGroupRow; ++t) {
+      const uint32_t o = (uint32_t)__shfl((int)v, t, kGroupRow);
+      r += o < v ? 1 : 0;
+      same += (o ^ v) < (1u << kNbShift) && t < d ? 1 : 0;
+    }
+    if (in && same > 1) atomicMin(&C.err, kErrDup);
+    if (in) place(x, base, r, low, up, v);
+  }
+  for (int x = tid; x < nt; x += T) {
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    const int up = (int)ldg(&S.up[x]), low = d - ((int)ldg(&S.up[x + 1]) - up);
+    uint32_t v[kThreadRow];
+#pragma unroll
+    for (int j = 0; j < kThreadRow; ++j) v[j] = j < d ? ldg(&S.slots[base + j]) : kNoSlot;
+#pragma unroll
+    for (int j = 0; j < kThreadRow; ++j) {
+      int r = 0, same = 0;
+#pragma unroll
+      for (int t = 0; t < kThreadRow; ++t) {
+        r += v[t] < v[j] ? 1 : 0;
+        same += (v[t] ^ v[j]) < (1u << kNbShift) && t < d ? 1 : 0;
+      }
+      if (j < d && same > 1) atomicMin(&C.err, kErrDup);
+      if (j < d) place(x, base, r, low, up, v[j]);
+    }
   }
   __syncthreads();
   if (C.err != kNoErr) {
@@ -1030,9 +1103,8 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
     int x = 0;
     if (lane == 0) x = n - 1 - atomicAdd(&C.next, 1);
     x = __shfl(x, 0, kWave);
-    if (x < 0) break;
+    if (x < ng) break;
     const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
-    if (d < 2) continue;
     const uint32_t tb = ldg(&S.tab[x]);
     const int lg = (int)(tb & 15);
     uint32_t* t = S.slots + (tb >> 4);
@@ -1041,6 +1113,29 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
       const uint32_t v = ldg(&S.rows[base + j]);
       uint32_t h = bucket_of((int)(v >> kNbShift), lg);
       while (atomicCAS(&t[h], kNoSlot, v) != kNoSlot) h = (h + 1) & mask;  // at most 2/3 full
+    }
+  }
+  for (int x = g0; x < ng; x += kStep) {
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    if (gl >= d) continue;
+    const uint32_t tb = ldg(&S.tab[x]), v = ldg(&S.rows[base + gl]);
+    const int lg = (int)(tb & 15);
+    uint32_t* t = S.slots + (tb >> 4);
+    uint32_t h = bucket_of((int)(v >> kNbShift), lg);
+    while (atomicCAS(&t[h], kNoSlot, v) != kNoSlot) h = (h + 1) & ((1u << lg) - 1u);
+  }
+  for (int x = tid; x < nt; x += T) {
+    const int base = (int)ldg(&S.rp[x]), d = (int)ldg(&S.rp[x + 1]) - base;
+    if (d < 2) continue;
+    const uint32_t tb = ldg(&S.tab[x]);
+    const int lg = (int)(tb & 15);
+    uint32_t used = 0;  // slots taken: the table is this thread's alone
+    for (int j = 0; j < d; ++j) {
+      const uint32_t v = ldg(&S.rows[base + j]);
+      uint32_t h = bucket_of((int)(v >> kNbShift), lg);
+      while (used >> h & 1u) h = (h + 1) & ((1u << lg) - 1u);
+      used |= 1u << h;
+      S.slots[(tb >> 4) + h] = v;
     }
   }
   __syncthreads();  // every wavefront has seen the end of the list
@@ -1055,7 +1150,7 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
     int a = 0;
     if (lane == 0) a = n - 1 - atomicAdd(&C.next, 1);
     a = __shfl(a, 0, kWave);
-    if (a < 0) break;
+    if (a < ng) break;
     const int ua = (int)ldg(&S.up[a]), da = (int)ldg(&S.up[a + 1]) - ua;
     if (da < 2) continue;
     const int oa = (int)ldg(&S.rp[a + 1]) - da;  // the out-neighbours end the row
@@ -1118,6 +1213,47 @@ __device__ void process_compact(const BatchArgs& A, int g, char* scratch, char* 
     for (int j = lane; j < (da + 1) / 2; j += kWave) W.cnt[j] = 0u;
     for (int i = lane; i < kBits; i += kWave) W.bits[i] = 0u;
     wave_sync();
+  }
+  // few out-neighbours: every two of them looked up, the upper in the lower one's table
+  // (a neighbour of no lower degree than a's, so it has one)
+  for (int x0 = g0; x0 - lane / kGroupRow < ng; x0 += kStep) {
+    const int a = x0 < ng ? x0 : ng - 1;
+    const int ua = (int)ldg(&S.up[a]), da = x0 < ng ? (int)ldg(&S.up[a + 1]) - ua : 0;
+    const uint32_t v = gl < da ? ldg(&S.rows[(int)ldg(&S.rp[a + 1]) - da + gl]) : 0u;
+    const int w = (int)(v >> kNbShift);
+    const uint32_t tw = gl < da ? ldg(&S.tab[w]) : 0u;
+    int cnt = 0;  // triangles on (a, w)
+    const int most = wave_max(da);
+    for (int i = 0; i + 1 < most; ++i) {
+      const uint32_t tb = (uint32_t)__shfl((int)tw, i, kGroupRow);
+      uint32_t f = kNoSlot;
+      if (i < gl && gl < da) f = table_find(S.slots, tb, w);
+      const uint64_t hits = ballot(f != kNoSlot) >> (lane - gl) & ((1ULL << kGroupRow) - 1ULL);
+      if (f != kNoSlot) {
+        atomicAdd(&S.sup[f & kIdMask], 1);
+        ++cnt;
+        tri += 1;
+      }
+      if (gl == i) cnt += __popcll(hits);
+    }
+    if (cnt) atomicAdd(&S.sup[ua + gl], cnt);
+    wsup += gl == 0 ? (unsigned long long)(da * (da - 1) / 2) : 0ULL;
+  }
+  for (int a = tid; a < nt; a += T) {
+    const int ua = (int)ldg(&S.up[a]), da = (int)ldg(&S.up[a + 1]) - ua;
+    const int oa = (int)ldg(&S.rp[a + 1]) - da;
+    wsup += (unsigned long long)(da * (da - 1) / 2);
+    for (int i = 0; i + 1 < da; ++i) {
+      const uint32_t tb = ldg(&S.tab[ldg(&S.rows[oa + i]) >> kNbShift]);
+      for (int j = i + 1; j < da; ++j) {
+        const uint32_t f = table_find(S.slots, tb, (int)(ldg(&S.rows[oa + j]) >> kNbShift));
+        if (f == kNoSlot) continue;
+        tri += 1;
+        atomicAdd(&S.sup[ua + i], 1);
+        atomicAdd(&S.sup[ua + j], 1);
+        atomicAdd(&S.sup[f & kIdMask], 1);
+      }
+    }
   }
   __syncthreads();
   const unsigned long long t2 = wall_clock64();
@@ -1424,7 +1560,7 @@ __global__ void __launch_bounds__(T) k_batch_compact(BatchArgs A) {
 // different XCDs (drawn, they went to the workgroups that started first, on a few XCDs:
 // 16 graphs of 290 K edges and 600 tiny ones 335 -> 365-410 ms).
 template <int T, int NI>
-__global__ void __launch_bounds__(T) k_batch_mixed(BatchArgs A) {
+__global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) k_batch_mixed(BatchArgs A) {
   extern __shared__ __align__(16) char lds[];
   __shared__ CompactCtl<T> C;
   const Slot S = slot_at(A, blockIdx.x);
@@ -1480,6 +1616,12 @@ BatchKernel batch_kernel(int T, int NI, Kind kind, int64_t n, int64_t m, size_t*
 }
 
 constexpr int kDefaultT = 1024, kDefaultG = 2;
+
+// A batch of none but tiny graphs, no more than compute units, goes to the general
+// kernel: its fewer steps, each fetched once, bound such a call (50 vertices and 98
+// edges: 93 us, compact 102).  From 128 vertices or 320 edges on the compact kernel is as
+// fast or faster, and with more graphs it is (3000 of 50 vertices 1.20 ms, general 1.22).
+constexpr int64_t kTinyN = 64, kTinyM = 256;
 
 int device_cus() {
   int dev = 0, cus = 0;
@@ -1539,6 +1681,12 @@ int split_batch(int32_t G, const int64_t* vo, const int64_t* eo, const truss_opt
       if (rc) return rc;
       B.big_ws = std::max(B.big_ws, b);
     }
+  }
+  if (!B.general && B.max_cn <= kTinyN && B.max_cm <= kTinyM && (int)B.order.size() <= device_cus()) {
+    B.general = true;
+    B.compact = false;
+    B.max_n = B.max_cn;
+    B.max_m = B.max_cm;
   }
   // a compact graph takes about a quarter of the time of a general one of as many edges
   auto cost = [&](int32_t g) {
