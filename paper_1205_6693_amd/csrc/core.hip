@@ -66,7 +66,8 @@ struct alignas(256) CoreCtl {
   int cmax;
   int phase;
   int admit;  // CoreAdmit, changed once
-  alignas(128) unsigned arrived;  // workgroups that have asked for admission
+  alignas(128) unsigned arrived[kGridGroups][32];  // workgroups that have started, per group (a line each)
+  alignas(128) unsigned groups;                    // groups all of whose workgroups have
 };
 
 // The stepped form: a sequence of identical launches of one kernel; the state says
@@ -128,7 +129,8 @@ __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int3
     c->cmax = 0;
     c->phase = kLevel;
     c->admit = kUndecided;
-    c->arrived = 0;
+    for (int g = 0; g < kGridGroups; ++g) c->arrived[g][0] = 0;
+    c->groups = 0;
     *st = CoreState{kStart, 0, 0, 0, 0, 0, 0, kIntMax, 0u};
   }
 }
@@ -139,7 +141,10 @@ __global__ void k_core_init(const int64_t* __restrict__ row_ptr, int32_t n, int3
 // thread) and asks after its first phase, when the others have long arrived: asked at
 // once, the answer took 8 us.
 __device__ __forceinline__ void core_arrive(CoreCtl* c) {
-  if (atomicAdd(&c->arrived, 1u) + 1 == gridDim.x) atomicCAS(&c->admit, kUndecided, kAdmitted);
+  const unsigned g = blockIdx.x % kGridGroups, size = (gridDim.x - g + kGridGroups - 1) / kGridGroups;
+  const unsigned ngroups = gridDim.x < (unsigned)kGridGroups ? gridDim.x : (unsigned)kGridGroups;
+  if (atomicAdd(&c->arrived[g][0], 1u) + 1 == size && atomicAdd(&c->groups, 1u) + 1 == ngroups)
+    atomicCAS(&c->admit, kUndecided, kAdmitted);
 }
 __device__ __forceinline__ bool core_admitted(CoreCtl* c) {
   __shared__ int s_yes;
