@@ -222,7 +222,7 @@ void layout(const truss_graph* g, Arena& a, Plan& p, DevGraph* dg_for_sizes) {
 }
 
 // The counters of the upper bound's long rows (2m + n + 1), in the build's temporaries:
-// those hold 2m + 1 and n + 1 eight-byte entries and more besides (relabelled builds).
+// those hold 2m + 1 eight-byte and n + 1 four-byte entries and more besides.
 int bound_counters(const DevGraph& dg, int32_t** hs) {
   if (dg.tmp_bytes < sizeof(int32_t) * (size_t)(2 * dg.m + dg.n + 1)) {
     set_last_error("workspace too small for the upper bound");
@@ -920,15 +920,6 @@ void set_last_error(const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(g_last_error, sizeof(g_last_error), fmt, ap);
   va_end(ap);
-}
-
-int device_grid_blocks(const void* kernel, int block, size_t lds) {
-  int dev = 0, cus = 0, occ = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, block, lds) != hipSuccess || occ < 1) occ = 1;
-  if (occ > 4) occ = 4;
-  return cus * occ;
 }
 
 }  // namespace truss

@@ -384,7 +384,7 @@ struct Layout {
   int32_t* tsz;
   size_t tmp_at, tmp_bytes;  // the temporaries' place in the arena
   // relabelling: vertex sort keys and values (ping-pong), their radix scratch, ranks, degrees
-  uint64_t *vkey, *vkey_alt;
+  uint32_t *vkey, *vkey_alt;
   int32_t *vval, *vval_alt, *vtmp, *rank, *vdeg;
 };
 
@@ -399,9 +399,10 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
   L.ev = a.take<int32_t>(m + 1);
   L.orow = a.take<int64_t>(n + 1);
   L.perm = edges ? a.take<int32_t>(m + 1) : nullptr;
-  L.rtab = a.take<int2>((size_t)rtab_capacity(m));
-  L.rtoff = a.take<int64_t>(n + 1);
-  L.tsz = a.take<int32_t>(n + 1);
+  // row tables: of relabelled builds alone
+  L.rtab = relabel ? a.take<int2>((size_t)rtab_capacity(m)) : nullptr;
+  L.rtoff = relabel ? a.take<int64_t>(n + 1) : nullptr;
+  L.tsz = relabel ? a.take<int32_t>(n + 1) : nullptr;
   L.row_ptr = edges ? a.take<int64_t>(n + 1) : nullptr;
   // temporaries: free once the build has returned (DevGraph::tmp)
   L.tmp_at = a.used;
@@ -425,8 +426,8 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
     L.rtmp = nullptr;
   }
   if (relabel) {
-    L.vkey = a.take<uint64_t>(n + 1);
-    L.vkey_alt = a.take<uint64_t>(n + 1);
+    L.vkey = a.take<uint32_t>(n + 1);
+    L.vkey_alt = a.take<uint32_t>(n + 1);
     L.vval = a.take<int32_t>(n + 1);
     L.vval_alt = a.take<int32_t>(n + 1);
     L.vtmp = a.take<int32_t>(radix_tmp_elems(n + 1));
@@ -444,10 +445,9 @@ void carve(const truss_graph* g, bool relabel, Arena& a, Layout& L) {
 
 // ranks of the vertices in (degree, id) order; degrees from row_ptr, else from deg
 void degree_ranks(const int64_t* row_ptr, const int32_t* deg, int32_t n, int vb, Layout& L, hipStream_t s) {
-  uint32_t* key = reinterpret_cast<uint32_t*>(L.vkey);
-  uint32_t* key_alt = reinterpret_cast<uint32_t*>(L.vkey_alt);
-  hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, deg, n, vb, key, L.vval);
-  const bool alt = radix_sort_u32(key, L.vval, key_alt, L.vval_alt, n, vb, L.vtmp, s);
+  hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, row_ptr, deg, n, vb, L.vkey,
+                     L.vval);
+  const bool alt = radix_sort_u32(L.vkey, L.vval, L.vkey_alt, L.vval_alt, n, vb, L.vtmp, s);
   hipLaunchKernelGGL(k_ranks, dim3(grid_for(n > 0 ? n : 1)), dim3(kT), 0, s, alt ? L.vval_alt : L.vval, n, L.rank);
 }
 

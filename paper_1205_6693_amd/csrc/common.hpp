@@ -87,12 +87,6 @@ __device__ __forceinline__ int wave_incl_max(int x) {
   return x;
 }
 
-// first lane (lowest id) of a non-empty mask broadcasts `x`
-template <typename T>
-__device__ __forceinline__ T wave_bcast(T x, int src) {
-  return __shfl(x, src, kWave);
-}
-
 // ---- device-scope atomics ---------------------------------------------------
 
 __device__ __forceinline__ int atomic_load_relaxed(const int* p) {

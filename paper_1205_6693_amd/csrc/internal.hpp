@@ -42,8 +42,6 @@ struct Arena {
 size_t scan_tmp_elems(int64_t count);
 void scan_exclusive_i32_to_i64(const int32_t* in, int64_t* out, int64_t count, int64_t* tmp,
                                hipStream_t s);
-void scan_exclusive_i32_to_i32(const int32_t* in, int32_t* out, int64_t count, int32_t* tmp,
-                               hipStream_t s);
 
 // ---- radix sort (LSD, 8-bit digits, stable) -------------------------------------
 // Sorts (keys, vals) of length n by the low `bits` bits of the keys, passing
@@ -206,7 +204,6 @@ int run_subgraph(const SubgraphRun& r, const truss_options* opts, void* ws, size
 
 void set_last_error(const char* fmt, ...);
 int validate_options(const truss_options* o);  // TRUSS_OK or TRUSS_E_INVAL (message set)
-int device_grid_blocks(const void* kernel, int block, size_t lds);
 
 }  // namespace truss
 

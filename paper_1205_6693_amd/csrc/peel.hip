@@ -105,7 +105,6 @@ enum Phase : int {
   PH_SWEEP = 0,    // minimum live support and the next level's first frontier
   PH_START = 1,    // level start: collect live edges with sup <= k-2
   PH_PROC = 2,     // destroy the triangles of F_r
-  PH_UNUSED = 3,
   PH_DENSE = 4,    // dense mode: collect the next frontier by re-scan
   PH_COMPACT = 5,  // return to the host: drop removed entries from the rows
   PH_DONE = 6
@@ -154,12 +153,10 @@ struct alignas(256) PeelCtl {
   unsigned long long t_last;            // wall clock at the previous barrier
   unsigned long long t_phase[8];        // time spent per phase (100 MHz ticks)
   int err;
-  int launches;
   // scheduling
   int probe;               // membership probe of the current level: 0 row hash table, 1 binary search
   int sched;               // TRUSS_SCHED_* in effect
   int fix_bits, fix_vals;  // action bits fixed by the options
-  int m_edges;
   int qbits;               // bits of the edge count in w_q
   int input_err;           // RunHead::err when the peeling began
   unsigned long long sup_total;
@@ -266,12 +263,6 @@ __device__ __forceinline__ PhaseState phase_state(const unsigned long long* pub)
 }
 static_assert(TRUSS_PEEL_SPARSE < 4 && TRUSS_PEEL_DENSE < 4 && PH_DONE < 8, "fields of PUB_FLAGS");
 
-// The heuristic's action for a level (bit 0 probe, bit 1 mode).
-__device__ __forceinline__ int heuristic_action(const float* x) {
-  (void)x;
-  return 0;
-}
-
 // ---- control step: the first wavefront of the last workgroup to reach a barrier ---------------
 // All inputs are loaded first (independent loads in flight together; the
 // published state is at hand), the decision is made in registers and released,
@@ -372,7 +363,8 @@ __device__ __forceinline__ void control_step(PeelCtl* c, const PeelArgs& P, Phas
             if ((a & fix_bits) == fix_vals) mask |= 1u << a;
           act = argmin_allowed(sc, kPeelA, mask);
         } else {
-          const int pref = sched == TRUSS_SCHED_PLAIN ? 3 : heuristic_action(x);
+          // the heuristic: sparse and the row hash table, whatever the level
+          const int pref = sched == TRUSS_SCHED_PLAIN ? 3 : 0;
           act = (pref & ~fix_bits) | fix_vals;
         }
         st.mode = (act & 2) ? (int)TRUSS_PEEL_DENSE : (int)TRUSS_PEEL_SPARSE;
@@ -1306,13 +1298,11 @@ __global__ void __launch_bounds__(256) k_peel_init(PeelCtl* c, const int64_t* __
     c->t_last = 0;
     for (int b = 0; b < 8; ++b) c->t_phase[b] = 0;
     c->err = 0;
-    c->launches = 0;
     c->probe = 0;
     c->sched = sched;
     c->fix_bits = fix_bits;
     c->fix_vals = fix_vals;
     c->stop_level = stop_level;
-    c->m_edges = (int)m;
     c->qbits = qbits;
     c->lvl_sub0 = 0;
     c->prev_sub = 0;

@@ -386,10 +386,6 @@ void scan_exclusive_i32_to_i64(const int32_t* in, int64_t* out, int64_t count, i
   scan_impl<int32_t, int64_t>(in, out, count, tmp, s);
 }
 
-void scan_exclusive_i32_to_i32(const int32_t* in, int32_t* out, int64_t count, int32_t* tmp, hipStream_t s) {
-  scan_impl<int32_t, int32_t>(in, out, count, tmp, s);
-}
-
 size_t radix_tmp_elems(int64_t n) {
   const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
   return (size_t)(2 * 256 * ntiles + 1) + scan_tmp_elems(256 * ntiles);
