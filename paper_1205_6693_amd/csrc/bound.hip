@@ -100,9 +100,11 @@ __global__ void __launch_bounds__(kT) k_psi(const int32_t* __restrict__ eu, cons
                                             const int32_t* __restrict__ ch, int64_t m, int32_t* __restrict__ psi,
                                             const int* err) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m || invalid(err)) return;
+  if (e >= m) return;
+  const bool bad = invalid(err);
   const int s = sup[e];
   const int u = eu[e], v = ev[e];
+  if (bad) return;  // (h and ch have not been written)
   const int hu = h[u], hv = h[v];
   const int xu = (s >= hu && ch[u] == hu) ? hu - 1 : hu;
   const int xv = (s >= hv && ch[v] == hv) ? hv - 1 : hv;

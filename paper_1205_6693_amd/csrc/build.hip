@@ -46,9 +46,9 @@ __global__ void k_build_init(RunHead* head, int32_t* __restrict__ deg, int64_t n
 __global__ void k_rtab_sizes(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ tsz, const int* err) {
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (v >= n) return;
-  const int64_t d = invalid(err) ? 0 : row_ptr[v + 1] - row_ptr[v];
+  const int64_t d = row_ptr[v + 1] - row_ptr[v];
   int64_t sz = 0;
-  if (d > 0) {
+  if (d > 0 && !invalid(err)) {
     sz = 4;
     while (sz < 2 * d) sz <<= 1;
   }
@@ -147,9 +147,11 @@ __global__ void k_sym_upper(const int32_t* __restrict__ eu, const int32_t* __res
                             int32_t* __restrict__ col, int32_t* __restrict__ seid,
                             const int64_t* __restrict__ rtoff, int2* __restrict__ rtab, const int* err) {
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= m || invalid(err)) return;
+  if (e >= m) return;
+  const bool bad = invalid(err);  // (tested where the other loads have come)
   int32_t u = eu[e], v = ev[e];
   int64_t pos = lowpre[u + 1] + e;
+  if (bad) return;
   col[pos] = v;
   seid[pos] = (int32_t)e;
   rtab_put(rtab, rtoff, u, v, (int32_t)e);
@@ -164,11 +166,13 @@ __global__ void k_sym_lower(const uint32_t* __restrict__ tkey, const int32_t* __
                             int32_t* __restrict__ seid, const int64_t* __restrict__ rtoff,
                             int2* __restrict__ rtab, const int* err) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m || invalid(err)) return;
+  if (t >= m) return;
+  const bool bad = invalid(err);
   int32_t e = tval[t];
   int32_t v = (int32_t)tkey[t];
   int32_t u = eu[e];
   int64_t pos = uppre[v] + t;
+  if (bad) return;
   col[pos] = u;
   seid[pos] = e;
   rtab_put(rtab, rtoff, v, u, e);
@@ -340,9 +344,10 @@ __global__ void k_csr_sym_check(const int32_t* __restrict__ col_in, const int32_
                                 const int64_t* __restrict__ rtoff, const int64_t* __restrict__ orow,
                                 const int32_t* __restrict__ ocol, int* err) {
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= m2 || invalid(err)) return;
+  if (j >= m2) return;
+  const bool bad = invalid(err);
   const int32_t v = rowid[j], w = col_in[j];
-  if (w >= v || w < 0) return;  // (an id out of range is reported by k_csr_check)
+  if (bad || w >= v || w < 0) return;  // (an id out of range is reported by k_csr_check)
   const int32_t x = rank[v], y = rank[w];
   if (rtab) {
     const int64_t off = rtoff[x], slots = rtoff[x + 1] - off;

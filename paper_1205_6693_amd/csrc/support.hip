@@ -95,7 +95,9 @@ __global__ void __launch_bounds__(kBinT) k_sup_bin(const int64_t* __restrict__ o
   __syncthreads();
   const int64_t a = blockIdx.x * (int64_t)kBinT + threadIdx.x;
   int d = 0;
-  if (a < n && !invalid(err)) d = (int)(orow[a + 1] - orow[a]);
+  const bool bad = invalid(err);
+  if (a < n) d = (int)(orow[a + 1] - orow[a]);
+  if (bad) d = 0;
   int bin = -1;
   if (d >= 2) bin = d <= kWaveMax ? 0 : d <= kBlockMax1 ? 1 : d <= kBlockMax2 ? 2 : 3;
   int local = 0;
