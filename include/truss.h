@@ -153,12 +153,13 @@ typedef struct truss_stats {
   int32_t launches;         /* peeling kernel launches (one more per row compaction) */
   int64_t frontier_hist[6]; /* sub-rounds by frontier size: 1, 2-16, 17-256,
                                257-4096, 4097-65536, larger                      */
-  int64_t heavy_rounds;     /* sub-rounds in which long walks were cut into pieces */
+  int64_t heavy_rounds;     /* sub-rounds of more than 1024 walked row entries      */
   double ms_phase[6];       /* peeling time by phase: live-list sweep, level start,
                                frontier rounds, unused, dense re-scan, unused     */
   double ms_peel_kernel;    /* time inside the persistent peeling kernel, all launches
                                (truss_batch: the batch kernel's graph launch)     */
-  int64_t support_work;     /* truss_batch: row entries walked while counting support */
+  int64_t support_work;     /* truss_batch: row entries walked and pairs of neighbours
+                               looked up while counting support                   */
 } truss_stats;
 
 /* Fills *opts with defaults: AUTO strategies, heuristic scheduler. */
@@ -178,7 +179,12 @@ int truss_support(const truss_graph *g, int32_t *sup_out, int64_t *triangles,
 /* Truss number of every edge (Definition 2; the k-classes of Definition 3).
  *   truss_out (device) int32[m], values in [2, k_max], indexed as above.
  *   opts (host, nullable) options; NULL = truss_default_options.
- *   stats (host, nullable) filled on success. */
+ *   stats (host, nullable) filled on success.
+ * The workgroups of the peeling kernel wait for one another and must all be
+ * resident: decompositions that overlap on one GPU (streams, threads,
+ * processes) can each hold part of its compute units and then end with
+ * TRUSS_E_INTERNAL after 30 s.  Run them one after another, or many small
+ * graphs as a batch.  Core numbers may overlap with anything. */
 int truss_decompose(const truss_graph *g, int32_t *truss_out, const truss_options *opts,
                     truss_stats *stats, void *ws, size_t ws_bytes, void *stream);
 
@@ -196,9 +202,9 @@ int truss_decompose(const truss_graph *g, int32_t *truss_out, const truss_option
  * graph is validated as an edge list; the failing graph of smallest index
  * decides the returned code (the other graphs' outputs are then unspecified).
  * The workspace holds the offsets, a scratch slot per concurrent workgroup
- * (about 8 bytes per vertex and 48 per edge of the largest batched graph; 16
- * and 50 where that has at most 2^13 vertices and 2^18 edges; for
- * up to four workgroups per compute unit) and the device-wide path's workspace
+ * (about 8 bytes per vertex and 48 per edge of the largest batched graph, or
+ * 16 and 50 for as much of it as 2^13 vertices and 2^18 edges, whichever is
+ * more; for up to four workgroups per compute unit) and the device-wide path's workspace
  * for the largest remaining graph. */
 int truss_batch_workspace_size(int32_t num_graphs, const int64_t *vtx_off, const int64_t *edge_off,
                                const truss_options *opts, size_t *bytes);

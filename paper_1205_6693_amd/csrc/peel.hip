@@ -1148,7 +1148,8 @@ __device__ __forceinline__ void peel_body() {
 // wavefronts per SIMD) with one entry per thread, which hides more latency
 // when walks are long.  Entries per thread, measured: narrow 1 / 2 / 3 / 4: 13.2 / 13.3 /
 // 13.8 / 14.3 ms on R-MAT of 1.2 M edges, 90.7 / 83.5 / 85.7 / 87.2 on 15.7 M; wide
-// 1 / 2: 1173 / 1202 ms on R-MAT 23, where two spill.  Buckets read by halves / at once:
+// 1 / 2: 1173 / 1202 ms on R-MAT 23 (at 64 registers both spill, 40 and 52 bytes of scratch a
+// lane).  Buckets read by halves / at once:
 // narrow 86.4 / 83.8 ms on 15.7 M edges, wide 1173 / 1224 on R-MAT 23.  All state lives in global
 // memory between launches.
 __global__ void __launch_bounds__(kT) k_peel(PeelArgs) { peel_body<2, 2, false>(); }
